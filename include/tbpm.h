@@ -531,11 +531,15 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               unused.  0: gather from global memory
  *   vec         states of a row each thread holds (1, 2 or 4; capped by the
  *               padded state count)
- *   fused       1 .. 6: evaluate two Clenshaw orders per launch: each tile
- *               stages its rows and their two-hop neighbourhood in LDS and
- *               computes the first order on its rows and their neighbours,
- *               the second on its own rows.  The value t is the LDS tier: a
- *               tile uses at most 1/(t+2) of a CU's 160 KiB (bigger tiles and
+ *   fused       1 .. 6: evaluate several Clenshaw orders per launch.
+ *               Operators of at most 4 stored elements per row: each tile
+ *               stages its rows and the rows up to d hops away in LDS and
+ *               evaluates d orders on them (d up to 17, as far as the rows
+ *               within reach stay few); the library chooses tiles and d from
+ *               the sizes, whatever the value; vec, unroll and wg_chunks are
+ *               unused.  Other operators: two orders, each tile staging its
+ *               two-hop neighbourhood; the value t is the LDS tier: a tile
+ *               uses at most 1/(t+2) of a CU's 160 KiB (bigger tiles and
  *               smaller halos, or more resident workgroups).  Two
  *               extra state-sized work vectors are allocated; staged and
  *               wg_chunks are unused and unroll applies to the orders left
@@ -547,6 +551,12 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               runs alone, and a middle one when their count is odd.  Falls
  *               back to the plain shape when the series has fewer than 4
  *               terms or no tile fits.  0: one order per launch.
+ * A handle (or batch) whose configuration for a precision was never set nor
+ * autotuned also evaluates several orders per launch, where the operator has
+ * at most 4 stored elements per row and a propagation has more than 64 samples
+ * (shorter ones would not repay building the tile tables) and the extra work
+ * vectors fit the free device memory; FP32 states are the same bit for bit,
+ * FP64 results the same to rounding.
  */
 typedef struct {
     int32_t wg_chunks;
@@ -588,8 +598,8 @@ tbpm_status tbpm_stream_copy(const void *src, void *dst, size_t bytes, void *str
 
 /*
  * Enqueue n_launch back-to-back launches of the interior Clenshaw pass kernel
- * (b_j = c_j v + 2 H~ b_{j+1} - b_{j+2}), or of the two-order launch when the
- * fused shape is configured, on H's work buffers, for timing the dominant
+ * (b_j = c_j v + 2 H~ b_{j+1} - b_{j+2}), or of the interior launch of several
+ * orders when the last propagation took that shape, on H's work buffers, for timing the dominant
  * kernel in isolation.  The launches chain as in a time step: each reads what
  * the one before wrote, and consecutive launches walk the tiles in opposite
  * directions.  A tbpm_propagate call with the same n_states and prec must

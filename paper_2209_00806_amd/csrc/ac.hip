@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kWG) void k_gather_values(const int64_t *__restrict
 }
 
 __global__ __launch_bounds__(kWG) void k_join(const d2 *__restrict__ jpsi, const d2 *__restrict__ psi,
-                                              int64_t n_rows, int log2s, int log2s2, int S, d2 *__restrict__ out) {
+                                              int64_t n_rows, int log2s, int log2s2, int log2sb, int S,
+                                              d2 *__restrict__ out) {
     const int64_t total = n_rows << log2s2;
     const int64_t stride = (int64_t)gridDim.x * kWG;
     const int m2 = (1 << log2s2) - 1;
@@ -53,12 +54,12 @@ __global__ __launch_bounds__(kWG) void k_join(const d2 *__restrict__ jpsi, const
             v = jpsi[(r << log2s) + c];
         else if (c < 2 * S)
             v = psi[(r << log2s) + c - S];
-        out[i] = v;
+        out[state_index(r, c, log2sb, n_rows)] = v;
     }
 }
 
 __global__ __launch_bounds__(kWG) void k_pack(const d2 *__restrict__ blk, const d2 *__restrict__ fblk,
-                                              int64_t n_rows, int log2s2, int S, const int32_t *__restrict__ perm,
+                                              int64_t n_rows, int log2sb, int S, const int32_t *__restrict__ perm,
                                               d2 *__restrict__ out) {
     const int64_t total = n_rows * 2 * S;
     const int64_t stride = (int64_t)gridDim.x * kWG;
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(kWG) void k_pack(const d2 *__restrict__ blk, const 
         const int64_t r = i / (2 * S);
         const int c = (int)(i % (2 * S));
         const int64_t ro = perm ? (int64_t)perm[r] : r;
-        const int64_t src = (r << log2s2) + c;
+        const int64_t src = state_index(r, c, log2sb, n_rows);
         d2 v = fblk[src];
         if (c < S) {
             const d2 b = blk[src];
@@ -77,11 +78,11 @@ __global__ __launch_bounds__(kWG) void k_pack(const d2 *__restrict__ blk, const 
     }
 }
 
-// state: the propagated block, [rows][2^log2s2] at precision R; thread t
-// handles state t & (SP-1) of its rows (SP = 2^log2sp >= S)
+// state: the propagated block at precision R, states in blocks of 2^log2sb;
+// thread t handles state t & (SP-1) of its rows (SP = 2^log2sp >= S)
 template <typename R>
 __global__ __launch_bounds__(kWG) void k_jcorr(const TileDesc *__restrict__ tiles, int n_tiles, int log2sp, int S,
-                                               int log2s2, const void *__restrict__ state,
+                                               int log2sb, int64_t n_rows, const void *__restrict__ state,
                                                const uint32_t *__restrict__ soff, const int32_t *__restrict__ col,
                                                const d2 *__restrict__ jval, double *__restrict__ partials) {
     using C = typename CxT<R>::T;
@@ -102,12 +103,12 @@ __global__ __launch_bounds__(kWG) void k_jcorr(const TileDesc *__restrict__ tile
         for (int k = 0; k < w; ++k) {
             const int64_t slot = base + (int64_t)k * kSliceRows;
             const d2 j = jval[slot];
-            const C x = psi[((int64_t)col[slot] << log2s2) + s];
+            const C x = psi[state_index(col[slot], s, log2sb, n_rows)];
             const double xr = (double)x.x, xi = (double)x.y;
             ar = fma(j.x, xr, fma(-j.y, xi, ar));
             ai = fma(j.x, xi, fma(j.y, xr, ai));
         }
-        const C y = psi[(r << log2s2) + S + s];
+        const C y = psi[state_index(r, S + s, log2sb, n_rows)];
         const double yr = (double)y.x, yi = (double)y.y;
         dre = fma(yr, ar, fma(yi, ai, dre));  // conj(y) * (ar + i ai)
         dim = fma(yr, ai, fma(-yi, ar, dim));
@@ -196,28 +197,28 @@ hipError_t launch_gather_values(const int64_t *ell_csr, int64_t ell_size, const 
 }
 
 hipError_t launch_join(const double *jpsi, const double *psi, int64_t n_rows, int32_t log2s, int32_t log2s2,
-                       int32_t S, double *out, hipStream_t st) {
+                       int32_t log2sb, int32_t S, double *out, hipStream_t st) {
     hipLaunchKernelGGL(k_join, dim3((unsigned)grid_for_n(n_rows << log2s2)), dim3(kWG), 0, st, (const d2 *)jpsi,
-                       (const d2 *)psi, n_rows, log2s, log2s2, S, (d2 *)out);
+                       (const d2 *)psi, n_rows, log2s, log2s2, log2sb, S, (d2 *)out);
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, int32_t log2s2, int32_t S,
+hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, int32_t log2sb, int32_t S,
                        const int32_t *perm, double *out, hipStream_t st) {
     hipLaunchKernelGGL(k_pack, dim3((unsigned)grid_for_n(n_rows * 2 * S)), dim3(kWG), 0, st, (const d2 *)blk,
-                       (const d2 *)fblk, n_rows, log2s2, S, perm, (d2 *)out);
+                       (const d2 *)fblk, n_rows, log2sb, S, perm, (d2 *)out);
     return hipGetLastError();
 }
 
-hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2s2,
-                        const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
+hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2sb,
+                        int64_t n_rows, const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
                         double *partials, hipStream_t st) {
     if (fp32)
-        hipLaunchKernelGGL(k_jcorr<float>, dim3((unsigned)n_tiles), dim3(kWG), 0, st, tiles, n_tiles, log2sp, S, log2s2,
-                           state, slice_off, col, (const d2 *)jval, partials);
+        hipLaunchKernelGGL(k_jcorr<float>, dim3((unsigned)n_tiles), dim3(kWG), 0, st, tiles, n_tiles, log2sp, S, log2sb,
+                           n_rows, state, slice_off, col, (const d2 *)jval, partials);
     else
         hipLaunchKernelGGL(k_jcorr<double>, dim3((unsigned)n_tiles), dim3(kWG), 0, st, tiles, n_tiles, log2sp, S,
-                           log2s2, state, slice_off, col, (const d2 *)jval, partials);
+                           log2sb, n_rows, state, slice_off, col, (const d2 *)jval, partials);
     return hipGetLastError();
 }
 

@@ -462,7 +462,7 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_hamiltonian *H, const double *psi0, int3
         if (st != TBPM_OK) return st;
     }
     double *n2 = norm2 ? norm2 : (double *)eng.qe_norm2.ptr;
-    e = launch_qe_finalize((const double *)eng.qe_acc.ptr, n_rows, log2s, n_states, n_energies, eng.mat.perm,
+    e = launch_qe_finalize((const double *)eng.qe_acc.ptr, n_rows, log2s, eng.last_log2sb, n_states, n_energies, eng.mat.perm,
                            (double *)eng.qe_part.ptr, n2, states, hs);
     if (e != hipSuccess) return hip_fail(e, "launch quasi-eigenstate normalisation");
     if (flags & TBPM_FLAG_ASYNC) return TBPM_OK;
@@ -541,11 +541,14 @@ tbpm_status tbpm_ac_corr(tbpm_hamiltonian *H, const double *j_alpha, const doubl
         // psi2 = f(H) psi0
         st = eng.apply_ell((const double *)eng.ac_jb.ptr, log2s, src, jpsi, hs);
         if (st != TBPM_OK) return st;
-        e = launch_join((const double *)jpsi, (const double *)src, n, log2s, log2s2, n_states, (double *)blk, hs);
+        Engine::ChainShape cs;
+        const bool chain = eng.series_chain((int32_t)a.size(), 2 * n_states, cs);
+        const int32_t log2sb = chain ? cs.log2sb() : log2s2;
+        e = launch_join((const double *)jpsi, (const double *)src, n, log2s, log2s2, log2sb, n_states, (double *)blk, hs);
         if (e != hipSuccess) return hip_fail(e, "join states");
-        st = eng.apply_series(a, f, log2s2, blk, fblk, w0, w1, hs, w2, w3);
+        st = eng.apply_series(a, f, log2s2, blk, fblk, w0, w1, hs, w2, w3, chain ? &cs : nullptr);
         if (st != TBPM_OK) return st;
-        e = launch_pack((const double *)blk, (const double *)fblk, n, log2s2, n_states, eng.mat.perm,
+        e = launch_pack((const double *)blk, (const double *)fblk, n, log2sb, n_states, eng.mat.perm,
                         (double *)eng.ac_block.ptr, hs);
         if (e != hipSuccess) return hip_fail(e, "pack states");
         const double *p0 = (const double *)eng.ac_block.ptr;
@@ -820,6 +823,7 @@ tbpm_status tbpm_set_launch_config(tbpm_hamiltonian *H, tbpm_precision prec, con
     if (!H || !cfg || !valid_prec(prec)) return fail(TBPM_E_ARG, "bad argument");
     if (!valid_cfg(*cfg)) return fail(TBPM_E_ARG, "invalid launch configuration");
     H->eng.cfgs[prec] = *cfg;
+    H->eng.cfg_set[prec] = true;
     return TBPM_OK;
 }
 
@@ -833,6 +837,7 @@ tbpm_status tbpm_batch_set_launch_config(tbpm_batch *B, tbpm_precision prec, con
     if (!B || !cfg || !valid_prec(prec)) return fail(TBPM_E_ARG, "bad argument");
     if (!valid_cfg(*cfg)) return fail(TBPM_E_ARG, "invalid launch configuration");
     B->eng.cfgs[prec] = *cfg;
+    B->eng.cfg_set[prec] = true;
     return TBPM_OK;
 }
 

@@ -1,0 +1,168 @@
+// Host side of the chain kernel (several Clenshaw orders per launch): when it
+// is taken, the tile tables, and the launches.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "tbpm_engine.h"
+
+namespace tbpm {
+
+#define TRY_HIP(expr, what)                              \
+    do {                                                 \
+        hipError_t e_ = (expr);                          \
+        if (e_ != hipSuccess) return hip_fail(e_, what); \
+    } while (0)
+
+// Rows of members that keep the caller's order and are too small to be
+// renumbered at upload, in a bisection order of their own: tiles take their rows
+// from it (the storage order, and with it every sum's order, stays).
+void Engine::chain_orders() {
+    if (!ch_orders.empty()) return;
+    const int32_t ni = n_inst();
+    std::vector<std::vector<int32_t>> orders(ni);
+    const int threads = (int)std::min<int64_t>(ni, host_threads((int64_t)h_col.size()));
+    run_chunks(ni, std::max(1, threads), [&](int, int64_t lo, int64_t hi) {
+        for (int64_t i = lo; i < hi; ++i) {
+            const int64_t r0 = inst_row0[i], n = inst_row0[i + 1] - r0;
+            if (!member_perm[i].empty() || n <= kChainMinTile || n >= kReorderMinRows) continue;
+            std::vector<int64_t> rp(n + 1, 0);
+            std::vector<int32_t> cc;
+            for (int64_t r = r0; r < r0 + n; ++r) {
+                const int64_t s0 = h_slice_off[r / kSliceRows], w = (h_slice_off[r / kSliceRows + 1] - s0) / kSliceRows;
+                for (int64_t e = 0; e < w; ++e) {
+                    const int32_t g = h_col[s0 + e * kSliceRows + r % kSliceRows];
+                    if (g != r) cc.push_back((int32_t)(g - r0));
+                }
+                rp[r - r0 + 1] = (int64_t)cc.size();
+            }
+            orders[i] = bisection_order(n, rp.data(), cc.data(), kChainMinTile, 1);
+        }
+    });
+    ch_orders = std::move(orders);
+}
+
+// Tile size and depth.  The more workgroups there are, the larger a tile may be
+// (fewer rows evaluated and staged more than once); an operator too small to
+// give every CU a workgroup takes small tiles and more orders per launch.
+// Measured per time step of 17 orders (graphene L x L, S FP64 states): 64-row
+// tiles of 17 orders 11.3 us against 20.5 us for 512-row tiles of 6 (L = 64,
+// S = 1); 128 rows, 9 orders 14.3 us against 19.7 (L = 128); 512 rows, 6 orders
+// 182 us against 195 for 256 rows, 9 orders and 319 for 128 rows, 9 orders
+// (L = 512, S = 4).  One order per launch: 55, 63 and 531 us.
+tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs) {
+    if (mat.max_width < 1 || mat.max_width > kChainWidth || n_orders < 2) return fail(TBPM_E_ARG, "rows too wide");
+    cs.vs = fp32 && s_user > 1 ? 2 : 1;
+    cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
+    const int64_t rows = chain_rows(mat.is_complex);
+    const int64_t units = mat.n_rows * cs.n_blk;
+    int64_t T = kChainMinTile;
+    while (T < rows / 2 && T * 2 * 256 <= units) T *= 2;
+    chain_orders();
+    const int64_t max_rows = rows + rows / 4;
+    for (; T >= kChainMinTile; T /= 2) {
+        const int32_t cap = std::min<int32_t>(n_orders, T >= 512 ? 6 : (T >= 128 ? 9 : 17));
+        if (ch.T != T || ch.cap != cap || ch.depth == 0) {
+            const int32_t D = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, max_rows);
+            if (D < std::min(n_orders, 3)) continue;
+            ChainTables t;
+            chain_tables(h_slice_off, h_col, inst_row0, ch_orders, T, D, rows, max_rows, t);
+            if (t.depth < 1) continue;
+            const size_t nt = t.tiles.size();
+            ch = ChainState{};
+            TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
+            hipError_t e = hipSuccess;
+            auto up = [&](DevBuf &d, const void *src, size_t bytes) {
+                if (e == hipSuccess) e = d.ensure(bytes);
+                if (e == hipSuccess) e = hipMemcpy(d.ptr, src, bytes, hipMemcpyHostToDevice);
+            };
+            up(ch_tiles, t.tiles.data(), sizeof(TileDesc) * nt);
+            up(ch_tile0, t.inst_tile0.data(), sizeof(int32_t) * t.inst_tile0.size());
+            up(ch_cnt, t.cnt.data(), sizeof(int32_t) * t.cnt.size());
+            up(ch_toff, t.toff.data(), sizeof(int32_t) * nt);
+            up(ch_loff, t.loff.data(), sizeof(int32_t) * nt);
+            up(ch_rowmap, t.rowmap.data(), sizeof(uint32_t) * t.rowmap.size());
+            up(ch_lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
+            if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();  // the caller goes on with another launch shape
+                return fail(TBPM_E_OOM, "no memory for the chain tables");
+            }
+            TRY_HIP(e, "upload chain tables");
+            ch.T = T;
+            ch.cap = cap;
+            ch.depth = t.depth;
+            ch.n_tiles = (int32_t)nt;
+            ch.n_local = (int64_t)t.lidx.size() / 4;
+            ch.contiguous = t.contiguous;
+            ch.max_stage = t.max_stage;
+        }
+        // few tiles: their state blocks go to several workgroups each
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch.n_tiles - 1) / ch.n_tiles));
+        // the orders of one evaluation, in launches of nearly equal depth
+        const int32_t n_launch = (n_orders + ch.depth - 1) / ch.depth;
+        cs.depths.clear();
+        for (int32_t l = 0, left = n_orders; l < n_launch; ++l) {
+            cs.depths.push_back(left / (n_launch - l));
+            left -= cs.depths.back();
+        }
+        return TBPM_OK;
+    }
+    return fail(TBPM_E_ARG, "no chain tile fits");
+}
+
+bool Engine::chain_fits(const ChainShape &cs, bool fp32, size_t vec) {
+    auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+    const size_t rb = fp32 ? 4 : 8;
+    size_t need = grow(v, vec) + grow(ba, vec) + grow(phi0, vec * (fp32 ? 2 : 1)) +
+                  grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * chain_width()) +
+                  grow(ch_tons, rb * (size_t)ch.n_local);
+    if (cs.depths.size() > 1) need += grow(bb, vec) + grow(bc, vec);
+    if (cs.depths.size() > 2) need += grow(bd, vec);
+    if (need == 0) return true;
+    size_t free_b = 0, total_b = 0;
+    return hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + ((size_t)256 << 20) <= free_b;
+}
+
+// The tiles' copies of the matrix entries, from the values the handle holds now
+// (75 us for 2M rows; a propagation reads them once per launch).
+tbpm_status Engine::chain_values(bool fp32, hipStream_t st) {
+    const size_t rb = fp32 ? 4 : 8;
+    const int32_t W = chain_width();
+    TRY_HIP(ch_tval.ensure(rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * W), "alloc chain values");
+    TRY_HIP(ch_tons.ensure(rb * (size_t)ch.n_local), "alloc chain values");
+    ChainTileTab t{(const int32_t *)ch_cnt.ptr, (const int32_t *)ch_toff.ptr, (const int32_t *)ch_loff.ptr,
+                   (const uint32_t *)ch_rowmap.ptr, ch.depth, W};
+    TRY_HIP(launch_chain_values(fp32, mat.is_complex, t, ch.n_tiles, mat, ch_tval.ptr, ch_tons.ptr, st),
+            "launch chain values");
+    return TBPM_OK;
+}
+
+ChainParams Engine::chain_params(const ChainShape &cs) const {
+    ChainParams p{};
+    p.tiles = (const TileDesc *)ch_tiles.ptr;
+    p.n_tiles = ch.n_tiles;
+    p.n_blk = cs.n_blk;
+    p.n_grp = cs.n_grp;
+    p.grp_blk = (cs.n_blk + cs.n_grp - 1) / cs.n_grp;
+    p.table_depth = ch.depth;
+    p.contiguous = ch.contiguous ? 1 : 0;
+    p.n_inst = n_inst();
+    p.n_rows = (uint32_t)mat.n_rows;
+    p.cnt = (const int32_t *)ch_cnt.ptr;
+    p.toff = (const int32_t *)ch_toff.ptr;
+    p.loff = (const int32_t *)ch_loff.ptr;
+    p.rowmap = (const uint32_t *)ch_rowmap.ptr;
+    p.lidx = (const uint16_t *)ch_lidx.ptr;
+    p.tval = ch_tval.ptr;
+    p.tons = ch_tons.ptr;
+    return p;
+}
+
+tbpm_status Engine::chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const {
+    hipError_t e = launch_chain(fp32, mat.is_complex, chain_width(), cs.vs, ch.max_stage[p.depth - 1],
+                                ch.max_stage[p.depth], p, st);
+    if (e != hipSuccess) return hip_fail(e, "launch chain");
+    return TBPM_OK;
+}
+
+}  // namespace tbpm

@@ -46,6 +46,11 @@ __device__ __forceinline__ C hmad(C h, C x, C acc) {
     return acc;
 }
 
+// element (row, s) of states stored in blocks of 2^log2sb states, [block][n_rows][2^log2sb]
+__device__ __forceinline__ int64_t state_index(int64_t row, int s, int log2sb, int64_t n_rows) {
+    return ((((int64_t)(s >> log2sb)) * n_rows + row) << log2sb) + (s & ((1 << log2sb) - 1));
+}
+
 template <bool NT, typename T>
 __device__ __forceinline__ T ldv(const T *p) {
     if constexpr (NT)

@@ -7,10 +7,11 @@
 //   b_j     = c_j v + 2 H~ b_{j+1} - b_{j+2},   j = M-4 .. 1
 //   psi'    = c_0 v + H~ b_1 - b_2                            (+ C_{k+1}, ||psi'||^2)
 // i.e. M-1 sparse passes over three state-sized buffers (v, A, B): every pass
-// writes its output over a buffer that only the same element reads.  The
-// passes of one step and the correlation reduce are captured once in a HIP
-// graph and replayed N_t - 1 times; a device step counter tells the reduce
-// which C_k it is producing.
+// writes its output over a buffer that only the same element reads.  Where the
+// operator suits it, several of these orders run per launch (chain.hip, or two
+// in fused.hip).  The launches of 16 steps and their correlation reduces are
+// captured once in a HIP graph and replayed; a device step counter tells the
+// reduce which C_k it is producing.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -79,7 +80,7 @@ void PinnedBuf::release() {
 bool GraphKey::operator==(const GraphKey &o) const {
     if (s_pad != o.s_pad || s_user != o.s_user || fp32 != o.fp32 || mmax != o.mmax || n_inst != o.n_inst ||
         chunks != o.chunks || remap != o.remap || nt != o.nt || unroll != o.unroll || staged != o.staged || vec != o.vec ||
-        fused != o.fused || n_tiles != o.n_tiles || tiles_chunks != o.tiles_chunks || tiles_unit != o.tiles_unit ||
+        fused != o.fused || chain_depth != o.chain_depth || chain_grp != o.chain_grp || n_tiles != o.n_tiles || tiles_chunks != o.tiles_chunks || tiles_unit != o.tiles_unit ||
         lds_units != o.lds_units || n_steps != o.n_steps || n_qe != o.n_qe || jc_states != o.jc_states ||
         steps != o.steps || ckpt != o.ckpt)
         return false;
@@ -131,7 +132,6 @@ static double halo_cost(const HostCsr &h, const std::vector<int32_t> &perm, cons
 // 1 takes the bisection order, -1 takes the bisection order for members of
 // at least kReorderMinRows rows when it cuts the halo cost by 15% or more.
 static std::vector<int32_t> member_order(const HostCsr &h, int32_t mode) {
-    constexpr int64_t kReorderMinRows = 16384;
     if (mode == 0 || h.n < 2 || (mode < 0 && h.n < kReorderMinRows)) return {};
     std::vector<int32_t> perm = bisection_order(h.n, h.row_ptr.data(), h.col.data(), 32);
     if (mode < 0) {
@@ -289,8 +289,11 @@ void Engine::release() {
                       &fu_hw,    &fu_hidx,  &bc,       &bd,        &ckpt_slot, &corr_scratch, &qe_coef,
                       &qe_acc,   &qe_part,  &qe_norm2, &ac_ja,     &ac_jb,     &ac_csr,       &ac_zero,
                       &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &hay_u,     &hay_y,        &hay_s,
-                      &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner};
+                      &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner, &ch_tiles, &ch_tile0,
+                      &ch_cnt,   &ch_toff,  &ch_loff,  &ch_rowmap, &ch_lidx, &ch_tval, &ch_tons};
     for (DevBuf *b : bufs) b->release();
+    ch = ChainState{};
+    ch_orders.clear();
     partner_ready = false;
     staging.release();
     if (staging_done) (void)hipEventDestroy(staging_done);
@@ -595,30 +598,46 @@ tbpm_status Engine::run(const RunArgs &a) {
     const int32_t vs = std::min(cfg.vec, s_pad);
     const int32_t log2u = log2s - (vs == 4 ? 2 : (vs == 2 ? 1 : 0));
     const int32_t unit_bytes = (int32_t)esize * vs;
-    bool fused = cfg.fused != 0 && mmax >= 4;
-    bool staged = cfg.staged != 0 && !fused;
+    bool fused = cfg.fused != 0;
+    bool staged = cfg.staged != 0 && !(fused && mmax >= 4);
     // the staged shape takes rows wider than kStagedRowBytes one block of
     // states at a time (units of a block: 2^log2ub)
     int32_t log2ub = log2u;
     while (staged && log2ub > 0 && ((int64_t)unit_bytes << log2ub) > kStagedRowBytes) --log2ub;
     tbpm_status st = TBPM_OK;
+    // Several orders per launch for operators that suit it: where the fused shape
+    // is configured, and where nobody chose a configuration and the propagation
+    // is long enough to repay the tile tables.
+    ChainShape cs;
+    bool chain = (fused || (!cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps)) &&
+                 chain_prepare(a.s_user, fp32, n_passes, cs) == TBPM_OK;
+    if (chain && !fused && !chain_fits(cs, fp32, esize * (size_t)mat.n_rows * s_pad)) chain = false;
+    if (chain) staged = false;
+    fused = fused && !chain && mmax >= 4;  // two orders per launch need four terms
     if (fused && build_fused_tiles(s_pad, log2u, unit_bytes, cfg.fused) != TBPM_OK) fused = false;  // fall back
     if (staged && build_staged_tiles(s_pad, log2ub, unit_bytes, cfg.staged) != TBPM_OK) staged = false;
-    if (!staged && !fused) st = build_tiles(s_pad, chunks, vs);
+    if (!staged && !fused && !chain) st = build_tiles(s_pad, chunks, vs);
     if (st != TBPM_OK) return st;
-    const int32_t n_tiles = (int32_t)h_tiles.size();
+    const int32_t n_tiles = chain ? ch.n_tiles : (int32_t)h_tiles.size();
     const int64_t n_el = mat.n_rows * s_pad;
     if (n_el >= (int64_t)INT32_MAX) return fail(TBPM_E_ARG, "n_orb * n_states (padded to a power of two) must be < 2^31");
+    if (chain) {
+        st = chain_values(fp32, a.stream);
+        if (st != TBPM_OK) return st;
+    }
+    // work vectors of the chain schedule: one launch per step writes psi to one
+    // other vector, two launches need three, more need four
+    const size_t ch_bufs = !chain ? 0 : (cs.depths.size() == 1 ? 1 : (cs.depths.size() == 2 ? 3 : 4));
 
     TRY_HIP(v.ensure(esize * n_el), "alloc v");
     TRY_HIP(ba.ensure(esize * n_el), "alloc A");
-    TRY_HIP(bb.ensure(esize * n_el), "alloc B");
-    if (fused) {
-        TRY_HIP(bc.ensure(esize * n_el), "alloc C");
-        TRY_HIP(bd.ensure(esize * n_el), "alloc D");
-    }
+    if (!chain || ch_bufs > 1) TRY_HIP(bb.ensure(esize * n_el), "alloc B");
+    if (fused || ch_bufs > 2) TRY_HIP(bc.ensure(esize * n_el), "alloc C");
+    if (fused || ch_bufs > 3) TRY_HIP(bd.ensure(esize * n_el), "alloc D");
     TRY_HIP(phi0.ensure(16 * n_el), "alloc phi0");
-    TRY_HIP(partials.ensure(sizeof(double) * 3 * (size_t)n_tiles * s_pad), "alloc partials");
+    // the chain's correlation partials of all steps of a graph are summed together
+    const int64_t part_stride = 3 * (int64_t)n_tiles * s_pad;
+    TRY_HIP(partials.ensure(sizeof(double) * (size_t)part_stride * (chain ? kStepsPerGraph : 1)), "alloc partials");
     TRY_HIP(counter.ensure(sizeof(int32_t) * 64), "alloc counter");
     TRY_HIP(coef.ensure(sizeof(PassCoef) * (size_t)n_passes * ni), "alloc coef");
     TRY_HIP(norm2_all.ensure(sizeof(double) * (size_t)ni * a.n_steps * a.s_user), "alloc norm2");
@@ -683,25 +702,30 @@ tbpm_status Engine::run(const RunArgs &a) {
         hj[1] = nullptr;
         TRY_HIP(hipMemcpyAsync(jc_tab.ptr, hj, jc_bytes, hipMemcpyHostToDevice, a.stream), "upload correlation table");
     }
-    const int64_t n_el_all = mat.n_rows * s_pad;
+    // states in blocks of 2^log2sb (one block of all of them outside the chain)
+    const int32_t log2sb = chain ? cs.log2sb() : log2s;
+    last_log2sb = log2sb;
+    // elements of the states that are propagated (whole blocks come first)
+    const int64_t n_el_all = chain ? mat.n_rows * cs.n_blk * cs.vs : n_el;
+    void *bufptr[5] = {v.ptr, ba.ptr, bb.ptr, bc.ptr, bd.ptr};
     int32_t log2sp = 0;
     while ((1 << log2sp) < a.jc_states) ++log2sp;
     // per-step work after the correlation: quasi-eigenstate accumulation and
     // the optical-conductivity correlation
     auto enqueue_qe = [&](hipStream_t s) -> tbpm_status {
         if (a.n_qe > 0) {
-            hipError_t e = launch_qe_accum(fp32, v.ptr, a.qe_acc, n_el_all, (const double *)qe_coef.ptr, a.n_qe,
+            hipError_t e = launch_qe_accum(fp32, bufptr[0], a.qe_acc, n_el, n_el_all, (const double *)qe_coef.ptr, a.n_qe,
                                            (const int32_t *)counter.ptr, s);
             if (e != hipSuccess) return hip_fail(e, "launch quasi-eigenstate accumulation");
         }
         if (a.jc_states > 0) {
-            hipError_t e = launch_jcorr(fp32, (const TileDesc *)tiles.ptr, (int32_t)h_tiles.size(), log2sp, a.jc_states,
-                                        log2s, v.ptr, mat.slice_off, mat.col, a.jc_val, (double *)partials.ptr, s);
+            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp, a.jc_states, log2sb, mat.n_rows, bufptr[0],
+                                        mat.slice_off, mat.col, a.jc_val, (double *)partials.ptr, s);
             if (e != hipSuccess) return hip_fail(e, "launch current correlation");
             ReduceParams jr{};
             jr.partials = (const double *)partials.ptr;
-            jr.n_tiles = (int32_t)h_tiles.size();
-            jr.inst_tile0 = (const int32_t *)inst_tile0.ptr;
+            jr.n_tiles = n_tiles;
+            jr.inst_tile0 = (const int32_t *)(chain ? ch_tile0.ptr : inst_tile0.ptr);
             jr.log2s = log2sp;
             jr.s_user = a.jc_states;
             jr.n_steps = a.n_steps;
@@ -716,14 +740,13 @@ tbpm_status Engine::run(const RunArgs &a) {
     };
     TRY_HIP(hipEventRecord(staging_done, a.stream), "record staging");
 
-    void *bufptr[5] = {v.ptr, ba.ptr, bb.ptr, bc.ptr, bd.ptr};
     const double *const *d_psi0 = (const double *const *)ptr_tab.ptr;
     double *const *d_corr = (double *const *)ptr_tab.ptr + ni;
     double *const *d_norm2 = (double *const *)ptr_tab.ptr + 2 * ni;
 
     // C_0
     InitParams ip{};
-    ip.tiles = (const TileDesc *)tiles.ptr;
+    ip.tiles = (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr);
     ip.n_tiles = n_tiles;
     ip.log2s = log2s;
     ip.s_user = a.s_user;
@@ -734,11 +757,13 @@ tbpm_status Engine::run(const RunArgs &a) {
     ip.partials = (double *)partials.ptr;
     ip.counter = (int32_t *)counter.ptr;
     ip.perm = mat.perm;
+    ip.log2sb = log2sb;
+    ip.n_rows = mat.n_rows;
     TRY_HIP(launch_init(fp32, ip, a.stream), "launch init");
     ReduceParams rp{};
     rp.partials = (const double *)partials.ptr;
     rp.n_tiles = n_tiles;
-    rp.inst_tile0 = (const int32_t *)inst_tile0.ptr;
+    rp.inst_tile0 = (const int32_t *)(chain ? ch_tile0.ptr : inst_tile0.ptr);
     rp.log2s = log2s;
     rp.s_user = a.s_user;
     rp.n_steps = a.n_steps;
@@ -770,6 +795,11 @@ tbpm_status Engine::run(const RunArgs &a) {
     };
     std::vector<Launch> sched;
     const bool last_pair = fused && n_passes >= 4 && !a.ckpt && a.n_qe == 0 && a.jc_states == 0;
+    // a step leaves psi in another buffer
+    const bool psi_moves = last_pair || chain;
+    // steps whose correlation is summed by one launch: all of a graph's, or one
+    // where each step's own sample number is needed
+    const bool per_step = a.ckpt || a.n_qe > 0 || a.jc_states > 0;
     if (fused) {
         const int n_mid = n_passes - 3;
         int cur = 0, prev = -1;  // buffers of b_{j+1} and b_{j+2} (0: psi, -1: none)
@@ -809,7 +839,66 @@ tbpm_status Engine::run(const RunArgs &a) {
     // one time step; consecutive launches walk the tiles in opposite
     // directions (walk: the direction of the next launch)
     int32_t walk = 0;
+    // one time step by the chain kernel; `local`: its place among the steps whose
+    // correlation is summed together
+    auto chain_step = [&](hipStream_t s, int32_t local) -> tbpm_status {
+        ChainParams cp = chain_params(cs);
+        cp.xcd_remap = cfg.xcd_remap;
+        cp.alt = 1;  // c_j = (-i)^j times a real number
+        int x = 0, b2 = -1, p0 = 0;
+        for (size_t l = 0; l < cs.depths.size(); ++l) {
+            const int32_t d = cs.depths[l];
+            const bool last = l + 1 == cs.depths.size();
+            auto free_buf = [&](int k) {  // the k-th lowest work buffer that is not read
+                for (int b = 1; b <= 4; ++b)
+                    if (b != x && b != b2 && k-- == 0) return b;
+                return -1;
+            };
+            const int o1 = free_buf(0), o2 = free_buf(1);
+            cp.depth = d;
+            cp.first = l == 0;
+            cp.turned = (n_passes - 1 - p0) & 1;  // the first order of this launch is j = n_passes - 1 - p0
+            cp.reverse = walk;
+            walk ^= 1;
+            cp.x = bufptr[x];
+            cp.v = bufptr[0];
+            cp.b2 = b2 >= 0 ? bufptr[b2] : nullptr;
+            cp.coef = (const PassCoef *)coef.ptr + (size_t)p0 * ni;
+            cp.out_prev = last ? nullptr : bufptr[o1];
+            cp.out_last = last ? bufptr[o1] : bufptr[o2];
+            cp.partials = last ? (double *)partials.ptr + (int64_t)local * part_stride : nullptr;
+            cp.phi0 = (const double *)phi0.ptr;
+            cp.ckpt = a.ckpt;
+            cp.ckpt_slot = a.ckpt ? (const int32_t *)ckpt_slot.ptr : nullptr;
+            cp.counter = (const int32_t *)counter.ptr;
+            cp.perm = mat.perm;
+            cp.ckpt_stride = mat.n_rows * a.s_user;
+            cp.s_user = a.s_user;
+            tbpm_status cst = chain_launch(fp32, cs, cp, s);
+            if (cst != TBPM_OK) return cst;
+            if (last) std::swap(bufptr[0], bufptr[o1]);
+            b2 = o1;
+            x = o2;
+            p0 += d;
+        }
+        return TBPM_OK;
+    };
+    auto chain_steps = [&](hipStream_t s, int32_t steps) -> tbpm_status {
+        const int32_t sum = per_step ? 1 : steps;
+        for (int32_t q = 0; q < steps; ++q) {
+            tbpm_status cst = chain_step(s, per_step ? 0 : q);
+            if (cst != TBPM_OK) return cst;
+            if ((q + 1) % sum == 0) {
+                hipError_t e = launch_chain_reduce(ni, sum, part_stride, rp, (int32_t *)counter.ptr, s);
+                if (e != hipSuccess) return hip_fail(e, "launch reduce");
+                if (per_step) cst = enqueue_qe(s);
+                if (cst != TBPM_OK) return cst;
+            }
+        }
+        return TBPM_OK;
+    };
     auto enqueue_step = [&](hipStream_t s) -> tbpm_status {
+        if (chain) return chain_steps(s, 1);
         if (fused) {
             for (size_t q = 0; q < sched.size(); ++q) {
                 const Launch &l = sched[q];
@@ -957,16 +1046,19 @@ tbpm_status Engine::run(const RunArgs &a) {
             key.tiles_unit = tiles_unit;
             key.lds_units = fused ? fu_lds_units : (staged ? stage_units : 0);
 
+            key.chain_depth = chain ? ch.depth : 0;
+            key.chain_grp = chain ? cs.n_grp : 0;
             key.n_steps = a.n_steps;
             key.n_qe = a.n_qe;
             key.jc_states = a.jc_states;
             key.ckpt = a.ckpt;
-            const void *kb[22] = {v.ptr,       ba.ptr,      bb.ptr,        phi0.ptr,    partials.ptr, coef.ptr,
+            const void *kb[31] = {v.ptr,       ba.ptr,      bb.ptr,        phi0.ptr,    partials.ptr, coef.ptr,
                                   tiles.ptr,   norm2_all.ptr, bc.ptr,      bd.ptr,      st_uoff.ptr,  st_ucol.ptr,
                                   st_lidx.ptr, fu_hidx.ptr, fu_n1.ptr,     fu_hoff.ptr, fu_hw.ptr,
                                   a.ckpt ? ckpt_slot.ptr : nullptr, a.n_qe > 0 ? qe_coef.ptr : nullptr,
                                   a.n_qe > 0 ? a.qe_acc : nullptr, a.jc_states > 0 ? a.jc_val : nullptr,
-                                  a.jc_states > 0 ? jc_norm.ptr : nullptr};
+                                  a.jc_states > 0 ? jc_norm.ptr : nullptr, ch_tiles.ptr, ch_tile0.ptr, ch_cnt.ptr,
+                                  ch_toff.ptr, ch_loff.ptr, ch_rowmap.ptr, ch_lidx.ptr, ch_tval.ptr, ch_tons.ptr};
             static_assert(sizeof(kb) == sizeof(key.bufs), "graph key buffers");
             std::memcpy(key.bufs, kb, sizeof(kb));
             // Graphs of kStepsPerGraph time steps (small operators are bound by
@@ -987,7 +1079,10 @@ tbpm_status Engine::run(const RunArgs &a) {
                 TRY_HIP(hipStreamBeginCapture(capture_stream, hipStreamCaptureModeThreadLocal), "begin capture");
                 walk = 0;  // a graph of an even number of launches keeps the alternation across replays
                 tbpm_status cst = TBPM_OK;
-                for (int32_t q = 0; q < steps && cst == TBPM_OK; ++q) cst = enqueue_step(capture_stream);
+                if (chain)
+                    cst = chain_steps(capture_stream, steps);
+                else
+                    for (int32_t q = 0; q < steps && cst == TBPM_OK; ++q) cst = enqueue_step(capture_stream);
                 hipGraph_t g = nullptr;
                 hipError_t ee = hipStreamEndCapture(capture_stream, &g);
                 if (cst != TBPM_OK) {
@@ -1004,13 +1099,13 @@ tbpm_status Engine::run(const RunArgs &a) {
                 gkey = key;
                 return TBPM_OK;
             };
-            // With the last pair a step moves psi to another buffer, so a graph
+            // With the last pair, or the chain, a step moves psi to another buffer, so a graph
             // replayed more than once must hold an even number of steps: the
             // remainder is then one graph of n_rest steps, launched once (the
             // full graphs, when replayed, hold kStepsPerGraph steps, an even
             // number, and leave the buffers as they found them).
             static_assert(kStepsPerGraph % 2 == 0, "a replayed step graph must hold an even number of steps");
-            const int32_t rest_steps = last_pair ? std::max<int32_t>(n_rest, 1) : 1;
+            const int32_t rest_steps = psi_moves ? std::max<int32_t>(n_rest, 1) : 1;
             st = cached(graph_exec, graph_key, spg);
             if (st == TBPM_OK && n_rest > 0) st = cached(graph_exec1, graph_key1, rest_steps);
             if (st != TBPM_OK) return st;
@@ -1022,7 +1117,8 @@ tbpm_status Engine::run(const RunArgs &a) {
 
     last_s_pad = s_pad;
     last_fp32 = fp32 ? 1 : 0;
-    last_staged = fused ? 2 : (staged ? 1 : 0);
+    last_staged = chain ? 3 : (fused ? 2 : (staged ? 1 : 0));
+    last_chain = cs;
     last_vs = vs;
     last_log2ub = log2ub;
     if (a.flags & TBPM_FLAG_ASYNC) return TBPM_OK;
@@ -1051,8 +1147,14 @@ tbpm_status Engine::run(const RunArgs &a) {
     return TBPM_OK;
 }
 
+bool Engine::series_chain(int32_t K, int32_t s_user, ChainShape &cs) {
+    // as for propagations: 17 orders stand for a time step
+    const bool want = cfgs[0].fused > 0 || (!cfg_set[0] && K - 1 > 17 * kChainAutoSteps);
+    return want && K >= 4 && chain_prepare(s_user, false, K - 1, cs) == TBPM_OK;
+}
+
 tbpm_status Engine::apply_series(const std::vector<double> &a_in, double f, int32_t log2s, const void *src, void *dst,
-                                 void *w0, void *w1, hipStream_t st, void *w2, void *w3) {
+                                 void *w0, void *w1, hipStream_t st, void *w2, void *w3, const ChainShape *cs) {
     // Clenshaw for sum_{k<K} a_k T_k(x), x = H/f (zero-padded to K >= 3):
     //   b_{K-2} = a_{K-2} v + 2 a_{K-1} x v                       (FIRST)
     //   b_{K-3} = (a_{K-3} - a_{K-1}) v + 2 x b_{K-2}             (NOB2)
@@ -1088,14 +1190,14 @@ tbpm_status Engine::apply_series(const std::vector<double> &a_in, double f, int3
     // four rotating blocks (a pair's outputs go to the two blocks it does not
     // read), the last pair writing the result; an order left over runs alone.
     const int32_t s_pad = 1 << log2s;
-    bool pairs = w2 && w3 && K >= 4 && cfgs[0].fused > 0;
+    bool pairs = !cs && w2 && w3 && K >= 4 && cfgs[0].fused > 0;
     int32_t pvs = 1, log2pvs = 0;
     while (pvs < cfgs[0].vec && pvs < s_pad && pvs < 4) {
         pvs <<= 1;
         ++log2pvs;
     }
     if (pairs && build_fused_tiles(s_pad, log2s - log2pvs, 16 * pvs, cfgs[0].fused) != TBPM_OK) pairs = false;
-    if (!pairs && (!tiles.ptr || tiles_s == 0)) {
+    if (!pairs && !cs && (!tiles.ptr || tiles_s == 0)) {
         tbpm_status s = build_tiles(s_pad, cfg.wg_chunks, 1);
         if (s != TBPM_OK) return s;
     }
@@ -1107,6 +1209,36 @@ tbpm_status Engine::apply_series(const std::vector<double> &a_in, double f, int3
     for (size_t i = 0; i < seq.size(); ++i) hc[i] = seq[i].c;
     TRY_HIP(hipMemcpyAsync(coef.ptr, hc, cb, hipMemcpyHostToDevice, st), "upload series coefficients");
     TRY_HIP(hipEventRecord(staging_done, st), "record staging");
+    if (cs) {
+        tbpm_status s = chain_values(false, st);
+        if (s != TBPM_OK) return s;
+        ChainParams cp = chain_params(*cs);
+        cp.xcd_remap = cfgs[0].xcd_remap;
+        cp.v = src;
+        void *wb[4] = {w0, w1, w2, w3};
+        int x = -1, b2 = -1, p0 = 0;  // buffers of b_{k+1} (-1: the input) and b_{k+2} (-1: none)
+        for (size_t l = 0; l < cs->depths.size(); ++l) {
+            const int32_t d = cs->depths[l];
+            const bool last = l + 1 == cs->depths.size();
+            int fr[2], nf = 0;
+            for (int q = 0; q < 4 && nf < 2; ++q)
+                if (q != x && q != b2) fr[nf++] = q;
+            cp.depth = d;
+            cp.first = l == 0;
+            cp.x = x < 0 ? src : wb[x];
+            cp.b2 = b2 < 0 ? nullptr : wb[b2];
+            cp.coef = (const PassCoef *)coef.ptr + p0;
+            cp.out_prev = last ? nullptr : wb[fr[0]];
+            cp.out_last = last ? dst : wb[fr[1]];
+            cp.reverse = (int32_t)(l & 1);
+            s = chain_launch(false, *cs, cp, st);
+            if (s != TBPM_OK) return s;
+            b2 = fr[0];
+            x = fr[1];
+            p0 += d;
+        }
+        return TBPM_OK;
+    }
     PassParams pp{};
     pp.tiles = (const TileDesc *)tiles.ptr;
     pp.n_tiles = (int32_t)h_tiles.size();
@@ -1239,9 +1371,35 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         s_pad <<= 1;
         ++log2s;
     }
-    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || tiles_s != s_pad)
+    const bool chain = last_staged == 3;
+    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || (!chain && tiles_s != s_pad) ||
+        (chain && ch.depth == 0))
         return fail(TBPM_E_ARG, "tbpm_bench_pass needs a prior tbpm_propagate with the same n_states and precision");
     cfg = cfgs[fp32 ? 1 : 0];
+    if (chain) {
+        // an interior launch: b_{j+1} in B, b_{j+2} in A, outputs to C and D
+        TRY_HIP(ba.ensure(v.bytes), "alloc A");
+        TRY_HIP(bb.ensure(v.bytes), "alloc B");
+        TRY_HIP(bc.ensure(v.bytes), "alloc C");
+        TRY_HIP(bd.ensure(v.bytes), "alloc D");
+        ChainParams cp = chain_params(last_chain);
+        cp.xcd_remap = cfg.xcd_remap;
+        cp.alt = 1;
+        cp.depth = *std::max_element(last_chain.depths.begin(), last_chain.depths.end());
+        cp.v = v.ptr;
+        cp.coef = (const PassCoef *)coef.ptr;  // the first orders' coefficients: finite, bounded
+        for (int32_t i = 0; i < n_launch; ++i) {
+            const bool odd = (i & 1) != 0;
+            cp.x = odd ? bd.ptr : bb.ptr;
+            cp.b2 = odd ? bc.ptr : ba.ptr;
+            cp.out_prev = odd ? ba.ptr : bc.ptr;
+            cp.out_last = odd ? bb.ptr : bd.ptr;
+            cp.reverse = odd ? 1 : 0;
+            tbpm_status s = chain_launch(fp32, last_chain, cp, stream);
+            if (s != TBPM_OK) return s;
+        }
+        return TBPM_OK;
+    }
     PassParams pp{};
     pp.tiles = (const TileDesc *)tiles.ptr;
     pp.n_tiles = (int32_t)h_tiles.size();

@@ -585,6 +585,186 @@ bool two_hop_tables(const std::vector<int64_t> &slice_off, const std::vector<int
 }
 
 // ---------------------------------------------------------------------------
+// tiles of the chain kernel
+// ---------------------------------------------------------------------------
+// The parts of at most T rows of every member.
+static std::vector<TileDesc> chain_parts(const std::vector<int64_t> &inst_row0, int64_t T) {
+    std::vector<TileDesc> tops;
+    std::vector<std::pair<int64_t, int64_t>> stack;
+    for (int32_t i = 0; i + 1 < (int32_t)inst_row0.size(); ++i) {
+        stack.assign(1, {inst_row0[i], inst_row0[i + 1]});
+        while (!stack.empty()) {
+            const auto [lo, hi] = stack.back();
+            stack.pop_back();
+            if (hi <= lo) continue;
+            if (hi - lo > T) {
+                const int64_t mid = lo + (hi - lo) / 2;
+                stack.push_back({mid, hi});
+                stack.push_back({lo, mid});
+            } else {
+                tops.push_back(TileDesc{lo, (int32_t)(hi - lo), i});
+            }
+        }
+    }
+    return tops;
+}
+
+// The local rows of a tile: its own, then shell after shell (each sorted); c[h]
+// the rows within h hops.  Stops, and returns false, once a bound is passed at
+// hop c_h = reached + 1.  A row that is not local carries another tag.
+static bool chain_shells(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
+                         const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders,
+                         const TileDesc &td, int32_t D, int64_t max_eval, int64_t max_rows, std::vector<int32_t> &tag,
+                         int32_t visit, std::vector<uint32_t> &rows, std::vector<int32_t> &c, int32_t &reached) {
+    const int64_t SR = kSliceRows;
+    const std::vector<int32_t> &ord = orders[td.inst];
+    const int64_t m0 = inst_row0[td.inst];
+    rows.clear();
+    for (int64_t r = td.row0; r < td.row0 + td.rows; ++r) {
+        const int64_t g = ord.empty() ? r : m0 + ord[r - m0];
+        tag[g] = visit;
+        rows.push_back((uint32_t)g);
+    }
+    c[0] = td.rows;
+    reached = 0;
+    if (td.rows > max_eval) return false;
+    size_t from = 0;
+    for (int32_t h = 1; h <= D; ++h) {
+        const size_t end = rows.size();
+        for (size_t p = from; p < end; ++p) {
+            const int64_t r = rows[p];
+            const int64_t s0 = slice_off[r / SR], w = (slice_off[r / SR + 1] - s0) / SR;
+            for (int64_t e = 0; e < w; ++e) {
+                const int32_t g = col[s0 + e * SR + r % SR];
+                if (tag[g] != visit) {
+                    tag[g] = visit;
+                    rows.push_back((uint32_t)g);
+                }
+            }
+        }
+        from = end;
+        std::sort(rows.begin() + end, rows.end());
+        c[h] = (int32_t)rows.size();
+        // hop h may be the last one staged, or one more that is evaluated
+        if ((int64_t)rows.size() > max_rows) return false;
+        reached = h;
+        if (h < D && (int64_t)rows.size() > max_eval) return false;
+    }
+    return true;
+}
+
+int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
+                    const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
+                    int32_t cap, int64_t max_eval, int64_t max_rows) {
+    const std::vector<TileDesc> tops = chain_parts(inst_row0, T);
+    std::vector<int32_t> tag(inst_row0.back(), -1), c(cap + 1), depth;
+    std::vector<uint32_t> rows;
+    const size_t n = tops.size(), samples = std::min<size_t>(n, 48);
+    for (size_t k = 0; k < samples; ++k) {
+        int32_t reached = 0;
+        (void)chain_shells(slice_off, col, inst_row0, orders, tops[k * n / samples], cap, max_eval, max_rows, tag,
+                           (int32_t)k, rows, c, reached);
+        depth.push_back(reached);
+    }
+    std::sort(depth.begin(), depth.end());
+    return depth.empty() ? 0 : depth[depth.size() / 16];
+}
+
+void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
+                  const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
+                  int32_t D, int64_t max_eval, int64_t max_rows, ChainTables &t) {
+    const int64_t SR = kSliceRows;
+    const int32_t n_inst = (int32_t)inst_row0.size() - 1;
+    const int64_t n = inst_row0[n_inst];
+    t = ChainTables{};
+    // the parts of at most T rows; those past a bound are halved further
+    for (int32_t i = 0; i < n_inst; ++i)
+        if (!orders[i].empty()) t.contiguous = false;
+    const std::vector<TileDesc> tops = chain_parts(inst_row0, T);
+    const int64_t nt0 = (int64_t)tops.size();
+    const int threads = (int)std::max<int64_t>(1, std::min<int64_t>(nt0, host_threads((int64_t)col.size())));
+    // each chunk's tiles: counts, local rows and local indices; a row that is
+    // not local to the tile at hand carries another tile's tag
+    struct Part {
+        std::vector<TileDesc> tiles;
+        std::vector<int32_t> cnt;
+        std::vector<uint32_t> rows;
+        std::vector<uint16_t> lidx;
+        bool ok = true;
+    };
+    std::vector<Part> parts(threads);
+    run_chunks(nt0, threads, [&](int k, int64_t lo, int64_t hi) {
+        Part &pt = parts[k];
+        std::vector<int32_t> tag(n, -1);
+        std::vector<uint16_t> at(n);
+        std::vector<uint32_t> rows;
+        std::vector<TileDesc> todo;
+        std::vector<int32_t> c(D + 1);
+        int32_t visit = 0;
+        for (int64_t q = lo; q < hi && pt.ok; ++q) {
+            todo.assign(1, tops[q]);
+            while (!todo.empty()) {
+                const TileDesc td = todo.back();
+                todo.pop_back();
+                int32_t reached = 0;
+                const bool fits = chain_shells(slice_off, col, inst_row0, orders, td, D, max_eval, max_rows, tag,
+                                               ++visit, rows, c, reached);
+                if (!fits) {
+                    if (td.rows < 8) {
+                        pt.ok = false;
+                        return;
+                    }
+                    todo.push_back(TileDesc{td.row0 + td.rows / 2, td.rows - td.rows / 2, td.inst});
+                    todo.push_back(TileDesc{td.row0, td.rows / 2, td.inst});
+                    continue;
+                }
+                for (size_t l = 0; l < rows.size(); ++l) at[rows[l]] = (uint16_t)l;
+                const size_t i0 = pt.lidx.size();
+                pt.lidx.resize(i0 + 4 * (size_t)c[D - 1]);
+                for (int32_t l = 0; l < c[D - 1]; ++l) {
+                    const int64_t r = rows[l];
+                    const int64_t s0 = slice_off[r / SR], w = (slice_off[r / SR + 1] - s0) / SR;
+                    uint16_t *li = &pt.lidx[i0 + 4 * (size_t)l];
+                    for (int64_t e = 0; e < 4; ++e) li[e] = e < w ? at[col[s0 + e * SR + r % SR]] : (uint16_t)l;
+                }
+                pt.rows.insert(pt.rows.end(), rows.begin(), rows.end());
+                pt.cnt.insert(pt.cnt.end(), c.begin(), c.end());
+                pt.tiles.push_back(td);
+            }
+        }
+    });
+    int64_t n_rows = 0, n_eval = 0;
+    for (const Part &pt : parts) {
+        if (!pt.ok) return;
+        n_rows += (int64_t)pt.rows.size();
+        n_eval += (int64_t)pt.lidx.size() / 4;
+    }
+    if (n_rows >= (int64_t)INT32_MAX) return;
+    t.depth = D;
+    t.max_stage.assign(D + 1, 0);
+    t.inst_tile0.assign(n_inst + 1, 0);
+    t.rowmap.reserve(n_rows);
+    t.lidx.reserve(4 * n_eval);
+    for (const Part &pt : parts) {
+        int64_t ro = (int64_t)t.rowmap.size(), le = (int64_t)t.lidx.size() / 4;
+        for (size_t q = 0; q < pt.tiles.size(); ++q) {
+            const int32_t *c = &pt.cnt[q * (D + 1)];
+            for (int32_t h = 0; h <= D; ++h) t.max_stage[h] = std::max(t.max_stage[h], c[h]);
+            t.toff.push_back((int32_t)ro);
+            t.loff.push_back((int32_t)le);
+            ro += c[D];
+            le += c[D - 1];
+            t.tiles.push_back(pt.tiles[q]);
+            t.inst_tile0[pt.tiles[q].inst + 1] = (int32_t)t.tiles.size();
+        }
+        t.cnt.insert(t.cnt.end(), pt.cnt.begin(), pt.cnt.end());
+        t.rowmap.insert(t.rowmap.end(), pt.rows.begin(), pt.rows.end());
+        t.lidx.insert(t.lidx.end(), pt.lidx.begin(), pt.lidx.end());
+    }
+    for (int32_t i = 0; i < n_inst; ++i) t.inst_tile0[i + 1] = std::max(t.inst_tile0[i + 1], t.inst_tile0[i]);
+}
+
+// ---------------------------------------------------------------------------
 // locality order: recursive bisection of the row graph
 // ---------------------------------------------------------------------------
 std::vector<int32_t> bisection_order(int64_t n, const int64_t *row_ptr, const int32_t *col, int32_t leaf,

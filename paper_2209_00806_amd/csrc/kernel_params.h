@@ -130,6 +130,63 @@ struct FusedParams {
     double *partials;
 };
 
+// Several Clenshaw orders per launch (chain.hip).
+constexpr int kChainMaxDepth = 24;  // orders per launch
+constexpr int kChainWidth = 4;      // most stored elements per row
+// Threads of a workgroup and local rows a thread evaluates: a tile's rows up to
+// depth - 1 hops away are at most chain_rows.
+constexpr int kChainRowsPerThread = 2;
+constexpr int chain_threads(bool cplx) { return cplx ? 256 : 512; }
+constexpr int chain_rows(bool cplx) { return chain_threads(cplx) * kChainRowsPerThread; }
+
+struct ChainParams {
+    const TileDesc *tiles;
+    int32_t n_tiles;
+    int32_t n_blk;         // state blocks of VS states
+    int32_t n_grp, grp_blk;  // workgroups per tile and the state blocks each takes in turn
+    int32_t xcd_remap;
+    int32_t reverse;       // walk the tiles last to first (see tile_of_block)
+    int32_t depth;         // orders of this launch
+    int32_t table_depth;   // orders the tile tables serve
+    int32_t contiguous;    // own rows are row0 .. row0 + rows - 1 (else through rowmap)
+    int32_t n_inst;
+    uint32_t n_rows;
+    const int32_t *cnt;    // [n_tiles][table_depth + 1]: local rows up to h hops away
+    const int32_t *toff;   // [n_tiles] offset of the tile's local rows in rowmap
+    const int32_t *loff;   // [n_tiles] offset of the tile's rows in lidx, tval and tons
+    const uint32_t *rowmap;
+    const uint16_t *lidx;  // [row][4] local indices of the stored elements
+    const void *tval;      // per tile [width][rows]
+    const void *tons;
+    const void *x;         // b_{j+1} (or psi), state blocks [n_blk][n_rows][VS]
+    const void *v;         // psi; null: the alpha terms are absent
+    const void *b2;        // b_{j+2}, or null
+    void *out_last, *out_prev;  // the last order's and the last but one's outputs on own rows, or null
+    void *out_all;         // or: every order but the last at out_all + k out_stride bytes
+    int64_t out_stride;
+    // alpha of the orders: with alt, real and imaginary in turn (real first, or
+    // imaginary first with turned); without, all real.  beta is real except in
+    // the first order of a time step (first), which may have any alpha and beta.
+    int32_t alt, turned, first;
+    const PassCoef *coef;  // [depth][n_inst]
+    // fused correlation of the last order, or null
+    const double *phi0;    // complex128, in state blocks
+    double *partials;      // [S][3][n_tiles]
+    // stored states of the fused correlation's launch, as in PassParams
+    double *ckpt;
+    const int32_t *ckpt_slot;
+    const int32_t *counter;
+    const int32_t *perm;
+    int64_t ckpt_stride;
+    int32_t s_user;
+};
+
+struct ChainTileTab {
+    const int32_t *cnt, *toff, *loff;
+    const uint32_t *rowmap;
+    int32_t table_depth, width;
+};
+
 struct InitParams {
     const TileDesc *tiles;
     int32_t n_tiles;
@@ -142,6 +199,9 @@ struct InitParams {
     double *partials;            // [S][3][n_tiles]
     int32_t *counter;
     const int32_t *perm;         // internal row -> caller's row in its member, or null
+    // states in blocks of 2^log2sb, [block][n_rows][2^log2sb] (log2sb = log2s: one block)
+    int32_t log2sb;
+    int64_t n_rows;
 };
 
 struct ReduceParams {

@@ -377,7 +377,6 @@ __global__ __launch_bounds__(kWG) void k_init(const InitParams p) {
     const int log2s = p.log2s;
     const int64_t smask = (1 << log2s) - 1;
     const int64_t n_el = (int64_t)td.rows << log2s;
-    const int64_t e0 = td.row0 << log2s;
     const d2 *__restrict__ src = (const d2 *)p.psi0[td.inst];
     const int64_t lrow0 = td.row0 - p.inst_row0[td.inst];
     C *v = (C *)p.v;
@@ -393,14 +392,18 @@ __global__ __launch_bounds__(kWG) void k_init(const InitParams p) {
         C o;
         o.x = (R)a.x;
         o.y = (R)a.y;
-        v[e0 + e] = o;
-        phi0[e0 + e] = a;
+        const int64_t at = state_index(td.row0 + (e >> log2s), s, p.log2sb, p.n_rows);
+        v[at] = o;
+        phi0[at] = a;
         const double ox = (double)o.x, oy = (double)o.y;
         dre = fma(a.x, ox, fma(a.y, oy, dre));
         dim = fma(a.x, oy, fma(-a.y, ox, dim));
         nrm = fma(ox, ox, fma(oy, oy, nrm));
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicExch(p.counter, 0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        atomicExch(p.counter, 0);
+        atomicExch(p.counter + 1, 0);
+    }
     block_state_partials(dre, dim, nrm, log2s, p.partials, blockIdx.x, p.n_tiles);
 }
 

@@ -186,6 +186,8 @@ tbpm_status propagate_noalloc(tbpm_hamiltonian *H, const double *psi0, int32_t s
     ip.partials = partials;
     ip.counter = counter;
     ip.perm = eng.mat.perm;
+    ip.log2sb = log2s;
+    ip.n_rows = n;
     e = launch_init(fp32, ip, st);
     if (e != hipSuccess) return hip_fail(e, "launch init");
     ReduceParams rp{};

@@ -22,14 +22,14 @@ namespace {
 
 template <typename R>
 __global__ __launch_bounds__(kWG) void k_qe_accum(const void *__restrict__ state, d2 *__restrict__ acc, int64_t n_el,
-                                                  const d2 *__restrict__ coef, int n_e,
+                                                  int64_t n_used, const d2 *__restrict__ coef, int n_e,
                                                   const int32_t *__restrict__ counter) {
     using C = typename CxT<R>::T;
     const C *psi = (const C *)state;
     const int k = *(volatile const int32_t *)counter;
     const d2 *row = coef + (int64_t)k * n_e;
     const int64_t stride = (int64_t)gridDim.x * kWG;
-    for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_el; e += stride) {
+    for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_used; e += stride) {
         const C x = psi[e];
         const double xr = (double)x.x, xi = (double)x.y;
         for (int j = 0; j < n_e; ++j) {
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kWG) void k_qe_accum(const void *__restrict__ state
 // Per-block partial sums of |acc|^2 per state: block (b, j) covers rows
 // [b * rows_per_block, ...) of energy j; out[j][s][3][n_blk] as written by
 // block_state_partials (component 2 holds the squared norm).
-__global__ __launch_bounds__(kWG) void k_qe_partials(const d2 *__restrict__ acc, int64_t n_rows, int log2s,
+__global__ __launch_bounds__(kWG) void k_qe_partials(const d2 *__restrict__ acc, int64_t n_rows, int log2s, int log2sb,
                                                      int64_t rows_per_block, int n_blk, double *__restrict__ out) {
     const int j = blockIdx.y;
     const int S = 1 << log2s;
@@ -54,7 +54,10 @@ __global__ __launch_bounds__(kWG) void k_qe_partials(const d2 *__restrict__ acc,
     const int64_t e1 = min(n_el, e0 + (rows_per_block << log2s));
     const d2 *a = acc + (int64_t)j * n_el;
     double nrm = 0.0;
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += kWG) nrm = fma(a[e].x, a[e].x, fma(a[e].y, a[e].y, nrm));
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += kWG) {
+        const d2 v = a[state_index(e >> log2s, (int)(e & (S - 1)), log2sb, n_rows)];
+        nrm = fma(v.x, v.x, fma(v.y, v.y, nrm));
+    }
     block_state_partials(0.0, 0.0, nrm, log2s, out + (int64_t)j * S * 3 * n_blk, blockIdx.x, n_blk);
 }
 
@@ -79,7 +82,7 @@ __global__ __launch_bounds__(kWG) void k_qe_norms(const double *__restrict__ par
 
 // out[j][perm[r]][s] = acc[j][r][s] / sqrt(norm2[j][s]) for s < s_user
 __global__ __launch_bounds__(kWG) void k_qe_scatter(const d2 *__restrict__ acc, const double *__restrict__ norm2,
-                                                    int64_t n_rows, int log2s, int s_user, int n_e,
+                                                    int64_t n_rows, int log2s, int log2sb, int s_user, int n_e,
                                                     const int32_t *__restrict__ perm, d2 *__restrict__ out) {
     const int64_t n_el = n_rows << log2s;
     const int64_t total = (int64_t)n_e * n_rows * s_user;
@@ -90,7 +93,7 @@ __global__ __launch_bounds__(kWG) void k_qe_scatter(const d2 *__restrict__ acc, 
         const int j = (int)(i / ((int64_t)s_user * n_rows));
         const double n2 = norm2[(int64_t)j * s_user + s];
         const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-        const d2 a = acc[(int64_t)j * n_el + (r << log2s) + s];
+        const d2 a = acc[(int64_t)j * n_el + state_index(r, s, log2sb, n_rows)];
         d2 o;
         o.x = a.x * inv;
         o.y = a.y * inv;
@@ -107,26 +110,26 @@ int64_t grid_of(int64_t n) {
 
 }  // namespace
 
-hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, const double *coef, int32_t n_e,
-                           const int32_t *counter, hipStream_t st) {
-    const dim3 grid((unsigned)grid_of(n_el)), block(kWG);
+hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, int64_t n_used, const double *coef,
+                           int32_t n_e, const int32_t *counter, hipStream_t st) {
+    const dim3 grid((unsigned)grid_of(n_used)), block(kWG);
     if (fp32)
-        hipLaunchKernelGGL(k_qe_accum<float>, grid, block, 0, st, state, (d2 *)acc, n_el, (const d2 *)coef, n_e,
+        hipLaunchKernelGGL(k_qe_accum<float>, grid, block, 0, st, state, (d2 *)acc, n_el, n_used, (const d2 *)coef, n_e,
                            counter);
     else
-        hipLaunchKernelGGL(k_qe_accum<double>, grid, block, 0, st, state, (d2 *)acc, n_el, (const d2 *)coef, n_e,
+        hipLaunchKernelGGL(k_qe_accum<double>, grid, block, 0, st, state, (d2 *)acc, n_el, n_used, (const d2 *)coef, n_e,
                            counter);
     return hipGetLastError();
 }
 
 int32_t qe_partial_blocks(int64_t n_rows) { return (int32_t)std::min<int64_t>(4096, std::max<int64_t>(1, n_rows / 256)); }
 
-hipError_t launch_qe_finalize(const double *acc, int64_t n_rows, int32_t log2s, int32_t s_user, int32_t n_e,
-                              const int32_t *perm, double *partials, double *norm2, double *out, hipStream_t st) {
+hipError_t launch_qe_finalize(const double *acc, int64_t n_rows, int32_t log2s, int32_t log2sb, int32_t s_user,
+                              int32_t n_e, const int32_t *perm, double *partials, double *norm2, double *out, hipStream_t st) {
     const int32_t n_blk = qe_partial_blocks(n_rows);
     const int64_t rpb = (n_rows + n_blk - 1) / n_blk;
     hipLaunchKernelGGL(k_qe_partials, dim3((unsigned)n_blk, (unsigned)n_e), dim3(kWG), 0, st, (const d2 *)acc, n_rows,
-                       log2s, rpb, n_blk, partials);
+                       log2s, log2sb, rpb, n_blk, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_qe_norms, dim3((unsigned)(n_e * s_user)), dim3(kWG), 0, st, (const double *)partials, log2s,
@@ -134,7 +137,7 @@ hipError_t launch_qe_finalize(const double *acc, int64_t n_rows, int32_t log2s, 
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_qe_scatter, dim3((unsigned)grid_of((int64_t)n_e * n_rows * s_user)), dim3(kWG), 0, st,
-                       (const d2 *)acc, (const double *)norm2, n_rows, log2s, s_user, n_e, perm, (d2 *)out);
+                       (const d2 *)acc, (const double *)norm2, n_rows, log2s, log2sb, s_user, n_e, perm, (d2 *)out);
     return hipGetLastError();
 }
 

@@ -76,15 +76,26 @@ struct GraphKey {
     int32_t n_tiles = 0, tiles_chunks = 0, tiles_unit = 0, lds_units = 0;
     int32_t n_steps = 0, n_qe = 0, jc_states = 0, steps = 0;
     const void *ckpt = nullptr;
-    const void *bufs[22] = {};
+    const void *bufs[31] = {};
+    int32_t chain_depth = 0, chain_grp = 0;
     bool operator==(const GraphKey &o) const;
 };
+
+// Members of fewer rows keep the caller's order at upload (automatic row order).
+constexpr int64_t kReorderMinRows = 16384;
+// Fewest rows of a chain tile (members of fewer rows are one tile).
+constexpr int32_t kChainMinTile = 64;
+// Handles whose launch configuration nobody chose take several orders per launch
+// from this many time steps on: the tile tables cost about as much as the launches
+// of 8 (2M rows) to 60 (8192 rows) time steps save.
+constexpr int32_t kChainAutoSteps = 64;
 
 struct Engine {
     DevMatrix mat;
     std::vector<int64_t> inst_row0;  // [n_inst + 1]
     tbpm_launch_config cfgs[2] = {{2, 1, 1, 1, 0, 1, 0}, {4, 0, 1, 2, 0, 2, 0}};  // FP64, FP32-mixed
     tbpm_launch_config cfg{2, 1, 1, 1, 0, 1, 0};                                   // the one in use
+    bool cfg_set[2] = {false, false};  // the caller or the autotuner chose the configuration
     // host copy of the sliced ELL columns (for building staged tiles)
     std::vector<int64_t> h_slice_off;
     std::vector<int32_t> h_col;
@@ -96,6 +107,34 @@ struct Engine {
     DevBuf fu_n1, fu_hoff, fu_hw, fu_hidx, bc, bd;
     int32_t fu_lds_units = 0;
     size_t fu_max_rows = 0;
+    // tiles of the chain kernel (several orders per launch): tables on the
+    // device, and their matrix entries (taken anew by every call that uses them)
+    DevBuf ch_tiles, ch_tile0, ch_cnt, ch_toff, ch_loff, ch_rowmap, ch_lidx, ch_tval, ch_tons;
+    struct ChainState {
+        int64_t T = 0;    // rows per tile the tables were built for
+        int32_t cap = 0;  // and the most orders asked for
+        int32_t depth = 0, n_tiles = 0;  // orders they serve (0: no tables)
+        int64_t n_local = 0;             // evaluated rows over all tiles
+        bool contiguous = true;
+        std::vector<int32_t> max_stage;  // [depth + 1]
+    } ch;
+    std::vector<std::vector<int32_t>> ch_orders;  // per member: row order its tiles follow (empty: as stored)
+    struct ChainShape {
+        int32_t vs = 1, n_blk = 1, n_grp = 1;
+        std::vector<int32_t> depths;  // orders of each launch of one evaluation
+        int32_t log2sb() const { return vs == 2 ? 1 : 0; }
+    };
+    void chain_orders();
+    int32_t chain_width() const { return mat.max_width <= 3 ? 3 : 4; }
+    // tables and launch sequence for n_orders orders on s_user states;
+    // TBPM_E_ARG if the operator does not suit the kernel
+    tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs);
+    // whether the vectors (vec bytes each) and tables that the chain needs beyond
+    // the ones held fit the device memory that is free
+    bool chain_fits(const ChainShape &cs, bool fp32, size_t vec);
+    tbpm_status chain_values(bool fp32, hipStream_t st);
+    ChainParams chain_params(const ChainShape &cs) const;
+    tbpm_status chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const;
     int device = -1;
 
     // work buffers
@@ -184,8 +223,13 @@ struct Engine {
     // dst = sum_k a[k] T_k(H/f) src on [rows][2^log2s] FP64 internal blocks
     // (Clenshaw; w0, w1 work blocks, and w2, w3 for two orders per launch
     // when the fused shape is configured; src kept)
+    // cs: as series_chain set it (several orders per launch, states in its
+    // blocks), or null
     tbpm_status apply_series(const std::vector<double> &a, double f, int32_t log2s, const void *src, void *dst,
-                             void *w0, void *w1, hipStream_t st, void *w2 = nullptr, void *w3 = nullptr);
+                             void *w0, void *w1, hipStream_t st, void *w2 = nullptr, void *w3 = nullptr,
+                             const ChainShape *cs = nullptr);
+    // whether a series of K terms on s_user FP64 states takes several orders per launch
+    bool series_chain(int32_t K, int32_t s_user, ChainShape &cs);
     // dst = J src for J given as complex128 values in the ELL layout of H
     tbpm_status apply_ell(const double *jval, int32_t log2s, const void *src, void *dst, hipStream_t st);
     // Haydock (Lanczos) recursion of every column of psi0 (device, caller's
@@ -203,6 +247,8 @@ struct Engine {
     // back-to-back launches of the interior pass on the current buffers
     tbpm_status bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipStream_t stream);
     int32_t last_s_pad = 0, last_fp32 = -1, last_staged = 0, last_vs = 1, last_log2ub = 0;
+    int32_t last_log2sb = 0;  // state blocks of the last run's vectors and quasi-eigenstate accumulators
+    ChainShape last_chain;
 
     tbpm_status build_tiles(int32_t s_pad, int32_t chunks, int32_t vs);
     // staged tiles for s_pad states of unit_bytes per VS states (log2u units per row);

@@ -159,24 +159,41 @@ hipError_t launch_adjoint_pair(int kind, bool cplx, int vs, const AdjPairParams 
 hipError_t launch_pair(int kind, bool fp32, bool cplx, bool nontemporal, int vs, const FusedParams &p,
                        hipStream_t st);
 
+// several orders per launch (chain.hip): operators of at most kChainWidth
+// elements per row, vs states per block (1, or 2 in FP32); max_eval, max_stage:
+// the most local rows of a tile within depth - 1 and depth hops
+hipError_t launch_chain(bool fp32, bool cplx, int width, int vs, int max_eval, int max_stage, const ChainParams &p,
+                        hipStream_t st);
+hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int32_t n_tiles, const DevMatrix &m,
+                               void *tval, void *tons, hipStream_t st);
+// sums the partials of n_local steps (step_stride doubles apart) into samples
+// *counter + 1 .. *counter + n_local, then advances the counter
+hipError_t launch_chain_reduce(int n_inst, int n_local, int64_t step_stride, const ReduceParams &p, int32_t *counter,
+                               hipStream_t st);
+
 // quasi-eigenstate launchers (quasi.hip)
 // acc[j][e] += coef[k][j] * state[e] for j < n_e, k = *counter (state at R precision)
-hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, const double *coef, int32_t n_e,
+// (n_used elements of it; acc[j] lies j n_el elements on)
+hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, int64_t n_used, const double *coef,
+                           int32_t n_e,
                            const int32_t *counter, hipStream_t st);
 int32_t qe_partial_blocks(int64_t n_rows);  // partials need n_e * S * 3 * blocks doubles
 // norm2[j][s] = ||acc[j][:, s]||^2 and out[j][perm[r]][s] = acc[j][r][s] / sqrt(norm2[j][s]), s < s_user
-hipError_t launch_qe_finalize(const double *acc, int64_t n_rows, int32_t log2s, int32_t s_user, int32_t n_e,
+// (states in blocks of 2^log2sb)
+hipError_t launch_qe_finalize(const double *acc, int64_t n_rows, int32_t log2s, int32_t log2sb, int32_t s_user,
+                              int32_t n_e,
                               const int32_t *perm, double *partials, double *norm2, double *out, hipStream_t st);
 
 // optical-conductivity launchers (ac.hip)
 hipError_t launch_gather_values(const int64_t *ell_csr, int64_t ell_size, const double *csr_val, double *ell_val,
                                 hipStream_t st);
+// joined blocks have 2^log2s2 states, stored in blocks of 2^log2sb
 hipError_t launch_join(const double *jpsi, const double *psi, int64_t n_rows, int32_t log2s, int32_t log2s2,
-                       int32_t S, double *out, hipStream_t st);
-hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, int32_t log2s2, int32_t S,
+                       int32_t log2sb, int32_t S, double *out, hipStream_t st);
+hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, int32_t log2sb, int32_t S,
                        const int32_t *perm, double *out, hipStream_t st);
-hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2s2,
-                        const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
+hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2sb,
+                        int64_t n_rows, const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
                         double *partials, hipStream_t st);
 hipError_t launch_ac_cond(const double *corr, int32_t n_steps, int32_t n_states, double dt, double beta, double area,
                           int window, double *omegas, double *sigma, hipStream_t st);
@@ -270,6 +287,30 @@ struct TwoHopTables {
     std::vector<int32_t> inst_tile0, uoff, ucol, n1, hoff, hw;
     std::vector<uint16_t> lidx, hidx;
 };
+// Tiles of the chain kernel (chain.hip): each member's rows, in its order
+// (empty: as stored), halved until a part has at most T rows, and further until
+// the rows within depth - 1 hops are at most max_eval and those within depth
+// hops at most max_rows.  A tile's local rows are its own rows, then the rows
+// 1, 2, ... depth hops away.  depth = 0: no tiling fits.
+struct ChainTables {
+    int32_t depth = 0;
+    bool contiguous = true;
+    std::vector<TileDesc> tiles;
+    std::vector<int32_t> inst_tile0, cnt, toff, loff;
+    std::vector<uint32_t> rowmap;
+    std::vector<uint16_t> lidx;      // [row][4]
+    std::vector<int32_t> max_stage;  // [depth + 1]: most rows within h hops
+};
+void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
+                  const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
+                  int32_t depth, int64_t max_eval, int64_t max_rows, ChainTables &t);
+
+// The depth to build tiles of T rows for: the largest up to cap that nearly all
+// of a sample of tiles reach within the bounds; 0 if none
+int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
+                    const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
+                    int32_t cap, int64_t max_eval, int64_t max_rows);
+
 // LDS budget of a fused-shape tile for tier t = 1 .. 6: 1/(t+2) of a CU's
 // 160 KiB, i.e. room for t+2 resident workgroups per CU
 constexpr int kFusedTiers = 6;

@@ -45,6 +45,8 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
     if (e == hipSuccess) e = hipEventCreate(&t1);
     tbpm_status st = TBPM_OK;
     tbpm_launch_config keep = eng.cfgs[fp32 ? 1 : 0], win = keep;
+    const bool keep_set = eng.cfg_set[fp32 ? 1 : 0];
+    eng.cfg_set[fp32 ? 1 : 0] = true;
     double win_ms = 1e300;
     if (e != hipSuccess) st = hip_fail(e, "autotune setup");
     // plain shapes: chunks x unroll x vec x (remap 0/1, non-temporal); staged shapes, tier outer: LDS tier 1 x vec x
@@ -56,6 +58,8 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
     while (s_pad < n_states) s_pad <<= 1;
     const int chunk_list[] = {1, 2, 4, 8, 16};
     const bool wide_rows = eng.mat.n_rows > 0 && (double)eng.mat.ell_size > 8.0 * (double)eng.mat.n_rows;
+    Engine::ChainShape cs;
+    const bool chain = st == TBPM_OK && eng.chain_prepare(n_states, fp32, 17, cs) == TBPM_OK;
     auto vec_ok = [&](int vec) { return !(fp32 && vec == 1 && s_pad > 1); };  // 8-byte units never beat 16
     for (int vec = 1; vec <= 4 && vec <= s_pad; vec *= 2) {
         if (!vec_ok(vec)) continue;
@@ -75,12 +79,13 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
                 for (int nt = 0; nt <= (tier == 1 ? 1 : 0); ++nt)
                     cands.push_back(tbpm_launch_config{2, remap, nt, 1, tier, vec, 0});
         }
-    // fused shapes, tier outer; the two-hop halo grows with the square of
+    // fused shapes, tier outer; where they run several orders per launch the
+    // library picks tiles and states per thread itself; the two-hop halo grows with the square of
     // the row width, so fusing pays off only for sparse rows
     if (!wide_rows)
-        for (int tier = 1; tier <= kFusedTiers; ++tier)
-            for (int vec = 1; vec <= 4 && vec <= s_pad; vec *= 2)
-                if (!(fp32 && vec == 1 && s_pad > 1))
+        for (int tier = 1; tier <= (chain ? 1 : kFusedTiers); ++tier)
+            for (int vec = 1; vec <= (chain ? 1 : 4) && vec <= s_pad; vec *= 2)
+                if (chain || !(fp32 && vec == 1 && s_pad > 1))
                     for (int remap = 1; remap <= 6; ++remap)
                         cands.push_back(tbpm_launch_config{2, remap, 1, 1, 0, vec, tier});
     // time one shape on `steps` time steps (after a warm-up run that builds
@@ -133,6 +138,7 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
     corr.release();
     if (st != TBPM_OK) {
         eng.cfgs[fp32 ? 1 : 0] = keep;
+        eng.cfg_set[fp32 ? 1 : 0] = keep_set;
         return st;
     }
     eng.cfgs[fp32 ? 1 : 0] = win;

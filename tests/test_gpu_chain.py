@@ -1,0 +1,121 @@
+"""Several Clenshaw orders per launch (rows of at most four stored elements)
+against one order per launch and the oracle, where tiles, shells, blocks of
+states and launch sequences end.
+
+Bars: against the one-order kernels, FP64 correlations to 1e-12 of their largest
+value (a few thousand operations of rounding 1e-16, in another order), and
+FP32-mixed ones to 1e-12 as well: the FP32 states are the same bit for bit, and
+only their FP64 sums run in another order.  Against the oracle 1e-10 (FP64)."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2209_00806_amd import inputs, tbpm
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+CHAIN = dict(wg_chunks=2, xcd_remap=5, nontemporal=1, unroll=1, staged=0, vec=2, fused=2)
+
+
+def _rel(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def _cplx(lat, rng):
+    i = np.repeat(np.arange(lat.n_orb), np.diff(lat.row_ptr))
+    a = rng.uniform(0, 2 * np.pi, lat.n_orb)
+    lat.val = lat.val * np.exp(1j * (a[i] - a[lat.col]))
+    return lat
+
+
+def _lattice(kind, rng):
+    lat = {
+        "ring5": lambda: inputs.from_bonds(5, np.arange(5), (np.arange(5) + 1) % 5, np.full(5, -2.7), np.zeros(5)),
+        "graphene_small": lambda: inputs.graphene(23, 19),  # tiles follow an order of their own
+        "graphene": lambda: inputs.graphene(113, 89),  # renumbered, several tiles, ragged sizes
+        "square_open": lambda: inputs.square(61, 47, pbc=False),  # rows of 2 to 4 elements
+        "graphene_complex": lambda: _cplx(inputs.graphene(41, 37), rng),
+        "square_complex": lambda: _cplx(inputs.square(45, 53), rng),
+    }[kind]()
+    lat.onsite = inputs.anderson(rng, lat.n_orb, 1.0)
+    return lat
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["ring5", "graphene_small", "graphene", "square_open", "graphene_complex",
+                                  "square_complex"])
+def test_chain_matches_one_order_per_launch(kind, precision):
+    rng = np.random.default_rng(3)
+    lat = _lattice(kind, rng)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    # states: one, odd counts (padded blocks), more than one workgroup's share;
+    # dt f = pi (17 orders), 0.3 (few orders, one launch), 9 (many launches);
+    # 35 samples: whole graphs and a remainder
+    for S, z, nt in ((1, math.pi, 35), (3, math.pi, 18), (8, 0.3, 9), (5, 9.0, 5), (1, 1e-7, 4)):
+        psi_np = inputs.random_phase_states(rng, lat.n_orb, S)
+        psi = torch.from_numpy(psi_np).cuda()
+        H.set_launch_config()
+        ref, n_ref = tbpm.propagate(H, psi, nt, z / f, f, precision=precision, return_norm=True)
+        H.set_launch_config(**CHAIN)
+        for graph in (True, False):
+            got, n_got = tbpm.propagate(H, psi, nt, z / f, f, precision=precision, return_norm=True, graph=graph)
+            assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-12, (S, z, nt, graph)
+            assert _rel(n_got.cpu().numpy(), n_ref.cpu().numpy()) < 1e-12, (S, z, nt, graph)
+        if precision == "fp64":
+            want, _, _ = oracle.propagate(lat.row_ptr, lat.col, lat.val, lat.onsite, psi_np, nt, z / f, f)
+            assert _rel(got.cpu().numpy(), want) < 1e-10, (S, z, nt)
+    H.close()
+
+
+@pytest.mark.parametrize("kind", ["graphene_small", "graphene", "square_complex"])
+def test_chain_stored_states(kind):
+    """Checkpoints, snapshots and quasi-eigenstates (states leave the blocks in the caller's order)."""
+    rng = np.random.default_rng(4)
+    lat = _lattice(kind, rng)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    dt = math.pi / f
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    for S in (1, 3):
+        psi = torch.from_numpy(inputs.random_phase_states(rng, lat.n_orb, S)).cuda()
+        out = []
+        for shape in ({}, CHAIN):
+            H.set_launch_config(**shape)
+            _, ck = tbpm.propagate(H, psi, 23, dt, f, ckpt_every=5)
+            out.append([ck, tbpm.propagate_snapshots(H, psi, [19, 0, 2], dt, f),
+                        tbpm.propagate_snapshots(H, psi, [18, 3], dt, f, precision="fp32"),
+                        tbpm.quasi_eigenstates(H, psi, [-0.7, 1.1], 20, dt, f)])
+        for a, b in zip(*out):
+            assert _rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-12
+    H.close()
+
+
+def test_chain_without_a_configuration():
+    """A handle nobody configured takes several orders per launch for long runs, with current values and in
+    batches of members below and above a tile; configured handles keep their shape."""
+    rng = np.random.default_rng(5)
+    lats = [_lattice(k, rng) for k in ("ring5", "graphene_small", "graphene", "square_open")]
+    fs = [1.05 * oracle.gershgorin(l.row_ptr, l.val, l.onsite) for l in lats]
+    psis = [torch.from_numpy(inputs.random_phase_states(rng, l.n_orb, 2)).cuda() for l in lats]
+    hams = [tbpm.Hamiltonian.from_lattice(l) for l in lats]
+    for precision in ("fp64", "fp32"):
+        B = tbpm.Batch(hams)
+        got = B.propagate(psis, 70, [math.pi / f for f in fs], fs, precision=precision)
+        B.set_launch_config()
+        ref = B.propagate(psis, 70, [math.pi / f for f in fs], fs, precision=precision)
+        for a, b in zip(got, ref):
+            assert _rel(a.cpu().numpy(), b.cpu().numpy()) < 1e-11
+        B.close()
+    lat, H, psi, f = lats[2], hams[2], psis[2], fs[2]
+    first = tbpm.propagate(H, psi, 70, math.pi / f, f)
+    on = torch.from_numpy(lat.onsite * 0.5).cuda()
+    H.set_values(torch.from_numpy(lat.val * 0.9).cuda(), on)
+    got = tbpm.propagate(H, psi, 70, math.pi / f, f)
+    H.set_launch_config()
+    ref = tbpm.propagate(H, psi, 70, math.pi / f, f)
+    assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-11
+    assert _rel(first.cpu().numpy(), ref.cpu().numpy()) > 1e-3  # the values did change
