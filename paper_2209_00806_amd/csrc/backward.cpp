@@ -4,8 +4,9 @@
 // phi0, psi_{mK} from tbpm_propagate), keeping every step's Clenshaw vectors
 // b_1 .. b_{M-2} (b_{M-1} = c_{M-1} psi_l is recomputed on the fly); the
 // adjoint then runs backwards through the segment, one fused kernel per
-// Chebyshev order j (see backward.hip).  Device memory: (K+1) + K (M-2)
-// state vectors for the segment plus four adjoint vectors.
+// Chebyshev order j (see backward.hip), or one per several orders
+// (k_chain_adjoint).  Device memory: (K+1) + K (M-2) state vectors for the
+// segment plus four or five adjoint vectors.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,7 +60,24 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     // non-temporal streaming; the single-order adjoint keeps one state per
     // thread.  The two-hop tables depend on the bytes of a row only, so one
     // set serves every unit width (the LDS size in units follows the width).
-    bool pairs = eng.cfgs[0].fused > 0 && M - 2 >= 2;
+    // Rows of up to four elements take the chain shape instead, for the replay
+    // and for the adjoint, under the rule of the propagation and where its
+    // tables and vectors fit into memory.
+    Engine::ChainShape cs;
+    const int32_t seg_len = std::min<int32_t>(K, std::max<int32_t>(N - 1, 1));
+    const int32_t n_b = M - 2;  // stored b_1 .. b_{M-2} per step
+    const size_t n_store = (size_t)(seg_len + 1) + (size_t)seg_len * n_b;
+    const size_t gacc_bytes = (cplx ? 16 : 8) * (size_t)std::max<int64_t>(eng.mat.ell_size, 1);
+    bool chain = N >= 2 && (eng.cfgs[0].fused > 0 || (!eng.cfg_set[0] && N > kChainAutoSteps)) &&
+                 n_rows * s_pad < (int64_t)INT32_MAX && eng.chain_prepare(s_user, false, M - 1, cs) == TBPM_OK;
+    if (chain) {
+        auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+        const size_t v1 = 16 * (size_t)n_rows * s_user;
+        chain = eng.chain_room(false, grow(eng.bwd_store, v1 * n_store) + grow(eng.bwd_adj, v1 * 5) +
+                                          grow(eng.phi0, v1) + grow(eng.bwd_gacc, gacc_bytes * cs.n_grp) +
+                                          grow(eng.bwd_gdiag, 8 * (size_t)n_rows * cs.n_grp));
+    }
+    bool pairs = !chain && eng.cfgs[0].fused > 0 && M - 2 >= 2;
     int32_t pvs = 1, log2pvs = 0;
     while (pvs < eng.cfgs[0].vec && pvs < s_pad && pvs < 4) {
         pvs <<= 1;
@@ -68,12 +86,18 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     const bool pnt = eng.cfgs[0].nontemporal != 0;
     if (pairs && eng.build_fused_tiles(s_pad, log2s - log2pvs, 16 * pvs, eng.cfgs[0].fused) != TBPM_OK)
         pairs = false;
-    tbpm_status s = pairs ? TBPM_OK : eng.build_tiles(s_pad, eng.cfg.wg_chunks, 1);
-    if (s != TBPM_OK) return s;
-    const int32_t n_tiles = (int32_t)eng.h_tiles.size();
-    const int64_t n_el = n_rows * s_pad;
-    if (n_el >= (int64_t)INT32_MAX) return fail(TBPM_E_ARG, "n_orb * n_states (padded to a power of two) must be < 2^31");
+    const int64_t n_el = chain ? n_rows * s_user : n_rows * s_pad;
+    if (n_rows * s_pad >= (int64_t)INT32_MAX) return fail(TBPM_E_ARG, "n_orb * n_states (padded to a power of two) must be < 2^31");
     const size_t vb = sizeof(double) * 2 * (size_t)n_el;
+    tbpm_status s = TBPM_OK;
+    if (chain)
+        s = eng.chain_values(false, st);
+    else if (!pairs)
+        s = eng.build_tiles(s_pad, eng.cfg.wg_chunks, 1);
+    if (s != TBPM_OK) return s;
+    const int32_t n_tiles = chain ? 0 : (int32_t)eng.h_tiles.size();
+    const int32_t log2sb = chain ? cs.log2sb() : log2s;
+    const int32_t n_copy = chain ? cs.n_grp : 1;
 
     if (N < 2) {
         TRY_HIP(launch_fill_zero(grad_val, 2 * nnz, st), "zero grad");
@@ -81,15 +105,12 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
         TRY_HIP(hipStreamSynchronize(st), "stream synchronize");
         return TBPM_OK;
     }
-    const int32_t seg_len = std::min<int32_t>(K, N - 1);
-    const int32_t n_b = M - 2;  // stored b_1 .. b_{M-2} per step
-    const size_t n_store = (size_t)(seg_len + 1) + (size_t)seg_len * n_b;
     TRY_HIP(eng.bwd_store.ensure(vb * n_store), "alloc segment store (reduce ckpt_every)");
-    TRY_HIP(eng.bwd_adj.ensure(vb * (pairs ? 5 : 4)), "alloc adjoint vectors");
+    TRY_HIP(eng.bwd_adj.ensure(vb * (pairs || chain ? 5 : 4)), "alloc adjoint vectors");
     TRY_HIP(eng.phi0.ensure(vb), "alloc phi0");
-    TRY_HIP(eng.bwd_gacc.ensure((cplx ? 16 : 8) * (size_t)std::max<int64_t>(eng.mat.ell_size, 1)), "alloc gradient");
-    TRY_HIP(eng.bwd_gdiag.ensure(8 * (size_t)n_rows), "alloc gradient");
-    TRY_HIP(eng.bwd_coef.ensure(sizeof(PassCoef) * n_passes), "alloc coefficients");
+    TRY_HIP(eng.bwd_gacc.ensure(gacc_bytes * n_copy), "alloc gradient");
+    TRY_HIP(eng.bwd_gdiag.ensure(8 * (size_t)n_rows * n_copy), "alloc gradient");
+    TRY_HIP(eng.bwd_coef.ensure(sizeof(PassCoef) * n_passes + sizeof(cd) * M), "alloc coefficients");
     if (!eng.partner_ready) {
         const std::vector<int32_t> part = ell_partner_slots(n_rows, eng.h_slice_off, eng.h_col);
         if (part.empty()) return fail(TBPM_E_NOT_HERMITIAN, "a stored element has no transposed partner");
@@ -106,6 +127,11 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     TRY_HIP(hipStreamSynchronize(st), "stream synchronize");
     TRY_HIP(hipMemcpy(eng.bwd_coef.ptr, hc.data(), sizeof(PassCoef) * n_passes, hipMemcpyHostToDevice),
             "upload coefficients");
+    // conj(c_j) behind the passes' coefficients
+    double *conj_c = (double *)((char *)eng.bwd_coef.ptr + sizeof(PassCoef) * n_passes);
+    std::vector<cd> hcc(M);
+    for (int j = 0; j < M; ++j) hcc[j] = std::conj(c[j]);
+    TRY_HIP(hipMemcpy(conj_c, hcc.data(), sizeof(cd) * M, hipMemcpyHostToDevice), "upload coefficients");
 
     // the replay needs psi_{l+1} but not its correlation: the last pass runs
     // as the same combination without the correlation stream
@@ -120,14 +146,14 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     double *adj = (double *)eng.bwd_adj.ptr;
     double *lam = adj, *acc = adj + 2 * n_el;
     double *rot[3] = {lam, adj + 4 * n_el, adj + 6 * n_el};
-    double *rot4 = pairs ? adj + 8 * n_el : nullptr;  // the fourth alpha buffer of the paired sweep
+    double *rot4 = pairs || chain ? adj + 8 * n_el : nullptr;  // the fourth alpha buffer of the paired sweep
     double *phi0p = (double *)eng.phi0.ptr;
 
-    TRY_HIP(launch_expand_states(psi0, eng.mat.perm, s_user, phi0p, log2s, n_rows, st), "expand psi0");
-    TRY_HIP(launch_lam_init(lam, phi0p, gcorr + 2 * (size_t)(N - 1) * s_user, s_user, log2s, n_rows, st),
+    TRY_HIP(launch_expand_states(psi0, eng.mat.perm, s_user, phi0p, log2sb, n_rows, st), "expand psi0");
+    TRY_HIP(launch_lam_init(lam, phi0p, gcorr + 2 * (size_t)(N - 1) * s_user, s_user, log2sb, n_rows, st),
             "adjoint init");
-    TRY_HIP(launch_fill_zero((double *)eng.bwd_gacc.ptr, (cplx ? 2 : 1) * eng.mat.ell_size, st), "zero gradient");
-    TRY_HIP(launch_fill_zero((double *)eng.bwd_gdiag.ptr, n_rows, st), "zero gradient");
+    TRY_HIP(launch_fill_zero((double *)eng.bwd_gacc.ptr, (cplx ? 2 : 1) * eng.mat.ell_size * n_copy, st), "zero gradient");
+    TRY_HIP(launch_fill_zero((double *)eng.bwd_gdiag.ptr, n_rows * n_copy, st), "zero gradient");
 
     // Clenshaw pass j of each plan entry (FIRST, NOB2, MID..., LAST)
     std::vector<int> pass_j(n_passes);
@@ -338,6 +364,85 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
         return e;
     };
 
+    // one step of the replay in the chain shape: every order's vector is stored
+    // (b_{M-2}, b_{M-3}, ... lie one vector apart, downwards), a launch goes on
+    // from the two that the one before stored last
+    auto replay_step_chain = [&](int32_t t) -> hipError_t {
+        ChainParams cp = eng.chain_params(cs);
+        cp.xcd_remap = eng.cfg.xcd_remap;
+        cp.alt = 1;
+        cp.out_stride = -(int64_t)vb;
+        hipError_t e = hipSuccess;
+        int32_t p0 = 0;
+        for (size_t i = 0; e == hipSuccess && i < cs.depths.size(); ++i) {
+            const int32_t d = cs.depths[i], j = pass_j[p0];
+            cp.depth = d;
+            cp.first = i == 0;
+            cp.turned = (n_passes - 1 - p0) & 1;
+            cp.reverse = walk;
+            walk ^= 1;
+            cp.v = psi_slot(t);
+            cp.x = p0 == 0 ? psi_slot(t) : b_slot(t, j + 1);
+            cp.b2 = p0 == 0 ? nullptr : b_slot(t, j + 2);
+            cp.coef = coefs + p0;
+            cp.out_all = b_slot(t, j);
+            cp.out_last = p0 + d == n_passes ? psi_slot(t + 1) : b_slot(t, j - d + 1);
+            e = launch_chain(false, cplx, eng.chain_width(), 1, eng.ch.max_stage[d - 1], eng.ch.max_stage[d], cp, st);
+            p0 += d;
+        }
+        return e;
+    };
+    // one step of the adjoint in the chain shape: orders j0 .. j0 + d - 1 per
+    // launch, the two last alphas stored for the next one.  lambda_l ends in 'acc'.
+    auto adjoint_step_chain = [&](int32_t t, int32_t l) -> hipError_t {
+        ChainParams cp = eng.chain_params(cs);
+        cp.xcd_remap = eng.cfg.xcd_remap;
+        cp.phi0 = phi0p;
+        cp.s_user = s_user;
+        ChainAdjoint ad{};
+        ad.bq_stride = (int64_t)vb;
+        ad.psi = psi_slot(t);
+        ad.bs_re = c[M - 1].real();
+        ad.bs_im = c[M - 1].imag();
+        ad.inv_f = 1.0 / f;
+        ad.gcorr_l = gcorr + 2 * (size_t)l * s_user;
+        ad.lam = acc;
+        ad.gacc = eng.bwd_gacc.ptr;
+        ad.gdiag = (double *)eng.bwd_gdiag.ptr;
+        ad.ell_size = eng.mat.ell_size;
+        ad.slice_off = eng.mat.slice_off;
+        double *X = rot[0], *P = nullptr, *fr[2] = {rot[1], rot[2]};
+        hipError_t e = hipSuccess;
+        int32_t j0 = 0;
+        for (size_t i = 0; e == hipSuccess && i < cs.depths.size(); ++i) {
+            const int32_t d = cs.depths[i];
+            const bool last = j0 + d == n_passes;
+            cp.depth = d;
+            cp.reverse = walk;
+            walk ^= 1;
+            cp.x = X;
+            cp.b2 = P;
+            cp.out_prev = last ? nullptr : fr[0];
+            cp.out_last = last ? nullptr : fr[1];
+            ad.bq = b_slot(t, j0 + 1);
+            ad.cc = conj_c + 2 * j0;
+            ad.first = j0 == 0;
+            ad.final_ = last;
+            e = launch_chain_adjoint(cplx, eng.chain_width(), eng.ch.T, eng.ch.max_stage[d - 1], eng.ch.max_stage[d], cp,
+                                     ad, st);
+            // the old x and alpha_{j-1} (the fourth buffer after the first launch)
+            // take the next outputs
+            double *np = fr[0], *nx = fr[1];
+            fr[0] = X;
+            fr[1] = P ? P : rot4;
+            X = nx;
+            P = np;
+            j0 += d;
+        }
+        std::swap(rot[0], acc);
+        return e;
+    };
+
     const int32_t n_seg = (N - 1 + K - 1) / K;
     for (int32_t seg = n_seg - 1; seg >= 0; --seg) {
         const int32_t l0 = seg * K;
@@ -346,10 +451,14 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
             TRY_HIP(hipMemcpyAsync(psi_slot(0), phi0p, vb, hipMemcpyDeviceToDevice, st), "segment start");
         else
             TRY_HIP(launch_expand_states(ckpt + 2 * (size_t)(seg - 1) * n_rows * s_user, eng.mat.perm, s_user,
-                                         psi_slot(0), log2s, n_rows, st),
+                                         psi_slot(0), log2sb, n_rows, st),
                     "segment start");
         // forward replay, keeping b_1 .. b_{M-2} of every step
         for (int32_t t = 0; t < len; ++t) {
+            if (chain) {
+                TRY_HIP(replay_step_chain(t), "replay chain");
+                continue;
+            }
             if (pairs) {
                 TRY_HIP(replay_step_pairs(t), "replay pair");
                 continue;
@@ -373,6 +482,10 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
         // adjoint sweep through the segment
         for (int32_t t = len - 1; t >= 0; --t) {
             const int32_t l = l0 + t;
+            if (chain) {
+                TRY_HIP(adjoint_step_chain(t, l), "adjoint chain");
+                continue;
+            }
             if (pairs) {
                 TRY_HIP(adjoint_step_pairs(t, l), "adjoint pair");
                 continue;
@@ -409,7 +522,8 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
         }
     }
     TRY_HIP(launch_grad_scatter(eng.bwd_gacc.ptr, (const double *)eng.bwd_gdiag.ptr, eng.mat.ell_csr,
-                                eng.mat.ell_size, cplx, 1.0 / f, grad_val, grad_onsite, eng.mat.perm, n_rows, st),
+                                eng.mat.ell_size, cplx, 1.0 / f, grad_val, grad_onsite, eng.mat.perm, n_rows,
+                                chain ? (const int32_t *)eng.bwd_partner.ptr : nullptr, n_copy, st),
             "gradient scatter");
     TRY_HIP(hipStreamSynchronize(st), "stream synchronize");
     TRY_HIP(hipGetLastError(), "kernel execution");

@@ -387,31 +387,35 @@ __global__ __launch_bounds__(kWG) void k_adj_pair(const AdjPairParams p) {
     }
 }
 
+// Blocks of 2^log2sb states, [row][state] within a block; grid.y walks the blocks.
 __global__ __launch_bounds__(kWG) void k_expand(const d2 *__restrict__ src, const int32_t *__restrict__ perm,
-                                                int s_user, d2 *__restrict__ dst, int log2s, int64_t n_el) {
+                                                int s_user, d2 *__restrict__ dst, int log2sb, int n_blk, int64_t n_el) {
     const int64_t stride = (int64_t)gridDim.x * kWG;
-    for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_el; e += stride) {
-        const int64_t row = perm ? (int64_t)perm[e >> log2s] : (e >> log2s);
-        const int s = (int)(e & ((1 << log2s) - 1));
-        d2 a;
-        a.x = 0.0;
-        a.y = 0.0;
-        if (s < s_user) a = src[row * s_user + s];
-        dst[e] = a;
-    }
+    for (int blk = (int)blockIdx.y; blk < n_blk; blk += (int)gridDim.y)
+        for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_el; e += stride) {
+            const int64_t row = perm ? (int64_t)perm[e >> log2sb] : (e >> log2sb);
+            const int s = (blk << log2sb) + (int)(e & ((1 << log2sb) - 1));
+            d2 a;
+            a.x = 0.0;
+            a.y = 0.0;
+            if (s < s_user) a = src[row * s_user + s];
+            dst[(int64_t)blk * n_el + e] = a;
+        }
 }
 
 __global__ __launch_bounds__(kWG) void k_lam_init(d2 *__restrict__ lam, const d2 *__restrict__ phi0,
-                                                  const d2 *__restrict__ g, int s_user, int log2s, int64_t n_el) {
+                                                  const d2 *__restrict__ g, int s_user, int log2sb, int n_blk,
+                                                  int64_t n_el) {
     const int64_t stride = (int64_t)gridDim.x * kWG;
-    for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_el; e += stride) {
-        const int s = (int)(e & ((1 << log2s) - 1));
-        d2 a;
-        a.x = 0.0;
-        a.y = 0.0;
-        if (s < s_user) a = cmul(g[s], phi0[e]);
-        lam[e] = a;
-    }
+    for (int blk = (int)blockIdx.y; blk < n_blk; blk += (int)gridDim.y)
+        for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_el; e += stride) {
+            const int s = (blk << log2sb) + (int)(e & ((1 << log2sb) - 1));
+            d2 a;
+            a.x = 0.0;
+            a.y = 0.0;
+            if (s < s_user) a = cmul(g[s], phi0[(int64_t)blk * n_el + e]);
+            lam[(int64_t)blk * n_el + e] = a;
+        }
 }
 
 __global__ __launch_bounds__(kWG) void k_fill_zero(double *__restrict__ p, int64_t n) {
@@ -419,27 +423,36 @@ __global__ __launch_bounds__(kWG) void k_fill_zero(double *__restrict__ p, int64
     for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += stride) p[i] = 0.0;
 }
 
+// partner == null: slot q's gradient is gacc[q].  Otherwise (k_chain_adjoint) it
+// is kept in the slot of the transposed element, in n_copy copies ell_size /
+// n_rows apart.
 template <bool CH>
 __global__ __launch_bounds__(kWG) void k_grad_scatter(const void *__restrict__ gacc, const double *__restrict__ gdiag,
                                                       const int64_t *__restrict__ ell_csr, int64_t ell_size,
                                                       double inv_f, d2 *__restrict__ grad_val,
                                                       double *__restrict__ grad_onsite,
-                                                      const int32_t *__restrict__ perm, int64_t n_rows) {
+                                                      const int32_t *__restrict__ perm, int64_t n_rows,
+                                                      const int32_t *__restrict__ partner, int n_copy) {
     const int64_t stride = (int64_t)gridDim.x * kWG;
     for (int64_t q = (int64_t)blockIdx.x * kWG + threadIdx.x; q < ell_size; q += stride) {
         const int64_t pos = ell_csr[q];
         if (pos < 0) continue;
+        const int64_t src = partner ? partner[q] : q;
         d2 v;
-        if constexpr (CH) {
-            v = ((const d2 *)gacc)[q] * inv_f;
-        } else {
-            v.x = ((const double *)gacc)[q] * inv_f;
-            v.y = 0.0;
+        v.x = v.y = 0.0;
+        for (int c = 0; c < n_copy; ++c) {
+            if constexpr (CH)
+                v += ((const d2 *)gacc)[c * ell_size + src];
+            else
+                v.x += ((const double *)gacc)[c * ell_size + src];
         }
-        grad_val[pos] = v;
+        grad_val[pos] = v * inv_f;
     }
-    for (int64_t r = (int64_t)blockIdx.x * kWG + threadIdx.x; r < n_rows; r += stride)
-        grad_onsite[perm ? perm[r] : r] = gdiag[r] * inv_f;
+    for (int64_t r = (int64_t)blockIdx.x * kWG + threadIdx.x; r < n_rows; r += stride) {
+        double v = 0.0;
+        for (int c = 0; c < n_copy; ++c) v += gdiag[c * n_rows + r];
+        grad_onsite[perm ? perm[r] : r] = v * inv_f;
+    }
 }
 
 int64_t grid_for(int64_t n) {
@@ -497,19 +510,21 @@ hipError_t launch_adjoint_pair(int kind, bool cplx, int vs, const AdjPairParams 
     return launch_adj_pair_t<false, 1>(kind, p, st);
 }
 
-hipError_t launch_expand_states(const double *src, const int32_t *perm, int32_t s_user, double *dst, int32_t log2s,
+hipError_t launch_expand_states(const double *src, const int32_t *perm, int32_t s_user, double *dst, int32_t log2sb,
                                 int64_t n_rows, hipStream_t st) {
-    const int64_t n_el = n_rows << log2s;
-    hipLaunchKernelGGL(k_expand, dim3((unsigned)grid_for(n_el)), dim3(kWG), 0, st, (const d2 *)src, perm, s_user,
-                       (d2 *)dst, log2s, n_el);
+    const int64_t n_el = n_rows << log2sb;
+    const int n_blk = (s_user + (1 << log2sb) - 1) >> log2sb;
+    hipLaunchKernelGGL(k_expand, dim3((unsigned)grid_for(n_el), (unsigned)(n_blk < 65535 ? n_blk : 65535)), dim3(kWG),
+                       0, st, (const d2 *)src, perm, s_user, (d2 *)dst, log2sb, n_blk, n_el);
     return hipGetLastError();
 }
 
 hipError_t launch_lam_init(double *lam, const double *phi0, const double *gcorr_last, int32_t s_user,
-                           int32_t log2s, int64_t n_rows, hipStream_t st) {
-    const int64_t n_el = n_rows << log2s;
-    hipLaunchKernelGGL(k_lam_init, dim3((unsigned)grid_for(n_el)), dim3(kWG), 0, st, (d2 *)lam, (const d2 *)phi0,
-                       (const d2 *)gcorr_last, s_user, log2s, n_el);
+                           int32_t log2sb, int64_t n_rows, hipStream_t st) {
+    const int64_t n_el = n_rows << log2sb;
+    const int n_blk = (s_user + (1 << log2sb) - 1) >> log2sb;
+    hipLaunchKernelGGL(k_lam_init, dim3((unsigned)grid_for(n_el), (unsigned)(n_blk < 65535 ? n_blk : 65535)), dim3(kWG),
+                       0, st, (d2 *)lam, (const d2 *)phi0, (const d2 *)gcorr_last, s_user, log2sb, n_blk, n_el);
     return hipGetLastError();
 }
 
@@ -520,14 +535,14 @@ hipError_t launch_fill_zero(double *p, int64_t n, hipStream_t st) {
 
 hipError_t launch_grad_scatter(const void *gacc, const double *gdiag, const int64_t *ell_csr, int64_t ell_size,
                                bool cplx, double inv_f, double *grad_val, double *grad_onsite, const int32_t *perm,
-                               int64_t n_rows, hipStream_t st) {
+                               int64_t n_rows, const int32_t *partner, int32_t n_copy, hipStream_t st) {
     const int64_t work = ell_size > n_rows ? ell_size : n_rows;
     if (cplx)
         hipLaunchKernelGGL(k_grad_scatter<true>, dim3((unsigned)grid_for(work)), dim3(kWG), 0, st, gacc, gdiag, ell_csr,
-                           ell_size, inv_f, (d2 *)grad_val, grad_onsite, perm, n_rows);
+                           ell_size, inv_f, (d2 *)grad_val, grad_onsite, perm, n_rows, partner, n_copy);
     else
         hipLaunchKernelGGL(k_grad_scatter<false>, dim3((unsigned)grid_for(work)), dim3(kWG), 0, st, gacc, gdiag,
-                           ell_csr, ell_size, inv_f, (d2 *)grad_val, grad_onsite, perm, n_rows);
+                           ell_csr, ell_size, inv_f, (d2 *)grad_val, grad_onsite, perm, n_rows, partner, n_copy);
     return hipGetLastError();
 }
 

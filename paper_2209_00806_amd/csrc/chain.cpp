@@ -110,17 +110,23 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
     return fail(TBPM_E_ARG, "no chain tile fits");
 }
 
-bool Engine::chain_fits(const ChainShape &cs, bool fp32, size_t vec) {
-    auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+// room for `need` more bytes and the tiles' matrix entries
+bool Engine::chain_room(bool fp32, size_t need) {
+    auto grow = [](const DevBuf &b, size_t n) { return n > b.bytes ? n : (size_t)0; };
     const size_t rb = fp32 ? 4 : 8;
-    size_t need = grow(v, vec) + grow(ba, vec) + grow(phi0, vec * (fp32 ? 2 : 1)) +
-                  grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * chain_width()) +
-                  grow(ch_tons, rb * (size_t)ch.n_local);
-    if (cs.depths.size() > 1) need += grow(bb, vec) + grow(bc, vec);
-    if (cs.depths.size() > 2) need += grow(bd, vec);
+    need += grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * chain_width()) +
+            grow(ch_tons, rb * (size_t)ch.n_local);
     if (need == 0) return true;
     size_t free_b = 0, total_b = 0;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + ((size_t)256 << 20) <= free_b;
+}
+
+bool Engine::chain_fits(const ChainShape &cs, bool fp32, size_t vec) {
+    auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+    size_t need = grow(v, vec) + grow(ba, vec) + grow(phi0, vec * (fp32 ? 2 : 1));
+    if (cs.depths.size() > 1) need += grow(bb, vec) + grow(bc, vec);
+    if (cs.depths.size() > 2) need += grow(bd, vec);
+    return chain_room(fp32, need);
 }
 
 // The tiles' copies of the matrix entries, from the values the handle holds now

@@ -73,8 +73,21 @@ __device__ __forceinline__ double wave_sum(double x) {
 // their workgroups have 4 waves (three of them per CU).
 constexpr int chain_waves(bool ch) { return ch ? 3 : 4; }
 
-template <typename R, bool CH, int W, int VS, int NT, int NR>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain(const ChainParams p) {
+// The body of k_chain and k_chain_adjoint.  In the adjoint (ADJ) an order is
+//     alpha_{j+1} = 2 H~ alpha_j - alpha_{j-1}   (H~ alpha_0 for j = 0),
+// lambda gains conj(c_{j+1}) alpha_{j+1}, and own row q adds to the gradient of
+// its transposed elements (p, q) Re/Im of alpha_j[p] conj(w b_{j+1}[q]): alpha_j
+// at p is read from LDS for the product anyway, b at the own row is the only
+// stream of its own, and the sums over orders and state blocks stay in registers
+// until the workgroup ends (one read-modify-write per tile and launch, no sum
+// across lanes).
+// Measured, DOS and its gradient on graphene 256^2, 4 FP64 states: 38.6 ms with the
+// replay storing every order and the adjoint 5 or 6 orders per launch, 63.7 ms with
+// two orders per launch of both (there the adjoint was 29 ms of it, bound by the
+// read-modify-write of the gradient for every pair of orders and the sums over
+// lanes).
+template <typename R, bool CH, int W, int VS, int NT, int NR, bool ADJ>
+__device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjoint &ad) {
     extern __shared__ __align__(16) unsigned char chain_mem[];
     using V = VecT<R, VS>;
     using HV = typename HValT<R, CH>::T;
@@ -168,20 +181,44 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
     // lane k holds order k's coefficient (the nonzero part of alpha) and its
     // number of rows: the loop reads them with readlane, where scalar loads
     // would make every order's LDS reads wait for them
-    const PassCoef *cf = p.coef + td.inst;
-    R alpha_l;
+    const PassCoef *cf = p.coef + (ADJ ? 0 : td.inst);
+    R alpha_l = R(0), beta, beta_last;
     int lim_l;
     {
         const int k = min(tid & 63, depth - 1);
-        const PassCoef c = cf[(int64_t)k * p.n_inst];
-        alpha_l = (R)(c.ai != 0.0 ? c.ai : c.ar);
-        if (p.turned && !(k & 1)) alpha_l = (R)c.ai;
-        if (p.turned && (k & 1)) alpha_l = -(R)c.ar;
         lim_l = cnt[depth - 1 - k];
+        if constexpr (ADJ) {
+            beta = beta_last = (R)(2.0 * ad.inv_f);
+        } else {
+            const PassCoef c = cf[(int64_t)k * p.n_inst];
+            alpha_l = (R)(c.ai != 0.0 ? c.ai : c.ar);
+            if (p.turned && !(k & 1)) alpha_l = (R)c.ai;
+            if (p.turned && (k & 1)) alpha_l = -(R)c.ar;
+            beta = (R)cf[(int64_t)(p.first && depth > 1 ? 1 : 0) * p.n_inst].br;
+            beta_last = (R)cf[(int64_t)(depth - 1) * p.n_inst].br;
+        }
     }
-    const R beta = (R)cf[(int64_t)(p.first && depth > 1 ? 1 : 0) * p.n_inst].br;
-    const R beta_last = (R)cf[(int64_t)(depth - 1) * p.n_inst].br;
     uint32_t eb = 0;
+    // adjoint: the gradient sums of the own row (slot 0), its lambda and weighted b
+    const bool own = tid < n_own;
+    double ga[ADJ ? W : 1], gi[ADJ && CH ? W : 1], gd = 0.0;
+    d2 lam, bw, bn, cc_l;
+    if constexpr (ADJ) {
+#pragma unroll
+        for (int i = 0; i < W; ++i) ga[i] = 0.0;
+        if constexpr (CH) {
+#pragma unroll
+            for (int i = 0; i < W; ++i) gi[i] = 0.0;
+        }
+        cc_l = ((const d2 *)ad.cc)[min(tid & 63, depth - 1) + 1];
+    }
+    // b of order k at the own row
+    auto load_b = [&](int k) {
+        const char *src = ad.final_ && k + 1 == depth ? (const char *)ad.psi : (const char *)ad.bq + (int64_t)k * ad.bq_stride;
+        d2 z;
+        z.x = z.y = 0.0;
+        return own ? ((const d2 *)src)[eb + g[0]] : z;
+    };
 
     // B <- alpha psi + beta (H X) - B on the first N slots of this wave; IMAG:
     // alpha is imaginary (a its imaginary part)
@@ -194,9 +231,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
 #pragma unroll
             for (int i = 0; i < W; ++i) xc[q][i] = at(na[q][i] + rd);
         V acc[N];
+        if constexpr (ADJ) {
+            gd = fma(X[0][0], bw.x, fma(X[0][1], bw.y, gd));
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                ga[i] = fma(xc[0][i][0], bw.x, fma(xc[0][i][1], bw.y, ga[i]));
+                if constexpr (CH) gi[i] = fma(xc[0][i][1], bw.x, fma(-xc[0][i][0], bw.y, gi[i]));
+            }
+        }
 #pragma unroll
         for (int q = 0; q < N; ++q) {
-            if constexpr (sizeof(R) == 8) {
+            if constexpr (ADJ) {
+                B[q] = -B[q];
+            } else if constexpr (sizeof(R) == 8) {
 #pragma unroll
                 for (int i = 0; i < VS; ++i) {
                     if constexpr (IMAG) {
@@ -264,12 +311,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
     auto order = [&](auto imag_c, int k, V(&X)[NR], V(&B)[NR], uint32_t rd) {
         __syncthreads();
         const int act = read_lane(lim_l, k) - wbase;
-        const R a = read_lane(alpha_l, k);
-        const R bt = k + 1 == depth ? beta_last : beta;
+        const R a = ADJ ? R(0) : read_lane(alpha_l, k);
+        R bt = k + 1 == depth ? beta_last : beta;
+        if constexpr (ADJ) {
+            const bool j0 = ad.first && k == 0;
+            if (j0) bt = ad.inv_f;
+            // the weighted b of this order, and the load of the next one's
+            const double w = j0 ? 1.0 : 2.0;
+            bw = bn * w;
+            if (ad.final_ && k + 1 == depth) {
+                d2 bs;
+                bs.x = ad.bs_re;
+                bs.y = ad.bs_im;
+                bw = cmul(bs, bn) * w;
+            }
+            if (k + 1 < depth) bn = load_b(k + 1);
+        }
         if (NR >= 2 && act > NT)
             slots(std::integral_constant<int, NR>{}, imag_c, X, B, a, bt, rd);
         else if (act > 0)
             slots(std::integral_constant<int, 1>{}, imag_c, X, B, a, bt, rd);
+        if constexpr (ADJ) {
+            d2 c, v0;
+            c.x = read_lane(cc_l.x, k);
+            c.y = read_lane(cc_l.y, k);
+            v0.x = B[0][0];
+            v0.y = B[0][1];
+            lam += cmul(c, v0);
+        }
     };
     auto keep = [&](int k, V(&B)[NR], uint32_t wr) {
         // inactive rows' values are written too: no row reads them
@@ -297,8 +366,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             if (tid + q * NT < n_eval) at(own_at + OFF + (uint32_t)(q * NT) * RB) = xo[q];
-            if (p.v == p.x) ps[q] = xo[q];
-            if (p.turned) {  // i psi: the first order's alpha is imaginary, the second's real
+            if (!ADJ && p.v == p.x) ps[q] = xo[q];
+            if (!ADJ && p.turned) {  // i psi: the first order's alpha is imaginary, the second's real
 #pragma unroll
                 for (int i = 0; i < VS; ++i) {
                     const R t = ps[q][2 * i];
@@ -310,9 +379,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
         if (tid < n_shell) at(own_at + OFF + (uint32_t)n_eval * RB) = xs;
         for (int l = tid + NT; l < n_shell; l += NT)
             at(lds0 + OFF + (uint32_t)(n_eval + l) * RB) = x[eb + grow_of(n_eval + l)];
+        if constexpr (ADJ) {
+            bn = load_b(0);
+            lam.x = lam.y = 0.0;
+            if (ad.first) {
+                d2 x0;
+                x0.x = xo[0][0];
+                x0.y = xo[0][1];
+                lam = cmul(((const d2 *)ad.cc)[0], x0);
+            } else if (own) {
+                lam = ((const d2 *)ad.lam)[eb + g[0]];
+            }
+        }
         __builtin_amdgcn_s_setprio(0);
         for (int k = 0; k < depth; k += 2) {
-            if (k == 0 && p.first) {
+            if (!ADJ && k == 0 && p.first) {
                 __syncthreads();
                 first_order();
 #pragma unroll
@@ -322,7 +403,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
             }
             keep(k, bq, 0u);
             if (k + 1 < depth) {
-                if (p.alt)
+                if (!ADJ && p.alt)
                     order(std::integral_constant<bool, true>{}, k + 1, bq, xo, 0u);
                 else
                     order(std::integral_constant<bool, false>{}, k + 1, bq, xo, 0u);
@@ -333,7 +414,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
 #pragma unroll
             for (int q = 0; q < NR; ++q) xo[q] = bq[q];
         }
-        if (p.partials) {
+        if constexpr (ADJ) {
+            if (own) {
+                if (ad.final_ && blk < p.s_user)
+                    lam += cmul(((const d2 *)ad.gcorr_l)[blk], ((const d2 *)p.phi0)[eb + g[0]]);
+                ((d2 *)ad.lam)[eb + g[0]] = lam;
+            }
+        } else if (p.partials) {
             // <phi0|psi'> and ||psi'||^2 of the own rows, per state of the block
             double dre[VS], dim[VS], nrm[VS];
 #pragma unroll
@@ -384,6 +471,37 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(
         }
         if (blk + 1 < blk1) __syncthreads();  // the next block's rows overwrite the LDS
     }
+    if constexpr (ADJ) {
+        if (own) {
+            const uint32_t row = g[0], sl = row / kSliceRows, off = ad.slice_off[sl];
+            const int w = (int)((ad.slice_off[sl + 1] - off) / kSliceRows);
+            HV *ga_out = (HV *)ad.gacc + (int64_t)grp * ad.ell_size + off + row % kSliceRows;
+            ad.gdiag[(int64_t)grp * p.n_rows + row] += gd;
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+                if (i < w) {
+                    if constexpr (CH) {
+                        HV v = ga_out[i * kSliceRows];
+                        v.x += ga[i];
+                        v.y += gi[i];
+                        ga_out[i * kSliceRows] = v;
+                    } else {
+                        ga_out[i * kSliceRows] += ga[i];
+                    }
+                }
+        }
+    }
+}
+
+template <typename R, bool CH, int W, int VS, int NT, int NR>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain(const ChainParams p) {
+    chain_body<R, CH, W, VS, NT, NR, false>(p, ChainAdjoint{});
+}
+
+template <bool CH, int W, int NT, int NR>
+__global__ __launch_bounds__(NT)
+    __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain_adjoint(const ChainParams p, const ChainAdjoint ad) {
+    chain_body<double, CH, W, 1, NT, NR, true>(p, ad);
 }
 
 // The tile tables' matrix entries: for every local row of a tile (up to
@@ -487,13 +605,38 @@ hipError_t launch_chain_r(bool cplx, int width, const ChainParams &p, size_t lds
 
 }  // namespace
 
+static bool chain_valid(bool cplx, int width, int max_eval, const ChainParams &p) {
+    return p.depth >= 1 && p.depth <= p.table_depth && p.depth <= kChainMaxDepth && max_eval <= chain_rows(cplx) &&
+           width >= 1 && width <= kChainWidth && p.n_blk >= 1 && p.n_grp >= 1 && p.grp_blk >= 1;
+}
+
+hipError_t launch_chain_adjoint(bool cplx, int width, int max_own, int max_eval, int max_stage, const ChainParams &p,
+                                const ChainAdjoint &ad, hipStream_t st) {
+    if (p.n_tiles <= 0) return hipSuccess;
+    // own rows are slot 0 of a thread
+    if (!chain_valid(cplx, width, max_eval, p) || max_own > chain_threads(cplx)) return hipErrorInvalidValue;
+    const int rows = chain_rows(cplx);
+    const size_t lds = (size_t)16 * (rows + std::max(rows, max_stage));
+    if (lds > 64 * 1024) return hipErrorInvalidValue;
+    const dim3 grid(p.n_grp > 1 ? (unsigned)(((p.n_tiles + 7) / 8) * 8 * p.n_grp) : (unsigned)p.n_tiles);
+    const dim3 block(chain_threads(cplx));
+    constexpr int TR = chain_threads(false), TC = chain_threads(true), NR = kChainRowsPerThread;
+    if (cplx && width <= 3)
+        hipLaunchKernelGGL((k_chain_adjoint<true, 3, TC, NR>), grid, block, lds, st, p, ad);
+    else if (cplx)
+        hipLaunchKernelGGL((k_chain_adjoint<true, 4, TC, NR>), grid, block, lds, st, p, ad);
+    else if (width <= 3)
+        hipLaunchKernelGGL((k_chain_adjoint<false, 3, TR, NR>), grid, block, lds, st, p, ad);
+    else
+        hipLaunchKernelGGL((k_chain_adjoint<false, 4, TR, NR>), grid, block, lds, st, p, ad);
+    return hipGetLastError();
+}
+
 hipError_t launch_chain(bool fp32, bool cplx, int width, int vs, int max_eval, int max_stage, const ChainParams &p,
                         hipStream_t st) {
     if (p.n_tiles <= 0) return hipSuccess;
     const int rows = chain_rows(cplx);
-    if (p.depth < 1 || p.depth > p.table_depth || p.depth > kChainMaxDepth || max_eval > rows || width < 1 ||
-        width > kChainWidth || p.n_blk < 1 || p.n_grp < 1 || p.grp_blk < 1)
-        return hipErrorInvalidValue;
+    if (!chain_valid(cplx, width, max_eval, p)) return hipErrorInvalidValue;
     // both buffers, and at least the partial sums of the correlation
     const size_t lds = (size_t)(fp32 ? 8 : 16) * vs * (rows + std::max(rows, max_stage));
     if (lds > 64 * 1024) return hipErrorInvalidValue;

@@ -131,6 +131,7 @@ struct Engine {
     tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs);
     // whether the vectors (vec bytes each) and tables that the chain needs beyond
     // the ones held fit the device memory that is free
+    bool chain_room(bool fp32, size_t need);
     bool chain_fits(const ChainShape &cs, bool fp32, size_t vec);
     tbpm_status chain_values(bool fp32, hipStream_t st);
     ChainParams chain_params(const ChainShape &cs) const;

@@ -164,6 +164,8 @@ hipError_t launch_pair(int kind, bool fp32, bool cplx, bool nontemporal, int vs,
 // the most local rows of a tile within depth - 1 and depth hops
 hipError_t launch_chain(bool fp32, bool cplx, int width, int vs, int max_eval, int max_stage, const ChainParams &p,
                         hipStream_t st);
+hipError_t launch_chain_adjoint(bool cplx, int width, int max_own, int max_eval, int max_stage, const ChainParams &p,
+                                const ChainAdjoint &ad, hipStream_t st);
 hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int32_t n_tiles, const DevMatrix &m,
                                void *tval, void *tons, hipStream_t st);
 // sums the partials of n_local steps (step_stride doubles apart) into samples
@@ -246,17 +248,16 @@ hipError_t launch_kubo_bastin(const double *mu, int32_t n_mom, double rescale, d
                               double *energies, double *weight, double *sigma, hipStream_t st);
 
 hipError_t launch_adjoint_pass(int kind, bool cplx, const AdjParams &p, hipStream_t st);
-// dst[r][s] = src[perm[r]][s] (src[r][s] if perm is null), zero for s >= s_user
-hipError_t launch_expand_states(const double *src, const int32_t *perm, int32_t s_user, double *dst, int32_t log2s,
-                                int64_t n_rows,
-                                hipStream_t st);
+// dst[r][s] = src[perm[r]][s] (src[r][s] if perm is null), zero for s >= s_user;
+// dst in blocks of 2^log2sb states (state_index)
+hipError_t launch_expand_states(const double *src, const int32_t *perm, int32_t s_user, double *dst, int32_t log2sb,
+                                int64_t n_rows, hipStream_t st);
 hipError_t launch_lam_init(double *lam, const double *phi0, const double *gcorr_last, int32_t s_user,
-                           int32_t log2s, int64_t n_rows, hipStream_t st);
+                           int32_t log2sb, int64_t n_rows, hipStream_t st);
 hipError_t launch_fill_zero(double *p, int64_t n, hipStream_t st);
 hipError_t launch_grad_scatter(const void *gacc, const double *gdiag, const int64_t *ell_csr, int64_t ell_size,
                                bool cplx, double inv_f, double *grad_val, double *grad_onsite, const int32_t *perm,
-                               int64_t n_rows,
-                               hipStream_t st);
+                               int64_t n_rows, const int32_t *partner, int32_t n_copy, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Host helpers (host.cpp)

@@ -119,3 +119,37 @@ def test_chain_without_a_configuration():
     ref = tbpm.propagate(H, psi, 70, math.pi / f, f)
     assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-11
     assert _rel(first.cpu().numpy(), ref.cpu().numpy()) > 1e-3  # the values did change
+
+
+@pytest.mark.parametrize("kind", ["ring5", "graphene_small", "graphene", "square_open", "graphene_complex",
+                                  "square_complex", "chain5"])
+def test_chain_backward_matches_one_order_per_launch(kind):
+    """The replay that stores every order and the adjoint's several orders per launch (chain5, six elements per
+    row: the two-order launches).  A gradient is a sum of some 1e5 products of states with errors of 1e-14 against
+    each other: 1e-11 of the largest gradient, and 1e-10 against the oracle."""
+    rng = np.random.default_rng(6)
+    if kind == "chain5":
+        i = np.arange(300)
+        lat = inputs.from_bonds(300, np.concatenate([i, i, i]), np.concatenate([(i + d) % 300 for d in (1, 2, 7)]),
+                                -1.0 - rng.random(900), rng.uniform(-1, 1, 300))
+    else:
+        lat = _lattice(kind, rng)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    # one, odd and many states (groups of blocks); 17, few and many orders; segments with a remainder
+    for S, z, nt, K in ((1, math.pi, 12, 4), (3, math.pi, 8, 3), (8, 0.3, 6, 8), (5, 9.0, 4, 2), (2, 1e-7, 3, 1)):
+        psi_np = inputs.random_phase_states(rng, lat.n_orb, S)
+        psi = torch.from_numpy(psi_np).cuda()
+        g = rng.standard_normal((nt, S)) + 1j * rng.standard_normal((nt, S))
+        gd = torch.from_numpy(g).cuda()
+        out = []
+        for shape in ({}, CHAIN):
+            H.set_launch_config(**shape)
+            _, ck = tbpm.propagate(H, psi, nt, z / f, f, ckpt_every=K)
+            out.append([t.cpu().numpy() for t in tbpm.backward(H, psi, nt, z / f, f, gd, K, ck)])
+        for a, b in zip(*out):
+            assert _rel(b, a) < 1e-11, (S, z, nt)
+        if lat.n_orb < 10000:
+            for b, w in zip(out[1], oracle.backward(lat.row_ptr, lat.col, lat.val, lat.onsite, psi_np, nt, z / f, f, g)):
+                assert _rel(b if H.info()["is_complex"] else b.real, w if H.info()["is_complex"] else w.real) < 1e-10
+    H.close()
