@@ -5,7 +5,7 @@
 // b_1 .. b_{M-2} (b_{M-1} = c_{M-1} psi_l is recomputed on the fly); the
 // adjoint then runs backwards through the segment, one fused kernel per
 // Chebyshev order j (see backward.hip), or one per several orders
-// (k_chain_adjoint).  Device memory: (K+1) + K (M-2) state vectors for the
+// (k_chain_cheb).  Device memory: (K+1) + K (M-2) state vectors for the
 // segment plus four or five adjoint vectors.
 #include <hip/hip_runtime.h>
 
@@ -399,7 +399,7 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
         cp.xcd_remap = eng.cfg.xcd_remap;
         cp.phi0 = phi0p;
         cp.s_user = s_user;
-        ChainAdjoint ad{};
+        ChainCheb ad{};
         ad.bq_stride = (int64_t)vb;
         ad.psi = psi_slot(t);
         ad.bs_re = c[M - 1].real();
@@ -428,8 +428,8 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
             ad.cc = conj_c + 2 * j0;
             ad.first = j0 == 0;
             ad.final_ = last;
-            e = launch_chain_adjoint(cplx, eng.chain_width(), eng.ch.T, eng.ch.max_stage[d - 1], eng.ch.max_stage[d], cp,
-                                     ad, st);
+            e = launch_chain_cheb(kChainAdjoint, cplx, eng.chain_width(), (int)eng.ch.T, eng.ch.max_stage[d - 1],
+                                  eng.ch.max_stage[d], cp, ad, st);
             // the old x and alpha_{j-1} (the fourth buffer after the first launch)
             // take the next outputs
             double *np = fr[0], *nx = fr[1];

@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kWG) void k_fill_zero(double *__restrict__ p, int64
     for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += stride) p[i] = 0.0;
 }
 
-// partner == null: slot q's gradient is gacc[q].  Otherwise (k_chain_adjoint) it
+// partner == null: slot q's gradient is gacc[q].  Otherwise (k_chain_cheb) it
 // is kept in the slot of the transposed element, in n_copy copies ell_size /
 // n_rows apart.
 template <bool CH>

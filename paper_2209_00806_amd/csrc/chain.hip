@@ -73,9 +73,10 @@ __device__ __forceinline__ double wave_sum(double x) {
 // their workgroups have 4 waves (three of them per CU).
 constexpr int chain_waves(bool ch) { return ch ? 3 : 4; }
 
-// The body of k_chain and k_chain_adjoint.  In the adjoint (ADJ) an order is
-//     alpha_{j+1} = 2 H~ alpha_j - alpha_{j-1}   (H~ alpha_0 for j = 0),
-// lambda gains conj(c_{j+1}) alpha_{j+1}, and own row q adds to the gradient of
+// The body of k_chain (Clenshaw orders) and k_chain_cheb (Chebyshev orders
+//     T_{j+1} = 2 H~ T_j - T_{j-1},   T_1 = H~ T_0).
+// kChainCurrent also applies a current operator to every T_j from the same
+// neighbours in LDS.  In the adjoint (kChainAdjoint, T_j = alpha_j) lambda gains conj(c_{j+1}) alpha_{j+1}, and own row q adds to the gradient of
 // its transposed elements (p, q) Re/Im of alpha_j[p] conj(w b_{j+1}[q]): alpha_j
 // at p is read from LDS for the product anyway, b at the own row is the only
 // stream of its own, and the sums over orders and state blocks stay in registers
@@ -86,9 +87,10 @@ constexpr int chain_waves(bool ch) { return ch ? 3 : 4; }
 // two orders per launch of both (there the adjoint was 29 ms of it, bound by the
 // read-modify-write of the gradient for every pair of orders and the sums over
 // lanes).
-template <typename R, bool CH, int W, int VS, int NT, int NR, bool ADJ>
-__device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjoint &ad) {
+template <typename R, bool CH, int W, int VS, int NT, int NR, int MODE>
+__device__ __forceinline__ void chain_body(const ChainParams &p, const ChainCheb &ad) {
     extern __shared__ __align__(16) unsigned char chain_mem[];
+    constexpr bool CHEB = MODE != kChainClenshaw, ADJ = MODE == kChainAdjoint, CUR = MODE == kChainCurrent;
     using V = VecT<R, VS>;
     using HV = typename HValT<R, CH>::T;
     // the groups of state blocks of a tile run on one XCD (workgroup g goes to XCD g & 7)
@@ -181,13 +183,13 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
     // lane k holds order k's coefficient (the nonzero part of alpha) and its
     // number of rows: the loop reads them with readlane, where scalar loads
     // would make every order's LDS reads wait for them
-    const PassCoef *cf = p.coef + (ADJ ? 0 : td.inst);
+    const PassCoef *cf = p.coef + (CHEB ? 0 : td.inst);
     R alpha_l = R(0), beta, beta_last;
     int lim_l;
     {
         const int k = min(tid & 63, depth - 1);
         lim_l = cnt[depth - 1 - k];
-        if constexpr (ADJ) {
+        if constexpr (CHEB) {
             beta = beta_last = (R)(2.0 * ad.inv_f);
         } else {
             const PassCoef c = cf[(int64_t)k * p.n_inst];
@@ -203,6 +205,17 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
     const bool own = tid < n_own;
     double ga[ADJ ? W : 1], gi[ADJ && CH ? W : 1], gd = 0.0;
     d2 lam, bw, bn, cc_l;
+    // the current operator's elements of the own row
+    d2 jv[CUR ? W : 1], jx;
+    if constexpr (CUR) {
+        const uint32_t sl = g[0] / kSliceRows, off = ad.slice_off[sl];
+        const int w = (int)((ad.slice_off[sl + 1] - off) / kSliceRows);
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            jv[i].x = jv[i].y = 0.0;
+            if (own && i < w) jv[i] = ((const d2 *)ad.jval)[off + i * kSliceRows + g[0] % kSliceRows];
+        }
+    }
     if constexpr (ADJ) {
 #pragma unroll
         for (int i = 0; i < W; ++i) ga[i] = 0.0;
@@ -231,6 +244,14 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
 #pragma unroll
             for (int i = 0; i < W; ++i) xc[q][i] = at(na[q][i] + rd);
         V acc[N];
+        if constexpr (CUR) {
+            jx.x = jx.y = 0.0;
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                jx.x = fma(jv[i].x, xc[0][i][0], fma(-jv[i].y, xc[0][i][1], jx.x));
+                jx.y = fma(jv[i].x, xc[0][i][1], fma(jv[i].y, xc[0][i][0], jx.y));
+            }
+        }
         if constexpr (ADJ) {
             gd = fma(X[0][0], bw.x, fma(X[0][1], bw.y, gd));
 #pragma unroll
@@ -241,7 +262,7 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
         }
 #pragma unroll
         for (int q = 0; q < N; ++q) {
-            if constexpr (ADJ) {
+            if constexpr (CHEB) {
                 B[q] = -B[q];
             } else if constexpr (sizeof(R) == 8) {
 #pragma unroll
@@ -311,11 +332,12 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
     auto order = [&](auto imag_c, int k, V(&X)[NR], V(&B)[NR], uint32_t rd) {
         __syncthreads();
         const int act = read_lane(lim_l, k) - wbase;
-        const R a = ADJ ? R(0) : read_lane(alpha_l, k);
+        const R a = CHEB ? R(0) : read_lane(alpha_l, k);
         R bt = k + 1 == depth ? beta_last : beta;
+        if constexpr (CHEB)
+            if (ad.first && k == 0) bt = ad.inv_f;
         if constexpr (ADJ) {
             const bool j0 = ad.first && k == 0;
-            if (j0) bt = ad.inv_f;
             // the weighted b of this order, and the load of the next one's
             const double w = j0 ? 1.0 : 2.0;
             bw = bn * w;
@@ -331,6 +353,8 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
             slots(std::integral_constant<int, NR>{}, imag_c, X, B, a, bt, rd);
         else if (act > 0)
             slots(std::integral_constant<int, 1>{}, imag_c, X, B, a, bt, rd);
+        if constexpr (CUR)
+            if (own) stv<true>((d2 *)((char *)ad.jout + (int64_t)k * ad.jout_stride) + (eb + g[0]), jx);
         if constexpr (ADJ) {
             d2 c, v0;
             c.x = read_lane(cc_l.x, k);
@@ -366,8 +390,8 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             if (tid + q * NT < n_eval) at(own_at + OFF + (uint32_t)(q * NT) * RB) = xo[q];
-            if (!ADJ && p.v == p.x) ps[q] = xo[q];
-            if (!ADJ && p.turned) {  // i psi: the first order's alpha is imaginary, the second's real
+            if (!CHEB && p.v == p.x) ps[q] = xo[q];
+            if (!CHEB && p.turned) {  // i psi: the first order's alpha is imaginary, the second's real
 #pragma unroll
                 for (int i = 0; i < VS; ++i) {
                     const R t = ps[q][2 * i];
@@ -393,7 +417,7 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
         }
         __builtin_amdgcn_s_setprio(0);
         for (int k = 0; k < depth; k += 2) {
-            if (!ADJ && k == 0 && p.first) {
+            if (!CHEB && k == 0 && p.first) {
                 __syncthreads();
                 first_order();
 #pragma unroll
@@ -403,7 +427,7 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
             }
             keep(k, bq, 0u);
             if (k + 1 < depth) {
-                if (!ADJ && p.alt)
+                if (!CHEB && p.alt)
                     order(std::integral_constant<bool, true>{}, k + 1, bq, xo, 0u);
                 else
                     order(std::integral_constant<bool, false>{}, k + 1, bq, xo, 0u);
@@ -420,7 +444,7 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
                     lam += cmul(((const d2 *)ad.gcorr_l)[blk], ((const d2 *)p.phi0)[eb + g[0]]);
                 ((d2 *)ad.lam)[eb + g[0]] = lam;
             }
-        } else if (p.partials) {
+        } else if (!CHEB && p.partials) {
             // <phi0|psi'> and ||psi'||^2 of the own rows, per state of the block
             double dre[VS], dim[VS], nrm[VS];
 #pragma unroll
@@ -495,13 +519,13 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainAdjo
 
 template <typename R, bool CH, int W, int VS, int NT, int NR>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain(const ChainParams p) {
-    chain_body<R, CH, W, VS, NT, NR, false>(p, ChainAdjoint{});
+    chain_body<R, CH, W, VS, NT, NR, kChainClenshaw>(p, ChainCheb{});
 }
 
-template <bool CH, int W, int NT, int NR>
+template <bool CH, int W, int NT, int NR, int MODE>
 __global__ __launch_bounds__(NT)
-    __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain_adjoint(const ChainParams p, const ChainAdjoint ad) {
-    chain_body<double, CH, W, 1, NT, NR, true>(p, ad);
+    __attribute__((amdgpu_waves_per_eu(chain_waves(CH)))) void k_chain_cheb(const ChainParams p, const ChainCheb ad) {
+    chain_body<double, CH, W, 1, NT, NR, MODE>(p, ad);
 }
 
 // The tile tables' matrix entries: for every local row of a tile (up to
@@ -610,8 +634,22 @@ static bool chain_valid(bool cplx, int width, int max_eval, const ChainParams &p
            width >= 1 && width <= kChainWidth && p.n_blk >= 1 && p.n_grp >= 1 && p.grp_blk >= 1;
 }
 
-hipError_t launch_chain_adjoint(bool cplx, int width, int max_own, int max_eval, int max_stage, const ChainParams &p,
-                                const ChainAdjoint &ad, hipStream_t st) {
+template <int MODE>
+static void launch_cheb_t(bool cplx, int width, dim3 grid, size_t lds, const ChainParams &p, const ChainCheb &ad,
+                          hipStream_t st) {
+    constexpr int TR = chain_threads(false), TC = chain_threads(true), NR = kChainRowsPerThread;
+    if (cplx && width <= 3)
+        hipLaunchKernelGGL((k_chain_cheb<true, 3, TC, NR, MODE>), grid, dim3(TC), lds, st, p, ad);
+    else if (cplx)
+        hipLaunchKernelGGL((k_chain_cheb<true, 4, TC, NR, MODE>), grid, dim3(TC), lds, st, p, ad);
+    else if (width <= 3)
+        hipLaunchKernelGGL((k_chain_cheb<false, 3, TR, NR, MODE>), grid, dim3(TR), lds, st, p, ad);
+    else
+        hipLaunchKernelGGL((k_chain_cheb<false, 4, TR, NR, MODE>), grid, dim3(TR), lds, st, p, ad);
+}
+
+hipError_t launch_chain_cheb(int mode, bool cplx, int width, int max_own, int max_eval, int max_stage,
+                             const ChainParams &p, const ChainCheb &ad, hipStream_t st) {
     if (p.n_tiles <= 0) return hipSuccess;
     // own rows are slot 0 of a thread
     if (!chain_valid(cplx, width, max_eval, p) || max_own > chain_threads(cplx)) return hipErrorInvalidValue;
@@ -619,16 +657,14 @@ hipError_t launch_chain_adjoint(bool cplx, int width, int max_own, int max_eval,
     const size_t lds = (size_t)16 * (rows + std::max(rows, max_stage));
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const dim3 grid(p.n_grp > 1 ? (unsigned)(((p.n_tiles + 7) / 8) * 8 * p.n_grp) : (unsigned)p.n_tiles);
-    const dim3 block(chain_threads(cplx));
-    constexpr int TR = chain_threads(false), TC = chain_threads(true), NR = kChainRowsPerThread;
-    if (cplx && width <= 3)
-        hipLaunchKernelGGL((k_chain_adjoint<true, 3, TC, NR>), grid, block, lds, st, p, ad);
-    else if (cplx)
-        hipLaunchKernelGGL((k_chain_adjoint<true, 4, TC, NR>), grid, block, lds, st, p, ad);
-    else if (width <= 3)
-        hipLaunchKernelGGL((k_chain_adjoint<false, 3, TR, NR>), grid, block, lds, st, p, ad);
+    if (mode == kChainAdjoint)
+        launch_cheb_t<kChainAdjoint>(cplx, width, grid, lds, p, ad, st);
+    else if (mode == kChainCurrent)
+        launch_cheb_t<kChainCurrent>(cplx, width, grid, lds, p, ad, st);
+    else if (mode == kChainCheb)
+        launch_cheb_t<kChainCheb>(cplx, width, grid, lds, p, ad, st);
     else
-        hipLaunchKernelGGL((k_chain_adjoint<false, 4, TR, NR>), grid, block, lds, st, p, ad);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -181,24 +181,32 @@ struct ChainParams {
     int32_t s_user;
 };
 
-// The adjoint's several orders per launch: x = alpha_j, b2 = alpha_{j-1} (null for
-// j = 0), no v; per order the gradient of every stored element and on-site
-// energy from alpha_j at the neighbours and b_{j+1} at the own row, and lambda.
-struct ChainAdjoint {
+// Several orders of the Chebyshev recursion T_{j+1} = 2 H~ T_j - T_{j-1} per
+// launch: x = T_j, b2 = T_{j-1} (null for j = 0), no v.
+struct ChainCheb {
+    double inv_f;
+    const uint32_t *slice_off;
+    int32_t first, final_;  // the launch holds j = 0 / the last order of a time step
+    // kChainCurrent: jout + k jout_stride = J T_{j+k}, J without on-site entries
+    // (complex, in the order of the sliced ELL's slots)
+    const void *jval;
+    void *jout;
+    int64_t jout_stride;  // bytes
+    // kChainAdjoint: T_j = alpha_j; per order the gradient of every stored element
+    // and on-site energy from alpha_j at the neighbours and b_{j+1} at the own
+    // row, and lambda
     const void *bq;        // b_{j+1} of the first order; the next orders' bq_stride bytes on
     int64_t bq_stride;
     const void *psi;       // last order of a time step (final): b_{M-1} = bs psi in bq's place
     double bs_re, bs_im;
-    double inv_f;
     const double *cc;      // conj(c_j) from the first order's j on, complex
     const double *gcorr_l; // final: complex [s_user], lambda += gcorr_l phi0
     void *lam;             // lambda accumulator, state blocks
     void *gacc;            // [n_grp][ell_size] double (real H) or double2: own slot of (q, p), gradient of (p, q)
     double *gdiag;         // [n_grp][n_rows]
     int64_t ell_size;
-    const uint32_t *slice_off;
-    int32_t first, final_; // the launch holds the first / the last order of the time step
 };
+enum { kChainClenshaw = 0, kChainAdjoint = 1, kChainCheb = 2, kChainCurrent = 3 };
 
 struct ChainTileTab {
     const int32_t *cnt, *toff, *loff;

@@ -32,7 +32,25 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
         ++log2s;
     }
     const int64_t n = mat.n_rows;
-    const int64_t K = n * s_pad;  // inner dimension of the moment product
+    // Rows of up to four elements: several Chebyshev orders per launch (two
+    // per launch, or one, otherwise), under the rule of the propagation.
+    // L_m are written as they arise, and the current operator meets T_n in LDS, so
+    // that T_n is not stored but for the two that the next launch reads.  Graphene
+    // 512^2, 512 moments, one state: both recursions 4.6 ms (1024 orders; their
+    // stores alone, 8.6 GB, take 1.8 ms at the rate of a copy), 12.0 ms with two
+    // orders per launch and the operator in launches of its own.
+    ChainShape cs;
+    bool chain = n_mom >= 3 &&
+                 (cfgs[0].fused > 0 || (!cfg_set[0] && 2 * (int64_t)n_mom > 17 * (int64_t)kChainAutoSteps)) &&
+                 chain_prepare(s_user, false, n_mom - 1, cs) == TBPM_OK;
+    if (chain) {
+        const size_t vs1 = 16 * (size_t)n * s_user + 768, nbc = (size_t)std::min<int32_t>(n_mom, 128);
+        auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+        // 1 GiB for the product's parts at the most common sizes
+        chain = chain_room(false, grow(kp_store, vs1 * n_mom) + grow(kp_rblk, vs1 * nbc) + grow(kp_vec, vs1 * 5) +
+                                      ((size_t)1 << 30));
+    }
+    const int64_t K = n * (chain ? s_user : s_pad);  // inner dimension of the moment product
     const int32_t nb = std::min<int32_t>(n_mom, 128);
     const size_t vec = sizeof(double) * 2 * (size_t)K;
     // vectors of the L store and the R block lie vstride bytes apart: a pad
@@ -62,7 +80,7 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     // (the Clenshaw pair with alpha = 0 is the three-term recursion: the second
     // order subtracts the first's input): L_m straight into the store, T_n
     // over four rotating blocks.
-    bool pairs = cfgs[0].fused > 0 && n_mom >= 4;
+    bool pairs = !chain && cfgs[0].fused > 0 && n_mom >= 4;
     int32_t pvs = 1, log2pvs = 0;
     while (pvs < cfgs[0].vec && pvs < s_pad && pvs < 4) {
         pvs <<= 1;
@@ -70,7 +88,10 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     }
     const bool pnt = cfgs[0].nontemporal != 0;
     if (pairs && build_fused_tiles(s_pad, log2s - log2pvs, 16 * pvs, cfgs[0].fused) != TBPM_OK) pairs = false;
-    if (!pairs) {
+    if (chain) {
+        tbpm_status s0 = chain_values(false, st);
+        if (s0 != TBPM_OK) return s0;
+    } else if (!pairs) {
         tbpm_status s0 = build_tiles(s_pad, cfg.wg_chunks, 1);
         if (s0 != TBPM_OK) return s0;
     }
@@ -155,14 +176,53 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     char *Rb = (char *)kp_rblk.ptr;
     char *vb = (char *)kp_vec.ptr;
     void *r = vb, *t0 = vb + vec, *t1 = vb + 2 * vec;
-    TRY_HIP(launch_expand_states(psi0, mat.perm, s_user, (double *)r, log2s, n, st), "load random vectors");
+    TRY_HIP(launch_expand_states(psi0, mat.perm, s_user, (double *)r, chain ? cs.log2sb() : log2s, n, st), "load random vectors");
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     if (timing)
         for (auto &e : ev) TRY_HIP(hipEventCreate(&e), "hipEventCreate");
     if (timing) TRY_HIP(hipEventRecord(ev[0], st), "record");
 
+    // orders [k0, k0 + d) of a Chebyshev recursion from T_k0 = x, T_{k0-1} = b2:
+    // T_{k0+1+k} at out + k vstride (none stored if out is null but the last
+    // two, prev and last), J T_{k0+k} at jout + k vstride
+    auto cheb = [&](int32_t k0, int32_t d, const void *x, const void *b2, void *out, void *prev, void *last,
+                    const double *jval, void *jout) -> hipError_t {
+        ChainParams cp = chain_params(cs);
+        cp.xcd_remap = cfg.xcd_remap;
+        cp.depth = d;
+        cp.reverse = walk;
+        walk ^= 1;
+        cp.x = x;
+        cp.b2 = b2;
+        cp.out_all = out;
+        cp.out_stride = (int64_t)vstride;
+        cp.out_prev = prev;
+        cp.out_last = last;
+        ChainCheb cc{};
+        cc.inv_f = 1.0 / f;
+        cc.slice_off = mat.slice_off;
+        cc.first = k0 == 0;
+        cc.jval = jval;
+        cc.jout = jout;
+        cc.jout_stride = (int64_t)vstride;
+        return launch_chain_cheb(jval ? kChainCurrent : kChainCheb, mat.is_complex, chain_width(), (int)ch.T,
+                                 ch.max_stage[d - 1], ch.max_stage[d], cp, cc, st);
+    };
+
     // L_0 = v_a r, L_1 = H~ L_0, L_{m+1} = 2 H~ L_m - L_{m-1}, in place in the store
-    TRY_HIP(pass(kPassFirst, true, ja, r, nullptr, Ls, c_j), "launch current operator");
+    if (chain) {
+        TRY_HIP(cheb(0, 1, r, nullptr, nullptr, nullptr, nullptr, ja, Ls), "launch current operator");
+        int32_t m = 0;  // L_m is the newest
+        for (const int32_t d : cs.depths) {
+            char *x = Ls + vstride * (size_t)m;
+            TRY_HIP(cheb(m, d, x, m == 0 ? nullptr : x - vstride, x + vstride, nullptr, x + vstride * (size_t)d, nullptr,
+                         nullptr),
+                    "launch Chebyshev chain");
+            m += d;
+        }
+    } else {
+        TRY_HIP(pass(kPassFirst, true, ja, r, nullptr, Ls, c_j), "launch current operator");
+    }
     int32_t m_done = 1;  // orders written so far
     if (pairs) {
         TRY_HIP(pass(kPassFirst, false, nullptr, Ls, nullptr, Ls + vstride, c_1), "launch Chebyshev pass");
@@ -172,7 +232,7 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
                          Ls + vstride * (size_t)(m_done + 1)),
                     "launch Chebyshev pair");
     }
-    for (int32_t m = m_done; m < n_mom; ++m) {
+    for (int32_t m = m_done; !chain && m < n_mom; ++m) {
         void *out = Ls + vstride * (size_t)m;
         const void *x = Ls + vstride * (size_t)(m - 1);
         if (m == 1)
@@ -191,6 +251,9 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     // over T_{n-4} and T_{n-3}, whose current-operator passes are done)
     void *tq[4] = {vb + 3 * vec, t0, t1, vb + 4 * vec};
     int32_t produced = 0;  // T_0 = r
+    // the chain's T recursion: (x, b2) the two newest orders, two more buffers
+    // for the next launch's last two
+    const void *cx = r, *cb2 = nullptr;
     float gemm_ms = 0.0f;
     for (int32_t n0 = 0; n0 < n_mom; n0 += nb) {
         const int32_t cnt = std::min(nb, n_mom - n0);
@@ -216,7 +279,7 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
             const void *tcur = nn == 0 ? r : tq[nn & 3];
             TRY_HIP(pass(kPassFirst, true, jb, tcur, nullptr, Rb + vstride * (size_t)j, c_j), "launch current operator");
         }
-        for (int32_t j = 0; !pairs && j < cnt; ++j) {
+        for (int32_t j = 0; !pairs && !chain && j < cnt; ++j) {
             const int32_t nn = n0 + j;
             if (nn == 1) {
                 TRY_HIP(pass(kPassFirst, false, nullptr, r, nullptr, t0, c_1), "launch Chebyshev pass");
@@ -232,6 +295,20 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
                 tc = prev;
             }
             TRY_HIP(pass(kPassFirst, true, jb, tc, nullptr, Rb + vstride * (size_t)j, c_j), "launch current operator");
+        }
+        for (int32_t j = 0; chain && j < cnt;) {
+            // a block's orders in launches of nearly equal depth
+            const int32_t n_launch = (cnt - j + ch.depth - 1) / ch.depth, d = (cnt - j) / n_launch;
+            void *o[2] = {nullptr, nullptr};
+            for (int b = 1, i = 0; b < 5 && i < 2; ++b) {
+                void *t = vb + (size_t)b * vec;
+                if (t != cx && t != cb2) o[i++] = t;
+            }
+            TRY_HIP(cheb(n0 + j, d, cx, cb2, nullptr, d > 1 ? o[0] : nullptr, o[1], jb, Rb + vstride * (size_t)j),
+                    "launch Chebyshev chain");
+            cb2 = d > 1 ? o[0] : cx;
+            cx = o[1];
+            j += d;
         }
         hipEvent_t g0 = nullptr, g1 = nullptr;
         if (timing) {

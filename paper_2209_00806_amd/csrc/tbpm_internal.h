@@ -164,8 +164,10 @@ hipError_t launch_pair(int kind, bool fp32, bool cplx, bool nontemporal, int vs,
 // the most local rows of a tile within depth - 1 and depth hops
 hipError_t launch_chain(bool fp32, bool cplx, int width, int vs, int max_eval, int max_stage, const ChainParams &p,
                         hipStream_t st);
-hipError_t launch_chain_adjoint(bool cplx, int width, int max_own, int max_eval, int max_stage, const ChainParams &p,
-                                const ChainAdjoint &ad, hipStream_t st);
+// several Chebyshev orders (mode: kChainCheb, kChainCurrent or kChainAdjoint);
+// max_own: the most rows of a tile
+hipError_t launch_chain_cheb(int mode, bool cplx, int width, int max_own, int max_eval, int max_stage,
+                             const ChainParams &p, const ChainCheb &ad, hipStream_t st);
 hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int32_t n_tiles, const DevMatrix &m,
                                void *tval, void *tons, hipStream_t st);
 // sums the partials of n_local steps (step_stride doubles apart) into samples

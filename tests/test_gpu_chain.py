@@ -153,3 +153,29 @@ def test_chain_backward_matches_one_order_per_launch(kind):
             for b, w in zip(out[1], oracle.backward(lat.row_ptr, lat.col, lat.val, lat.onsite, psi_np, nt, z / f, f, g)):
                 assert _rel(b if H.info()["is_complex"] else b.real, w if H.info()["is_complex"] else w.real) < 1e-10
     H.close()
+
+
+@pytest.mark.parametrize("kind", ["graphene_small", "graphene", "square_open", "graphene_complex", "square_complex"])
+def test_chain_moments_match_one_order_per_launch(kind):
+    """Kubo-Bastin moments with several Chebyshev orders per launch and the current operator applied in them:
+    fewest moments, one block of moments and a remainder, odd state counts.  A moment sums products of vectors
+    with errors of M 1e-16: 1e-12 of the largest moment."""
+    rng = np.random.default_rng(7)
+    lat = _lattice(kind, rng)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    if kind.startswith("graphene"):
+        ja, jb = inputs.current_values(lat, 0), inputs.current_values(lat, 1)
+    else:  # any antisymmetric displacements
+        i = np.repeat(np.arange(lat.n_orb), np.diff(lat.row_ptr))
+        x = rng.uniform(0, 1, lat.n_orb)
+        ja = 1j * lat.val * (x[lat.col] - x[i])
+        jb = 1j * lat.val * (np.sin(9 * x)[lat.col] - np.sin(9 * x)[i])
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    for S, M in ((1, 2), (1, 3), (3, 4), (2, 130), (1, 261)):
+        psi = torch.from_numpy(inputs.random_phase_states(rng, lat.n_orb, S)).cuda()
+        out = []
+        for shape in ({}, CHAIN):
+            H.set_launch_config(**shape)
+            out.append(tbpm.kpm_moments(H, ja, jb, psi, M, f).cpu().numpy())
+        assert _rel(out[1], out[0]) < 1e-12, (S, M)
+    H.close()
