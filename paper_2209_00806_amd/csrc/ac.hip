@@ -120,30 +120,41 @@ __global__ __launch_bounds__(kWG) void k_jcorr(const TileDesc *__restrict__ tile
 // w_j = j pi / (N_t dt), sigma(0) = 0; the phase w_j t_k = pi (j k mod 2N)/N
 // is reduced exactly in integers, the sum is compensated.
 __global__ __launch_bounds__(kWG) void k_ac_cond(const d2 *__restrict__ corr, int n_steps, int n_states, double dt,
-                                                 double beta, double area, int window, double *__restrict__ omegas,
-                                                 double *__restrict__ sigma) {
-    const int j = blockIdx.x * kWG + threadIdx.x;
-    if (j >= n_steps) return;
+                                                 double beta, double area, int window, int log2l,
+                                                 double *__restrict__ omegas, double *__restrict__ sigma) {
+    __shared__ double c[kWG];
+    const int lane = (int)threadIdx.x & ((1 << log2l) - 1);
+    const int64_t j = ((int64_t)blockIdx.x * kWG + threadIdx.x) >> log2l;
+    const int64_t two_n = 2 * (int64_t)n_steps;
+    // m = j k mod 2N of the lane's terms k = 1 + lane, 1 + lane + L, ...
+    int64_t m = (j * (1 + lane)) % two_n;
+    const int64_t dm = (j << log2l) % two_n;
+    double sum = 0.0, comp = 0.0;
+    for (int k0 = 1; k0 < n_steps; k0 += kWG) {
+        const int k = k0 + (int)threadIdx.x;
+        double im = 0.0;
+        if (k < n_steps) {
+            for (int s = 0; s < n_states; ++s) im += corr[(int64_t)k * n_states + s].y;
+            im /= n_states;
+            im *= 2.0 * (window == TBPM_WIN_HANN ? 0.5 * (1.0 + cospi((double)k / n_steps)) : 1.0);
+        }
+        c[threadIdx.x] = im;
+        __syncthreads();
+        const int kn = min(kWG, n_steps - k0);
+        if (j < n_steps) {
+            for (int kk = lane; kk < kn; kk += 1 << log2l) {
+                kadd(sum, comp, c[kk] * sinpi((double)m / n_steps));
+                m += dm;
+                if (m >= two_n) m -= two_n;
+            }
+        }
+        __syncthreads();
+    }
+    sum = kadd_lanes(sum, comp, log2l);
+    if (j >= n_steps || lane != 0) return;
     const double w_j = M_PI * j / (n_steps * dt);
     omegas[j] = w_j;
-    if (j == 0) {
-        sigma[0] = 0.0;
-        return;
-    }
-    const int64_t two_n = 2 * (int64_t)n_steps;
-    double sum = 0.0, comp = 0.0;
-    for (int k = 1; k < n_steps; ++k) {
-        double im = 0.0;
-        for (int s = 0; s < n_states; ++s) im += corr[(int64_t)k * n_states + s].y;
-        im /= n_states;
-        const double wk = window == TBPM_WIN_HANN ? 0.5 * (1.0 + cospi((double)k / n_steps)) : 1.0;
-        const int64_t m = ((int64_t)j * k) % two_n;
-        const double term = wk * sinpi((double)m / n_steps) * 2.0 * im;
-        const double t = sum + term;  // Neumaier
-        comp += fabs(sum) >= fabs(term) ? (sum - t) + term : (term - t) + sum;
-        sum = t;
-    }
-    sigma[j] = (exp(-beta * w_j) - 1.0) / (w_j * area) * (sum + comp) * dt;
+    sigma[j] = j == 0 ? 0.0 : (exp(-beta * w_j) - 1.0) / (w_j * area) * sum * dt;
 }
 
 // P int phi(u) / (u - m) du for the unit hat phi(u) = max(0, 1 - |u|):
@@ -166,19 +177,18 @@ __device__ __forceinline__ double kk_hat(int64_t m) {
 // Im sigma_k = -(1/pi) P int Re sigma(|w|)/(w - w_k) dw on the grid w_j = j dw
 // with Re sigma = sum_j y_j phi(w/dw - j) (linear between grid points, zero
 // one spacing past the last) and its mirror image for w < 0: node 0 gives
-// y_0 g(k), node j >= 1 gives y_j (g(k - j) + g(k + j)).  One thread per k;
-// the sum over j is compensated (Neumaier) and runs in a fixed order.
-__global__ __launch_bounds__(kWG) void k_ac_kk(const double *__restrict__ re, int n, double *__restrict__ im) {
-    const int k = blockIdx.x * kWG + threadIdx.x;
-    if (k >= n) return;
-    double sum = re[0] * kk_hat(k), comp = 0.0;
-    for (int j = 1; j < n; ++j) {
-        const double term = re[j] * (kk_hat((int64_t)k - j) + kk_hat((int64_t)k + j));
-        const double t = sum + term;
-        comp += fabs(sum) >= fabs(term) ? (sum - t) + term : (term - t) + sum;
-        sum = t;
-    }
-    im[k] = -(sum + comp) / M_PI;
+// y_0 g(k), node j >= 1 gives y_j (g(k - j) + g(k + j)).  2^log2l
+// lanes per k; the sum over j is compensated (Neumaier) and runs in a fixed order.
+__global__ __launch_bounds__(kWG) void k_ac_kk(const double *__restrict__ re, int n, int log2l,
+                                               double *__restrict__ im) {
+    const int lane = (int)threadIdx.x & ((1 << log2l) - 1);
+    const int64_t k = ((int64_t)blockIdx.x * kWG + threadIdx.x) >> log2l;
+    double sum = 0.0, comp = 0.0;
+    if (k < n)
+        for (int j = lane; j < n; j += 1 << log2l)
+            kadd(sum, comp, j == 0 ? re[0] * kk_hat(k) : re[j] * (kk_hat(k - j) + kk_hat(k + j)));
+    sum = kadd_lanes(sum, comp, log2l);
+    if (k < n && lane == 0) im[k] = -sum / M_PI;
 }
 
 int64_t grid_for_n(int64_t n) {
@@ -223,14 +233,16 @@ hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32
 }
 
 hipError_t launch_ac_kk(const double *re, int32_t n, double *im, hipStream_t st) {
-    hipLaunchKernelGGL(k_ac_kk, dim3((unsigned)((n + kWG - 1) / kWG)), dim3(kWG), 0, st, re, n, im);
+    const int l = transform_log2_lanes(n);
+    hipLaunchKernelGGL(k_ac_kk, dim3((unsigned)((((int64_t)n << l) + kWG - 1) / kWG)), dim3(kWG), 0, st, re, n, l, im);
     return hipGetLastError();
 }
 
 hipError_t launch_ac_cond(const double *corr, int32_t n_steps, int32_t n_states, double dt, double beta, double area,
                           int window, double *omegas, double *sigma, hipStream_t st) {
-    hipLaunchKernelGGL(k_ac_cond, dim3((unsigned)((n_steps + kWG - 1) / kWG)), dim3(kWG), 0, st, (const d2 *)corr,
-                       n_steps, n_states, dt, beta, area, window, omegas, sigma);
+    const int l = transform_log2_lanes(n_steps);
+    hipLaunchKernelGGL(k_ac_cond, dim3((unsigned)((((int64_t)n_steps << l) + kWG - 1) / kWG)), dim3(kWG), 0, st,
+                       (const d2 *)corr, n_steps, n_states, dt, beta, area, window, l, omegas, sigma);
     return hipGetLastError();
 }
 

@@ -51,6 +51,35 @@ __device__ __forceinline__ int64_t state_index(int64_t row, int s, int log2sb, i
     return ((((int64_t)(s >> log2sb)) * n_rows + row) << log2sb) + (s & ((1 << log2sb) - 1));
 }
 
+// Neumaier-compensated accumulation
+__device__ __forceinline__ void kadd(double &sum, double &comp, double x) {
+    const double t = sum + x;
+    comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
+    sum = t;
+}
+
+// The spectral transforms give every output 2^log2l lanes of a wave, which take
+// its terms in turn: the total of their compensated sums, in a fixed order.
+__device__ __forceinline__ double kadd_lanes(double sum, double comp, int log2l) {
+    for (int off = 1; off < (1 << log2l); off <<= 1) {
+        const double s2 = __shfl_xor(sum, off), c2 = __shfl_xor(comp, off);
+        kadd(sum, comp, s2);
+        comp += c2;
+    }
+    return sum + comp;
+}
+
+// Lanes per output: as many as make 2^18 threads (four waves a SIMD), a wave at
+// most.  One thread per output left most of the chip idle: the sine transform of
+// 257 samples took 149 us on two workgroups and takes 7 us on 65, the
+// Kramers-Kronig sums 339 and 13 us, the DOS of 1024 samples 585 us on 8
+// workgroups (of 512 samples 7 us now).
+inline int transform_log2_lanes(int64_t n_out) {
+    int l = 0;
+    while (l < 6 && (n_out << l) < (1 << 18)) ++l;
+    return l;
+}
+
 template <bool NT, typename T>
 __device__ __forceinline__ T ldv(const T *p) {
     if constexpr (NT)

@@ -470,20 +470,21 @@ __device__ __forceinline__ double window_w(int k, int n, int window) {
     return window == TBPM_WIN_HANN ? 0.5 * (1.0 + cospi((double)k / (double)n)) : 1.0;
 }
 
-// Neumaier-compensated accumulation
-__device__ __forceinline__ void kadd(double &sum, double &comp, double x) {
-    const double t = sum + x;
-    comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-    sum = t;
-}
-
 __global__ __launch_bounds__(kWG) void k_dos(const double *__restrict__ corr, int nt, int S, double dt,
-                                             int window, double *__restrict__ energies,
+                                             int window, int log2l, double *__restrict__ energies,
                                              double *__restrict__ dos) {
     __shared__ double cre[kWG], cim[kWG];
-    const int jidx = blockIdx.x * kWG + threadIdx.x;
-    const int64_t j = (int64_t)jidx - nt;
+    const int lane = (int)threadIdx.x & ((1 << log2l) - 1);
+    const int64_t jidx = ((int64_t)blockIdx.x * kWG + threadIdx.x) >> log2l;
+    const int64_t j = jidx - nt;
     const int64_t two_n = 2 * (int64_t)nt;
+    // m = j k mod 2N of the lane's terms k = lane, lane + L, ...
+    auto mod = [&](int64_t x) {
+        const int64_t m = x % two_n;
+        return m < 0 ? m + two_n : m;
+    };
+    int64_t m = mod(j * lane);
+    const int64_t dm = mod(j << log2l);
     double sum = 0.0, comp = 0.0;
     for (int k0 = 0; k0 < nt; k0 += kWG) {
         const int k = k0 + threadIdx.x;
@@ -503,31 +504,39 @@ __global__ __launch_bounds__(kWG) void k_dos(const double *__restrict__ corr, in
         __syncthreads();
         const int kn = min(kWG, nt - k0);
         if (jidx < two_n) {
-            for (int kk = 0; kk < kn; ++kk) {
-                const int64_t kg = k0 + kk;
-                int64_t m = (j * kg) % two_n;
-                if (m < 0) m += two_n;
+            for (int kk = lane; kk < kn; kk += 1 << log2l) {
                 double sn, cs;
                 sincospi((double)m / (double)nt, &sn, &cs);
                 kadd(sum, comp, cre[kk] * cs - cim[kk] * sn);
+                m += dm;
+                if (m >= two_n) m -= two_n;
             }
         }
         __syncthreads();
     }
-    if (jidx < two_n) {
+    sum = kadd_lanes(sum, comp, log2l);
+    if (jidx < two_n && lane == 0) {
         energies[jidx] = (double)j * M_PI / ((double)nt * dt);
-        dos[jidx] = (sum + comp) * dt / (2.0 * M_PI);
+        dos[jidx] = sum * dt / (2.0 * M_PI);
     }
 }
 
 // Adjoint of k_dos: gcorr[k][s] = (1/S) (dt/pi) w_k sum_j g_j e^{-i E_j t_k}
 // for k >= 1 and (1/S)(dt/2pi) w_0 sum_j g_j for k = 0.
 __global__ __launch_bounds__(kWG) void k_dos_backward(const double *__restrict__ gdos, int nt, int S,
-                                                      double dt, int window,
+                                                      double dt, int window, int log2l,
                                                       double *__restrict__ gcorr) {
     __shared__ double g[kWG];
-    const int k = blockIdx.x * kWG + threadIdx.x;
+    const int lane = (int)threadIdx.x & ((1 << log2l) - 1);
+    const int64_t k = ((int64_t)blockIdx.x * kWG + threadIdx.x) >> log2l;
     const int64_t two_n = 2 * (int64_t)nt;
+    // m = (q - N) k mod 2N of the lane's terms q = lane, lane + L, ...
+    auto mod = [&](int64_t x) {
+        const int64_t m = x % two_n;
+        return m < 0 ? m + two_n : m;
+    };
+    int64_t m = mod((lane - (int64_t)nt) * k);
+    const int64_t dm = mod(k << log2l);
     double sr = 0.0, cr = 0.0, si = 0.0, ci = 0.0;
     for (int64_t j0 = 0; j0 < two_n; j0 += kWG) {
         const int64_t jj = j0 + threadIdx.x;
@@ -535,24 +544,25 @@ __global__ __launch_bounds__(kWG) void k_dos_backward(const double *__restrict__
         __syncthreads();
         const int jn = (int)min((int64_t)kWG, two_n - j0);
         if (k < nt) {
-            for (int q = 0; q < jn; ++q) {
-                const int64_t j = j0 + q - nt;
-                int64_t m = (j * (int64_t)k) % two_n;
-                if (m < 0) m += two_n;
+            for (int q = lane; q < jn; q += 1 << log2l) {
                 double sn, cs;
                 sincospi((double)m / (double)nt, &sn, &cs);
                 kadd(sr, cr, g[q] * cs);
                 kadd(si, ci, -g[q] * sn);
+                m += dm;
+                if (m >= two_n) m -= two_n;
             }
         }
         __syncthreads();
     }
+    sr = kadd_lanes(sr, cr, log2l);
+    si = kadd_lanes(si, ci, log2l);
     if (k < nt) {
-        const double w = window_w(k, nt, window) * (k == 0 ? 0.5 : 1.0) * dt / M_PI / (double)S;
+        const double w = window_w((int)k, nt, window) * (k == 0 ? 0.5 : 1.0) * dt / M_PI / (double)S;
         d2 o;
-        o.x = (sr + cr) * w;
-        o.y = (k == 0) ? 0.0 : (si + ci) * w;
-        for (int s = 0; s < S; ++s) ((d2 *)gcorr)[(int64_t)k * S + s] = o;
+        o.x = sr * w;
+        o.y = (k == 0) ? 0.0 : si * w;
+        for (int s = lane; s < S; s += 1 << log2l) ((d2 *)gcorr)[k * S + s] = o;
     }
 }
 
@@ -731,15 +741,17 @@ hipError_t launch_reduce(int n_inst, int s_pad, const ReduceParams &p, hipStream
 hipError_t launch_dos(const double *corr, int32_t n_steps, int32_t n_states, double dt, int window,
                       double *energies, double *dos, hipStream_t st) {
     const int64_t n_e = 2 * (int64_t)n_steps;
-    hipLaunchKernelGGL(k_dos, dim3((unsigned)((n_e + kWG - 1) / kWG)), dim3(kWG), 0, st, corr, n_steps, n_states,
-                       dt, window, energies, dos);
+    const int l = transform_log2_lanes(n_e);
+    hipLaunchKernelGGL(k_dos, dim3((unsigned)(((n_e << l) + kWG - 1) / kWG)), dim3(kWG), 0, st, corr, n_steps,
+                       n_states, dt, window, l, energies, dos);
     return hipGetLastError();
 }
 
 hipError_t launch_dos_backward(const double *gdos, int32_t n_steps, int32_t n_states, double dt,
                                int window, double *gcorr, hipStream_t st) {
-    hipLaunchKernelGGL(k_dos_backward, dim3((unsigned)((n_steps + kWG - 1) / kWG)), dim3(kWG), 0, st, gdos,
-                       n_steps, n_states, dt, window, gcorr);
+    const int l = transform_log2_lanes(n_steps);
+    hipLaunchKernelGGL(k_dos_backward, dim3((unsigned)((((int64_t)n_steps << l) + kWG - 1) / kWG)), dim3(kWG), 0, st,
+                       gdos, n_steps, n_states, dt, window, l, gcorr);
     return hipGetLastError();
 }
 

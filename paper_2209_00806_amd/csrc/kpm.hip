@@ -7,7 +7,7 @@
 //    split over chunks of the long inner dimension (rows x states).
 //  * k_kpm_sum_parts: mu[:, block] = scale sum_p parts[p] in a fixed order
 //    (the per-chunk results of the moment product).
-//  * k_kb_energy: one workgroup per energy E~_k = cos(theta_k) of the
+//  * k_kb_energy: one workgroup per energy (or four) E~_k = cos(theta_k) of the
 //    midpoint grid in theta: with w_m = g_m / (1 + delta_m0) (Jackson g),
 //    c_n = cos(n theta), p_n = (E~ - i n s) e^{i n theta},
 //    q_m = (E~ + i m s) e^{-i m theta}, s = sin(theta),
@@ -194,11 +194,16 @@ __global__ __launch_bounds__(kWG) void k_kpm_sum_parts(const d2 *__restrict__ pa
         d2 a;
         a.x = 0.0;
         a.y = 0.0;
-        for (int p = 0; p < n_parts; ++p) {
-            const d2 v = parts[(int64_t)p * part_stride + i];
-            a.x += v.x;
-            a.y += v.y;
+        int p = 0;
+        // sixteen loads in flight, added in order (512 parts of 512 x 128: 82 us, 221 one by one)
+        for (; p + 16 <= n_parts; p += 16) {
+            d2 v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = parts[(int64_t)(p + q) * part_stride + i];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) a += v[q];
         }
+        for (; p < n_parts; ++p) a += parts[(int64_t)p * part_stride + i];
         a.x *= scale;
         a.y *= scale;
         out[i] = a;
@@ -224,79 +229,115 @@ __device__ __forceinline__ double jackson_w(int m, int n_mom) {
     return m == 0 ? 0.5 * g : g;
 }
 
-// mu: [M][M] with mu_mn at m + n*M (column n contiguous over m)
+// mu: [M][M] with mu_mn at m + n*M (column n contiguous over m).  A workgroup
+// takes NE energies, so that an element of mu read from the L2 serves all of
+// them (with one, 1024 energies of 512 moments read 4.3 GB: 266 us against 167 with
+// four; MAXM bounds the LDS, 53 KB at NE = 4 and 512 moments).
+template <int NE, int MAXM>
 __global__ __launch_bounds__(kWG) void k_kb_energy(const d2 *__restrict__ mu, int n_mom, double th_lo, double dth,
-                                                   double rescale, double *__restrict__ energies,
+                                                   double rescale, int n_energy, double *__restrict__ energies,
                                                    double *__restrict__ weight) {
-    __shared__ double w_s[kMaxMomentsLds];
-    __shared__ d2 p_s[kMaxMomentsLds];
-    __shared__ double c_s[kMaxMomentsLds];
+    __shared__ double w_s[MAXM];
+    __shared__ d2 p_s[MAXM][NE];
+    __shared__ double c_s[MAXM][NE];
     __shared__ double red[kWG];
-    const int k = blockIdx.x;
-    const double th = th_lo + (k + 0.5) * dth;
-    double sn, x;
-    sincos(th, &sn, &x);
+    const int k0 = blockIdx.x * NE;
+    double th[NE], sn[NE], x[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        th[e] = th_lo + (k0 + e + 0.5) * dth;
+        sincos(th[e], &sn[e], &x[e]);
+    }
     for (int n = threadIdx.x; n < n_mom; n += kWG) {
         const double w = jackson_w(n, n_mom);
-        double sa, ca;
-        sincos(n * th, &sa, &ca);
         w_s[n] = w;
-        c_s[n] = w * ca;  // w_n cos(n theta)
-        // w_n (x - i n s)(cos + i sin)
-        d2 pv;
-        pv.x = w * (x * ca + n * sn * sa);
-        pv.y = w * (x * sa - n * sn * ca);
-        p_s[n] = pv;
-    }
-    __syncthreads();
-    double acc = 0.0;  // real part of F
-    for (int m = threadIdx.x; m < n_mom; m += kWG) {
-        double apx = 0.0, apy = 0.0, acx = 0.0, acy = 0.0;
-        for (int n = 0; n < n_mom; ++n) {
-            const d2 a = mu[m + (int64_t)n * n_mom];
-            const d2 pv = p_s[n];
-            const double cv = c_s[n];
-            apx = fma(a.x, pv.x, fma(-a.y, pv.y, apx));
-            apy = fma(a.x, pv.y, fma(a.y, pv.x, apy));
-            acx = fma(a.x, cv, acx);
-            acy = fma(a.y, cv, acy);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            double sa, ca;
+            sincos(n * th[e], &sa, &ca);
+            c_s[n][e] = w * ca;  // w_n cos(n theta)
+            // w_n (x - i n s)(cos + i sin)
+            d2 pv;
+            pv.x = w * (x[e] * ca + n * sn[e] * sa);
+            pv.y = w * (x[e] * sa - n * sn[e] * ca);
+            p_s[n][e] = pv;
         }
-        const double wm = w_s[m];
-        double sa, ca;
-        sincos(m * th, &sa, &ca);
-        // c_m (A p)_m, real part
-        double re = ca * apx;
-        // q_m (A c)_m with q_m = (x + i m s)(cos - i sin)
-        const double qx = x * ca + m * sn * sa, qy = m * sn * ca - x * sa;
-        re += qx * acx - qy * acy;
-        acc = fma(wm, re, acc);
     }
-    red[threadIdx.x] = acc;
     __syncthreads();
-    for (int h = kWG / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
+    double acc[NE];  // real part of F
+#pragma unroll
+    for (int e = 0; e < NE; ++e) acc[e] = 0.0;
+    for (int m = threadIdx.x; m < n_mom; m += kWG) {
+        double apx[NE], apy[NE], acx[NE], acy[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) apx[e] = apy[e] = acx[e] = acy[e] = 0.0;
+        constexpr int U = NE > 1 ? 8 : 1;
+        int n = 0;
+        auto add = [&](const d2 &a, int nn) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const d2 pv = p_s[nn][e];
+                const double cv = c_s[nn][e];
+                apx[e] = fma(a.x, pv.x, fma(-a.y, pv.y, apx[e]));
+                apy[e] = fma(a.x, pv.y, fma(a.y, pv.x, apy[e]));
+                acx[e] = fma(a.x, cv, acx[e]);
+                acy[e] = fma(a.y, cv, acy[e]);
+            }
+        };
+        for (; n + U <= n_mom; n += U) {
+            d2 a[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) a[q] = mu[m + (int64_t)(n + q) * n_mom];
+#pragma unroll
+            for (int q = 0; q < U; ++q) add(a[q], n + q);
+        }
+        for (; n < n_mom; ++n) add(mu[m + (int64_t)n * n_mom], n);
+        const double wm = w_s[m];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            double sa, ca;
+            sincos(m * th[e], &sa, &ca);
+            // c_m (A p)_m, real part
+            double re = ca * apx[e];
+            // q_m (A c)_m with q_m = (x + i m s)(cos - i sin)
+            const double qx = x[e] * ca + m * sn[e] * sa, qy = m * sn[e] * ca - x[e] * sa;
+            re += qx * acx[e] - qy * acy[e];
+            acc[e] = fma(wm, re, acc[e]);
+        }
     }
-    if (threadIdx.x == 0) {
-        const double d = (1.0 - x) * (1.0 + x);
-        energies[k] = rescale * x;
-        weight[k] = red[0] * sn * dth / (d * d);
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        __syncthreads();
+        red[threadIdx.x] = acc[e];
+        __syncthreads();
+        for (int h = kWG / 2; h > 0; h >>= 1) {
+            if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0 && k0 + e < n_energy) {
+            const double d = (1.0 - x[e]) * (1.0 + x[e]);
+            energies[k0 + e] = rescale * x[e];
+            weight[k0 + e] = red[0] * sn[e] * dth / (d * d);
+        }
     }
 }
 
+// one wave per chemical potential (25 of 1024 energies: 11 us, 364 us with a thread each)
 __global__ __launch_bounds__(kWG) void k_kb_sigma(const double *__restrict__ energies,
                                                   const double *__restrict__ weight, int n_energy,
                                                   const double *__restrict__ mus, int n_mu, double beta,
                                                   double scale, double *__restrict__ sigma) {
-    const int j = blockIdx.x * kWG + threadIdx.x;
+    const int64_t j = ((int64_t)blockIdx.x * kWG + threadIdx.x) >> 6;
+    const int lane = (int)threadIdx.x & 63;
     if (j >= n_mu) return;
     const double mu = mus[j];
     double s = 0.0;
-    for (int k = 0; k < n_energy; ++k) {
+    for (int k = lane; k < n_energy; k += 64) {
         const double fd = 0.5 * (1.0 - tanh(0.5 * beta * (energies[k] - mu)));
         s = fma(fd, weight[k], s);
     }
-    sigma[j] = scale * s;
+    for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
+    if (lane == 0) sigma[j] = scale * s;
 }
 
 }  // namespace
@@ -342,11 +383,16 @@ hipError_t launch_kpm_sum_parts(const double *parts, int64_t n_el, int32_t n_par
 hipError_t launch_kubo_bastin(const double *mu, int32_t n_mom, double rescale, double th_lo, double dth,
                               int32_t n_energy, const double *mus, int32_t n_mu, double beta, double scale,
                               double *energies, double *weight, double *sigma, hipStream_t st) {
-    hipLaunchKernelGGL(k_kb_energy, dim3((unsigned)n_energy), dim3(kWG), 0, st, (const d2 *)mu, n_mom, th_lo, dth,
-                       rescale, energies, weight);
+    // four energies per workgroup where they fill the CUs that way
+    if (n_mom <= 512 && n_energy >= 1024)
+        hipLaunchKernelGGL((k_kb_energy<4, 512>), dim3((unsigned)((n_energy + 3) / 4)), dim3(kWG), 0, st,
+                           (const d2 *)mu, n_mom, th_lo, dth, rescale, n_energy, energies, weight);
+    else
+        hipLaunchKernelGGL((k_kb_energy<1, kMaxMomentsLds>), dim3((unsigned)n_energy), dim3(kWG), 0, st,
+                           (const d2 *)mu, n_mom, th_lo, dth, rescale, n_energy, energies, weight);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_kb_sigma, dim3((unsigned)((n_mu + kWG - 1) / kWG)), dim3(kWG), 0, st, energies, weight,
+    hipLaunchKernelGGL(k_kb_sigma, dim3((unsigned)(((int64_t)n_mu * 64 + kWG - 1) / kWG)), dim3(kWG), 0, st, energies, weight,
                        n_energy, mus, n_mu, beta, scale, sigma);
     return hipGetLastError();
 }

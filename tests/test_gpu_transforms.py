@@ -1,0 +1,103 @@
+"""The spectral transforms where the lanes per output change (64 lanes up to
+4096 outputs, fewer beyond) and where tiles of 256 terms end, against FFTs of
+the same windowed series and against the oracle.
+
+Bars: a sine or cosine and its product are good to some 3e-16, the compensated
+sums add nothing to that, an FFT less than log2(n) 1e-16 of the norm: 2e-15 of
+the sum of the terms' absolute values bounds both."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2209_00806_amd import tbpm
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("nt", [1, 2, 63, 64, 257, 2048, 2051, 5003, 40009])
+def test_transforms_vs_fft(nt):
+    print(f"case transforms nt={nt}", flush=True)
+    rng = np.random.default_rng(nt)
+    S, dt, beta, area = 3, 0.37, 5.0, 2.5
+    c = rng.standard_normal((nt, S)) + 1j * rng.standard_normal((nt, S))
+    k = np.arange(nt)
+    w = 0.5 * (1.0 + np.cos(np.pi * k / nt))
+    wc = w * c.mean(axis=1)
+    two = np.where(k == 0, 1.0, 2.0)
+    # DOS
+    e, d = tbpm.dos(_dev(c), dt)
+    z = np.zeros(2 * nt, dtype=complex)
+    z[:nt] = two * wc
+    ref = np.roll((np.fft.ifft(z) * 2 * nt).real, nt) * dt / (2 * np.pi)
+    np.testing.assert_allclose(e.cpu().numpy(), np.arange(-nt, nt) * np.pi / (nt * dt), rtol=1e-14)
+    assert np.max(np.abs(d.cpu().numpy() - ref)) <= 2e-15 * np.sum(np.abs(z)) * dt / (2 * np.pi) + 1e-300
+    # its adjoint
+    g = rng.standard_normal(2 * nt)
+    got = tbpm.dos_backward(_dev(g), nt, S, dt).cpu().numpy()
+    gr = np.fft.fft(np.roll(g, -nt))[:nt] * w * dt / np.pi / S
+    gr[0] = gr[0].real * 0.5
+    assert np.max(np.abs(got - gr[:, None])) <= 2e-15 * np.sum(np.abs(g)) * dt / np.pi / S
+    # optical conductivity
+    om, sg = tbpm.ac_cond(_dev(c), dt, beta, area)
+    om, sg = om.cpu().numpy(), sg.cpu().numpy()
+    im = np.zeros(2 * nt)
+    im[1:nt] = 2.0 * wc[1:].imag
+    s = -np.fft.fft(im)[:nt].imag
+    scale = np.zeros(nt)
+    scale[1:] = (np.exp(-beta * om[1:]) - 1.0) / (om[1:] * area) * dt
+    assert sg[0] == 0.0
+    assert np.all(np.abs(sg - scale * s) <= 2e-15 * np.sum(np.abs(im)) * np.abs(scale))
+
+
+@pytest.mark.parametrize("n", [4097, 8200])
+def test_kramers_kronig_many_points(n):
+    re = np.random.default_rng(n).standard_normal(n)
+    re[0] = 0.0
+    im = tbpm.ac_cond_imag(_dev(re)).cpu().numpy()
+    # the oracle's integral over the segments in extended precision: in float64 its logarithms' differences, times
+    # distances of thousands, are good to some 1e-9 only at these sizes
+    y = re.astype(np.longdouble)
+    xs = np.arange(-n, n + 1).astype(np.longdouble)
+    ys = np.concatenate([[0.0], y[:0:-1], y, [0.0]])
+    x0, y0, slope = xs[:-1], ys[:-1], np.diff(ys)
+    la = np.log(np.arange(1, 2 * n + 1).astype(np.longdouble))
+    ln = np.concatenate([la[::-1], [0.0], la])  # ln|d|, d = -2n .. 2n, 0 at d = 0
+    ref = np.zeros(n)
+    for k in range(n):
+        l = ln[n - k:3 * n - k + 1]  # d = x - k
+        ref[k] = -np.sum((y0 + slope * (k - x0)) * (l[1:] - l[:-1]) + slope) / np.longdouble(np.pi)
+    coarse = oracle.ac_cond_imag(re)
+    assert np.max(np.abs(ref - coarse)) < 1e-8 * np.max(np.abs(ref))
+    assert np.max(np.abs(im - ref)) < 1e-10 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("M,n_e", [(2, 1024), (257, 1027), (512, 1030), (513, 1025), (512, 1023)])
+def test_kubo_bastin_several_energies_per_workgroup(M, n_e):
+    """Four energies per workgroup (up to 512 moments, from 1024 energies) and one, against the oracle's sum over
+    both indices in factored form (checked against the oracle itself where it is quick)."""
+    rng = np.random.default_rng(M)
+    mu = rng.standard_normal((M, M)) + 1j * rng.standard_normal((M, M))
+    mus = np.linspace(-6.0, 6.0, 67)
+    f, lo, hi, beta, area = 9.0, -8.8, 8.7, 4.0, 3.0
+    sg, en, _ = tbpm.kubo_bastin(_dev(mu), f, lo, hi, n_e, beta, mus, area)
+    w = oracle.jackson(M) / np.where(np.arange(M) == 0, 2.0, 1.0)
+    t0, t1 = np.arccos(hi / f), np.arccos(lo / f)
+    th = t0 + (np.arange(n_e) + 0.5) * (t1 - t0) / n_e
+    x, s, m = np.cos(th)[:, None], np.sin(th)[:, None], np.arange(M)[None, :]
+    c = w * np.cos(m * th[:, None])
+    p = w * (x - 1j * m * s) * np.exp(1j * m * th[:, None])
+    q = w * (x + 1j * m * s) * np.exp(-1j * m * th[:, None])
+    val = (np.sum(c * (p @ mu.T), axis=1) + np.sum(q * (c @ mu.T), axis=1)).real / (1.0 - x[:, 0] ** 2) ** 2
+    fd = oracle.fermi(f * x, beta, mus[None, :])
+    ref = 4.0 / (np.pi * area * f * f) * np.sum(fd * (val * s[:, 0] * (t1 - t0) / n_e)[:, None], axis=0)
+    assert np.max(np.abs(sg.cpu().numpy() - ref)) < 1e-10 * np.max(np.abs(ref))
+    assert np.all(np.diff(en.cpu().numpy()) < 0)
+    if M < 10:
+        want = oracle.kubo_bastin(mu, f, lo, hi, n_e, beta, mus, area)
+        assert np.max(np.abs(ref - want)) < 1e-12 * np.max(np.abs(want))
