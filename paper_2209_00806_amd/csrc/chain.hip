@@ -449,8 +449,9 @@ __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainCheb
             double dre[VS], dim[VS], nrm[VS];
 #pragma unroll
             for (int i = 0; i < VS; ++i) dre[i] = dim[i] = nrm[i] = 0.0;
-            // the counter still holds the step before the one this launch ends
-            const int64_t ckpt = p.ckpt_slot ? (int64_t)p.ckpt_slot[*(volatile const int32_t *)p.counter + 1] : -1;
+            // the counter holds the step before those not summed yet
+            const int64_t ckpt =
+                p.ckpt_slot ? (int64_t)p.ckpt_slot[*(volatile const int32_t *)p.counter + 1 + p.local] : -1;
 #pragma unroll
             for (int q = 0; q < NR; ++q) {
                 if (tid + q * NT < n_own) {
@@ -556,7 +557,7 @@ __global__ __launch_bounds__(kWG) void k_chain_values(const ChainTileTab t, cons
 // member in a fixed order into sample counter + 1 + step; the last workgroup
 // to finish advances the counter (every workgroup has read it by then).
 __global__ __launch_bounds__(kWG) void k_chain_reduce(const ReduceParams p, int n_local, int64_t step_stride,
-                                                      int32_t *counter) {
+                                                      int32_t *counter, int advance) {
     __shared__ double red[3][kWG];
     const int k0 = *(volatile const int32_t *)counter;
     const int per = gridDim.x / n_local;
@@ -605,6 +606,7 @@ __global__ __launch_bounds__(kWG) void k_chain_reduce(const ReduceParams p, int 
             if (p.norm2[inst]) p.norm2[inst][o] = red[2][0];
             if (p.norm2_all) p.norm2_all[(int64_t)inst * p.n_steps * p.s_user + o] = red[2][0];
         }
+        if (!advance) return;
         __threadfence();
         if (atomicAdd(counter + 1, 1) == (int)gridDim.x - 1) {
             atomicExch(counter + 1, 0);
@@ -703,9 +705,9 @@ hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int3
 }
 
 hipError_t launch_chain_reduce(int n_inst, int n_local, int64_t step_stride, const ReduceParams &p, int32_t *counter,
-                               hipStream_t st) {
+                               bool advance, hipStream_t st) {
     hipLaunchKernelGGL(k_chain_reduce, dim3((unsigned)(n_local * n_inst * p.s_user)), dim3(kWG), 0, st, p, n_local,
-                       step_stride, counter);
+                       step_stride, counter, advance ? 1 : 0);
     return hipGetLastError();
 }
 

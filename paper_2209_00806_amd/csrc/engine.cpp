@@ -288,7 +288,7 @@ void Engine::release() {
                       &bwd_gacc, &bwd_gdiag, &bwd_coef, &st_uoff, &st_ucol, &st_lidx, &fu_n1, &fu_hoff,
                       &fu_hw,    &fu_hidx,  &bc,       &bd,        &ckpt_slot, &corr_scratch, &qe_coef,
                       &qe_acc,   &qe_part,  &qe_norm2, &ac_ja,     &ac_jb,     &ac_csr,       &ac_zero,
-                      &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &hay_u,     &hay_y,        &hay_s,
+                      &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &jc_part,  &ch_hist,   &hay_u,     &hay_y,        &hay_s,
                       &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner, &ch_tiles, &ch_tile0,
                       &ch_cnt,   &ch_toff,  &ch_loff,  &ch_rowmap, &ch_lidx, &ch_tval, &ch_tons};
     for (DevBuf *b : bufs) b->release();
@@ -641,6 +641,18 @@ tbpm_status Engine::run(const RunArgs &a) {
     TRY_HIP(counter.ensure(sizeof(int32_t) * 64), "alloc counter");
     TRY_HIP(coef.ensure(sizeof(PassCoef) * (size_t)n_passes * ni), "alloc coef");
     TRY_HIP(norm2_all.ensure(sizeof(double) * (size_t)ni * a.n_steps * a.s_user), "alloc norm2");
+    // The chain keeps the states of kHistSteps steps where every step's state is
+    // accumulated (n_qe) or correlated (jc_states): one launch then takes them all.
+    // Without the memory for it the accumulation runs after every step.
+    const size_t hist_vec = esize * (size_t)n_el;
+    bool hist = chain && (a.n_qe > 0 || a.jc_states > 0) && a.n_steps > 1;
+    if (hist && chain_room(fp32, hist_vec * kHistSteps > ch_hist.bytes ? hist_vec * kHistSteps : 0)) {
+        hipError_t he = ch_hist.ensure(hist_vec * kHistSteps);
+        if (he == hipErrorOutOfMemory) (void)hipGetLastError();
+        hist = he == hipSuccess;
+    } else {
+        hist = false;
+    }
     TRY_HIP(ptr_tab.ensure(sizeof(void *) * 3 * (size_t)ni), "alloc pointer table");
     TRY_HIP(inst_row0_dev.ensure(sizeof(int64_t) * (ni + 1)), "alloc inst_row0");
 
@@ -654,6 +666,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     if (a.jc_states > 0) {
         TRY_HIP(jc_tab.ensure(jc_bytes), "alloc correlation table");
         TRY_HIP(jc_norm.ensure(sizeof(double) * (size_t)a.n_steps * a.jc_states), "alloc correlation scratch");
+        TRY_HIP(jc_part.ensure(sizeof(double) * (size_t)part_stride * (chain ? kStepsPerGraph : 1)), "alloc partials");
     }
 
     // stage the small tables through pinned memory, stream-ordered
@@ -707,23 +720,35 @@ tbpm_status Engine::run(const RunArgs &a) {
     last_log2sb = log2sb;
     // elements of the states that are propagated (whole blocks come first)
     const int64_t n_el_all = chain ? mat.n_rows * cs.n_blk * cs.vs : n_el;
-    void *bufptr[5] = {v.ptr, ba.ptr, bb.ptr, bc.ptr, bd.ptr};
+    auto hist_slot = [&](int32_t local) { return (void *)((char *)ch_hist.ptr + hist_vec * (size_t)(local % kHistSteps)); };
+    // psi starts where the last step of a graph leaves it
+    void *bufptr[5] = {hist ? hist_slot(kHistSteps - 1) : v.ptr, ba.ptr, bb.ptr, bc.ptr, bd.ptr};
     int32_t log2sp = 0;
     while ((1 << log2sp) < a.jc_states) ++log2sp;
-    // per-step work after the correlation: quasi-eigenstate accumulation and
-    // the optical-conductivity correlation
-    auto enqueue_qe = [&](hipStream_t s) -> tbpm_status {
+    // work on psi after the correlation: quasi-eigenstate accumulation and
+    // the optical-conductivity correlation (partials), for the states of `cnt`
+    // steps from state[0] on; `local`: the place of the first among the steps not
+    // summed yet, -1 for the step that the counter stands at
+    auto accumulate = [&](hipStream_t s, const void *state, int32_t local, int32_t cnt) -> tbpm_status {
         if (a.n_qe > 0) {
-            hipError_t e = launch_qe_accum(fp32, bufptr[0], a.qe_acc, n_el, n_el_all, (const double *)qe_coef.ptr, a.n_qe,
-                                           (const int32_t *)counter.ptr, s);
+            hipError_t e = launch_qe_accum(fp32, state, a.qe_acc, n_el, n_el_all, (const double *)qe_coef.ptr, a.n_qe,
+                                           (const int32_t *)counter.ptr, 1 + local, cnt, n_el, s);
             if (e != hipSuccess) return hip_fail(e, "launch quasi-eigenstate accumulation");
         }
         if (a.jc_states > 0) {
-            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp, a.jc_states, log2sb, mat.n_rows, bufptr[0],
-                                        mat.slice_off, mat.col, a.jc_val, (double *)partials.ptr, s);
+            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp,
+                                        a.jc_states, log2sb, mat.n_rows, state, mat.slice_off, mat.col, a.jc_val,
+                                        (double *)jc_part.ptr + std::max(local, 0) * part_stride, cnt, n_el, part_stride, s);
             if (e != hipSuccess) return hip_fail(e, "launch current correlation");
+        }
+        return TBPM_OK;
+    };
+    // sums of the correlation's partials of `cnt` steps; -1: of the step that the
+    // counter stands at
+    auto sum_jc = [&](hipStream_t s, int32_t cnt) -> tbpm_status {
+        if (a.jc_states > 0) {
             ReduceParams jr{};
-            jr.partials = (const double *)partials.ptr;
+            jr.partials = (const double *)jc_part.ptr;
             jr.n_tiles = n_tiles;
             jr.inst_tile0 = (const int32_t *)(chain ? ch_tile0.ptr : inst_tile0.ptr);
             jr.log2s = log2sp;
@@ -733,10 +758,15 @@ tbpm_status Engine::run(const RunArgs &a) {
             jr.corr = (double *const *)jc_tab.ptr;
             jr.norm2 = (double *const *)jc_tab.ptr + 1;
             jr.norm2_all = (double *)jc_norm.ptr;
-            e = launch_reduce(1, s_pad, jr, s);
+            hipError_t e = cnt < 0 ? launch_reduce(1, s_pad, jr, s)
+                                   : launch_chain_reduce(1, cnt, part_stride, jr, (int32_t *)counter.ptr, false, s);
             if (e != hipSuccess) return hip_fail(e, "launch current correlation reduce");
         }
         return TBPM_OK;
+    };
+    auto enqueue_qe = [&](hipStream_t s) -> tbpm_status {
+        const tbpm_status ast = accumulate(s, bufptr[0], -1, 1);
+        return ast == TBPM_OK ? sum_jc(s, -1) : ast;
     };
     TRY_HIP(hipEventRecord(staging_done, a.stream), "record staging");
 
@@ -752,7 +782,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     ip.s_user = a.s_user;
     ip.psi0 = d_psi0;
     ip.inst_row0 = (const int64_t *)inst_row0_dev.ptr;
-    ip.v = v.ptr;
+    ip.v = bufptr[0];
     ip.phi0 = (double *)phi0.ptr;
     ip.partials = (double *)partials.ptr;
     ip.counter = (int32_t *)counter.ptr;
@@ -797,9 +827,6 @@ tbpm_status Engine::run(const RunArgs &a) {
     const bool last_pair = fused && n_passes >= 4 && !a.ckpt && a.n_qe == 0 && a.jc_states == 0;
     // a step leaves psi in another buffer
     const bool psi_moves = last_pair || chain;
-    // steps whose correlation is summed by one launch: all of a graph's, or one
-    // where each step's own sample number is needed
-    const bool per_step = a.ckpt || a.n_qe > 0 || a.jc_states > 0;
     if (fused) {
         const int n_mid = n_passes - 3;
         int cur = 0, prev = -1;  // buffers of b_{j+1} and b_{j+2} (0: psi, -1: none)
@@ -865,18 +892,22 @@ tbpm_status Engine::run(const RunArgs &a) {
             cp.b2 = b2 >= 0 ? bufptr[b2] : nullptr;
             cp.coef = (const PassCoef *)coef.ptr + (size_t)p0 * ni;
             cp.out_prev = last ? nullptr : bufptr[o1];
-            cp.out_last = last ? bufptr[o1] : bufptr[o2];
+            cp.out_last = last ? (hist ? hist_slot(local) : bufptr[o1]) : bufptr[o2];
             cp.partials = last ? (double *)partials.ptr + (int64_t)local * part_stride : nullptr;
             cp.phi0 = (const double *)phi0.ptr;
             cp.ckpt = a.ckpt;
             cp.ckpt_slot = a.ckpt ? (const int32_t *)ckpt_slot.ptr : nullptr;
+            cp.local = local;
             cp.counter = (const int32_t *)counter.ptr;
             cp.perm = mat.perm;
             cp.ckpt_stride = mat.n_rows * a.s_user;
             cp.s_user = a.s_user;
             tbpm_status cst = chain_launch(fp32, cs, cp, s);
             if (cst != TBPM_OK) return cst;
-            if (last) std::swap(bufptr[0], bufptr[o1]);
+            if (last && hist)
+                bufptr[0] = hist_slot(local);
+            else if (last)
+                std::swap(bufptr[0], bufptr[o1]);
             b2 = o1;
             x = o2;
             p0 += d;
@@ -884,21 +915,20 @@ tbpm_status Engine::run(const RunArgs &a) {
         return TBPM_OK;
     };
     auto chain_steps = [&](hipStream_t s, int32_t steps) -> tbpm_status {
-        const int32_t sum = per_step ? 1 : steps;
         for (int32_t q = 0; q < steps; ++q) {
-            tbpm_status cst = chain_step(s, per_step ? 0 : q);
+            tbpm_status cst = chain_step(s, q);
+            if (cst == TBPM_OK && !hist)
+                cst = accumulate(s, bufptr[0], q, 1);
+            else if (cst == TBPM_OK && ((q + 1) % kHistSteps == 0 || q + 1 == steps))
+                cst = accumulate(s, hist_slot(0), q / kHistSteps * kHistSteps, q % kHistSteps + 1);
             if (cst != TBPM_OK) return cst;
-            if ((q + 1) % sum == 0) {
-                hipError_t e = launch_chain_reduce(ni, sum, part_stride, rp, (int32_t *)counter.ptr, s);
-                if (e != hipSuccess) return hip_fail(e, "launch reduce");
-                if (per_step) cst = enqueue_qe(s);
-                if (cst != TBPM_OK) return cst;
-            }
         }
-        return TBPM_OK;
+        const tbpm_status cst = sum_jc(s, steps);
+        if (cst != TBPM_OK) return cst;
+        hipError_t e = launch_chain_reduce(ni, steps, part_stride, rp, (int32_t *)counter.ptr, true, s);
+        return e == hipSuccess ? TBPM_OK : hip_fail(e, "launch reduce");
     };
     auto enqueue_step = [&](hipStream_t s) -> tbpm_status {
-        if (chain) return chain_steps(s, 1);
         if (fused) {
             for (size_t q = 0; q < sched.size(); ++q) {
                 const Launch &l = sched[q];
@@ -1023,9 +1053,11 @@ tbpm_status Engine::run(const RunArgs &a) {
 
     if (a.n_steps > 1) {
         if (a.flags & TBPM_FLAG_NO_GRAPH) {
-            for (int32_t k = 1; k < a.n_steps; ++k) {
-                st = enqueue_step(a.stream);
+            for (int32_t k = 1; k < a.n_steps;) {
+                const int32_t steps = chain ? std::min<int32_t>(kStepsPerGraph, a.n_steps - k) : 1;
+                st = chain ? chain_steps(a.stream, steps) : enqueue_step(a.stream);
                 if (st != TBPM_OK) return st;
+                k += steps;
             }
         } else {
             GraphKey key;
@@ -1052,13 +1084,14 @@ tbpm_status Engine::run(const RunArgs &a) {
             key.n_qe = a.n_qe;
             key.jc_states = a.jc_states;
             key.ckpt = a.ckpt;
-            const void *kb[31] = {v.ptr,       ba.ptr,      bb.ptr,        phi0.ptr,    partials.ptr, coef.ptr,
+            const void *kb[33] = {v.ptr,       ba.ptr,      bb.ptr,        phi0.ptr,    partials.ptr, coef.ptr,
                                   tiles.ptr,   norm2_all.ptr, bc.ptr,      bd.ptr,      st_uoff.ptr,  st_ucol.ptr,
                                   st_lidx.ptr, fu_hidx.ptr, fu_n1.ptr,     fu_hoff.ptr, fu_hw.ptr,
                                   a.ckpt ? ckpt_slot.ptr : nullptr, a.n_qe > 0 ? qe_coef.ptr : nullptr,
                                   a.n_qe > 0 ? a.qe_acc : nullptr, a.jc_states > 0 ? a.jc_val : nullptr,
                                   a.jc_states > 0 ? jc_norm.ptr : nullptr, ch_tiles.ptr, ch_tile0.ptr, ch_cnt.ptr,
-                                  ch_toff.ptr, ch_loff.ptr, ch_rowmap.ptr, ch_lidx.ptr, ch_tval.ptr, ch_tons.ptr};
+                                  ch_toff.ptr, ch_loff.ptr, ch_rowmap.ptr, ch_lidx.ptr, ch_tval.ptr, ch_tons.ptr,
+                                  hist ? ch_hist.ptr : nullptr, a.jc_states > 0 ? jc_part.ptr : nullptr};
             static_assert(sizeof(kb) == sizeof(key.bufs), "graph key buffers");
             std::memcpy(key.bufs, kb, sizeof(kb));
             // Graphs of kStepsPerGraph time steps (small operators are bound by

@@ -130,6 +130,9 @@ struct FusedParams {
     double *partials;
 };
 
+// Time steps whose states one accumulation launch takes (k_qe_accum, k_jcorr).
+constexpr int kHistSteps = 8;
+
 // Several Clenshaw orders per launch (chain.hip).
 constexpr int kChainMaxDepth = 24;  // orders per launch
 constexpr int kChainWidth = 4;      // most stored elements per row
@@ -175,6 +178,7 @@ struct ChainParams {
     // stored states of the fused correlation's launch, as in PassParams
     double *ckpt;
     const int32_t *ckpt_slot;
+    int32_t local;  // steps since the counter was advanced
     const int32_t *counter;
     const int32_t *perm;
     int64_t ckpt_stride;

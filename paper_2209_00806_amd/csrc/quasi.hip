@@ -3,13 +3,13 @@
 // accumulated while the states are propagated (forward, then with -dt), and
 // normalised per energy and state at the end.
 //
-// k_qe_accum runs once per time step inside the step graph: it reads the
-// current state psi(k dt) (the engine's state buffer, [rows][S] at the
-// recursion precision) once and updates n_E FP64 accumulators
-// acc[j][rows][S] += coef[k][j] psi, where k is the device step counter and
-// coef[k][j] = w_|k| e^{i E_j t_k} is a host-built table.  It is a streaming
-// kernel: 8 or 16 bytes read and 32 bytes read and written per energy and
-// element.
+// k_qe_accum runs inside the step graph: it reads the states psi(k dt) of up to
+// kHistSteps time steps (state buffers at the recursion precision) once and
+// updates n_E FP64 accumulators acc[j][rows][S] += coef[k][j] psi, k in order from
+// the device step counter on, coef[k][j] = w_|k| e^{i E_j t_k} a host-built table.
+// It is a streaming kernel: 8 or 16 bytes read per element and step, and 32 bytes
+// read and written per energy and element, once for all of its steps: eight
+// steps of graphene 256^2 at eight energies take 16.6 us, one step 15.6.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -23,20 +23,28 @@ namespace {
 template <typename R>
 __global__ __launch_bounds__(kWG) void k_qe_accum(const void *__restrict__ state, d2 *__restrict__ acc, int64_t n_el,
                                                   int64_t n_used, const d2 *__restrict__ coef, int n_e,
-                                                  const int32_t *__restrict__ counter) {
+                                                  const int32_t *__restrict__ counter, int k_off, int n_states,
+                                                  int64_t state_stride) {
     using C = typename CxT<R>::T;
     const C *psi = (const C *)state;
-    const int k = *(volatile const int32_t *)counter;
+    const int k = *(volatile const int32_t *)counter + k_off;
     const d2 *row = coef + (int64_t)k * n_e;
     const int64_t stride = (int64_t)gridDim.x * kWG;
     for (int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x; e < n_used; e += stride) {
-        const C x = psi[e];
-        const double xr = (double)x.x, xi = (double)x.y;
+        C x[kHistSteps];
+#pragma unroll
+        for (int i = 0; i < kHistSteps; ++i)
+            if (i < n_states) x[i] = psi[e + i * state_stride];
         for (int j = 0; j < n_e; ++j) {
-            const d2 c = row[j];
             d2 a = acc[(int64_t)j * n_el + e];
-            a.x = fma(c.x, xr, fma(-c.y, xi, a.x));
-            a.y = fma(c.x, xi, fma(c.y, xr, a.y));
+#pragma unroll
+            for (int i = 0; i < kHistSteps; ++i)
+                if (i < n_states) {
+                    const d2 c = row[(int64_t)i * n_e + j];
+                    const double xr = (double)x[i].x, xi = (double)x[i].y;
+                    a.x = fma(c.x, xr, fma(-c.y, xi, a.x));
+                    a.y = fma(c.x, xi, fma(c.y, xr, a.y));
+                }
             acc[(int64_t)j * n_el + e] = a;
         }
     }
@@ -111,14 +119,16 @@ int64_t grid_of(int64_t n) {
 }  // namespace
 
 hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, int64_t n_used, const double *coef,
-                           int32_t n_e, const int32_t *counter, hipStream_t st) {
+                           int32_t n_e, const int32_t *counter, int32_t k_off, int32_t n_states, int64_t state_stride,
+                           hipStream_t st) {
+    if (n_states < 1 || n_states > kHistSteps) return hipErrorInvalidValue;
     const dim3 grid((unsigned)grid_of(n_used)), block(kWG);
     if (fp32)
         hipLaunchKernelGGL(k_qe_accum<float>, grid, block, 0, st, state, (d2 *)acc, n_el, n_used, (const d2 *)coef, n_e,
-                           counter);
+                           counter, k_off, n_states, state_stride);
     else
         hipLaunchKernelGGL(k_qe_accum<double>, grid, block, 0, st, state, (d2 *)acc, n_el, n_used, (const d2 *)coef, n_e,
-                           counter);
+                           counter, k_off, n_states, state_stride);
     return hipGetLastError();
 }
 

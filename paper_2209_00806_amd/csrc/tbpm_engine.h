@@ -76,7 +76,7 @@ struct GraphKey {
     int32_t n_tiles = 0, tiles_chunks = 0, tiles_unit = 0, lds_units = 0;
     int32_t n_steps = 0, n_qe = 0, jc_states = 0, steps = 0;
     const void *ckpt = nullptr;
-    const void *bufs[31] = {};
+    const void *bufs[33] = {};
     int32_t chain_depth = 0, chain_grp = 0;
     bool operator==(const GraphKey &o) const;
 };
@@ -148,7 +148,7 @@ struct Engine {
     // optical conductivity: J_alpha / J_beta in ELL layout, their CSR upload,
     // a zero on-site vector, preparation vectors, the packed block, and the
     // correlation's pointer table and norm scratch
-    DevBuf ac_ja, ac_jb, ac_csr, ac_zero, ac_vec, ac_block, jc_tab, jc_norm;
+    DevBuf ac_ja, ac_jb, ac_csr, ac_zero, ac_vec, ac_block, jc_tab, jc_norm, jc_part, ch_hist;
     // Haydock recursion: two Lanczos vectors, the product vector, per-state scalars
     DevBuf hay_u, hay_y, hay_s;
     // kernel-polynomial moments: the L store, a block of R, Chebyshev vectors,

@@ -173,14 +173,15 @@ hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int3
 // sums the partials of n_local steps (step_stride doubles apart) into samples
 // *counter + 1 .. *counter + n_local, then advances the counter
 hipError_t launch_chain_reduce(int n_inst, int n_local, int64_t step_stride, const ReduceParams &p, int32_t *counter,
-                               hipStream_t st);
+                               bool advance, hipStream_t st);
 
 // quasi-eigenstate launchers (quasi.hip)
-// acc[j][e] += coef[k][j] * state[e] for j < n_e, k = *counter (state at R precision)
-// (n_used elements of it; acc[j] lies j n_el elements on)
+// acc[j][e] += coef[k + i][j] * state_i[e] for j < n_e and i < n_states <= kHistSteps in
+// order, k = *counter + k_off (states at R precision, state_stride elements apart,
+// n_used elements of each; acc[j] lies j n_el elements on)
 hipError_t launch_qe_accum(bool fp32, const void *state, double *acc, int64_t n_el, int64_t n_used, const double *coef,
-                           int32_t n_e,
-                           const int32_t *counter, hipStream_t st);
+                           int32_t n_e, const int32_t *counter, int32_t k_off, int32_t n_states, int64_t state_stride,
+                           hipStream_t st);
 int32_t qe_partial_blocks(int64_t n_rows);  // partials need n_e * S * 3 * blocks doubles
 // norm2[j][s] = ||acc[j][:, s]||^2 and out[j][perm[r]][s] = acc[j][r][s] / sqrt(norm2[j][s]), s < s_user
 // (states in blocks of 2^log2sb)
@@ -198,7 +199,7 @@ hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, in
                        const int32_t *perm, double *out, hipStream_t st);
 hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2sb,
                         int64_t n_rows, const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
-                        double *partials, hipStream_t st);
+                        double *partials, int32_t n_states, int64_t state_stride, int64_t part_stride, hipStream_t st);
 hipError_t launch_ac_cond(const double *corr, int32_t n_steps, int32_t n_states, double dt, double beta, double area,
                           int window, double *omegas, double *sigma, hipStream_t st);
 // im[k] = Kramers-Kronig transform of re[0 .. n) on a uniform grid from 0

@@ -179,3 +179,26 @@ def test_chain_moments_match_one_order_per_launch(kind):
             out.append(tbpm.kpm_moments(H, ja, jb, psi, M, f).cpu().numpy())
         assert _rel(out[1], out[0]) < 1e-12, (S, M)
     H.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_steps", [2, 8, 9, 17, 18, 27, 41])
+def test_chain_accumulates_several_steps_per_launch(n_steps, precision):
+    """Quasi-eigenstates and current correlations take the states of up to eight steps per launch: runs that end
+    within a group of steps, at its end, within a graph and after it, against one step at a time (one order per
+    launch).  Sums of n_steps terms of rounding 1e-16: 1e-12."""
+    rng = np.random.default_rng(8)
+    lat = _lattice("graphene_small", rng)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    dt = math.pi / f
+    J = inputs.current_values(lat, 0)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    psi = torch.from_numpy(inputs.random_phase_states(rng, lat.n_orb, 3)).cuda()
+    out = []
+    for shape in ({}, CHAIN):
+        H.set_launch_config(**shape, precision=precision)
+        out.append([tbpm.quasi_eigenstates(H, psi, [-0.7, 1.1, 2.3], n_steps, dt, f, precision=precision),
+                    tbpm.ac_corr(H, J, J, psi, n_steps, dt, 10.0, 0.1, rescale=f, precision=precision)])
+    for a, b in zip(*out):
+        assert _rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-12
+    H.close()
