@@ -528,7 +528,11 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               for rows with many stored elements); the value t is the LDS
  *               tier, as for fused below: a tile's staged rows use at most
  *               1/(t+2) of a CU's 160 KiB.  wg_chunks and unroll are then
- *               unused.  0: gather from global memory
+ *               unused.  Real operators with 5 to 24 stored elements per row
+ *               and two blocks of states or more (two FP64 states, three FP32
+ *               ones): a workgroup also keeps its rows' elements in registers
+ *               and takes the blocks in turn; the library chooses the tiles,
+ *               whatever the value and vec.  0: gather from global memory
  *   vec         states of a row each thread holds (1, 2 or 4; capped by the
  *               padded state count)
  *   fused       1 .. 6: evaluate several Clenshaw orders per launch.
@@ -553,9 +557,10 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               terms or no tile fits.  0: one order per launch.
  * A handle (or batch) whose configuration for a precision was never set nor
  * autotuned also evaluates several orders per launch, where the operator has
- * at most 4 stored elements per row and a propagation has more than 64 samples
- * (shorter ones would not repay building the tile tables) and the extra work
- * vectors fit the free device memory; FP32 states are the same bit for bit,
+ * at most 4 stored elements per row, or takes the staged shape's second form,
+ * where that applies, for propagations of more than 64 samples (shorter ones
+ * would not repay building the tile tables) if the extra work vectors and
+ * tables fit the free device memory; FP32 states are the same bit for bit,
  * FP64 results the same to rounding.
  */
 typedef struct {

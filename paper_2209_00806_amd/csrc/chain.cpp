@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <thread>
 
 #include "tbpm_engine.h"
 
@@ -22,6 +23,8 @@ void Engine::chain_orders() {
     const int32_t ni = n_inst();
     std::vector<std::vector<int32_t>> orders(ni);
     const int threads = (int)std::min<int64_t>(ni, host_threads((int64_t)h_col.size()));
+    // 14400 rows of 19 elements: 35 ms with one thread, 12 with eight
+    const int32_t each = std::max(1, std::min(8, (int)std::thread::hardware_concurrency()) / std::max(1, threads));
     run_chunks(ni, std::max(1, threads), [&](int, int64_t lo, int64_t hi) {
         for (int64_t i = lo; i < hi; ++i) {
             const int64_t r0 = inst_row0[i], n = inst_row0[i + 1] - r0;
@@ -36,10 +39,55 @@ void Engine::chain_orders() {
                 }
                 rp[r - r0 + 1] = (int64_t)cc.size();
             }
-            orders[i] = bisection_order(n, rp.data(), cc.data(), kChainMinTile, 1);
+            orders[i] = bisection_order(n, rp.data(), cc.data(), kChainMinTile, n < 4096 ? 1 : each);
         }
     });
     ch_orders = std::move(orders);
+}
+
+// the orders of one evaluation, in launches of nearly equal depth (at most D)
+static void chain_split(int32_t n_orders, int32_t D, std::vector<int32_t> &depths) {
+    const int32_t n_launch = (n_orders + D - 1) / D;
+    depths.clear();
+    for (int32_t l = 0, left = n_orders; l < n_launch; ++l) {
+        depths.push_back(left / (n_launch - l));
+        left -= depths.back();
+    }
+}
+
+// tile tables of T rows for D orders, on the device
+tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows) {
+    ChainTables t;
+    chain_tables(h_slice_off, h_col, inst_row0, ch_orders, T, D, rows, max_rows, t, chain_width());
+    if (t.depth < 1) return fail(TBPM_E_ARG, "no tile fits");
+    const size_t nt = t.tiles.size();
+    ch = ChainState{};
+    TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
+    hipError_t e = hipSuccess;
+    auto up = [&](DevBuf &d, const void *src, size_t bytes) {
+        if (e == hipSuccess) e = d.ensure(bytes);
+        if (e == hipSuccess) e = hipMemcpy(d.ptr, src, bytes, hipMemcpyHostToDevice);
+    };
+    up(ch_tiles, t.tiles.data(), sizeof(TileDesc) * nt);
+    up(ch_tile0, t.inst_tile0.data(), sizeof(int32_t) * t.inst_tile0.size());
+    up(ch_cnt, t.cnt.data(), sizeof(int32_t) * t.cnt.size());
+    up(ch_toff, t.toff.data(), sizeof(int32_t) * nt);
+    up(ch_loff, t.loff.data(), sizeof(int32_t) * nt);
+    up(ch_rowmap, t.rowmap.data(), sizeof(uint32_t) * t.rowmap.size());
+    up(ch_lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();  // the caller goes on with another launch shape
+        return fail(TBPM_E_OOM, "no memory for the chain tables");
+    }
+    TRY_HIP(e, "upload chain tables");
+    ch.T = T;
+    ch.cap = cap;
+    ch.depth = t.depth;
+    ch.n_tiles = (int32_t)nt;
+    ch.n_local = (int64_t)t.lidx.size() / std::max(chain_width(), 4);
+    ch.contiguous = t.contiguous;
+    ch.max_stage = t.max_stage;
+    return TBPM_OK;
 }
 
 // Tile size and depth.  The more workgroups there are, the larger a tile may be
@@ -65,49 +113,45 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         if (ch.T != T || ch.cap != cap || ch.depth == 0) {
             const int32_t D = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, max_rows);
             if (D < std::min(n_orders, 3)) continue;
-            ChainTables t;
-            chain_tables(h_slice_off, h_col, inst_row0, ch_orders, T, D, rows, max_rows, t);
-            if (t.depth < 1) continue;
-            const size_t nt = t.tiles.size();
-            ch = ChainState{};
-            TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
-            hipError_t e = hipSuccess;
-            auto up = [&](DevBuf &d, const void *src, size_t bytes) {
-                if (e == hipSuccess) e = d.ensure(bytes);
-                if (e == hipSuccess) e = hipMemcpy(d.ptr, src, bytes, hipMemcpyHostToDevice);
-            };
-            up(ch_tiles, t.tiles.data(), sizeof(TileDesc) * nt);
-            up(ch_tile0, t.inst_tile0.data(), sizeof(int32_t) * t.inst_tile0.size());
-            up(ch_cnt, t.cnt.data(), sizeof(int32_t) * t.cnt.size());
-            up(ch_toff, t.toff.data(), sizeof(int32_t) * nt);
-            up(ch_loff, t.loff.data(), sizeof(int32_t) * nt);
-            up(ch_rowmap, t.rowmap.data(), sizeof(uint32_t) * t.rowmap.size());
-            up(ch_lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
-            if (e == hipErrorOutOfMemory) {
-                (void)hipGetLastError();  // the caller goes on with another launch shape
-                return fail(TBPM_E_OOM, "no memory for the chain tables");
-            }
-            TRY_HIP(e, "upload chain tables");
-            ch.T = T;
-            ch.cap = cap;
-            ch.depth = t.depth;
-            ch.n_tiles = (int32_t)nt;
-            ch.n_local = (int64_t)t.lidx.size() / 4;
-            ch.contiguous = t.contiguous;
-            ch.max_stage = t.max_stage;
+            tbpm_status st = chain_build(T, cap, D, rows, max_rows);
+            if (st == TBPM_E_ARG) continue;
+            if (st != TBPM_OK) return st;
         }
         // few tiles: their state blocks go to several workgroups each
         cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch.n_tiles - 1) / ch.n_tiles));
-        // the orders of one evaluation, in launches of nearly equal depth
-        const int32_t n_launch = (n_orders + ch.depth - 1) / ch.depth;
-        cs.depths.clear();
-        for (int32_t l = 0, left = n_orders; l < n_launch; ++l) {
-            cs.depths.push_back(left / (n_launch - l));
-            left -= cs.depths.back();
-        }
+        chain_split(n_orders, ch.depth, cs.depths);
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no chain tile fits");
+}
+
+// One order of a wide operator per launch (wide.hip), for two blocks of states or
+// more.  Tiles of up to 256 rows: a time step of bilayer 192^2 (17 orders) takes 328
+// us with 16 FP32 states against 343 with 512-row tiles (two workgroups per CU
+// instead of four) and 372 with 128 rows; the staged pass takes 433.  With one block
+// there is nothing to share the matrix entries among (FP64, one state: 165 us
+// against 155 staged).
+tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
+    cs.vs = fp32 ? 2 : 1;
+    cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
+    if (mat.max_width <= kChainWidth || mat.max_width > kWideWidth || mat.is_complex || cs.n_blk < 2 ||
+        mat.n_rows * 16 >= ((int64_t)1 << 32))
+        return fail(TBPM_E_ARG, "rows do not suit the wide pass");
+    const int64_t units = mat.n_rows * cs.n_blk;
+    int64_t T = kChainMinTile;
+    while (T < kWideThreads && T * 2 * 256 <= units) T *= 2;
+    chain_orders();
+    for (; T >= kChainMinTile; T /= 2) {
+        if (ch.T != T || ch.cap != 1 || ch.depth == 0) {
+            tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);
+            if (st == TBPM_E_ARG) continue;
+            if (st != TBPM_OK) return st;
+        }
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch.n_tiles - 1) / ch.n_tiles));
+        cs.depths.assign(1, 1);
+        return TBPM_OK;
+    }
+    return fail(TBPM_E_ARG, "no tile fits");
 }
 
 // room for `need` more bytes and the tiles' matrix entries
@@ -162,6 +206,13 @@ ChainParams Engine::chain_params(const ChainShape &cs) const {
     p.tval = ch_tval.ptr;
     p.tons = ch_tons.ptr;
     return p;
+}
+
+tbpm_status Engine::wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const {
+    p.lds_rows = ch.max_stage[1];
+    hipError_t e = launch_pass_wide(fp32, chain_width(), cs.vs, ch.max_stage[0], p, st);
+    if (e != hipSuccess) return hip_fail(e, "launch wide pass");
+    return TBPM_OK;
 }
 
 tbpm_status Engine::chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const {

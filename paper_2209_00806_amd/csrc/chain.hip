@@ -51,23 +51,6 @@ __device__ __forceinline__ double read_lane(double x, int l) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// sum over the wave, in lane 63 (rows of 16 lanes by shifts, then the rows by broadcasts)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
-    return x + __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-__device__ __forceinline__ double wave_sum(double x) {
-    x = dpp_add<0x111, 0xf>(x);  // row_shr:1
-    x = dpp_add<0x112, 0xf>(x);  // row_shr:2
-    x = dpp_add<0x114, 0xf>(x);  // row_shr:4
-    x = dpp_add<0x118, 0xf>(x);  // row_shr:8
-    x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
-    return dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
-}
-
 // Waves per SIMD: a real operator's thread fits 128 registers, which leaves room
 // for two workgroups of 8 waves per CU; complex matrix entries take more, so
 // their workgroups have 4 waves (three of them per CU).

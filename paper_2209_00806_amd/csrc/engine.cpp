@@ -612,16 +612,21 @@ tbpm_status Engine::run(const RunArgs &a) {
     bool chain = (fused || (!cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps)) &&
                  chain_prepare(a.s_user, fp32, n_passes, cs) == TBPM_OK;
     if (chain && !fused && !chain_fits(cs, fp32, esize * (size_t)mat.n_rows * s_pad)) chain = false;
-    if (chain) staged = false;
+    // operators of wider rows: a pass that keeps the rows' entries in registers, in
+    // place of the staged pass, and where nobody chose a configuration
+    bool wide = !chain && (staged || (!fused && !cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps)) &&
+                wide_prepare(a.s_user, fp32, cs) == TBPM_OK && chain_room(fp32, 0);
+    const bool blocked = chain || wide;  // states in blocks, tiles and their tables as of `ch`
+    if (blocked) staged = false;
     fused = fused && !chain && mmax >= 4;  // two orders per launch need four terms
     if (fused && build_fused_tiles(s_pad, log2u, unit_bytes, cfg.fused) != TBPM_OK) fused = false;  // fall back
     if (staged && build_staged_tiles(s_pad, log2ub, unit_bytes, cfg.staged) != TBPM_OK) staged = false;
-    if (!staged && !fused && !chain) st = build_tiles(s_pad, chunks, vs);
+    if (!staged && !fused && !blocked) st = build_tiles(s_pad, chunks, vs);
     if (st != TBPM_OK) return st;
-    const int32_t n_tiles = chain ? ch.n_tiles : (int32_t)h_tiles.size();
+    const int32_t n_tiles = blocked ? ch.n_tiles : (int32_t)h_tiles.size();
     const int64_t n_el = mat.n_rows * s_pad;
     if (n_el >= (int64_t)INT32_MAX) return fail(TBPM_E_ARG, "n_orb * n_states (padded to a power of two) must be < 2^31");
-    if (chain) {
+    if (blocked) {
         st = chain_values(fp32, a.stream);
         if (st != TBPM_OK) return st;
     }
@@ -715,11 +720,11 @@ tbpm_status Engine::run(const RunArgs &a) {
         hj[1] = nullptr;
         TRY_HIP(hipMemcpyAsync(jc_tab.ptr, hj, jc_bytes, hipMemcpyHostToDevice, a.stream), "upload correlation table");
     }
-    // states in blocks of 2^log2sb (one block of all of them outside the chain)
-    const int32_t log2sb = chain ? cs.log2sb() : log2s;
+    // states in blocks of 2^log2sb (else one block of all of them)
+    const int32_t log2sb = blocked ? cs.log2sb() : log2s;
     last_log2sb = log2sb;
     // elements of the states that are propagated (whole blocks come first)
-    const int64_t n_el_all = chain ? mat.n_rows * cs.n_blk * cs.vs : n_el;
+    const int64_t n_el_all = blocked ? mat.n_rows * cs.n_blk * cs.vs : n_el;
     auto hist_slot = [&](int32_t local) { return (void *)((char *)ch_hist.ptr + hist_vec * (size_t)(local % kHistSteps)); };
     // psi starts where the last step of a graph leaves it
     void *bufptr[5] = {hist ? hist_slot(kHistSteps - 1) : v.ptr, ba.ptr, bb.ptr, bc.ptr, bd.ptr};
@@ -736,7 +741,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             if (e != hipSuccess) return hip_fail(e, "launch quasi-eigenstate accumulation");
         }
         if (a.jc_states > 0) {
-            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp,
+            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(blocked ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp,
                                         a.jc_states, log2sb, mat.n_rows, state, mat.slice_off, mat.col, a.jc_val,
                                         (double *)jc_part.ptr + std::max(local, 0) * part_stride, cnt, n_el, part_stride, s);
             if (e != hipSuccess) return hip_fail(e, "launch current correlation");
@@ -750,7 +755,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             ReduceParams jr{};
             jr.partials = (const double *)jc_part.ptr;
             jr.n_tiles = n_tiles;
-            jr.inst_tile0 = (const int32_t *)(chain ? ch_tile0.ptr : inst_tile0.ptr);
+            jr.inst_tile0 = (const int32_t *)(blocked ? ch_tile0.ptr : inst_tile0.ptr);
             jr.log2s = log2sp;
             jr.s_user = a.jc_states;
             jr.n_steps = a.n_steps;
@@ -776,7 +781,7 @@ tbpm_status Engine::run(const RunArgs &a) {
 
     // C_0
     InitParams ip{};
-    ip.tiles = (const TileDesc *)(chain ? ch_tiles.ptr : tiles.ptr);
+    ip.tiles = (const TileDesc *)(blocked ? ch_tiles.ptr : tiles.ptr);
     ip.n_tiles = n_tiles;
     ip.log2s = log2s;
     ip.s_user = a.s_user;
@@ -793,7 +798,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     ReduceParams rp{};
     rp.partials = (const double *)partials.ptr;
     rp.n_tiles = n_tiles;
-    rp.inst_tile0 = (const int32_t *)(chain ? ch_tile0.ptr : inst_tile0.ptr);
+    rp.inst_tile0 = (const int32_t *)(blocked ? ch_tile0.ptr : inst_tile0.ptr);
     rp.log2s = log2s;
     rp.s_user = a.s_user;
     rp.n_steps = a.n_steps;
@@ -898,7 +903,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             cp.ckpt = a.ckpt;
             cp.ckpt_slot = a.ckpt ? (const int32_t *)ckpt_slot.ptr : nullptr;
             cp.local = local;
-            cp.counter = (const int32_t *)counter.ptr;
+            cp.counter = (int32_t *)counter.ptr;
             cp.perm = mat.perm;
             cp.ckpt_stride = mat.n_rows * a.s_user;
             cp.s_user = a.s_user;
@@ -1008,6 +1013,31 @@ tbpm_status Engine::run(const RunArgs &a) {
         }
         for (int p = 0; p < n_passes; ++p) {
             const PassPlan &pl = plan[p];
+            if (wide) {
+                const bool last = pl.kind == kPassLast || pl.kind == kPassLastNoB2;
+                ChainParams cp = chain_params(cs);
+                cp.xcd_remap = cfg.xcd_remap;
+                cp.bump = p == 0;
+                cp.local = -1;  // the counter stands at this step
+                cp.reverse = walk;
+                walk ^= 1;
+                cp.x = bufptr[pl.x];
+                cp.v = bufptr[pl.v];
+                cp.b2 = pl.b2 >= 0 ? bufptr[pl.b2] : nullptr;
+                cp.out_last = bufptr[pl.out];
+                cp.coef = (const PassCoef *)coef.ptr + (size_t)p * ni;
+                cp.partials = last ? (double *)partials.ptr : nullptr;
+                cp.phi0 = (const double *)phi0.ptr;
+                cp.ckpt = a.ckpt;
+                cp.ckpt_slot = a.ckpt ? (const int32_t *)ckpt_slot.ptr : nullptr;
+                cp.counter = (int32_t *)counter.ptr;
+                cp.perm = mat.perm;
+                cp.ckpt_stride = mat.n_rows * a.s_user;
+                cp.s_user = a.s_user;
+                tbpm_status wst = wide_launch(fp32, cs, cp, s);
+                if (wst != TBPM_OK) return wst;
+                continue;
+            }
             PassParams pp{};
             pp.tiles = (const TileDesc *)tiles.ptr;
             pp.n_tiles = n_tiles;
@@ -1078,8 +1108,8 @@ tbpm_status Engine::run(const RunArgs &a) {
             key.tiles_unit = tiles_unit;
             key.lds_units = fused ? fu_lds_units : (staged ? stage_units : 0);
 
-            key.chain_depth = chain ? ch.depth : 0;
-            key.chain_grp = chain ? cs.n_grp : 0;
+            key.chain_depth = blocked ? ch.depth : 0;  // 1: the wide pass
+            key.chain_grp = blocked ? cs.n_grp : 0;
             key.n_steps = a.n_steps;
             key.n_qe = a.n_qe;
             key.jc_states = a.jc_states;
@@ -1150,7 +1180,7 @@ tbpm_status Engine::run(const RunArgs &a) {
 
     last_s_pad = s_pad;
     last_fp32 = fp32 ? 1 : 0;
-    last_staged = chain ? 3 : (fused ? 2 : (staged ? 1 : 0));
+    last_staged = wide ? 4 : chain ? 3 : (fused ? 2 : (staged ? 1 : 0));
     last_chain = cs;
     last_vs = vs;
     last_log2ub = log2ub;
@@ -1404,9 +1434,9 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         s_pad <<= 1;
         ++log2s;
     }
-    const bool chain = last_staged == 3;
-    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || (!chain && tiles_s != s_pad) ||
-        (chain && ch.depth == 0))
+    const bool chain = last_staged == 3, wide = last_staged == 4;
+    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || (!chain && !wide && tiles_s != s_pad) ||
+        ((chain || wide) && ch.depth == 0))
         return fail(TBPM_E_ARG, "tbpm_bench_pass needs a prior tbpm_propagate with the same n_states and precision");
     cfg = cfgs[fp32 ? 1 : 0];
     if (chain) {
@@ -1429,6 +1459,23 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
             cp.out_last = odd ? bb.ptr : bd.ptr;
             cp.reverse = odd ? 1 : 0;
             tbpm_status s = chain_launch(fp32, last_chain, cp, stream);
+            if (s != TBPM_OK) return s;
+        }
+        return TBPM_OK;
+    }
+    if (wide) {
+        // as below: out over b_{j+2}, the order just written is gathered next
+        ChainParams cp = chain_params(last_chain);
+        cp.xcd_remap = cfg.xcd_remap;
+        cp.v = v.ptr;
+        cp.coef = (const PassCoef *)coef.ptr;
+        cp.counter = (int32_t *)counter.ptr;
+        for (int32_t i = 0; i < n_launch; ++i) {
+            const bool odd = (i & 1) != 0;
+            cp.x = odd ? bb.ptr : ba.ptr;
+            cp.b2 = cp.out_last = odd ? ba.ptr : bb.ptr;
+            cp.reverse = odd ? 1 : 0;
+            tbpm_status s = wide_launch(fp32, last_chain, cp, stream);
             if (s != TBPM_OK) return s;
         }
         return TBPM_OK;

@@ -672,7 +672,8 @@ int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int
 
 void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                   const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
-                  int32_t D, int64_t max_eval, int64_t max_rows, ChainTables &t) {
+                  int32_t D, int64_t max_eval, int64_t max_rows, ChainTables &t, int32_t width) {
+    const int64_t W = std::max(width, 4);
     const int64_t SR = kSliceRows;
     const int32_t n_inst = (int32_t)inst_row0.size() - 1;
     const int64_t n = inst_row0[n_inst];
@@ -720,12 +721,13 @@ void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32
                 }
                 for (size_t l = 0; l < rows.size(); ++l) at[rows[l]] = (uint16_t)l;
                 const size_t i0 = pt.lidx.size();
-                pt.lidx.resize(i0 + 4 * (size_t)c[D - 1]);
+                pt.lidx.resize(i0 + W * (size_t)c[D - 1]);
+                const int64_t rs = W > 4 ? 1 : 4, es = W > 4 ? c[D - 1] : 1;
                 for (int32_t l = 0; l < c[D - 1]; ++l) {
                     const int64_t r = rows[l];
                     const int64_t s0 = slice_off[r / SR], w = (slice_off[r / SR + 1] - s0) / SR;
-                    uint16_t *li = &pt.lidx[i0 + 4 * (size_t)l];
-                    for (int64_t e = 0; e < 4; ++e) li[e] = e < w ? at[col[s0 + e * SR + r % SR]] : (uint16_t)l;
+                    uint16_t *li = &pt.lidx[i0 + (size_t)(rs * l)];
+                    for (int64_t e = 0; e < W; ++e) li[es * e] = e < w ? at[col[s0 + e * SR + r % SR]] : (uint16_t)l;
                 }
                 pt.rows.insert(pt.rows.end(), rows.begin(), rows.end());
                 pt.cnt.insert(pt.cnt.end(), c.begin(), c.end());
@@ -737,16 +739,16 @@ void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32
     for (const Part &pt : parts) {
         if (!pt.ok) return;
         n_rows += (int64_t)pt.rows.size();
-        n_eval += (int64_t)pt.lidx.size() / 4;
+        n_eval += (int64_t)pt.lidx.size() / W;
     }
     if (n_rows >= (int64_t)INT32_MAX) return;
     t.depth = D;
     t.max_stage.assign(D + 1, 0);
     t.inst_tile0.assign(n_inst + 1, 0);
     t.rowmap.reserve(n_rows);
-    t.lidx.reserve(4 * n_eval);
+    t.lidx.reserve(W * n_eval);
     for (const Part &pt : parts) {
-        int64_t ro = (int64_t)t.rowmap.size(), le = (int64_t)t.lidx.size() / 4;
+        int64_t ro = (int64_t)t.rowmap.size(), le = (int64_t)t.lidx.size() / W;
         for (size_t q = 0; q < pt.tiles.size(); ++q) {
             const int32_t *c = &pt.cnt[q * (D + 1)];
             for (int32_t h = 0; h <= D; ++h) t.max_stage[h] = std::max(t.max_stage[h], c[h]);

@@ -142,6 +142,17 @@ constexpr int kChainRowsPerThread = 2;
 constexpr int chain_threads(bool cplx) { return cplx ? 256 : 512; }
 constexpr int chain_rows(bool cplx) { return chain_threads(cplx) * kChainRowsPerThread; }
 
+// The wide pass (wide.hip): most stored elements per row, threads of a workgroup
+// (one row each), and rows of a tile with those one hop away.
+constexpr int kWideWidth = 24;
+constexpr int kWideThreads = 256;
+constexpr int kWideStage = 1280;
+
+// elements per row that the tile tables hold
+constexpr int chain_table_width(int max_width) {
+    return max_width <= 3 ? 3 : (max_width > 20 && max_width <= 22 ? 22 : (max_width + 3) / 4 * 4);
+}
+
 struct ChainParams {
     const TileDesc *tiles;
     int32_t n_tiles;
@@ -179,10 +190,12 @@ struct ChainParams {
     double *ckpt;
     const int32_t *ckpt_slot;
     int32_t local;  // steps since the counter was advanced
-    const int32_t *counter;
+    int32_t *counter;
     const int32_t *perm;
     int64_t ckpt_stride;
     int32_t s_user;
+    // the wide pass: rows of a half of the LDS; advance the step counter
+    int32_t lds_rows, bump;
 };
 
 // Several orders of the Chebyshev recursion T_{j+1} = 2 H~ T_j - T_{j-1} per

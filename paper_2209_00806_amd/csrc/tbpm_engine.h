@@ -125,12 +125,15 @@ struct Engine {
         int32_t log2sb() const { return vs == 2 ? 1 : 0; }
     };
     void chain_orders();
-    int32_t chain_width() const { return mat.max_width <= 3 ? 3 : 4; }
+    int32_t chain_width() const { return chain_table_width(mat.max_width); }
     // tables and launch sequence for n_orders orders on s_user states;
     // TBPM_E_ARG if the operator does not suit the kernel
     tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs);
     // whether the vectors (vec bytes each) and tables that the chain needs beyond
     // the ones held fit the device memory that is free
+    tbpm_status chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows);
+    tbpm_status wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const;
+    tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs);
     bool chain_room(bool fp32, size_t need);
     bool chain_fits(const ChainShape &cs, bool fp32, size_t vec);
     tbpm_status chain_values(bool fp32, hipStream_t st);

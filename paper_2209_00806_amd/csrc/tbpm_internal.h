@@ -168,6 +168,8 @@ hipError_t launch_chain(bool fp32, bool cplx, int width, int vs, int max_eval, i
 // max_own: the most rows of a tile
 hipError_t launch_chain_cheb(int mode, bool cplx, int width, int max_own, int max_eval, int max_stage,
                              const ChainParams &p, const ChainCheb &ad, hipStream_t st);
+// one order of a wide operator (wide.hip); max_own: the most rows of a tile
+hipError_t launch_pass_wide(bool fp32, int width, int vs, int max_own, const ChainParams &p, hipStream_t st);
 hipError_t launch_chain_values(bool fp32, bool cplx, const ChainTileTab &t, int32_t n_tiles, const DevMatrix &m,
                                void *tval, void *tons, hipStream_t st);
 // sums the partials of n_local steps (step_stride doubles apart) into samples
@@ -302,12 +304,13 @@ struct ChainTables {
     std::vector<TileDesc> tiles;
     std::vector<int32_t> inst_tile0, cnt, toff, loff;
     std::vector<uint32_t> rowmap;
-    std::vector<uint16_t> lidx;      // [row][4]
+    // [row][4]; with more than four elements per row, per tile [element][evaluated row]
+    std::vector<uint16_t> lidx;
     std::vector<int32_t> max_stage;  // [depth + 1]: most rows within h hops
 };
 void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                   const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
-                  int32_t depth, int64_t max_eval, int64_t max_rows, ChainTables &t);
+                  int32_t depth, int64_t max_eval, int64_t max_rows, ChainTables &t, int32_t width = 4);
 
 // The depth to build tiles of T rows for: the largest up to cap that nearly all
 // of a sample of tiles reach within the bounds; 0 if none

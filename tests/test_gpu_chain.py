@@ -202,3 +202,31 @@ def test_chain_accumulates_several_steps_per_launch(n_steps, precision):
     for a, b in zip(*out):
         assert _rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-12
     H.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,ny,band", [(9, 7, 0), (23, 21, 0), (67, 61, 0), (0, 5000, 3), (0, 5000, 5), (0, 5000, 7),
+                                        (0, 5000, 9)])
+def test_chain_wide_rows(nx, ny, band, precision):
+    """Two or three orders per launch of real operators with rows of 5 to 24 elements (bilayers, and bands of 6, 10,
+    14 and 18 elements for the other table widths) against one order per launch: bars as above."""
+    rng = np.random.default_rng(9)
+    if nx:
+        lat = inputs.twisted_bilayer(nx, ny)
+    else:
+        i = np.arange(ny)
+        lat = inputs.from_bonds(ny, np.concatenate([i] * band), np.concatenate([(i + d + 1) % ny for d in range(band)]),
+                                -0.2 - rng.random(ny * band), np.zeros(ny))
+    lat.onsite = inputs.anderson(rng, lat.n_orb, 1.0)
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    for S, z, nt in ((1, math.pi, 19), (3, math.pi, 6), (16, math.pi, 4), (8, 0.3, 9), (5, 9.0, 3), (2, 1e-7, 3)):
+        psi = torch.from_numpy(inputs.random_phase_states(rng, lat.n_orb, S)).cuda()
+        H.set_launch_config()
+        ref, n_ref = tbpm.propagate(H, psi, nt, z / f, f, precision=precision, return_norm=True)
+        for shape in (CHAIN, dict(wg_chunks=2, xcd_remap=3, nontemporal=0, unroll=1, staged=2, vec=4, fused=0)):
+            H.set_launch_config(**shape)
+            got, n_got = tbpm.propagate(H, psi, nt, z / f, f, precision=precision, return_norm=True)
+            assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-12, (S, z, nt)
+            assert _rel(n_got.cpu().numpy(), n_ref.cpu().numpy()) < 1e-12, (S, z, nt)
+    H.close()
