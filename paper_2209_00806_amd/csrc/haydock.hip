@@ -31,6 +31,7 @@ namespace tbpm {
 namespace {
 
 enum HayReduce : int { kHayA = 0, kHayB = 1, kHayInit = 2 };
+constexpr int kHayThreads = 1024;
 
 // One thread per (row, state) element: on the headline lattice with 8 chains
 // this runs ahead of units of 2 states (+3-7% per iteration) and of 4
@@ -214,6 +215,193 @@ __global__ __launch_bounds__(kWG) void k_hay_reduce(const double *__restrict__ i
     h[0] = inv;
 }
 
+// One iteration per launch, for operators of up to kChainWidth stored elements per
+// row, on the chain kernel's tile tables (two hops of them), states in blocks of one:
+//     u_{i+1} = (H u_i)/b_i - (a_i/b_i) u_i - (b_i/b_{i-1}) u_{i-1}
+// on the tile's own rows and those one hop away (one per thread; u_i of the rows
+// up to two hops away is in LDS), then H u_{i+1} on own rows, which is not
+// stored: it gives <u_{i+1}|H u_{i+1}>, and with ||u_{i+1}||^2 and Re <u_{i+1}|u_i>
+// the next a and b (k_hay_reduce3),
+//     a_{i+1} = <u_{i+1}|H u_{i+1}>/b_{i+1}^2 - (b_{i+1}/b_i) Re <u_{i+1}|u_i>/b_{i+1},
+// the same form of a as above.  first: the sums for u_0 = x alone.  u_i and
+// u_{i-1} are read on other tiles' rows, so u_{i+1} goes to a third vector.
+// Streams per iteration: u_i (and 35% of it again for the two hops), u_{i-1}
+// (15%), u_{i+1}: 3.5 state vectors in one pass, and one sum, instead of 6 in two.
+// Graphene 512^2, 8 states: 40 us and 4.6 us for the sums, 6 TB/s; the two-launch
+// form 39 + 31 us and 18 us.
+template <bool CH, int W>
+__global__ __launch_bounds__(kHayThreads) void k_hay_step(const ChainParams p, const double *__restrict__ hs) {
+    extern __shared__ __align__(16) unsigned char hay_mem[];
+    using HV = typename std::conditional<CH, d2, double>::type;
+    int grp = 0, tslot = (int)blockIdx.x;
+    if (p.n_grp > 1) {
+        const int r = (int)blockIdx.x >> 3;
+        grp = r % p.n_grp;
+        tslot = (r / p.n_grp) * 8 + ((int)blockIdx.x & 7);
+        if (tslot >= p.n_tiles) return;  // the last group of 8 tiles is partial
+    }
+    const int blk0 = grp * p.grp_blk, blk1 = min(blk0 + p.grp_blk, p.n_blk);
+    const int tile = tile_of_block(tslot, p.n_tiles, p.xcd_remap, p.reverse);
+    if (p.bump && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(p.counter, 1);
+    if (blk0 >= blk1) return;
+    const TileDesc td = p.tiles[tile];
+    const int32_t *cnt = p.cnt + (int64_t)tile * (p.table_depth + 1);
+    const int n_own = td.rows, n_eval = cnt[1], n_shell = cnt[2] - n_eval, n_tab = cnt[p.table_depth - 1];
+    const uint32_t *rowmap = p.rowmap + p.toff[tile];
+    const int64_t lo = p.loff[tile];
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const bool own = tid < n_own, eval = tid < n_eval, own_wave = (tid & ~63) < n_own;
+    const int lr = min(tid, n_eval - 1);
+    const uint32_t g = p.contiguous && lr < n_own ? (uint32_t)td.row0 + (uint32_t)lr : rowmap[lr];
+    const uint32_t gs = tid < n_shell ? rowmap[n_eval + tid] : g;
+    d2 *xs = (d2 *)hay_mem, *ys = xs + 2 * p.lds_rows;
+    double *red = (double *)(ys + nt);  // [2][waves][3]
+
+    HV h[W];
+    uint32_t na[W];
+    const double on = ((const double *)p.tons)[lo + lr];
+    {
+        const uint2 li = ((const uint2 *)p.lidx + lo)[lr];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            h[k] = ((const HV *)p.tval + lo * W)[(int64_t)k * n_tab + lr];
+            const uint32_t pair = k < 2 ? li.x : li.y;
+            na[k] = (k & 1) ? pair >> 16 : pair & 0xffffu;
+        }
+    }
+    auto row_of = [&](const void *base, int blk, uint32_t r) -> d2 & {
+        return ((d2 *)base + (int64_t)blk * p.n_rows)[r];
+    };
+    // unconditional loads (lanes without a row repeat one)
+    const void *b2p = p.b2 ? p.b2 : p.x;
+    d2 px, psh, pb;
+    auto load = [&](int blk) {
+        px = row_of(p.x, blk, g);
+        psh = row_of(p.x, blk, gs);
+        pb = row_of(b2p, blk, g);
+    };
+    auto put = [&](int blk, d2 *buf) {
+        if (eval) buf[tid] = px;
+        if (tid < n_shell) buf[n_eval + tid] = psh;
+        for (int l = tid + nt; l < n_shell; l += nt) buf[n_eval + l] = row_of(p.x, blk, rowmap[n_eval + l]);
+    };
+    // the partial sums of the block before (its waves' sums are behind a barrier)
+    auto flush = [&](int blk, int par) {
+        if (tid < 3) {
+            double a = 0.0;
+            for (int w = 0; w < (n_own + 63) / 64; ++w) a += red[(par * (nt / 64) + w) * 3 + tid];
+            p.partials[((int64_t)blk * 3 + tid) * p.n_tiles + tile] = a;
+        }
+    };
+    auto mul = [&](const d2 *buf, const d2 &self) {
+        d2 xc[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) xc[k] = buf[na[k]];
+        d2 acc;
+        acc.x = on * self.x;
+        acc.y = on * self.y;
+#pragma unroll
+        for (int k = 0; k < W; ++k) acc = hmad(h[k], xc[k], acc);
+        return acc;
+    };
+    d2 *cur = xs, *oth = xs + p.lds_rows;
+    load(blk0);
+    put(blk0, cur);
+    for (int blk = blk0; blk < blk1; ++blk) {
+        const int par = (blk - blk0) & 1;
+        const double s1 = hs[4 * blk], s3 = hs[4 * blk + 1], s2 = hs[4 * blk + 2];
+        __syncthreads();
+        const d2 u = px, um = pb;  // u_i, u_{i-1}
+        if (blk + 1 < blk1) load(blk + 1);
+        if (blk > blk0) flush(blk - 1, par ^ 1);
+        d2 un = u;
+        const d2 *src = cur;
+        if (!p.first) {
+            const d2 acc = mul(cur, u);
+            un.x = fma(s1, acc.x, fma(-s3, um.x, -s2 * u.x));
+            un.y = fma(s1, acc.y, fma(-s3, um.y, -s2 * u.y));
+            if (eval) ys[tid] = un;
+            if (own) row_of(p.out_last, blk, g) = un;
+            src = ys;
+            __syncthreads();
+        }
+        if (own_wave) {
+            const d2 z = mul(src, un);
+            double n2 = 0.0, hu = 0.0, cr = 0.0;
+            if (own) {
+                n2 = fma(un.x, un.x, un.y * un.y);
+                hu = fma(un.x, z.x, un.y * z.y);
+                cr = fma(un.x, u.x, un.y * u.y);
+            }
+            n2 = wave_sum(n2);
+            hu = wave_sum(hu);
+            cr = wave_sum(cr);
+            if (lane == 63) {
+                double *r = red + (par * (nt / 64) + wave) * 3;
+                r[0] = n2;
+                r[1] = hu;
+                r[2] = cr;
+            }
+        }
+        // the other half was read before the last barrier but one
+        if (blk + 1 < blk1) put(blk + 1, oth);
+        d2 *t = cur;
+        cur = oth;
+        oth = t;
+    }
+    __syncthreads();
+    flush(blk1 - 1, (blk1 - 1 - blk0) & 1);
+}
+
+// The scalars after k_hay_step, from the sums over tiles in a fixed order: one
+// workgroup per state.
+__global__ __launch_bounds__(kWG) void k_hay_reduce3(const double *__restrict__ part, int n_tiles, int s_user, int first,
+                                                     double thr, double *__restrict__ hs, int32_t *counter, int n_iter,
+                                                     double *__restrict__ a_out, double *__restrict__ b_out) {
+    __shared__ double red[3][kWG];
+    const int s = blockIdx.x;
+    const double *q = part + (int64_t)s * 3 * n_tiles;
+    double v[3][4] = {};
+    int t = threadIdx.x;
+    for (; t + 3 * kWG < n_tiles; t += 4 * kWG) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c][u] += q[(int64_t)c * n_tiles + t + u * kWG];
+    }
+    for (; t < n_tiles; t += kWG)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c][0] += q[(int64_t)c * n_tiles + t];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) red[c][threadIdx.x] = (v[c][0] + v[c][1]) + (v[c][2] + v[c][3]);
+    __syncthreads();
+    for (int w = kWG / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x != 0) return;
+    double *h = hs + 4 * s;
+    const double old = first ? 0.0 : h[0];
+    double b = sqrt(red[0][0]), inv = 0.0;
+    if (first)
+        inv = b > 0.0 ? 1.0 / b : 0.0;
+    else if (b > thr && old != 0.0)
+        inv = 1.0 / b;
+    else
+        b = 0.0;
+    const double cprev = first ? 0.0 : b * old;
+    const double a = inv * (inv * red[1][0]) - cprev * (inv * red[2][0]);
+    const int k = first ? -1 : *(volatile const int32_t *)counter - 1;  // iteration
+    if (k >= 0 && k < n_iter) b_out[(int64_t)k * s_user + s] = b;
+    if (k + 1 < n_iter) a_out[(int64_t)(k + 1) * s_user + s] = a;
+    h[0] = inv;
+    h[1] = cprev;
+    h[2] = a * inv;
+    if (first && s == 0) *counter = 0;
+}
+
 // d(E_j) = -(1/pi) Im G_0(E_j + i eps), G_0 by the continued fraction from
 // the deepest level up; one thread per (energy, state)
 __global__ __launch_bounds__(kWG) void k_hay_ldos(const double *__restrict__ a, const double *__restrict__ b,
@@ -280,6 +468,34 @@ hipError_t launch_hay_reduce(const double *partials, int32_t n_tiles, int32_t s_
     }
     hipLaunchKernelGGL(k_hay_reduce, dim3((unsigned)s_pad), dim3(kWG), 0, st, in, stride, n, s_user, (int)mode, thr,
                        hs, counter, n_iter, a_out, b_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_hay_step(bool cplx, int width, int max_eval, int max_stage, ChainParams p, const double *hs,
+                           hipStream_t st) {
+    if (p.n_tiles <= 0) return hipSuccess;
+    const unsigned nt = (unsigned)(max_eval + 63) / 64 * 64;
+    const size_t lds = 16 * (2 * (size_t)max_stage + nt) + sizeof(double) * 6 * (nt / 64);
+    if (max_eval < 1 || nt > kHayThreads || max_stage < max_eval || lds > 64 * 1024 || p.table_depth < 2 || width < 1 ||
+        width > kChainWidth || p.n_blk < 1 || p.n_grp < 1 || p.grp_blk < 1)
+        return hipErrorInvalidValue;
+    p.lds_rows = max_stage;
+    const dim3 grid(p.n_grp > 1 ? (unsigned)(((p.n_tiles + 7) / 8) * 8 * p.n_grp) : (unsigned)p.n_tiles), block(nt);
+    if (cplx && width <= 3)
+        hipLaunchKernelGGL((k_hay_step<true, 3>), grid, block, lds, st, p, hs);
+    else if (cplx)
+        hipLaunchKernelGGL((k_hay_step<true, 4>), grid, block, lds, st, p, hs);
+    else if (width <= 3)
+        hipLaunchKernelGGL((k_hay_step<false, 3>), grid, block, lds, st, p, hs);
+    else
+        hipLaunchKernelGGL((k_hay_step<false, 4>), grid, block, lds, st, p, hs);
+    return hipGetLastError();
+}
+
+hipError_t launch_hay_reduce3(const double *partials, int32_t n_tiles, int32_t s_user, bool first, double thr, double *hs,
+                              int32_t *counter, int32_t n_iter, double *a_out, double *b_out, hipStream_t st) {
+    hipLaunchKernelGGL(k_hay_reduce3, dim3((unsigned)s_user), dim3(kWG), 0, st, partials, n_tiles, s_user, first ? 1 : 0,
+                       thr, hs, counter, n_iter, a_out, b_out);
     return hipGetLastError();
 }
 

@@ -238,6 +238,8 @@ struct Engine {
     tbpm_status apply_ell(const double *jval, int32_t log2s, const void *src, void *dst, hipStream_t st);
     // Haydock (Lanczos) recursion of every column of psi0 (device, caller's
     // order, [rows][s_user] complex128): a_out, b_out device [n_iter][s_user]
+    tbpm_status haydock_chain(const ChainShape &cs, const double *psi0, int32_t s_user, int32_t n_iter, double thr,
+                              double *a_out, double *b_out, uint32_t flags, hipStream_t st);
     tbpm_status haydock(const double *psi0, int32_t s_user, int32_t n_iter, double thr, double *a_out, double *b_out,
                         uint32_t flags, hipStream_t st);
     // mu[n][m] (complex128, m contiguous) = (1/S) sum_s <r_s| v_a T_m(H/f) v_b T_n(H/f) |r_s>

@@ -227,6 +227,12 @@ int32_t hay_fold_count(int32_t n_tiles);
 hipError_t launch_hay_reduce(const double *partials, int32_t n_tiles, int32_t s_pad, int32_t s_user, int32_t mode,
                              double thr, double *hs, int32_t *counter, int32_t n_iter, double *a_out, double *b_out,
                              double *fold, hipStream_t st);
+// one iteration per launch on the chain kernel's tiles (max_eval, max_stage: the
+// most rows one and two hops away), and its scalars; first: those of u_0
+hipError_t launch_hay_step(bool cplx, int width, int max_eval, int max_stage, ChainParams p, const double *hs,
+                           hipStream_t st);
+hipError_t launch_hay_reduce3(const double *partials, int32_t n_tiles, int32_t s_user, bool first, double thr, double *hs,
+                              int32_t *counter, int32_t n_iter, double *a_out, double *b_out, hipStream_t st);
 hipError_t launch_hay_ldos(const double *a, const double *b, int32_t n_iter, int32_t n_states, const double *energies,
                            int64_t n_e, double eps, double *out, hipStream_t st);
 

@@ -230,3 +230,35 @@ def test_chain_wide_rows(nx, ny, band, precision):
             assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-12, (S, z, nt)
             assert _rel(n_got.cpu().numpy(), n_ref.cpu().numpy()) < 1e-12, (S, z, nt)
     H.close()
+
+
+@pytest.mark.parametrize("kind", ["ring5", "graphene_small", "graphene", "square_open", "graphene_complex",
+                                  "square_complex"])
+def test_chain_haydock_one_launch_per_iteration(kind):
+    """Lanczos coefficients with one launch per iteration against the two-launch form: odd state counts, start
+    vectors that span an invariant subspace (the ring: exact zeros after its fifth iteration) and a zero one,
+    lengths within and beyond a graph.  Both forms round differently, which the recursion amplifies slowly: 1e-9
+    of the Gershgorin bound over 50 iterations; graph and direct launches bit for bit."""
+    rng = np.random.default_rng(10)
+    lat = _lattice(kind, rng)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    g = H.info()["gershgorin"]
+    for S, n_iter in ((1, 50), (3, 13), (8, 29), (5, 1), (2, 6)):
+        st = inputs.random_phase_states(rng, lat.n_orb, S)
+        st[:, S - 1] = 0.0
+        st[:, 0] = 0.0
+        st[lat.n_orb // 2, 0] = 1.0
+        psi = torch.from_numpy(st).cuda()
+        H.set_launch_config()
+        a, b = (t.cpu().numpy() for t in tbpm.haydock(H, psi, n_iter))
+        H.set_launch_config(**CHAIN)
+        a1, b1 = (t.cpu().numpy() for t in tbpm.haydock(H, psi, n_iter))
+        a2, b2 = (t.cpu().numpy() for t in tbpm.haydock(H, psi, n_iter, graph=False))
+        assert np.array_equal(a1, a2) and np.array_equal(b1, b2)
+        m = min(n_iter, 4) if kind == "ring5" else n_iter  # what follows an exhausted subspace is rounding
+        assert np.max(np.abs(a1[:m] - a[:m])) < 1e-9 * g and np.max(np.abs(b1[:m] - b[:m])) < 1e-9 * g
+        if S > 1:
+            assert not a1[:, S - 1].any() and not b1[:, S - 1].any()
+        if kind == "ring5" and n_iter > 6:
+            assert not b1[5:, 0].any() and not a1[6:, 0].any()
+    H.close()
