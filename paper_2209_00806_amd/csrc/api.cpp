@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -476,8 +477,21 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_hamiltonian *H, const double *psi0, int3
 static tbpm_status upload_currents(tbpm_hamiltonian *H, const double *j_alpha, const double *j_beta, hipStream_t hs) {
     Engine &eng = H->eng;
     const int64_t nnz = H->csr.nnz();
-    for (int64_t p = 0; p < 2 * nnz; ++p)
-        if (!std::isfinite(j_alpha[p]) || !std::isfinite(j_beta[p])) return fail(TBPM_E_ARG, "non-finite current value");
+    // one array given as both operators is checked and copied once
+    const bool same = j_alpha == j_beta;
+    std::atomic<bool> bad{false};
+    try {
+        run_chunks(2 * nnz, host_threads(2 * nnz), [&](int, int64_t lo, int64_t hi) {
+            for (const double *v : {j_alpha, same ? nullptr : j_beta}) {
+                int inf = 0;  // no early exit: the loop is vectorised
+                for (int64_t p = lo; v && p < hi; ++p) inf |= !std::isfinite(v[p]);
+                if (inf) bad.store(true);
+            }
+        });
+    } catch (const std::bad_alloc &) {
+        return fail(TBPM_E_OOM, "host allocation failed");
+    }
+    if (bad.load()) return fail(TBPM_E_ARG, "non-finite current value");
     const size_t ell = sizeof(double) * 2 * (size_t)std::max<int64_t>(eng.mat.ell_size, 1);
     hipError_t e = eng.ac_csr.ensure(sizeof(double) * 2 * (size_t)std::max<int64_t>(nnz, 1));
     if (e == hipSuccess) e = eng.ac_ja.ensure(ell);
@@ -486,8 +500,8 @@ static tbpm_status upload_currents(tbpm_hamiltonian *H, const double *j_alpha, c
     const double *jv[2] = {j_alpha, j_beta};
     DevBuf *jd[2] = {&eng.ac_ja, &eng.ac_jb};
     for (int q = 0; q < 2; ++q) {
-        e = hipStreamSynchronize(hs);
-        if (e == hipSuccess && nnz > 0)
+        if (q == 0 || !same) e = hipStreamSynchronize(hs);
+        if (e == hipSuccess && nnz > 0 && (q == 0 || !same))
             e = hipMemcpy(eng.ac_csr.ptr, jv[q], sizeof(double) * 2 * (size_t)nnz, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = launch_gather_values(eng.mat.ell_csr, eng.mat.ell_size, (const double *)eng.ac_csr.ptr,

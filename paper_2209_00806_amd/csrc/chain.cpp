@@ -117,8 +117,11 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }
-        // few tiles: their state blocks go to several workgroups each
-        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch.n_tiles - 1) / ch.n_tiles));
+        // few tiles: their state blocks go to several workgroups each, up to what the
+        // chip holds at once (two workgroups per CU, three of complex operators:
+        // hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
+        const int64_t slots = mat.is_complex ? 768 : 512;
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + ch.n_tiles - 1) / ch.n_tiles));
         chain_split(n_orders, ch.depth, cs.depths);
         return TBPM_OK;
     }
