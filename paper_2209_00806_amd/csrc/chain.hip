@@ -28,7 +28,8 @@
 // next block prefetched into registers 1.81-1.97 ms (one workgroup per CU is
 // left), prefetched into LDS by loads that write LDS directly 1.37 ms, one row
 // per thread (1024 threads) 1.28 ms, two states per row and thread 1.87 ms, 256
-// threads with 256-row tiles and 5 orders 1.29 ms.
+// threads with 256-row tiles and 5 orders 1.29 ms.  Neighbour addresses without
+// bank conflicts (wrong neighbours) would give 1.10 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,17 +60,17 @@ constexpr int chain_waves(bool ch) { return ch ? 3 : 4; }
 // The body of k_chain (Clenshaw orders) and k_chain_cheb (Chebyshev orders
 //     T_{j+1} = 2 H~ T_j - T_{j-1},   T_1 = H~ T_0).
 // kChainCurrent also applies a current operator to every T_j from the same
-// neighbours in LDS.  In the adjoint (kChainAdjoint, T_j = alpha_j) lambda gains conj(c_{j+1}) alpha_{j+1}, and own row q adds to the gradient of
-// its transposed elements (p, q) Re/Im of alpha_j[p] conj(w b_{j+1}[q]): alpha_j
-// at p is read from LDS for the product anyway, b at the own row is the only
-// stream of its own, and the sums over orders and state blocks stay in registers
-// until the workgroup ends (one read-modify-write per tile and launch, no sum
-// across lanes).
-// Measured, DOS and its gradient on graphene 256^2, 4 FP64 states: 38.6 ms with the
-// replay storing every order and the adjoint 5 or 6 orders per launch, 63.7 ms with
-// two orders per launch of both (there the adjoint was 29 ms of it, bound by the
-// read-modify-write of the gradient for every pair of orders and the sums over
-// lanes).
+// neighbours in LDS.  In the adjoint (kChainAdjoint, T_j = alpha_j) lambda gains
+// conj(c_{j+1}) alpha_{j+1}, and own row q adds to the gradient of its transposed
+// elements (p, q) Re/Im of alpha_j[p] conj(w b_{j+1}[q]): alpha_j at p is read from
+// LDS for the product anyway, b at the own row is the only stream of its own, and
+// the sums over orders and state blocks stay in registers until the workgroup
+// ends (one read-modify-write per tile and launch, no sum across lanes).
+// Measured, DOS and its gradient on graphene 256^2, 4 FP64 states: 37.6 ms with the
+// replay storing every order and the adjoint 5 or 6 orders per launch (27 us a
+// launch, the replay's 25), 63.7 ms with two orders per launch of both, where the
+// adjoint was bound by the read-modify-write of the gradient for every pair of
+// orders and the sums over lanes.
 template <typename R, bool CH, int W, int VS, int NT, int NR, int MODE>
 __device__ __forceinline__ void chain_body(const ChainParams &p, const ChainCheb &ad) {
     extern __shared__ __align__(16) unsigned char chain_mem[];
