@@ -262,3 +262,42 @@ def test_chain_haydock_one_launch_per_iteration(kind):
         if kind == "ring5" and n_iter > 6:
             assert not b1[5:, 0].any() and not a1[6:, 0].any()
     H.close()
+
+
+def test_wide_rows_stored_states_and_batch():
+    """The wide pass with checkpoints, snapshots, quasi-eigenstates and current correlations (states leave the
+    blocks in the caller's order), and in a batch of members of uneven size: 1e-12 against one order per launch."""
+    rng = np.random.default_rng(11)
+    staged = dict(wg_chunks=2, xcd_remap=3, nontemporal=0, unroll=1, staged=2, vec=4, fused=0)
+    lats = [inputs.twisted_bilayer(n, n) for n in (7, 23, 12)]
+    for lat in lats:
+        lat.onsite = inputs.anderson(rng, lat.n_orb, 1.0)
+    fs = [1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite) for lat in lats]
+    hams = [tbpm.Hamiltonian.from_lattice(lat) for lat in lats]
+    H, lat, f = hams[1], lats[1], fs[1]
+    dt = math.pi / f
+    i = np.repeat(np.arange(lat.n_orb), np.diff(lat.row_ptr))
+    x = rng.uniform(0, 1, lat.n_orb)
+    J = 1j * lat.val * (x[lat.col] - x[i])
+    for S in (3, 6):
+        psi = torch.from_numpy(inputs.random_phase_states(rng, lat.n_orb, S)).cuda()
+        out = []
+        for shape in ({}, staged):
+            H.set_launch_config(**shape)
+            _, ck = tbpm.propagate(H, psi, 23, dt, f, ckpt_every=5)
+            out.append([ck, tbpm.propagate_snapshots(H, psi, [19, 0, 2], dt, f),
+                        tbpm.propagate_snapshots(H, psi, [18, 3], dt, f, precision="fp32"),
+                        tbpm.quasi_eigenstates(H, psi, [-0.7, 1.1], 20, dt, f),
+                        tbpm.quasi_eigenstates(H, psi, [0.4], 9, dt, f, precision="fp32"),
+                        tbpm.ac_corr(H, J, J, psi, 19, dt, 10.0, 0.1, rescale=f)])
+        for a, b in zip(*out):
+            assert _rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-12
+    B = tbpm.Batch(hams)
+    psis = [torch.from_numpy(inputs.random_phase_states(rng, l.n_orb, 5)).cuda() for l in lats]
+    for precision in ("fp64", "fp32"):
+        out = []
+        for shape in ({}, staged):
+            B.set_launch_config(**shape)
+            out.append(B.propagate(psis, 21, [math.pi / v for v in fs], fs, precision=precision))
+        for a, b in zip(*out):
+            assert _rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-12
