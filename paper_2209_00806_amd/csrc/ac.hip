@@ -202,7 +202,55 @@ int64_t grid_for_n(int64_t n) {
     return b < 1 ? 1 : b;
 }
 
+// Chebyshev coefficients of the Fermi function from n samples g_q at cos(2 pi q/n)
+// (n a power of two; g_{n-q} = g_q, so q <= n/2 suffices):
+//     a_k = (4/n) [ (g_0 + (-1)^k g_{n/2})/2 + sum_{0<q<n/2} g_q cos(2 pi q k/n) ],
+// half of it for k = 0.  2^log2l lanes per coefficient; the phase q k mod n is
+// exact.  last: the largest k with |a_k| >= tol.
+__global__ __launch_bounds__(kWG) void k_fermi_samples(double beta, double mu, double rescale, int n,
+                                                       double *__restrict__ g) {
+    const int q = blockIdx.x * kWG + threadIdx.x;
+    if (q > n / 2) return;
+    const double x = rescale * cospi(2.0 * (double)q / (double)n);
+    const double v = 0.5 * (1.0 - tanh(0.5 * beta * (x - mu)));
+    g[q] = q == 0 || q == n / 2 ? 0.5 * v : v;
+}
+
+__global__ __launch_bounds__(kWG) void k_fermi_cheb(const double *__restrict__ g, int n, int log2l, double tol,
+                                                    double *__restrict__ a, int *__restrict__ last) {
+    const int lane = (int)threadIdx.x & ((1 << log2l) - 1);
+    const uint32_t k = (uint32_t)(((int64_t)blockIdx.x * kWG + threadIdx.x) >> log2l), mask = (uint32_t)n - 1u;
+    const double step = 2.0 / (double)n;
+    double sum = 0.0, comp = 0.0;
+    if ((int)k < n / 2) {
+        uint32_t m = ((uint32_t)lane * k) & mask;
+        const uint32_t dm = (k << log2l) & mask;
+        for (int q = lane; q <= n / 2; q += 1 << log2l) {
+            kadd(sum, comp, g[q] * cospi((double)m * step));
+            m = (m + dm) & mask;
+        }
+    }
+    sum = kadd_lanes(sum, comp, log2l);
+    if ((int)k >= n / 2 || lane != 0) return;
+    const double v = (k == 0 ? 2.0 : 4.0) / (double)n * sum;
+    a[k] = v;
+    if (fabs(v) >= tol) atomicMax(last, (int)k);
+}
+
+__global__ void k_fermi_clear(int *last) { *last = 0; }
+
 }  // namespace
+
+hipError_t launch_fermi_cheb(double beta, double mu, double rescale, int32_t n, double tol, double *g, double *a,
+                             int32_t *last, hipStream_t st) {
+    if (n < 4 || (n & (n - 1)) || n > kFermiMaxSamples) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_fermi_clear, dim3(1), dim3(1), 0, st, last);
+    hipLaunchKernelGGL(k_fermi_samples, dim3((unsigned)(n / 2 + kWG) / kWG), dim3(kWG), 0, st, beta, mu, rescale, n, g);
+    const int l = transform_log2_lanes(n / 2);
+    hipLaunchKernelGGL(k_fermi_cheb, dim3((unsigned)((((int64_t)n / 2) << l) + kWG - 1) / kWG), dim3(kWG), 0, st, g, n, l,
+                       tol, a, last);
+    return hipGetLastError();
+}
 
 hipError_t launch_gather_values(const int64_t *ell_csr, int64_t ell_size, const double *csr_val, double *ell_val,
                                 hipStream_t st) {

@@ -288,7 +288,7 @@ void Engine::release() {
                       &bwd_gacc, &bwd_gdiag, &bwd_coef, &st_uoff, &st_ucol, &st_lidx, &fu_n1, &fu_hoff,
                       &fu_hw,    &fu_hidx,  &bc,       &bd,        &ckpt_slot, &corr_scratch, &qe_coef,
                       &qe_acc,   &qe_part,  &qe_norm2, &ac_ja,     &ac_jb,     &ac_csr,       &ac_zero,
-                      &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &jc_part,  &ch_hist,   &hay_u,     &hay_y,        &hay_s,
+                      &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &jc_part,  &ch_hist, &ac_fermi,   &hay_u,     &hay_y,        &hay_s,
                       &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner, &ch_tiles, &ch_tile0,
                       &ch_cnt,   &ch_toff,  &ch_loff,  &ch_rowmap, &ch_lidx, &ch_tval, &ch_tons};
     for (DevBuf *b : bufs) b->release();

@@ -151,7 +151,7 @@ struct Engine {
     // optical conductivity: J_alpha / J_beta in ELL layout, their CSR upload,
     // a zero on-site vector, preparation vectors, the packed block, and the
     // correlation's pointer table and norm scratch
-    DevBuf ac_ja, ac_jb, ac_csr, ac_zero, ac_vec, ac_block, jc_tab, jc_norm, jc_part, ch_hist;
+    DevBuf ac_ja, ac_jb, ac_csr, ac_zero, ac_vec, ac_block, jc_tab, jc_norm, jc_part, ch_hist, ac_fermi;
     // Haydock recursion: two Lanczos vectors, the product vector, per-state scalars
     DevBuf hay_u, hay_y, hay_s;
     // kernel-polynomial moments: the L store, a block of R, Chebyshev vectors,

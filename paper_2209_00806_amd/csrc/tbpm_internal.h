@@ -202,6 +202,11 @@ hipError_t launch_pack(const double *blk, const double *fblk, int64_t n_rows, in
 hipError_t launch_jcorr(bool fp32, const TileDesc *tiles, int32_t n_tiles, int32_t log2sp, int32_t S, int32_t log2sb,
                         int64_t n_rows, const void *state, const uint32_t *slice_off, const int32_t *col, const double *jval,
                         double *partials, int32_t n_states, int64_t state_stride, int64_t part_stride, hipStream_t st);
+// coefficients a[0 .. n/2) of the Fermi function's Chebyshev series from n samples
+// (a power of two), last: the largest k with |a_k| >= tol; g: n/2 + 1 doubles
+constexpr int32_t kFermiMaxSamples = 65536;
+hipError_t launch_fermi_cheb(double beta, double mu, double rescale, int32_t n, double tol, double *g, double *a,
+                             int32_t *last, hipStream_t st);
 hipError_t launch_ac_cond(const double *corr, int32_t n_steps, int32_t n_states, double dt, double beta, double area,
                           int window, double *omegas, double *sigma, hipStream_t st);
 // im[k] = Kramers-Kronig transform of re[0 .. n) on a uniform grid from 0

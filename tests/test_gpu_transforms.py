@@ -101,3 +101,22 @@ def test_kubo_bastin_several_energies_per_workgroup(M, n_e):
     if M < 10:
         want = oracle.kubo_bastin(mu, f, lo, hi, n_e, beta, mus, area)
         assert np.max(np.abs(ref - want)) < 1e-12 * np.max(np.abs(want))
+
+
+@pytest.mark.parametrize("beta,mu", [(0.05, 0.0), (2.0, 0.3), (38.7, -1.1), (160.0, 0.2)])
+def test_fermi_series_on_the_device(beta, mu):
+    """The Fermi function's coefficients from direct sums (1024 samples up to 65536; the coldest case needs more
+    and takes the host's) through the optical correlation against the oracle's series: both are good to the
+    tolerance of the coefficients, 1e-12 each over some thousand terms of alternating sign: 1e-10."""
+    from paper_2209_00806_amd import inputs
+    rng = np.random.default_rng(12)
+    lat = inputs.graphene(7, 5, onsite=inputs.anderson(rng, 70, 1.0))
+    J = inputs.current_values(lat, 0)
+    f = 1.02 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    psi = inputs.random_phase_states(rng, lat.n_orb, 2)
+    ref, _, _ = oracle.ac_corr(lat.row_ptr, lat.col, lat.val, lat.onsite, J, J, psi, 5, np.pi / f, f, beta, mu,
+                               fermi_tol=1e-13)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    got = tbpm.ac_corr(H, J, J, _dev(psi), 5, np.pi / f, beta, mu, rescale=f, fermi_tol=1e-13).cpu().numpy()
+    assert np.max(np.abs(got - ref)) < 1e-10 * np.max(np.abs(ref))
+    H.close()
