@@ -17,8 +17,11 @@ namespace tbpm {
 
 // Rows of members that keep the caller's order and are too small to be
 // renumbered at upload, in a bisection order of their own: tiles take their rows
-// from it (the storage order, and with it every sum's order, stays).
-void Engine::chain_orders() {
+// from it (the storage order, and with it every sum's order, stays).  keep_local:
+// not for members whose tiles in the caller's order reference few rows besides their
+// own (the wide pass, one hop: on bilayers in the builder's order a bisection saves
+// 5 to 8% of the rows, and takes 12 ms for 14400 of them).
+void Engine::chain_orders(bool keep_local) {
     if (!ch_orders.empty()) return;
     const int32_t ni = n_inst();
     std::vector<std::vector<int32_t>> orders(ni);
@@ -38,6 +41,24 @@ void Engine::chain_orders() {
                     if (g != r) cc.push_back((int32_t)(g - r0));
                 }
                 rp[r - r0 + 1] = (int64_t)cc.size();
+            }
+            if (keep_local) {
+                constexpr int64_t kRows = 256, kSamples = 16;
+                std::vector<int64_t> tag(n, -1);
+                int64_t own = 0, all = 0;
+                for (int64_t k = 0, blocks = (n + kRows - 1) / kRows, m = std::min(blocks, kSamples); k < m; ++k) {
+                    const int64_t a = k * blocks / m * kRows, b = std::min(n, a + kRows);
+                    own += b - a;
+                    all += b - a;
+                    for (int64_t p = rp[a]; p < rp[b]; ++p) {
+                        const int64_t c = cc[p];
+                        if ((c < a || c >= b) && tag[c] != k) {
+                            tag[c] = k;
+                            ++all;
+                        }
+                    }
+                }
+                if (2 * all <= 5 * own) continue;
             }
             orders[i] = bisection_order(n, rp.data(), cc.data(), kChainMinTile, n < 4096 ? 1 : each);
         }
@@ -143,7 +164,7 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
     const int64_t units = mat.n_rows * cs.n_blk;
     int64_t T = kChainMinTile;
     while (T < kWideThreads && T * 2 * 256 <= units) T *= 2;
-    chain_orders();
+    chain_orders(true);
     for (; T >= kChainMinTile; T /= 2) {
         if (ch.T != T || ch.cap != 1 || ch.depth == 0) {
             tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);

@@ -124,7 +124,7 @@ struct Engine {
         std::vector<int32_t> depths;  // orders of each launch of one evaluation
         int32_t log2sb() const { return vs == 2 ? 1 : 0; }
     };
-    void chain_orders();
+    void chain_orders(bool keep_local = false);
     int32_t chain_width() const { return chain_table_width(mat.max_width); }
     // tables and launch sequence for n_orders orders on s_user states;
     // TBPM_E_ARG if the operator does not suit the kernel

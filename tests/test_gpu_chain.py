@@ -208,8 +208,8 @@ def test_chain_accumulates_several_steps_per_launch(n_steps, precision):
 @pytest.mark.parametrize("nx,ny,band", [(9, 7, 0), (23, 21, 0), (67, 61, 0), (0, 5000, 3), (0, 5000, 5), (0, 5000, 7),
                                         (0, 5000, 9)])
 def test_chain_wide_rows(nx, ny, band, precision):
-    """Two or three orders per launch of real operators with rows of 5 to 24 elements (bilayers, and bands of 6, 10,
-    14 and 18 elements for the other table widths) against one order per launch: bars as above."""
+    """The wide pass of real operators with rows of 5 to 24 elements (bilayers, and bands of 6, 10, 14 and 18
+    elements for the other table widths) against the general one: bars as above."""
     rng = np.random.default_rng(9)
     if nx:
         lat = inputs.twisted_bilayer(nx, ny)
@@ -229,6 +229,32 @@ def test_chain_wide_rows(nx, ny, band, precision):
             got, n_got = tbpm.propagate(H, psi, nt, z / f, f, precision=precision, return_norm=True)
             assert _rel(got.cpu().numpy(), ref.cpu().numpy()) < 1e-12, (S, z, nt)
             assert _rel(n_got.cpu().numpy(), n_ref.cpu().numpy()) < 1e-12, (S, z, nt)
+    H.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,far", [(9, 0), (17, 1), (31, 0)])
+def test_wide_rows_in_any_order(nx, far, precision):
+    """The wide pass takes its tiles from the caller's order where that is local and from an order of its own where
+    it is not: bilayers with their rows shuffled, all of them or (far) every 16th, against the general pass."""
+    rng = np.random.default_rng(12)
+    lat = inputs.twisted_bilayer(nx, nx)
+    n = lat.n_orb
+    perm = np.arange(n)
+    moved = np.arange(0, n, 16) if far else np.arange(n)
+    perm[moved] = rng.permutation(moved)
+    i = np.repeat(np.arange(n), np.diff(lat.row_ptr))
+    up = i < lat.col
+    lat = inputs.from_bonds(n, perm[i[up]], perm[lat.col[up]], lat.val[up], inputs.anderson(rng, n, 1.0))
+    f = 1.05 * oracle.gershgorin(lat.row_ptr, lat.val, lat.onsite)
+    H = tbpm.Hamiltonian.from_lattice(lat)
+    for S, nt in ((8, 9), (3, 4)):
+        psi = torch.from_numpy(inputs.random_phase_states(rng, n, S)).cuda()
+        out = []
+        for shape in ({}, dict(wg_chunks=2, xcd_remap=3, nontemporal=0, unroll=1, staged=2, vec=4, fused=0)):
+            H.set_launch_config(**shape)
+            out.append(tbpm.propagate(H, psi, nt, math.pi / f, f, precision=precision))
+        assert _rel(out[1].cpu().numpy(), out[0].cpu().numpy()) < 1e-12
     H.close()
 
 
