@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <thread>
 
 #include "tbpm_engine.h"
@@ -25,13 +26,27 @@ void Engine::chain_orders(bool keep_local) {
     if (!ch_orders.empty()) return;
     const int32_t ni = n_inst();
     std::vector<std::vector<int32_t>> orders(ni);
-    const int threads = (int)std::min<int64_t>(ni, host_threads((int64_t)h_col.size()));
-    // 14400 rows of 19 elements: 35 ms with one thread, 12 with eight
-    const int32_t each = std::max(1, std::min(8, (int)std::thread::hardware_concurrency()) / std::max(1, threads));
-    run_chunks(ni, std::max(1, threads), [&](int, int64_t lo, int64_t hi) {
-        for (int64_t i = lo; i < hi; ++i) {
-            const int64_t r0 = inst_row0[i], n = inst_row0[i + 1] - r0;
-            if (!member_perm[i].empty() || n <= kChainMinTile || n >= kReorderMinRows) continue;
+    // the largest members first, up to 16 threads in all and 8 within a member
+    // (14400 rows of 19 elements: 35 ms with one, 12 with eight; a batch of 12
+    // members of 5000 to 20000 rows: 13.5 ms one member after another, 3.1 so)
+    auto size = [&](int32_t i) { return inst_row0[i + 1] - inst_row0[i]; };
+    std::vector<int32_t> todo;
+    int64_t rows = 0;
+    for (int32_t i = 0; i < ni; ++i) {
+        const int64_t n = size(i);
+        if (!member_perm[i].empty() || n <= kChainMinTile || n >= kReorderMinRows) continue;
+        todo.push_back(i);
+        rows += n;
+    }
+    std::stable_sort(todo.begin(), todo.end(), [&](int32_t i, int32_t j) { return size(i) > size(j); });
+    const int64_t avail = std::max(1, std::min(16, (int)std::thread::hardware_concurrency()));
+    const int threads = rows < 4096 ? 1 : (int)std::min<int64_t>(avail, (int64_t)todo.size());
+    std::atomic<size_t> at{0};
+    run_chunks(threads, threads, [&](int, int64_t, int64_t) {
+        for (size_t q; (q = at.fetch_add(1)) < todo.size();) {
+            const int32_t i = todo[q];
+            const int64_t r0 = inst_row0[i], n = size(i);
+            const int32_t each = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, avail * n / rows));
             std::vector<int64_t> rp(n + 1, 0);
             std::vector<int32_t> cc;
             for (int64_t r = r0; r < r0 + n; ++r) {
