@@ -425,6 +425,7 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_hamiltonian *H, const double *psi0, int3
     if (e != hipSuccess) return hip_fail(e, "clear accumulators");
     // coef[k][j] = w_k e^{i E_j t_k} for t_k = +k dt, then -k dt (k = 0 counted once)
     std::vector<double> coef(2 * (size_t)n_steps * n_energies);
+    int32_t layout = Engine::kLayoutFree;  // both runs add to qe_acc: the second keeps the first one's
     for (int pass = 0; pass < 2; ++pass) {
         const double sgn = pass == 0 ? 1.0 : -1.0;
         for (int32_t k = 0; k < n_steps; ++k) {
@@ -453,6 +454,7 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_hamiltonian *H, const double *psi0, int3
         a.qe_coef = coef.data();
         a.n_qe = n_energies;
         a.qe_acc = (double *)eng.qe_acc.ptr;
+        a.layout = &layout;
         a.flags = flags & ~(uint32_t)TBPM_FLAG_ASYNC;  // the coefficient table is rewritten for the second run
         a.stream = hs;
         try {

@@ -607,15 +607,27 @@ tbpm_status Engine::run(const RunArgs &a) {
     tbpm_status st = TBPM_OK;
     // Several orders per launch for operators that suit it: where the fused shape
     // is configured, and where nobody chose a configuration and the propagation
-    // is long enough to repay the tile tables.
+    // is long enough to repay the tile tables.  A layout that was chosen before is
+    // kept without a look at the free memory, which may differ by now.
+    const int32_t lay = a.layout ? *a.layout : kLayoutFree;
     ChainShape cs;
-    bool chain = (fused || (!cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps)) &&
-                 chain_prepare(a.s_user, fp32, n_passes, cs) == TBPM_OK;
-    if (chain && !fused && !chain_fits(cs, fp32, esize * (size_t)mat.n_rows * s_pad)) chain = false;
-    // operators of wider rows: a pass that keeps the rows' entries in registers, in
-    // place of the staged pass, and where nobody chose a configuration
-    bool wide = !chain && (staged || (!fused && !cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps)) &&
-                wide_prepare(a.s_user, fp32, cs) == TBPM_OK && chain_room(fp32, 0);
+    bool chain, wide;
+    if (lay == kLayoutFree) {
+        const bool automatic = !cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps;
+        chain = (fused || automatic) && chain_prepare(a.s_user, fp32, n_passes, cs) == TBPM_OK;
+        if (chain && !fused && !chain_fits(cs, fp32, esize * (size_t)mat.n_rows * s_pad)) chain = false;
+        // operators of wider rows: a pass that keeps the rows' entries in registers, in
+        // place of the staged pass, and where nobody chose a configuration
+        wide = !chain && (staged || (!fused && automatic)) && wide_prepare(a.s_user, fp32, cs) == TBPM_OK &&
+               chain_room(fp32, 0);
+    } else {
+        chain = lay == kLayoutChain;
+        wide = lay == kLayoutWide;
+        if (chain) st = chain_prepare(a.s_user, fp32, n_passes, cs);
+        if (wide) st = wide_prepare(a.s_user, fp32, cs);
+        if (st != TBPM_OK) return st;
+    }
+    if (a.layout) *a.layout = chain ? kLayoutChain : (wide ? kLayoutWide : kLayoutRows);
     const bool blocked = chain || wide;  // states in blocks, tiles and their tables as of `ch`
     if (blocked) staged = false;
     fused = fused && !chain && mmax >= 4;  // two orders per launch need four terms

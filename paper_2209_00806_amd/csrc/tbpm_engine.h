@@ -190,6 +190,8 @@ struct Engine {
 
     // the propagation driver (shared by single and batched entry points)
     struct RunArgs;
+    // how a run stores its states: by row, or in the blocks of the chain or of the wide pass
+    enum : int32_t { kLayoutFree = 0, kLayoutRows, kLayoutChain, kLayoutWide };
     struct RunArgs {
         const double *const *psi0;  // n_inst device pointers
         int32_t s_user;
@@ -213,6 +215,10 @@ struct Engine {
         const double *qe_coef;
         int32_t n_qe;
         double *qe_acc;
+        // calls of several runs that share state-sized arrays: kLayoutFree, and run
+        // stores the layout it takes; or that layout, which run then keeps.  Null:
+        // run chooses
+        int32_t *layout;
         // optical-conductivity correlation: after the initial state and every
         // step, jc_corr[k][s] = <block[:, S+s]| J |block[:, s]> for s < jc_states
         // (the block holds psi1 in columns 0..S-1 and psi2 in S..2S-1; J as

@@ -1,0 +1,47 @@
+"""CPU checks of the launch decisions of the library's host side:
+tests/host_engine_check.cpp, compiled with AddressSanitizer and UBSan against
+every host source of the library and a device made of host memory
+(tests/fake_device.h), whose free memory a check may change at any time."""
+import concurrent.futures as cf
+import glob
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if not cxx or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("g++ or the HIP headers are not available")
+    tmp = str(tmp_path_factory.mktemp("host_engine"))
+    srcs = sorted(glob.glob(os.path.join(ROOT, "paper_2209_00806_amd", "csrc", "*.cpp")))
+    srcs.append(os.path.join(ROOT, "tests", "host_engine_check.cpp"))
+    flags = ["-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+             "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"]
+    objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in srcs]
+
+    def compile_one(k):
+        subprocess.run([cxx, *flags, "-c", srcs[k], "-o", objs[k]], check=True, capture_output=True, timeout=600)
+
+    with cf.ThreadPoolExecutor(max_workers=6) as ex:
+        list(ex.map(compile_one, range(len(srcs))))
+    out = os.path.join(tmp, "host_engine_check")
+    subprocess.run([cxx, *flags, *objs, "-pthread", "-o", out], check=True, capture_output=True, timeout=600)
+    return out
+
+
+def _run(exe, name):
+    r = subprocess.run([exe, name], capture_output=True, text=True, timeout=300, env=ENV)
+    assert r.returncode == 0 and r.stdout.endswith("OK\n"), r.stdout + r.stderr
+
+
+def test_quasi_eigenstate_runs_share_a_layout(checker):
+    """Both runs of a quasi-eigenstate call add to the same accumulators: their states lie in one layout, also
+    when the memory that is free changes between the two decisions."""
+    _run(checker, "quasi_layout")
