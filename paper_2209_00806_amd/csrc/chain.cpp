@@ -98,6 +98,7 @@ tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows,
     if (t.depth < 1) return fail(TBPM_E_ARG, "no tile fits");
     const size_t nt = t.tiles.size();
     ch = ChainState{};
+    ++ch_stamp;
     TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
     hipError_t e = hipSuccess;
     auto up = [&](DevBuf &d, const void *src, size_t bytes) {
@@ -217,6 +218,7 @@ bool Engine::chain_fits(const ChainShape &cs, bool fp32, size_t vec) {
 tbpm_status Engine::chain_values(bool fp32, hipStream_t st) {
     const size_t rb = fp32 ? 4 : 8;
     const int32_t W = chain_width();
+    ++ch_stamp;
     TRY_HIP(ch_tval.ensure(rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * W), "alloc chain values");
     TRY_HIP(ch_tons.ensure(rb * (size_t)ch.n_local), "alloc chain values");
     ChainTileTab t{(const int32_t *)ch_cnt.ptr, (const int32_t *)ch_toff.ptr, (const int32_t *)ch_loff.ptr,
@@ -248,6 +250,7 @@ ChainParams Engine::chain_params(const ChainShape &cs) const {
 }
 
 tbpm_status Engine::wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const {
+    if (ch.depth != 1) return fail(TBPM_E_ARG, "the tile tables are not the wide pass's");
     p.lds_rows = ch.max_stage[1];
     hipError_t e = launch_pass_wide(fp32, chain_width(), cs.vs, ch.max_stage[0], p, st);
     if (e != hipSuccess) return hip_fail(e, "launch wide pass");
@@ -255,6 +258,7 @@ tbpm_status Engine::wide_launch(bool fp32, const ChainShape &cs, ChainParams &p,
 }
 
 tbpm_status Engine::chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const {
+    if (p.depth < 1 || p.depth > ch.depth) return fail(TBPM_E_ARG, "the tile tables serve fewer orders");
     hipError_t e = launch_chain(fp32, mat.is_complex, chain_width(), cs.vs, ch.max_stage[p.depth - 1],
                                 ch.max_stage[p.depth], p, st);
     if (e != hipSuccess) return hip_fail(e, "launch chain");

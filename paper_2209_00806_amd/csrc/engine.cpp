@@ -1194,6 +1194,9 @@ tbpm_status Engine::run(const RunArgs &a) {
     last_fp32 = fp32 ? 1 : 0;
     last_staged = wide ? 4 : chain ? 3 : (fused ? 2 : (staged ? 1 : 0));
     last_chain = cs;
+    last_s_user = a.s_user;
+    last_orders = n_passes;
+    last_stamp = ch_stamp;
     last_vs = vs;
     last_log2ub = log2ub;
     if (a.flags & TBPM_FLAG_ASYNC) return TBPM_OK;
@@ -1451,6 +1454,17 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         ((chain || wide) && ch.depth == 0))
         return fail(TBPM_E_ARG, "tbpm_bench_pass needs a prior tbpm_propagate with the same n_states and precision");
     cfg = cfgs[fp32 ? 1 : 0];
+    if ((chain || wide) && last_stamp != ch_stamp) {
+        // other calls have built tables or taken matrix entries since: the run's again
+        ChainShape cs;
+        tbpm_status s = chain ? chain_prepare(last_s_user, fp32, last_orders, cs) : wide_prepare(last_s_user, fp32, cs);
+        if (s != TBPM_OK) return s;
+        if (!chain_room(fp32, 0)) return fail(TBPM_E_OOM, "no memory for the chain tables");
+        s = chain_values(fp32, stream);
+        if (s != TBPM_OK) return s;
+        last_chain = cs;
+        last_stamp = ch_stamp;
+    }
     if (chain) {
         // an interior launch: b_{j+1} in B, b_{j+2} in A, outputs to C and D
         TRY_HIP(ba.ensure(v.bytes), "alloc A");
@@ -1477,6 +1491,8 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
     }
     if (wide) {
         // as below: out over b_{j+2}, the order just written is gathered next
+        TRY_HIP(ba.ensure(v.bytes), "alloc A");
+        TRY_HIP(bb.ensure(v.bytes), "alloc B");
         ChainParams cp = chain_params(last_chain);
         cp.xcd_remap = cfg.xcd_remap;
         cp.v = v.ptr;

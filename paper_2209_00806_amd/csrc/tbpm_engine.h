@@ -261,6 +261,10 @@ struct Engine {
     int32_t last_s_pad = 0, last_fp32 = -1, last_staged = 0, last_vs = 1, last_log2ub = 0;
     int32_t last_log2sb = 0;  // state blocks of the last run's vectors and quasi-eigenstate accumulators
     ChainShape last_chain;
+    int32_t last_s_user = 0, last_orders = 0;
+    // changes whenever the tile tables or their matrix entries do; and its value
+    // after the last run
+    int64_t ch_stamp = 0, last_stamp = -1;
 
     tbpm_status build_tiles(int32_t s_pad, int32_t chunks, int32_t vs);
     // staged tiles for s_pad states of unit_bytes per VS states (log2u units per row);

@@ -23,7 +23,7 @@ std::function<void(const tbpm::InitParams &)> on_init;
 std::function<void(int64_t n_el, int64_t n_used)> on_qe_accum;
 std::function<void(int log2s, int log2sb)> on_qe_finalize;
 std::function<void(const tbpm::ChainParams &, bool fp32)> on_chain, on_wide;
-std::function<void(int n_tiles)> on_values;
+std::function<void(bool fp32, int n_tiles)> on_values;
 std::function<void(bool fp32)> on_pass;
 // rows that a launch reads or writes of a buffer lie inside one block of memory
 inline bool holds(const void *p, size_t bytes) {
@@ -169,9 +169,9 @@ hipError_t launch_pass_wide(bool fp32, int, int, int, const ChainParams &p, hipS
     if (fake::on_wide) fake::on_wide(p, fp32);
     return hipSuccess;
 }
-hipError_t launch_chain_values(bool, bool, const ChainTileTab &, int32_t n_tiles, const DevMatrix &, void *, void *,
-                               hipStream_t) {
-    if (fake::on_values) fake::on_values(n_tiles);
+hipError_t launch_chain_values(bool fp32, bool, const ChainTileTab &, int32_t n_tiles, const DevMatrix &, void *,
+                               void *, hipStream_t) {
+    if (fake::on_values) fake::on_values(fp32, n_tiles);
     return hipSuccess;
 }
 hipError_t launch_chain_reduce(int, int, int64_t, const ReduceParams &, int32_t *, bool, hipStream_t) OK_

@@ -80,8 +80,63 @@ static void quasi_layout() {
             }
 }
 
+static void haydock(tbpm_hamiltonian *H, int S, int n_iter) {
+    Dev psi(2 * H->csr.n * S), a((size_t)n_iter * S), b((size_t)n_iter * S);
+    CHECK(tbpm_haydock(H, psi.p, S, n_iter, a.p, b.p, 0, nullptr) == TBPM_OK);
+}
+
+// Timing launches after a propagation, with calls in between that build tables for
+// other state counts or take the matrix entries in another precision: the launches
+// fit the tables that they are given, and these hold the run's precision.
+static void bench_pass() {
+    for (tbpm_precision prec : {TBPM_FP64, TBPM_FP32_MIXED})
+        for (std::vector<int64_t> hops : {std::vector<int64_t>{1}, std::vector<int64_t>{1, 2, 50}}) {
+            const bool fp32 = prec == TBPM_FP32_MIXED, narrow = hops.size() == 1;
+            tbpm_hamiltonian *H = ring(8192, hops);
+            const int S = narrow ? 1 : 4;
+            int values_fp32 = -1, values_tiles = 0, launches = 0, depth = 0;
+            fake::on_values = [&](bool p32, int n_tiles) {
+                values_fp32 = p32;
+                values_tiles = n_tiles;
+            };
+            auto look = [&](const ChainParams &p, bool p32) {
+                ++launches;
+                CHECK(p32 == (bool)values_fp32 && p.n_tiles == values_tiles);
+                CHECK(p.depth <= p.table_depth || !narrow);
+                CHECK(fake::holds(p.x, (fp32 ? 8 : 16) * (size_t)8192 * S));
+                depth = p.depth;
+            };
+            propagate(H, S, 70, 3.14159, prec);
+            fake::on_chain = fake::on_wide = look;
+            CHECK(tbpm_bench_pass(H, S, prec, 3, nullptr) == TBPM_OK);
+            CHECK(launches == 3);
+            const int own = depth;
+            for (int other = 0; other < 2; ++other) {
+                fake::on_chain = fake::on_wide = nullptr;
+                if (other == 0)
+                    haydock(H, 8, 70);  // tables of larger tiles, entries in FP64
+                else {
+                    // a propagation in the other precision, then the first one again: what
+                    // bench_pass is asked for is what came last
+                    propagate(H, S, 70, 3.14159, fp32 ? TBPM_FP64 : TBPM_FP32_MIXED);
+                    CHECK(tbpm_bench_pass(H, S, prec, 1, nullptr) == TBPM_E_ARG);
+                    propagate(H, S, 70, 3.14159, prec);
+                    haydock(H, 2, 70);
+                }
+                fake::on_chain = fake::on_wide = look;
+                launches = 0;
+                CHECK(tbpm_bench_pass(H, S, prec, 2, nullptr) == TBPM_OK);
+                CHECK(launches == 2 && depth == own);
+                CHECK(tbpm_bench_pass(H, S, prec, 2, nullptr) == TBPM_OK);
+            }
+            fake::on_chain = fake::on_wide = nullptr;
+            fake::on_values = nullptr;
+            tbpm_hamiltonian_destroy(H);
+        }
+}
+
 int main(int argc, char **argv) {
-    const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}};
+    const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -45,3 +45,9 @@ def test_quasi_eigenstate_runs_share_a_layout(checker):
     """Both runs of a quasi-eigenstate call add to the same accumulators: their states lie in one layout, also
     when the memory that is free changes between the two decisions."""
     _run(checker, "quasi_layout")
+
+
+def test_bench_pass_after_other_calls(checker):
+    """Timing launches follow the last propagation's shape and precision, whatever other calls on the handle
+    have made of its tile tables since."""
+    _run(checker, "bench_pass")
