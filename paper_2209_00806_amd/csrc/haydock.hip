@@ -293,10 +293,11 @@ __global__ __launch_bounds__(kHayThreads) void k_hay_step(const ChainParams p, c
             p.partials[((int64_t)blk * 3 + tid) * p.n_tiles + tile] = a;
         }
     };
-    auto mul = [&](const d2 *buf, const d2 &self) {
+    // inside: the neighbours of lanes without an own row may be out of buf's reach
+    auto mul = [&](const d2 *buf, const d2 &self, bool inside) {
         d2 xc[W];
 #pragma unroll
-        for (int k = 0; k < W; ++k) xc[k] = buf[na[k]];
+        for (int k = 0; k < W; ++k) xc[k] = buf[hay_place(own || !inside, na[k], (uint32_t)tid)];
         d2 acc;
         acc.x = on * self.x;
         acc.y = on * self.y;
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(kHayThreads) void k_hay_step(const ChainParams p, c
         d2 un = u;
         const d2 *src = cur;
         if (!p.first) {
-            const d2 acc = mul(cur, u);
+            const d2 acc = mul(cur, u, false);
             un.x = fma(s1, acc.x, fma(-s3, um.x, -s2 * u.x));
             un.y = fma(s1, acc.y, fma(-s3, um.y, -s2 * u.y));
             if (eval) ys[tid] = un;
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(kHayThreads) void k_hay_step(const ChainParams p, c
             __syncthreads();
         }
         if (own_wave) {
-            const d2 z = mul(src, un);
+            const d2 z = mul(src, un, true);
             double n2 = 0.0, hu = 0.0, cr = 0.0;
             if (own) {
                 n2 = fma(un.x, un.x, un.y * un.y);

@@ -153,6 +153,11 @@ constexpr int chain_table_width(int max_width) {
     return max_width <= 3 ? 3 : (max_width > 20 && max_width <= 22 ? 22 : (max_width + 3) / 4 * 4);
 }
 
+// The Haydock step's second product runs on whole waves, but the LDS it reads holds
+// u_{i+1} of the evaluated rows only (one per thread), and the neighbours of a row
+// that is not the tile's own may lie beyond them: such a lane reads its own place.
+constexpr uint32_t hay_place(bool own, uint32_t neighbour, uint32_t tid) { return own ? neighbour : tid; }
+
 struct ChainParams {
     const TileDesc *tiles;
     int32_t n_tiles;

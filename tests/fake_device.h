@@ -24,6 +24,7 @@ std::function<void(int64_t n_el, int64_t n_used)> on_qe_accum;
 std::function<void(int log2s, int log2sb)> on_qe_finalize;
 std::function<void(const tbpm::ChainParams &, bool fp32)> on_chain, on_wide;
 std::function<void(bool fp32, int n_tiles)> on_values;
+std::function<void(int width, int max_eval, int max_stage, const tbpm::ChainParams &)> on_hay;
 std::function<void(bool fp32)> on_pass;
 // rows that a launch reads or writes of a buffer lie inside one block of memory
 inline bool holds(const void *p, size_t bytes) {
@@ -209,7 +210,8 @@ hipError_t launch_hay_axpy(const TileDesc *, int32_t, int32_t, int32_t, int32_t,
 int32_t hay_fold_count(int32_t) { return 0; }
 hipError_t launch_hay_reduce(const double *, int32_t, int32_t, int32_t, int32_t, double, double *, int32_t *, int32_t,
                              double *, double *, double *, hipStream_t) OK_
-hipError_t launch_hay_step(bool, int, int, int, ChainParams p, const double *, hipStream_t) {
+hipError_t launch_hay_step(bool, int width, int max_eval, int max_stage, ChainParams p, const double *, hipStream_t) {
+    if (fake::on_hay) fake::on_hay(width, max_eval, max_stage, p);
     if (fake::on_chain) fake::on_chain(p, false);
     return hipSuccess;
 }

@@ -135,8 +135,44 @@ static void bench_pass() {
         }
 }
 
+// Every LDS place that a wave of the Haydock step reads lies in the vector that is
+// there: u_i of the staged rows in the first product, and u_{i+1} of the evaluated
+// rows, one per thread, in the second.
+static void haydock_places() {
+    int64_t lanes = 0, moved = 0;
+    fake::on_hay = [&](int width, int max_eval, int max_stage, const ChainParams &p) {
+        const uint32_t nt = (uint32_t)(max_eval + 63) / 64 * 64;
+        CHECK(nt <= 1024 && max_stage >= max_eval);
+        for (int t = 0; t < p.n_tiles; ++t) {
+            const int32_t *c = p.cnt + (int64_t)t * (p.table_depth + 1);
+            const int n_own = p.tiles[t].rows, n_eval = c[1];
+            CHECK(n_eval <= max_eval && c[2] <= max_stage);
+            for (uint32_t tid = 0; tid < nt && (int)(tid & ~63u) < n_own; ++tid) {
+                const int lr = std::min((int)tid, n_eval - 1);
+                for (int k = 0; k < width; ++k) {
+                    const uint32_t na = p.lidx[((int64_t)p.loff[t] + lr) * 4 + k];
+                    const uint32_t at = hay_place((int)tid < n_own, na, tid);
+                    CHECK((int)na < c[2] && at < nt && ((int)tid >= n_own || ((int)na < n_eval && at == na)));
+                    ++lanes;
+                    moved += na >= nt;
+                }
+            }
+        }
+    };
+    for (int64_t n : {100, 210, 777, 1500, 8192})
+        for (int S : {1, 8}) {
+            tbpm_hamiltonian *H = ring(n, n == 1500 ? std::vector<int64_t>{37, 53} : std::vector<int64_t>{1, 30});
+            haydock(H, S, 70);
+            tbpm_hamiltonian_destroy(H);
+        }
+    fake::on_hay = nullptr;
+    CHECK(lanes > 0 && moved > 0);
+    std::printf("%lld reads, %lld of them past the evaluated rows before\n", (long long)lanes, (long long)moved);
+}
+
 int main(int argc, char **argv) {
-    const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass}};
+    const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
+                                                           {"haydock_places", haydock_places}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -51,3 +51,9 @@ def test_bench_pass_after_other_calls(checker):
     """Timing launches follow the last propagation's shape and precision, whatever other calls on the handle
     have made of its tile tables since."""
     _run(checker, "bench_pass")
+
+
+def test_haydock_step_reads_inside_its_lds(checker):
+    """The second product of the Haydock step runs on whole waves; the lanes that have no own row stay inside the
+    vector of the evaluated rows."""
+    _run(checker, "haydock_places")
