@@ -91,6 +91,13 @@ static void chain_split(int32_t n_orders, int32_t D, std::vector<int32_t> &depth
     }
 }
 
+Engine::ChainReach &Engine::chain_reach(int64_t T) {
+    for (ChainReach &r : ch_reach)
+        if (r.T == T) return r;
+    ch_reach.push_back(ChainReach{T});
+    return ch_reach.back();
+}
+
 // tile tables of T rows for D orders, on the device
 tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows) {
     ChainTables t;
@@ -148,9 +155,16 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
     for (; T >= kChainMinTile; T /= 2) {
         const int32_t cap = std::min<int32_t>(n_orders, T >= 512 ? 6 : (T >= 128 ? 9 : 17));
         if (ch.T != T || ch.cap != cap || ch.depth == 0) {
-            const int32_t D = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, max_rows);
-            if (D < std::min(n_orders, 3)) continue;
+            ChainReach &r = chain_reach(T);
+            // a depth short of what was asked for is the rows' own, whatever is asked for
+            if (r.tried < cap && r.reach == r.tried) {
+                r.reach = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, max_rows);
+                r.tried = cap;
+            }
+            const int32_t D = std::min(cap, r.reach);
+            if (D < std::min(n_orders, 3) || D >= r.refused) continue;
             tbpm_status st = chain_build(T, cap, D, rows, max_rows);
+            if (st == TBPM_E_ARG) r.refused = D;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }
@@ -183,7 +197,10 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
     chain_orders(true);
     for (; T >= kChainMinTile; T /= 2) {
         if (ch.T != T || ch.cap != 1 || ch.depth == 0) {
+            ChainReach &r = chain_reach(T);
+            if (r.refused <= 1) continue;
             tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);
+            if (st == TBPM_E_ARG) r.refused = 1;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }

@@ -294,6 +294,7 @@ void Engine::release() {
     for (DevBuf *b : bufs) b->release();
     ch = ChainState{};
     ch_orders.clear();
+    ch_reach.clear();
     partner_ready = false;
     staging.release();
     if (staging_done) (void)hipEventDestroy(staging_done);

@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <complex>
 #include <cstdint>
 #include <string>
@@ -118,6 +119,14 @@ struct Engine {
         bool contiguous = true;
         std::vector<int32_t> max_stage;  // [depth + 1]
     } ch;
+    // what a sample of the tiles of T rows reached: reach orders of at most tried,
+    // and the fewest orders for which no tiling was found
+    struct ChainReach {
+        int64_t T;
+        int32_t tried = 0, reach = 0, refused = INT32_MAX;
+    };
+    std::vector<ChainReach> ch_reach;
+    ChainReach &chain_reach(int64_t T);
     std::vector<std::vector<int32_t>> ch_orders;  // per member: row order its tiles follow (empty: as stored)
     struct ChainShape {
         int32_t vs = 1, n_blk = 1, n_grp = 1;

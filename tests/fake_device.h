@@ -18,7 +18,8 @@ namespace fake {
 size_t total = (size_t)1 << 40, used = 0;
 size_t hidden = 0;  // bytes that hipMemGetInfo holds back (taken by others)
 std::map<void *, size_t> blocks;
-int syncs = 0;
+int uploads = 0;              // synchronous copies to the device
+bool device_alloc = false;    // inside an allocation of device memory
 std::function<void(const tbpm::InitParams &)> on_init;
 std::function<void(int64_t n_el, int64_t n_used)> on_qe_accum;
 std::function<void(int log2s, int log2sb)> on_qe_finalize;
@@ -41,7 +42,9 @@ hipError_t hipMalloc(void **p, size_t n) {
         *p = nullptr;
         return hipErrorOutOfMemory;
     }
+    fake::device_alloc = true;
     *p = std::calloc(1, n ? n : 1);
+    fake::device_alloc = false;
     if (!*p) return hipErrorOutOfMemory;
     fake::blocks[*p] = n;
     fake::used += n;
@@ -69,7 +72,8 @@ hipError_t hipMemGetInfo(size_t *f, size_t *t) {
     *t = fake::total;
     return hipSuccess;
 }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind kind) {
+    fake::uploads += kind == hipMemcpyHostToDevice;
     std::memcpy(d, s, n);
     return hipSuccess;
 }
@@ -77,10 +81,7 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
     std::memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipDeviceSynchronize() {
-    ++fake::syncs;
-    return hipSuccess;
-}
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDevice(int *d) {

@@ -4,6 +4,15 @@
 
 #include "fake_device.h"
 
+// the sanitizer's hook on every host allocation
+extern "C" int __sanitizer_install_malloc_and_free_hooks(void (*)(const volatile void *, size_t),
+                                                         void (*)(const volatile void *));
+// host allocations of at least big_size bytes that are not the device's memory
+static size_t big_size = SIZE_MAX;
+static int big_count = 0;
+static void note_alloc(const volatile void *, size_t n) { big_count += n >= big_size && !fake::device_alloc; }
+static void note_free(const volatile void *) {}
+
 using namespace tbpm;
 
 #define CHECK(c)                                                \
@@ -170,9 +179,61 @@ static void haydock_places() {
     std::printf("%lld reads, %lld of them past the evaluated rows before\n", (long long)lanes, (long long)moved);
 }
 
+// ring (hops {1}, or none) with `matchings` random pairings of its rows on top
+static tbpm_hamiltonian *irregular(int64_t n, bool ring, int matchings) {
+    std::vector<std::vector<int32_t>> adj(n);
+    uint64_t seed = 12345;
+    auto rnd = [&](int64_t m) {
+        seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+        return (int64_t)((seed >> 33) % (uint64_t)m);
+    };
+    auto bond = [&](int64_t a, int64_t b) {
+        adj[a].push_back((int32_t)b);
+        adj[b].push_back((int32_t)a);
+    };
+    for (int64_t r = 0; ring && r < n; ++r) bond(r, (r + 1) % n);
+    std::vector<int32_t> p(n);
+    for (int m = 0; m < matchings; ++m) {
+        for (int64_t r = 0; r < n; ++r) p[r] = (int32_t)r;
+        for (int64_t r = n - 1; r > 0; --r) std::swap(p[r], p[rnd(r + 1)]);
+        for (int64_t r = 0; r + 1 < n; r += 2) bond(p[r], p[r + 1]);
+    }
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> col;
+    for (int64_t r = 0; r < n; ++r) {
+        col.insert(col.end(), adj[r].begin(), adj[r].end());
+        rp.push_back((int64_t)col.size());
+    }
+    std::vector<double> val(2 * col.size(), 0.0), on(n, 0.1);
+    for (size_t q = 0; q < col.size(); ++q) val[2 * q] = -1.0;
+    tbpm_hamiltonian *H = nullptr;
+    CHECK(tbpm_hamiltonian_create(n, rp.data(), col.data(), val.data(), on.data(), 0, &H) == TBPM_OK);
+    return H;
+}
+
+// Operators whose tiles fit no size, or not the first one tried: a second call does
+// not look at the rows again (an array of all rows would be allocated).
+static void sizes_refused() {
+    const int64_t n = 12000;
+    CHECK(__sanitizer_install_malloc_and_free_hooks(note_alloc, note_free));
+    for (int kind = 0; kind < 3; ++kind) {
+        tbpm_hamiltonian *H = kind == 0 ? irregular(n, true, 1) : (kind == 1 ? irregular(n, true, 2) : irregular(n, false, 24));
+        for (int S : {1, 8}) {
+            propagate(H, S, 70);
+            big_size = 4 * (size_t)n;
+            big_count = 0;
+            propagate(H, S, 70);
+            big_size = SIZE_MAX;
+            CHECK(big_count == 0);
+        }
+        tbpm_hamiltonian_destroy(H);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
-                                                           {"haydock_places", haydock_places}};
+                                                           {"haydock_places", haydock_places},
+                                                           {"sizes_refused", sizes_refused}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -57,3 +57,8 @@ def test_haydock_step_reads_inside_its_lds(checker):
     """The second product of the Haydock step runs on whole waves; the lanes that have no own row stay inside the
     vector of the evaluated rows."""
     _run(checker, "haydock_places")
+
+
+def test_refused_tile_sizes_are_remembered(checker):
+    """A tile size that an operator's rows do not fit is not tried again by every call."""
+    _run(checker, "sizes_refused")
