@@ -387,7 +387,7 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
             cp.coef = coefs + p0;
             cp.out_all = b_slot(t, j);
             cp.out_last = p0 + d == n_passes ? psi_slot(t + 1) : b_slot(t, j - d + 1);
-            e = launch_chain(false, cplx, eng.chain_width(), 1, eng.ch.max_stage[d - 1], eng.ch.max_stage[d], cp, st);
+            e = launch_chain(false, cplx, eng.chain_width(), 1, eng.ch().max_stage[d - 1], eng.ch().max_stage[d], cp, st);
             p0 += d;
         }
         return e;
@@ -428,8 +428,8 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
             ad.cc = conj_c + 2 * j0;
             ad.first = j0 == 0;
             ad.final_ = last;
-            e = launch_chain_cheb(kChainAdjoint, cplx, eng.chain_width(), (int)eng.ch.T, eng.ch.max_stage[d - 1],
-                                  eng.ch.max_stage[d], cp, ad, st);
+            e = launch_chain_cheb(kChainAdjoint, cplx, eng.chain_width(), (int)eng.ch().T, eng.ch().max_stage[d - 1],
+                                  eng.ch().max_stage[d], cp, ad, st);
             // the old x and alpha_{j-1} (the fourth buffer after the first launch)
             // take the next outputs
             double *np = fr[0], *nx = fr[1];

@@ -91,6 +91,11 @@ static void chain_split(int32_t n_orders, int32_t D, std::vector<int32_t> &depth
     }
 }
 
+void Engine::ChainTab::release() {
+    for (DevBuf *b : {&tiles, &tile0, &cnt, &toff, &loff, &rowmap, &lidx}) b->release();
+    *this = ChainTab{};
+}
+
 Engine::ChainReach &Engine::chain_reach(int64_t T) {
     for (ChainReach &r : ch_reach)
         if (r.T == T) return r;
@@ -98,39 +103,57 @@ Engine::ChainReach &Engine::chain_reach(int64_t T) {
     return ch_reach.back();
 }
 
-// tile tables of T rows for D orders, on the device
+// the tables of (T, cap), if the handle has them
+bool Engine::chain_select(int64_t T, int32_t cap) {
+    for (int32_t i = 0; i < kChainTabs; ++i)
+        if (ch_tab[i].depth > 0 && ch_tab[i].T == T && ch_tab[i].cap == cap) {
+            ch_tab[i].used = ++ch_clock;
+            if (ch_sel != i) ++ch_stamp;
+            ch_sel = i;
+            return true;
+        }
+    return false;
+}
+
+// tile tables of T rows for D orders, on the device, in place of those not used for the longest time
 tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows) {
     ChainTables t;
     chain_tables(h_slice_off, h_col, inst_row0, ch_orders, T, D, rows, max_rows, t, chain_width());
     if (t.depth < 1) return fail(TBPM_E_ARG, "no tile fits");
     const size_t nt = t.tiles.size();
-    ch = ChainState{};
+    for (int32_t i = 0; i < kChainTabs; ++i)
+        if (ch_tab[i].used < ch_tab[ch_sel].used) ch_sel = i;
+    ChainTab &c = ch();
     ++ch_stamp;
-    TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
+    if (c.depth > 0) TRY_HIP(hipDeviceSynchronize(), "sync before tile rebuild");
+    c.depth = 0;
+    c.used = 0;
     hipError_t e = hipSuccess;
     auto up = [&](DevBuf &d, const void *src, size_t bytes) {
         if (e == hipSuccess) e = d.ensure(bytes);
         if (e == hipSuccess) e = hipMemcpy(d.ptr, src, bytes, hipMemcpyHostToDevice);
     };
-    up(ch_tiles, t.tiles.data(), sizeof(TileDesc) * nt);
-    up(ch_tile0, t.inst_tile0.data(), sizeof(int32_t) * t.inst_tile0.size());
-    up(ch_cnt, t.cnt.data(), sizeof(int32_t) * t.cnt.size());
-    up(ch_toff, t.toff.data(), sizeof(int32_t) * nt);
-    up(ch_loff, t.loff.data(), sizeof(int32_t) * nt);
-    up(ch_rowmap, t.rowmap.data(), sizeof(uint32_t) * t.rowmap.size());
-    up(ch_lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
+    up(c.tiles, t.tiles.data(), sizeof(TileDesc) * nt);
+    up(c.tile0, t.inst_tile0.data(), sizeof(int32_t) * t.inst_tile0.size());
+    up(c.cnt, t.cnt.data(), sizeof(int32_t) * t.cnt.size());
+    up(c.toff, t.toff.data(), sizeof(int32_t) * nt);
+    up(c.loff, t.loff.data(), sizeof(int32_t) * nt);
+    up(c.rowmap, t.rowmap.data(), sizeof(uint32_t) * t.rowmap.size());
+    up(c.lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();  // the caller goes on with another launch shape
         return fail(TBPM_E_OOM, "no memory for the chain tables");
     }
     TRY_HIP(e, "upload chain tables");
-    ch.T = T;
-    ch.cap = cap;
-    ch.depth = t.depth;
-    ch.n_tiles = (int32_t)nt;
-    ch.n_local = (int64_t)t.lidx.size() / std::max(chain_width(), 4);
-    ch.contiguous = t.contiguous;
-    ch.max_stage = t.max_stage;
+    c.T = T;
+    c.cap = cap;
+    c.n_tiles = (int32_t)nt;
+    c.n_local = (int64_t)t.lidx.size() / std::max(chain_width(), 4);
+    c.contiguous = t.contiguous;
+    c.max_stage = t.max_stage;
+    c.depth = t.depth;
+    c.id = ++ch_builds;
+    c.used = ++ch_clock;
     return TBPM_OK;
 }
 
@@ -154,7 +177,7 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
     const int64_t max_rows = rows + rows / 4;
     for (; T >= kChainMinTile; T /= 2) {
         const int32_t cap = std::min<int32_t>(n_orders, T >= 512 ? 6 : (T >= 128 ? 9 : 17));
-        if (ch.T != T || ch.cap != cap || ch.depth == 0) {
+        if (!chain_select(T, cap)) {
             ChainReach &r = chain_reach(T);
             // a depth short of what was asked for is the rows' own, whatever is asked for
             if (r.tried < cap && r.reach == r.tried) {
@@ -172,8 +195,8 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         // chip holds at once (two workgroups per CU, three of complex operators:
         // hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
         const int64_t slots = mat.is_complex ? 768 : 512;
-        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + ch.n_tiles - 1) / ch.n_tiles));
-        chain_split(n_orders, ch.depth, cs.depths);
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + ch().n_tiles - 1) / ch().n_tiles));
+        chain_split(n_orders, ch().depth, cs.depths);
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no chain tile fits");
@@ -196,7 +219,7 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
     while (T < kWideThreads && T * 2 * 256 <= units) T *= 2;
     chain_orders(true);
     for (; T >= kChainMinTile; T /= 2) {
-        if (ch.T != T || ch.cap != 1 || ch.depth == 0) {
+        if (!chain_select(T, 1)) {
             ChainReach &r = chain_reach(T);
             if (r.refused <= 1) continue;
             tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);
@@ -204,7 +227,7 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }
-        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch.n_tiles - 1) / ch.n_tiles));
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch().n_tiles - 1) / ch().n_tiles));
         cs.depths.assign(1, 1);
         return TBPM_OK;
     }
@@ -215,8 +238,8 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
 bool Engine::chain_room(bool fp32, size_t need) {
     auto grow = [](const DevBuf &b, size_t n) { return n > b.bytes ? n : (size_t)0; };
     const size_t rb = fp32 ? 4 : 8;
-    need += grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * chain_width()) +
-            grow(ch_tons, rb * (size_t)ch.n_local);
+    need += grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch().n_local * chain_width()) +
+            grow(ch_tons, rb * (size_t)ch().n_local);
     if (need == 0) return true;
     size_t free_b = 0, total_b = 0;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + ((size_t)256 << 20) <= free_b;
@@ -236,48 +259,48 @@ tbpm_status Engine::chain_values(bool fp32, hipStream_t st) {
     const size_t rb = fp32 ? 4 : 8;
     const int32_t W = chain_width();
     ++ch_stamp;
-    TRY_HIP(ch_tval.ensure(rb * (mat.is_complex ? 2 : 1) * (size_t)ch.n_local * W), "alloc chain values");
-    TRY_HIP(ch_tons.ensure(rb * (size_t)ch.n_local), "alloc chain values");
-    ChainTileTab t{(const int32_t *)ch_cnt.ptr, (const int32_t *)ch_toff.ptr, (const int32_t *)ch_loff.ptr,
-                   (const uint32_t *)ch_rowmap.ptr, ch.depth, W};
-    TRY_HIP(launch_chain_values(fp32, mat.is_complex, t, ch.n_tiles, mat, ch_tval.ptr, ch_tons.ptr, st),
+    TRY_HIP(ch_tval.ensure(rb * (mat.is_complex ? 2 : 1) * (size_t)ch().n_local * W), "alloc chain values");
+    TRY_HIP(ch_tons.ensure(rb * (size_t)ch().n_local), "alloc chain values");
+    ChainTileTab t{(const int32_t *)ch().cnt.ptr, (const int32_t *)ch().toff.ptr, (const int32_t *)ch().loff.ptr,
+                   (const uint32_t *)ch().rowmap.ptr, ch().depth, W};
+    TRY_HIP(launch_chain_values(fp32, mat.is_complex, t, ch().n_tiles, mat, ch_tval.ptr, ch_tons.ptr, st),
             "launch chain values");
     return TBPM_OK;
 }
 
 ChainParams Engine::chain_params(const ChainShape &cs) const {
     ChainParams p{};
-    p.tiles = (const TileDesc *)ch_tiles.ptr;
-    p.n_tiles = ch.n_tiles;
+    p.tiles = (const TileDesc *)ch().tiles.ptr;
+    p.n_tiles = ch().n_tiles;
     p.n_blk = cs.n_blk;
     p.n_grp = cs.n_grp;
     p.grp_blk = (cs.n_blk + cs.n_grp - 1) / cs.n_grp;
-    p.table_depth = ch.depth;
-    p.contiguous = ch.contiguous ? 1 : 0;
+    p.table_depth = ch().depth;
+    p.contiguous = ch().contiguous ? 1 : 0;
     p.n_inst = n_inst();
     p.n_rows = (uint32_t)mat.n_rows;
-    p.cnt = (const int32_t *)ch_cnt.ptr;
-    p.toff = (const int32_t *)ch_toff.ptr;
-    p.loff = (const int32_t *)ch_loff.ptr;
-    p.rowmap = (const uint32_t *)ch_rowmap.ptr;
-    p.lidx = (const uint16_t *)ch_lidx.ptr;
+    p.cnt = (const int32_t *)ch().cnt.ptr;
+    p.toff = (const int32_t *)ch().toff.ptr;
+    p.loff = (const int32_t *)ch().loff.ptr;
+    p.rowmap = (const uint32_t *)ch().rowmap.ptr;
+    p.lidx = (const uint16_t *)ch().lidx.ptr;
     p.tval = ch_tval.ptr;
     p.tons = ch_tons.ptr;
     return p;
 }
 
 tbpm_status Engine::wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const {
-    if (ch.depth != 1) return fail(TBPM_E_ARG, "the tile tables are not the wide pass's");
-    p.lds_rows = ch.max_stage[1];
-    hipError_t e = launch_pass_wide(fp32, chain_width(), cs.vs, ch.max_stage[0], p, st);
+    if (ch().depth != 1) return fail(TBPM_E_ARG, "the tile tables are not the wide pass's");
+    p.lds_rows = ch().max_stage[1];
+    hipError_t e = launch_pass_wide(fp32, chain_width(), cs.vs, ch().max_stage[0], p, st);
     if (e != hipSuccess) return hip_fail(e, "launch wide pass");
     return TBPM_OK;
 }
 
 tbpm_status Engine::chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const {
-    if (p.depth < 1 || p.depth > ch.depth) return fail(TBPM_E_ARG, "the tile tables serve fewer orders");
-    hipError_t e = launch_chain(fp32, mat.is_complex, chain_width(), cs.vs, ch.max_stage[p.depth - 1],
-                                ch.max_stage[p.depth], p, st);
+    if (p.depth < 1 || p.depth > ch().depth) return fail(TBPM_E_ARG, "the tile tables serve fewer orders");
+    hipError_t e = launch_chain(fp32, mat.is_complex, chain_width(), cs.vs, ch().max_stage[p.depth - 1],
+                                ch().max_stage[p.depth], p, st);
     if (e != hipSuccess) return hip_fail(e, "launch chain");
     return TBPM_OK;
 }

@@ -80,7 +80,8 @@ void PinnedBuf::release() {
 bool GraphKey::operator==(const GraphKey &o) const {
     if (s_pad != o.s_pad || s_user != o.s_user || fp32 != o.fp32 || mmax != o.mmax || n_inst != o.n_inst ||
         chunks != o.chunks || remap != o.remap || nt != o.nt || unroll != o.unroll || staged != o.staged || vec != o.vec ||
-        fused != o.fused || chain_depth != o.chain_depth || chain_grp != o.chain_grp || n_tiles != o.n_tiles || tiles_chunks != o.tiles_chunks || tiles_unit != o.tiles_unit ||
+        fused != o.fused || chain_depth != o.chain_depth || chain_grp != o.chain_grp ||
+        chain_id != o.chain_id || n_tiles != o.n_tiles || tiles_chunks != o.tiles_chunks || tiles_unit != o.tiles_unit ||
         lds_units != o.lds_units || n_steps != o.n_steps || n_qe != o.n_qe || jc_states != o.jc_states ||
         steps != o.steps || ckpt != o.ckpt)
         return false;
@@ -289,10 +290,10 @@ void Engine::release() {
                       &fu_hw,    &fu_hidx,  &bc,       &bd,        &ckpt_slot, &corr_scratch, &qe_coef,
                       &qe_acc,   &qe_part,  &qe_norm2, &ac_ja,     &ac_jb,     &ac_csr,       &ac_zero,
                       &ac_vec,   &ac_block, &jc_tab,   &jc_norm,   &jc_part,  &ch_hist, &ac_fermi,   &hay_u,     &hay_y,        &hay_s,
-                      &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner, &ch_tiles, &ch_tile0,
-                      &ch_cnt,   &ch_toff,  &ch_loff,  &ch_rowmap, &ch_lidx, &ch_tval, &ch_tons};
+                      &kp_store, &kp_rblk,  &kp_vec,   &kp_parts, &bwd_partner, &ch_tval, &ch_tons};
     for (DevBuf *b : bufs) b->release();
-    ch = ChainState{};
+    for (ChainTab &t : ch_tab) t.release();
+    ch_sel = 0;
     ch_orders.clear();
     ch_reach.clear();
     partner_ready = false;
@@ -636,7 +637,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     if (staged && build_staged_tiles(s_pad, log2ub, unit_bytes, cfg.staged) != TBPM_OK) staged = false;
     if (!staged && !fused && !blocked) st = build_tiles(s_pad, chunks, vs);
     if (st != TBPM_OK) return st;
-    const int32_t n_tiles = blocked ? ch.n_tiles : (int32_t)h_tiles.size();
+    const int32_t n_tiles = blocked ? ch().n_tiles : (int32_t)h_tiles.size();
     const int64_t n_el = mat.n_rows * s_pad;
     if (n_el >= (int64_t)INT32_MAX) return fail(TBPM_E_ARG, "n_orb * n_states (padded to a power of two) must be < 2^31");
     if (blocked) {
@@ -754,7 +755,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             if (e != hipSuccess) return hip_fail(e, "launch quasi-eigenstate accumulation");
         }
         if (a.jc_states > 0) {
-            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(blocked ? ch_tiles.ptr : tiles.ptr), n_tiles, log2sp,
+            hipError_t e = launch_jcorr(fp32, (const TileDesc *)(blocked ? ch().tiles.ptr : tiles.ptr), n_tiles, log2sp,
                                         a.jc_states, log2sb, mat.n_rows, state, mat.slice_off, mat.col, a.jc_val,
                                         (double *)jc_part.ptr + std::max(local, 0) * part_stride, cnt, n_el, part_stride, s);
             if (e != hipSuccess) return hip_fail(e, "launch current correlation");
@@ -768,7 +769,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             ReduceParams jr{};
             jr.partials = (const double *)jc_part.ptr;
             jr.n_tiles = n_tiles;
-            jr.inst_tile0 = (const int32_t *)(blocked ? ch_tile0.ptr : inst_tile0.ptr);
+            jr.inst_tile0 = (const int32_t *)(blocked ? ch().tile0.ptr : inst_tile0.ptr);
             jr.log2s = log2sp;
             jr.s_user = a.jc_states;
             jr.n_steps = a.n_steps;
@@ -794,7 +795,7 @@ tbpm_status Engine::run(const RunArgs &a) {
 
     // C_0
     InitParams ip{};
-    ip.tiles = (const TileDesc *)(blocked ? ch_tiles.ptr : tiles.ptr);
+    ip.tiles = (const TileDesc *)(blocked ? ch().tiles.ptr : tiles.ptr);
     ip.n_tiles = n_tiles;
     ip.log2s = log2s;
     ip.s_user = a.s_user;
@@ -811,7 +812,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     ReduceParams rp{};
     rp.partials = (const double *)partials.ptr;
     rp.n_tiles = n_tiles;
-    rp.inst_tile0 = (const int32_t *)(blocked ? ch_tile0.ptr : inst_tile0.ptr);
+    rp.inst_tile0 = (const int32_t *)(blocked ? ch().tile0.ptr : inst_tile0.ptr);
     rp.log2s = log2s;
     rp.s_user = a.s_user;
     rp.n_steps = a.n_steps;
@@ -1121,8 +1122,9 @@ tbpm_status Engine::run(const RunArgs &a) {
             key.tiles_unit = tiles_unit;
             key.lds_units = fused ? fu_lds_units : (staged ? stage_units : 0);
 
-            key.chain_depth = blocked ? ch.depth : 0;  // 1: the wide pass
+            key.chain_depth = blocked ? ch().depth : 0;  // 1: the wide pass
             key.chain_grp = blocked ? cs.n_grp : 0;
+            key.chain_id = blocked ? ch().id : 0;
             key.n_steps = a.n_steps;
             key.n_qe = a.n_qe;
             key.jc_states = a.jc_states;
@@ -1132,8 +1134,8 @@ tbpm_status Engine::run(const RunArgs &a) {
                                   st_lidx.ptr, fu_hidx.ptr, fu_n1.ptr,     fu_hoff.ptr, fu_hw.ptr,
                                   a.ckpt ? ckpt_slot.ptr : nullptr, a.n_qe > 0 ? qe_coef.ptr : nullptr,
                                   a.n_qe > 0 ? a.qe_acc : nullptr, a.jc_states > 0 ? a.jc_val : nullptr,
-                                  a.jc_states > 0 ? jc_norm.ptr : nullptr, ch_tiles.ptr, ch_tile0.ptr, ch_cnt.ptr,
-                                  ch_toff.ptr, ch_loff.ptr, ch_rowmap.ptr, ch_lidx.ptr, ch_tval.ptr, ch_tons.ptr,
+                                  a.jc_states > 0 ? jc_norm.ptr : nullptr, ch().tiles.ptr, ch().tile0.ptr, ch().cnt.ptr,
+                                  ch().toff.ptr, ch().loff.ptr, ch().rowmap.ptr, ch().lidx.ptr, ch_tval.ptr, ch_tons.ptr,
                                   hist ? ch_hist.ptr : nullptr, a.jc_states > 0 ? jc_part.ptr : nullptr};
             static_assert(sizeof(kb) == sizeof(key.bufs), "graph key buffers");
             std::memcpy(key.bufs, kb, sizeof(kb));
@@ -1451,8 +1453,7 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         ++log2s;
     }
     const bool chain = last_staged == 3, wide = last_staged == 4;
-    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || (!chain && !wide && tiles_s != s_pad) ||
-        ((chain || wide) && ch.depth == 0))
+    if (last_s_pad != s_pad || last_fp32 != (fp32 ? 1 : 0) || !v.ptr || (!chain && !wide && tiles_s != s_pad))
         return fail(TBPM_E_ARG, "tbpm_bench_pass needs a prior tbpm_propagate with the same n_states and precision");
     cfg = cfgs[fp32 ? 1 : 0];
     if ((chain || wide) && last_stamp != ch_stamp) {

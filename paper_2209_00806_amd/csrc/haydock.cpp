@@ -62,7 +62,7 @@ tbpm_status Engine::haydock_chain(const ChainShape &cs, const double *psi0, int3
     TRY_HIP(hay_u.ensure(2 * vec), "alloc Lanczos vectors");
     TRY_HIP(hay_y.ensure(vec), "alloc Lanczos vectors");
     TRY_HIP(hay_s.ensure(sizeof(double) * 4 * (size_t)s_user), "alloc Lanczos scalars");
-    TRY_HIP(partials.ensure(sizeof(double) * 3 * (size_t)ch.n_tiles * s_user), "alloc partials");
+    TRY_HIP(partials.ensure(sizeof(double) * 3 * (size_t)ch().n_tiles * s_user), "alloc partials");
     TRY_HIP(counter.ensure(sizeof(int32_t)), "alloc counter");
     double *u[3] = {(double *)hay_u.ptr, (double *)((char *)hay_u.ptr + vec), (double *)hay_y.ptr};
     double *hs = (double *)hay_s.ptr, *part = (double *)partials.ptr;
@@ -78,9 +78,9 @@ tbpm_status Engine::haydock_chain(const ChainShape &cs, const double *psi0, int3
         p.partials = part;
         p.counter = cnt;
         p.bump = out != nullptr;
-        hipError_t e = launch_hay_step(mat.is_complex, chain_width(), ch.max_stage[1], ch.max_stage[2], p, hs, s);
+        hipError_t e = launch_hay_step(mat.is_complex, chain_width(), ch().max_stage[1], ch().max_stage[2], p, hs, s);
         if (e == hipSuccess)
-            e = launch_hay_reduce3(part, ch.n_tiles, s_user, out == nullptr, thr, hs, cnt, n_iter, a_out, b_out, s);
+            e = launch_hay_reduce3(part, ch().n_tiles, s_user, out == nullptr, thr, hs, cnt, n_iter, a_out, b_out, s);
         return e;
     };
     TRY_HIP(launch_expand_states(psi0, mat.perm, s_user, u[0], cs.log2sb(), n, st), "load start vectors");
@@ -106,7 +106,7 @@ tbpm_status Engine::haydock(const double *psi0, int32_t s_user, int32_t n_iter, 
     // the rule of the propagation.
     ChainShape cs;
     bool chain = (cfgs[0].fused > 0 || (!cfg_set[0] && n_iter > kChainAutoSteps)) &&
-                 chain_prepare(s_user, false, 17, cs) == TBPM_OK && ch.depth >= 2;
+                 chain_prepare(s_user, false, 17, cs) == TBPM_OK && ch().depth >= 2;
     if (chain) {
         auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
         const size_t v1 = 16 * (size_t)n * s_user;

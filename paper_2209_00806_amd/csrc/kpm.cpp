@@ -205,8 +205,8 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
         cc.jval = jval;
         cc.jout = jout;
         cc.jout_stride = (int64_t)vstride;
-        return launch_chain_cheb(jval ? kChainCurrent : kChainCheb, mat.is_complex, chain_width(), (int)ch.T,
-                                 ch.max_stage[d - 1], ch.max_stage[d], cp, cc, st);
+        return launch_chain_cheb(jval ? kChainCurrent : kChainCheb, mat.is_complex, chain_width(), (int)ch().T,
+                                 ch().max_stage[d - 1], ch().max_stage[d], cp, cc, st);
     };
 
     // L_0 = v_a r, L_1 = H~ L_0, L_{m+1} = 2 H~ L_m - L_{m-1}, in place in the store
@@ -298,7 +298,7 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
         }
         for (int32_t j = 0; chain && j < cnt;) {
             // a block's orders in launches of nearly equal depth
-            const int32_t n_launch = (cnt - j + ch.depth - 1) / ch.depth, d = (cnt - j) / n_launch;
+            const int32_t n_launch = (cnt - j + ch().depth - 1) / ch().depth, d = (cnt - j) / n_launch;
             void *o[2] = {nullptr, nullptr};
             for (int b = 1, i = 0; b < 5 && i < 2; ++b) {
                 void *t = vb + (size_t)b * vec;

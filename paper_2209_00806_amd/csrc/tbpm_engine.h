@@ -79,6 +79,7 @@ struct GraphKey {
     const void *ckpt = nullptr;
     const void *bufs[33] = {};
     int32_t chain_depth = 0, chain_grp = 0;
+    int64_t chain_id = 0;
     bool operator==(const GraphKey &o) const;
 };
 
@@ -108,17 +109,29 @@ struct Engine {
     DevBuf fu_n1, fu_hoff, fu_hw, fu_hidx, bc, bd;
     int32_t fu_lds_units = 0;
     size_t fu_max_rows = 0;
-    // tiles of the chain kernel (several orders per launch): tables on the
-    // device, and their matrix entries (taken anew by every call that uses them)
-    DevBuf ch_tiles, ch_tile0, ch_cnt, ch_toff, ch_loff, ch_rowmap, ch_lidx, ch_tval, ch_tons;
-    struct ChainState {
-        int64_t T = 0;    // rows per tile the tables were built for
-        int32_t cap = 0;  // and the most orders asked for
+    // tiles of the chain kernel (several orders per launch) for at most T rows and
+    // cap orders: tables on the device, and what the host knows of them
+    struct ChainTab {
+        DevBuf tiles, tile0, cnt, toff, loff, rowmap, lidx;
+        int64_t T = 0;
+        int32_t cap = 0;
         int32_t depth = 0, n_tiles = 0;  // orders they serve (0: no tables)
         int64_t n_local = 0;             // evaluated rows over all tiles
         bool contiguous = true;
         std::vector<int32_t> max_stage;  // [depth + 1]
-    } ch;
+        int64_t id = 0, used = 0;        // one number per build; the last use
+        void release();
+    };
+    // Calls that differ in the states, the orders or the method may need other tiles: a
+    // handle keeps the tables of the last four kinds it used.  ch(): those in use.
+    static constexpr int kChainTabs = 4;
+    ChainTab ch_tab[kChainTabs];
+    int32_t ch_sel = 0;
+    int64_t ch_builds = 0, ch_clock = 0;
+    ChainTab &ch() { return ch_tab[ch_sel]; }
+    const ChainTab &ch() const { return ch_tab[ch_sel]; }
+    // the tiles' matrix entries (taken anew by every call that uses them)
+    DevBuf ch_tval, ch_tons;
     // what a sample of the tiles of T rows reached: reach orders of at most tried,
     // and the fewest orders for which no tiling was found
     struct ChainReach {
@@ -140,7 +153,9 @@ struct Engine {
     tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs);
     // whether the vectors (vec bytes each) and tables that the chain needs beyond
     // the ones held fit the device memory that is free
+    // selects the tables of (T, cap), made for D orders if they are not there
     tbpm_status chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows);
+    bool chain_select(int64_t T, int32_t cap);
     tbpm_status wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const;
     tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs);
     bool chain_room(bool fp32, size_t need);

@@ -211,6 +211,23 @@ static tbpm_hamiltonian *irregular(int64_t n, bool ring, int matchings) {
     return H;
 }
 
+// Calls that differ in states, orders, precision and method, in turn on one handle:
+// the second round finds the tables that the first one made.
+static void tables_kept() {
+    tbpm_hamiltonian *H = ring(20000, {1, 70});
+    int uploads = 0;
+    for (int round = 0; round < 3; ++round) {
+        propagate(H, 1, 70);
+        propagate(H, 8, 70);
+        propagate(H, 1, 70, 0.3);
+        propagate(H, 8, 70, 3.14159, TBPM_FP32_MIXED);
+        haydock(H, 8, 70);
+        if (round == 0) uploads = fake::uploads;
+        CHECK(fake::uploads == uploads);
+    }
+    tbpm_hamiltonian_destroy(H);
+}
+
 // Operators whose tiles fit no size, or not the first one tried: a second call does
 // not look at the rows again (an array of all rows would be allocated).
 static void sizes_refused() {
@@ -233,6 +250,7 @@ static void sizes_refused() {
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
+                                                           {"tables_kept", tables_kept},
                                                            {"sizes_refused", sizes_refused}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();

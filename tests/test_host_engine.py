@@ -59,6 +59,11 @@ def test_haydock_step_reads_inside_its_lds(checker):
     _run(checker, "haydock_places")
 
 
+def test_tables_are_kept_between_kinds_of_calls(checker):
+    """Calls of several kinds in turn on one handle build their tile tables once."""
+    _run(checker, "tables_kept")
+
+
 def test_refused_tile_sizes_are_remembered(checker):
     """A tile size that an operator's rows do not fit is not tried again by every call."""
     _run(checker, "sizes_refused")
