@@ -531,8 +531,9 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               unused.  Real operators with 5 to 24 stored elements per row
  *               and two blocks of states or more (two FP64 states, three FP32
  *               ones): a workgroup also keeps its rows' elements in registers
- *               and takes the blocks in turn; the library chooses the tiles,
- *               whatever the value and vec.  0: gather from global memory
+ *               and takes the blocks in turn, where a tile's rows reference few
+ *               others; the library chooses the tiles, whatever the value and
+ *               vec.  0: gather from global memory
  *   vec         states of a row each thread holds (1, 2 or 4; capped by the
  *               padded state count)
  *   fused       1 .. 6: evaluate several Clenshaw orders per launch.
@@ -541,7 +542,9 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               evaluates d orders on them (d up to 17, as far as the rows
  *               within reach stay few); the library chooses tiles and d from
  *               the sizes, whatever the value; vec, unroll and wg_chunks are
- *               unused.  Other operators: two orders, each tile staging its
+ *               unused.  Other operators, and those whose rows within reach
+ *               grow so fast that this would be the slower one (estimated from
+ *               a sample of the tiles): two orders, each tile staging its
  *               two-hop neighbourhood; the value t is the LDS tier: a tile
  *               uses at most 1/(t+2) of a CU's 160 KiB (bigger tiles and
  *               smaller halos, or more resident workgroups).  Two
@@ -559,8 +562,8 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  * autotuned also evaluates several orders per launch, where the operator has
  * at most 4 stored elements per row, or takes the staged shape's second form,
  * where that applies, for propagations of more than 64 samples (shorter ones
- * would not repay building the tile tables) if the extra work vectors and
- * tables fit the free device memory; FP32 states are the same bit for bit,
+ * would not repay building the tile tables) if they are estimated to be faster
+ * and the extra work vectors and tables fit the free device memory; FP32 states are the same bit for bit,
  * FP64 results the same to rounding.
  */
 typedef struct {

@@ -69,7 +69,7 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     const size_t n_store = (size_t)(seg_len + 1) + (size_t)seg_len * n_b;
     const size_t gacc_bytes = (cplx ? 16 : 8) * (size_t)std::max<int64_t>(eng.mat.ell_size, 1);
     bool chain = N >= 2 && (eng.cfgs[0].fused > 0 || (!eng.cfg_set[0] && N > kChainAutoSteps)) &&
-                 n_rows * s_pad < (int64_t)INT32_MAX && eng.chain_prepare(s_user, false, M - 1, cs) == TBPM_OK;
+                 n_rows * s_pad < (int64_t)INT32_MAX && eng.chain_prepare(s_user, false, M - 1, cs, Engine::kUseAdjoint) == TBPM_OK;
     if (chain) {
         auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
         const size_t v1 = 16 * (size_t)n_rows * s_user;

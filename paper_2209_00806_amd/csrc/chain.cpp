@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <thread>
 
 #include "tbpm_engine.h"
@@ -96,10 +97,15 @@ void Engine::ChainTab::release() {
     *this = ChainTab{};
 }
 
-Engine::ChainReach &Engine::chain_reach(int64_t T) {
+Engine::ChainReach &Engine::chain_reach(int64_t T, int32_t cap) {
     for (ChainReach &r : ch_reach)
-        if (r.T == T) return r;
-    ch_reach.push_back(ChainReach{T});
+        if (r.T == T && r.cap == cap) return r;
+    ChainReach r{T, cap};
+    const bool wide = mat.max_width > kChainWidth;
+    const int64_t rows = wide ? kWideThreads : chain_rows(mat.is_complex);
+    r.depth = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, wide ? kWideStage : rows + rows / 4,
+                          &r.sample, wide ? 1 : 0);
+    ch_reach.push_back(std::move(r));
     return ch_reach.back();
 }
 
@@ -157,6 +163,96 @@ tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows,
     return TBPM_OK;
 }
 
+// What one evaluation takes by the chain, and without it, in microseconds: the chain
+// evaluates and reads rows of its shells more than once, and on operators whose
+// shells grow fast that costs more than the launches and passes it saves.
+//
+// Two bounds per launch.  Memory: 5.4 TB/s for the 64-byte sectors of the staged rows
+// (x), of the evaluated rows (psi and b_{j+2}), the own rows' outputs and the tables;
+// shell rows far apart take a sector each.  Latency: every block of states of every
+// workgroup takes some 3 us of loads and barriers and 0.35 us per order, in rounds of
+// the workgroups that the chip holds.  Without the chain every pass streams its
+// vectors, or costs a launch.  Estimate and measurement per time step of 17 orders, us:
+//     states                          chain           one order per launch
+//     graphene 320^2            1    33 (31)       106 (73)
+//                              16   366 (242)      723 (667)
+//     1% of its bonds rewired   4   238 (226)      227 (232)
+//                              16   840 (823)      723 (690)
+//     a matching on a ring, 200000 rows
+//                               1   227 (169)      123 (129)
+//                              16  3000 (1733)     706 (695)
+//     diamond 2 x 30^3          1    47 (65)        60 (71)
+//                               4   100 (127)       87 (82)
+// Over 430 calls on lattices with 0 to 5% of their bonds rewired, ring matchings and
+// three-dimensional lattices, by all methods, the choice is within 5% of one order (or
+// two) per launch or faster; without it the chain was up to 3.2 times slower.
+static double chain_rounds(int64_t groups, int32_t slots) {
+    const double x = (double)groups / slots;
+    return x <= 0.9 ? 1.0 : x + 0.5;  // the last round is partial, and the number of groups an estimate
+}
+
+double Engine::chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use) const {
+    const double n16 = 16.0 * (double)mat.n_rows, vec = n16 * cs.n_blk, rate = 5.4e6;  // bytes per us
+    // bytes of matrix entries and local indices per evaluated row, in rows
+    const double tab = (8.0 + 8.0 + (mat.is_complex ? 16.0 : 8.0) * chain_width()) / 16.0;
+    const int32_t grp_blk = (cs.n_blk + cs.n_grp - 1) / cs.n_grp, groups = (cs.n_blk + grp_blk - 1) / grp_blk;
+    const double rounds = chain_rounds(s.tiles * groups, chain_slots()) * grp_blk;
+    // the adjoint's kernel keeps more in registers, and spills with four elements per row
+    auto adjoint_us = [&](int32_t d) { return (4.0 + 0.5 * d) * (chain_width() <= 3 ? 1.0 : (mat.is_complex ? 1.4 : 2.0)); };
+    auto launch = [&](int32_t d, double eval_streams, double own_rows, double block_us) {
+        const double tables = n16 * groups * (tab * s.rows[d - 1] + 0.25 * s.rows[d]);
+        const double bytes = vec * (s.sectors[d] + eval_streams * s.sectors[d - 1] + own_rows) + tables;
+        return 2.5 + std::max(rounds * block_us, bytes / rate);
+    };
+    if (use == kUseHaydock) return 4.6 + launch(2, 1, 1, 2.0);  // u_{i-1} is read one hop out; and the sums
+    double us = 0.0;
+    for (const int32_t d : cs.depths) {
+        if (use == kUseClenshaw) us += launch(d, 2, 2, 3.0 + 0.35 * d);
+        // no psi; an order's vector, or J times it, is stored, and for one of the two recursions the last two
+        if (use == kUseMoments) us += launch(d, 1, 1 + d, 3.0 + 0.35 * d);
+        // the replay stores every order; the adjoint reads them back, and lambda
+        if (use == kUseAdjoint) us += launch(d, 2, 2 + d, 3.0 + 0.35 * d) + launch(d, 1, 4 + d, adjoint_us(d));
+    }
+    return us;
+}
+
+// pairs: two orders per launch where the fused shape is configured (none for Haydock).
+// Such a launch reads the rows within two hops, whole sectors of them if a row's states
+// are fewer bytes, and a sector for each matrix entry of a shell row: 26 us for two
+// orders of the ring with one state (estimate 26), 41 (38) with four.
+double Engine::plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t n_orders, ChainUse use,
+                        bool pairs) const {
+    int32_t s_pad = 1;
+    while (s_pad < s_user) s_pad <<= 1;
+    const double row = (fp32 ? 8.0 : 16.0) * s_pad, vec = row * (double)mat.n_rows, rate = 5.4e6;
+    const double w = mat.max_width, table = (8.0 + w * (mat.is_complex ? 20.0 : 12.0)) * (double)mat.n_rows;
+    const double current = w * 20.0 * (double)mat.n_rows;  // a current operator's entries
+    auto hop = [&](int32_t h) { return row >= 64.0 ? s.rows[h] : s.sectors[h]; };
+    // one order per launch: no less than the launch, else a fixed part and the streams
+    // (the general pass as it is configured for FP32 without a choice takes longer)
+    const bool slow = fp32 && s_user > 1;
+    const double gather = row >= 64.0 ? 0.0 : 0.5 * (s.sectors[1] - 1.0);
+    const double order = std::max(slow ? 4.8 : 3.55, (slow ? 3.8 : 2.0) + ((4 + gather) * vec + table) / rate);
+    double clenshaw = n_orders * order;
+    if (pairs)
+        clenshaw = 0.5 * n_orders *
+                   std::max(slow ? 8.0 : 6.3, (slow ? 4.0 : 2.5) +
+                                                  (vec * (hop(2) + 2 * hop(1) + 2) + table +
+                                                   64.0 * w * (s.rows[1] - 1.0) * (double)mat.n_rows) / rate);
+    switch (use) {
+        case kUseMoments:  // half of the orders take a pass of the current operator as well
+            return clenshaw + n_orders * std::max(1.75, 1.5 + 0.5 * current / rate);
+        case kUseHaydock:  // two launches and two sums per iteration
+            return std::max(16.5, 14.0 + (6 * vec + table) / 4.9e6);
+        case kUseAdjoint: {  // replay, and an adjoint that updates the gradient
+            const double all = n_orders * std::max(9.0, 5.0 + (13 * vec + 3.5 * table) / rate);
+            return clenshaw + (pairs ? 0.75 : 1.0) * (all - n_orders * order);
+        }
+        default:
+            return clenshaw;
+    }
+}
+
 // Tile size and depth.  The more workgroups there are, the larger a tile may be
 // (fewer rows evaluated and staged more than once); an operator too small to
 // give every CU a workgroup takes small tiles and more orders per launch.
@@ -165,7 +261,7 @@ tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows,
 // S = 1); 128 rows, 9 orders 14.3 us against 19.7 (L = 128); 512 rows, 6 orders
 // 182 us against 195 for 256 rows, 9 orders and 319 for 128 rows, 9 orders
 // (L = 512, S = 4).  One order per launch: 55, 63 and 531 us.
-tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs) {
+tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use) {
     if (mat.max_width < 1 || mat.max_width > kChainWidth || n_orders < 2) return fail(TBPM_E_ARG, "rows too wide");
     cs.vs = fp32 && s_user > 1 ? 2 : 1;
     cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
@@ -174,32 +270,65 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
     int64_t T = kChainMinTile;
     while (T < rows / 2 && T * 2 * 256 <= units) T *= 2;
     chain_orders();
-    const int64_t max_rows = rows + rows / 4;
+    // few tiles: their state blocks go to several workgroups each, up to what the
+    // chip holds at once
+    const int64_t slots = chain_slots();
+    const bool pairs = cfgs[fp32 ? 1 : 0].fused > 0 && n_orders >= 3;
+    auto shape = [&](int64_t n_tiles, int32_t depth) {
+        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + n_tiles - 1) / n_tiles));
+        chain_split(n_orders, depth, cs.depths);
+    };
     for (; T >= kChainMinTile; T /= 2) {
         const int32_t cap = std::min<int32_t>(n_orders, T >= 512 ? 6 : (T >= 128 ? 9 : 17));
+        ChainReach &r = chain_reach(T, cap);
+        if (r.refused || r.depth < std::min(n_orders, 3)) continue;
+        shape(r.sample.tiles, r.depth);
+        if (chain_us(r.sample, cs, use) > plain_us(r.sample, s_user, fp32, n_orders, use, pairs)) continue;
         if (!chain_select(T, cap)) {
-            ChainReach &r = chain_reach(T);
-            // a depth short of what was asked for is the rows' own, whatever is asked for
-            if (r.tried < cap && r.reach == r.tried) {
-                r.reach = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, max_rows);
-                r.tried = cap;
-            }
-            const int32_t D = std::min(cap, r.reach);
-            if (D < std::min(n_orders, 3) || D >= r.refused) continue;
-            tbpm_status st = chain_build(T, cap, D, rows, max_rows);
-            if (st == TBPM_E_ARG) r.refused = D;
+            tbpm_status st = chain_build(T, cap, r.depth, rows, rows + rows / 4);
+            r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }
-        // few tiles: their state blocks go to several workgroups each, up to what the
-        // chip holds at once (two workgroups per CU, three of complex operators:
-        // hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
-        const int64_t slots = mat.is_complex ? 768 : 512;
-        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + ch().n_tiles - 1) / ch().n_tiles));
-        chain_split(n_orders, ch().depth, cs.depths);
+        shape(ch().n_tiles, ch().depth);
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no chain tile fits");
+}
+
+static int32_t wide_groups(int32_t n_blk, int64_t n_tiles) {
+    return (int32_t)std::min<int64_t>(n_blk, std::max<int64_t>(1, (512 + n_tiles - 1) / n_tiles));
+}
+
+// One wide pass, and the same by the general or the staged pass, in microseconds.  A
+// wide pass takes 3.6 us and, per block of states of a workgroup and round of 512
+// workgroups, 0.8 us and 0.2 us for every shell row of a thread (a little more from
+// the third on, which is not loaded ahead), or the sectors it reads at 12 TB/s from
+// the caches; the others gather each element from the cache.  Estimate and
+// measurement, us:
+//     states                                  wide            general
+//     bilayer 120^2, 19 elements       16    15 (15)       35 (33)
+//     cubic 60^3, 6 elements           16    41 (44)       60 (54)
+//     cubic 28^3                       16     8.2 (7.8)     7.9 (7.1)
+//     6 random pairings, 50000 rows    16    33 (32)       16 (18)
+//     20 random pairings, 20000 rows    4    18 (23)       11 (11)
+double Engine::wide_us(const ChainSample &s, int32_t n_blk) const {
+    const int32_t n_grp = wide_groups(n_blk, s.tiles), grp_blk = (n_blk + n_grp - 1) / n_grp;
+    const int32_t groups = (n_blk + grp_blk - 1) / grp_blk;
+    const double rounds = std::max(1.0, (double)(s.tiles * groups) / 512.0) * grp_blk;
+    const double own = (double)mat.n_rows / (double)s.tiles, threads = 64.0 * std::ceil(own / 64.0);
+    const double shell = own * (s.rows[1] - 1.0) / threads;
+    const double n16 = 16.0 * (double)mat.n_rows, tab = (16.0 + 10.0 * chain_width()) / 16.0;
+    const double bytes = n16 * (n_blk * (s.sectors[1] + 3.0) + groups * (tab + 0.25 * s.rows[1]));
+    return 3.6 + std::max(bytes / 12.0e6, rounds * (0.8 + 0.2 * shell + 0.02 * mat.max_width) +
+                                             grp_blk * 0.25 * std::max(0.0, shell - 2.0));
+}
+
+double Engine::wide_plain_us(int32_t s_user, bool fp32) const {
+    int32_t s_pad = 1;
+    while (s_pad < s_user) s_pad <<= 1;
+    const double vec = (fp32 ? 8.0 : 16.0) * s_pad * (double)mat.n_rows, w = mat.max_width;
+    return std::max(3.5 + 0.36 * w, 2.0 + vec * (3.0 + 0.45 * w) / 5.4e6);
 }
 
 // One order of a wide operator per launch (wide.hip), for two blocks of states or
@@ -219,15 +348,16 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
     while (T < kWideThreads && T * 2 * 256 <= units) T *= 2;
     chain_orders(true);
     for (; T >= kChainMinTile; T /= 2) {
+        ChainReach &r = chain_reach(T, 1);
+        if (r.refused || r.sample.depth < 1) continue;
+        if (wide_us(r.sample, cs.n_blk) > wide_plain_us(s_user, fp32)) continue;
         if (!chain_select(T, 1)) {
-            ChainReach &r = chain_reach(T);
-            if (r.refused <= 1) continue;
             tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);
-            if (st == TBPM_E_ARG) r.refused = 1;
+            r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
         }
-        cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (512 + ch().n_tiles - 1) / ch().n_tiles));
+        cs.n_grp = wide_groups(cs.n_blk, ch().n_tiles);
         cs.depths.assign(1, 1);
         return TBPM_OK;
     }

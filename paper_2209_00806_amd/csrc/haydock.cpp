@@ -106,7 +106,7 @@ tbpm_status Engine::haydock(const double *psi0, int32_t s_user, int32_t n_iter, 
     // the rule of the propagation.
     ChainShape cs;
     bool chain = (cfgs[0].fused > 0 || (!cfg_set[0] && n_iter > kChainAutoSteps)) &&
-                 chain_prepare(s_user, false, 17, cs) == TBPM_OK && ch().depth >= 2;
+                 chain_prepare(s_user, false, 17, cs, kUseHaydock) == TBPM_OK;
     if (chain) {
         auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
         const size_t v1 = 16 * (size_t)n * s_user;

@@ -655,19 +655,76 @@ static bool chain_shells(const std::vector<int64_t> &slice_off, const std::vecto
 
 int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                     const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
-                    int32_t cap, int64_t max_eval, int64_t max_rows) {
+                    int32_t cap, int64_t max_eval, int64_t max_rows, ChainSample *sample, int32_t at_least) {
     const std::vector<TileDesc> tops = chain_parts(inst_row0, T);
     std::vector<int32_t> tag(inst_row0.back(), -1), c(cap + 1), depth;
     std::vector<uint32_t> rows;
     const size_t n = tops.size(), samples = std::min<size_t>(n, 48);
+    int32_t visit = 0;
+    // rows within h hops of each sampled tile that was reached to the end, and the
+    // 64-byte sectors of four rows that they lie in
+    std::vector<int32_t> sector(sample ? inst_row0.back() / 4 + 1 : 0, -1);
+    struct Tile {
+        TileDesc td;
+        int32_t reached;
+        std::vector<int32_t> rows, sectors;
+    };
+    std::vector<Tile> tiles;
+    auto walk = [&](const TileDesc &td, int32_t D) {
+        Tile t{td, 0, {}, {}};
+        (void)chain_shells(slice_off, col, inst_row0, orders, td, D, max_eval, max_rows, tag, visit, rows, c, t.reached);
+        if (sample) {
+            t.rows.assign(c.begin(), c.begin() + t.reached + 1);
+            int32_t s = 0, l = 0;
+            for (int32_t h = 0; h <= t.reached; ++h) {
+                for (; l < c[h]; ++l)
+                    if (sector[rows[l] / 4] != visit) {
+                        sector[rows[l] / 4] = visit;
+                        ++s;
+                    }
+                t.sectors.push_back(s);
+            }
+        }
+        ++visit;
+        return t;
+    };
     for (size_t k = 0; k < samples; ++k) {
-        int32_t reached = 0;
-        (void)chain_shells(slice_off, col, inst_row0, orders, tops[k * n / samples], cap, max_eval, max_rows, tag,
-                           (int32_t)k, rows, c, reached);
-        depth.push_back(reached);
+        Tile t = walk(tops[k * n / samples], cap);
+        depth.push_back(t.reached);
+        if (sample) tiles.push_back(std::move(t));
     }
     std::sort(depth.begin(), depth.end());
-    return depth.empty() ? 0 : depth[depth.size() / 16];
+    const int32_t D = depth.empty() ? 0 : std::max(depth[depth.size() / 16], at_least);
+    if (!sample) return D;
+    // tiles that do not reach D are halved, as chain_tables does
+    *sample = ChainSample{};
+    sample->rows.assign(D + 1, 0.0);
+    sample->sectors.assign(D + 1, 0.0);
+    int64_t own = 0, pieces = 0;
+    while (D > 0 && !tiles.empty()) {
+        const Tile t = std::move(tiles.back());
+        tiles.pop_back();
+        if (t.reached < D && t.td.rows >= 8) {
+            const int32_t half = t.td.rows / 2;
+            tiles.push_back(walk(TileDesc{t.td.row0 + half, t.td.rows - half, t.td.inst}, D));
+            tiles.push_back(walk(TileDesc{t.td.row0, half, t.td.inst}, D));
+            continue;
+        }
+        own += t.td.rows;
+        ++pieces;
+        for (int32_t h = 0; h <= D; ++h) {
+            sample->rows[h] += t.rows[std::min(h, t.reached)];
+            sample->sectors[h] += 4.0 * t.sectors[std::min(h, t.reached)];
+        }
+    }
+    if (own == 0) return D;
+    for (int32_t h = 0; h <= D; ++h) {
+        sample->rows[h] /= (double)own;
+        sample->sectors[h] /= (double)own;
+    }
+    sample->depth = D;
+    sample->tiles = (int64_t)((double)n * (double)pieces / (double)samples + 0.5);
+    return D;
 }
 
 void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,

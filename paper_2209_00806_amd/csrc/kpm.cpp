@@ -42,7 +42,7 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     ChainShape cs;
     bool chain = n_mom >= 3 &&
                  (cfgs[0].fused > 0 || (!cfg_set[0] && 2 * (int64_t)n_mom > 17 * (int64_t)kChainAutoSteps)) &&
-                 chain_prepare(s_user, false, n_mom - 1, cs) == TBPM_OK;
+                 chain_prepare(s_user, false, n_mom - 1, cs, kUseMoments) == TBPM_OK;
     if (chain) {
         const size_t vs1 = 16 * (size_t)n * s_user + 768, nbc = (size_t)std::min<int32_t>(n_mom, 128);
         auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };

@@ -5,7 +5,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <climits>
 #include <complex>
 #include <cstdint>
 #include <string>
@@ -132,14 +131,15 @@ struct Engine {
     const ChainTab &ch() const { return ch_tab[ch_sel]; }
     // the tiles' matrix entries (taken anew by every call that uses them)
     DevBuf ch_tval, ch_tons;
-    // what a sample of the tiles of T rows reached: reach orders of at most tried,
-    // and the fewest orders for which no tiling was found
+    // what a sample says of tiles of T rows for up to cap orders; refused: no tiling was found
     struct ChainReach {
         int64_t T;
-        int32_t tried = 0, reach = 0, refused = INT32_MAX;
+        int32_t cap, depth = 0;
+        bool refused = false;
+        ChainSample sample;
     };
     std::vector<ChainReach> ch_reach;
-    ChainReach &chain_reach(int64_t T);
+    ChainReach &chain_reach(int64_t T, int32_t cap);
     std::vector<std::vector<int32_t>> ch_orders;  // per member: row order its tiles follow (empty: as stored)
     struct ChainShape {
         int32_t vs = 1, n_blk = 1, n_grp = 1;
@@ -148,9 +148,17 @@ struct Engine {
     };
     void chain_orders(bool keep_local = false);
     int32_t chain_width() const { return chain_table_width(mat.max_width); }
+    // what the orders of a chain are for; it decides what a launch reads and writes
+    // beside b_{j+1} and b_{j+2}, and what the same costs without the chain
+    enum ChainUse { kUseClenshaw, kUseMoments, kUseHaydock, kUseAdjoint };
     // tables and launch sequence for n_orders orders on s_user states;
     // TBPM_E_ARG if the operator does not suit the kernel
-    tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs);
+    tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use = kUseClenshaw);
+    // workgroups that the chip holds: two per CU, three of complex operators
+    // (hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
+    int32_t chain_slots() const { return mat.is_complex ? 768 : 512; }
+    double chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use) const;
+    double plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t n_orders, ChainUse use, bool pairs) const;
     // whether the vectors (vec bytes each) and tables that the chain needs beyond
     // the ones held fit the device memory that is free
     // selects the tables of (T, cap), made for D orders if they are not there
@@ -158,6 +166,8 @@ struct Engine {
     bool chain_select(int64_t T, int32_t cap);
     tbpm_status wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const;
     tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs);
+    double wide_us(const ChainSample &s, int32_t n_blk) const;
+    double wide_plain_us(int32_t s_user, bool fp32) const;
     bool chain_room(bool fp32, size_t need);
     bool chain_fits(const ChainShape &cs, bool fp32, size_t vec);
     tbpm_status chain_values(bool fp32, hipStream_t st);

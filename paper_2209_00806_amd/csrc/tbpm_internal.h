@@ -323,11 +323,21 @@ void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32
                   const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
                   int32_t depth, int64_t max_eval, int64_t max_rows, ChainTables &t, int32_t width = 4);
 
+// What a sample says of tiles of T rows made for depth orders: their number, and per
+// own row the rows within h hops and the rows of the 64-byte sectors (four rows of 16
+// bytes) that these lie in.
+struct ChainSample {
+    int32_t depth = 0;
+    int64_t tiles = 0;
+    std::vector<double> rows, sectors;  // [depth + 1]
+};
 // The depth to build tiles of T rows for: the largest up to cap that nearly all
-// of a sample of tiles reach within the bounds; 0 if none
+// of a sample of tiles reach within the bounds; 0 if none (or at_least: the others
+// are halved until they reach it)
 int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                     const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
-                    int32_t cap, int64_t max_eval, int64_t max_rows);
+                    int32_t cap, int64_t max_eval, int64_t max_rows, ChainSample *sample = nullptr,
+                    int32_t at_least = 0);
 
 // LDS budget of a fused-shape tile for tier t = 1 .. 6: 1/(t+2) of a CU's
 // 160 KiB, i.e. room for t+2 resident workgroups per CU

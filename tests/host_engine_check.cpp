@@ -247,11 +247,46 @@ static void sizes_refused() {
     }
 }
 
+// Operators whose shells grow fast keep one order per launch where the overlap of the
+// tiles costs more than the launches that it saves; regular ones, and small ones,
+// which are bound by launches, take the chain or the wide pass.
+static void overlap() {
+    int blocked = 0, passes = 0;
+    fake::on_chain = fake::on_wide = [&](const ChainParams &, bool) { ++blocked; };
+    fake::on_pass = [&](bool) { ++passes; };
+    auto takes = [&](tbpm_hamiltonian *H, int S, bool expect) {
+        blocked = passes = 0;
+        propagate(H, S, 70);
+        CHECK((blocked > 0) == expect && (passes > 0) == !expect);
+        tbpm_hamiltonian_destroy(H);
+    };
+    takes(irregular(60000, true, 1), 8, false);
+    takes(irregular(6000, true, 1), 1, true);
+    takes(ring(60000, {1, 250}), 8, true);
+    takes(ring(60000, {1}), 1, true);
+    takes(irregular(20000, false, 20), 8, false);
+    takes(irregular(20000, false, 6), 16, false);
+    takes(ring(20000, {1, 2, 3, 140, 141, 142}), 16, true);
+    // and the Haydock recursion
+    tbpm_hamiltonian *H = irregular(120000, true, 1);
+    blocked = 0;
+    haydock(H, 8, 70);
+    CHECK(blocked == 0);
+    tbpm_hamiltonian_destroy(H);
+    H = ring(60000, {1, 250});
+    haydock(H, 8, 70);
+    CHECK(blocked > 0);
+    tbpm_hamiltonian_destroy(H);
+    fake::on_chain = fake::on_wide = nullptr;
+    fake::on_pass = nullptr;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
                                                            {"tables_kept", tables_kept},
-                                                           {"sizes_refused", sizes_refused}};
+                                                           {"sizes_refused", sizes_refused},
+                                                           {"overlap", overlap}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -67,3 +67,8 @@ def test_tables_are_kept_between_kinds_of_calls(checker):
 def test_refused_tile_sizes_are_remembered(checker):
     """A tile size that an operator's rows do not fit is not tried again by every call."""
     _run(checker, "sizes_refused")
+
+
+def test_irregular_operators_keep_one_order_per_launch(checker):
+    """The shapes on tiles with shells are taken where they are the faster ones, by a sample of the tiles."""
+    _run(checker, "overlap")
