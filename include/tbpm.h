@@ -532,8 +532,8 @@ tbpm_status tbpm_propagate_batched(tbpm_batch *B, const double *const *psi0, int
  *               and two blocks of states or more (two FP64 states, three FP32
  *               ones): a workgroup also keeps its rows' elements in registers
  *               and takes the blocks in turn, where a tile's rows reference few
- *               others; the library chooses the tiles, whatever the value and
- *               vec.  0: gather from global memory
+ *               others; the library chooses the tiles and their order,
+ *               whatever the value, vec and xcd_remap.  0: gather from global memory
  *   vec         states of a row each thread holds (1, 2 or 4; capped by the
  *               padded state count)
  *   fused       1 .. 6: evaluate several Clenshaw orders per launch.

@@ -331,6 +331,17 @@ double Engine::wide_plain_us(int32_t s_user, bool fp32) const {
     return std::max(3.5 + 0.36 * w, 2.0 + vec * (3.0 + 0.45 * w) / 5.4e6);
 }
 
+// The order in which a wide pass's workgroups take the tiles, whatever the
+// configuration's, which was chosen for another kernel: each XCD a contiguous range
+// (1) while a vector leaves the caches room for the others, and runs of 64 tiles in
+// turn (6) beyond (70 samples, orders 1, 3 and 6: cubic 60^3, 16 FP64 states, 55 MB
+// a vector, 52.2, 60.1 and 56.2 ms; bilayer 448^2, 16 FP32 states, 103 MB, 109.9,
+// 109.8 and 108.6; 16 FP64 states 231, 225 and 225; cubic 110^3, 16 FP64 states, 341
+// MB, 394, 377 and 370).
+int32_t Engine::wide_tile_order(const ChainShape &cs) const {
+    return 16 * mat.n_rows * cs.n_blk > ((int64_t)96 << 20) ? 6 : 1;
+}
+
 // One order of a wide operator per launch (wide.hip), for two blocks of states or
 // more.  Tiles of up to 256 rows: a time step of bilayer 192^2 (17 orders) takes 328
 // us with 16 FP32 states against 343 with 512-row tiles (two workgroups per CU

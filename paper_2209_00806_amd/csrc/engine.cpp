@@ -1030,7 +1030,7 @@ tbpm_status Engine::run(const RunArgs &a) {
             if (wide) {
                 const bool last = pl.kind == kPassLast || pl.kind == kPassLastNoB2;
                 ChainParams cp = chain_params(cs);
-                cp.xcd_remap = cfg.xcd_remap;
+                cp.xcd_remap = wide_tile_order(cs);
                 cp.bump = p == 0;
                 cp.local = -1;  // the counter stands at this step
                 cp.reverse = walk;
@@ -1496,7 +1496,7 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         TRY_HIP(ba.ensure(v.bytes), "alloc A");
         TRY_HIP(bb.ensure(v.bytes), "alloc B");
         ChainParams cp = chain_params(last_chain);
-        cp.xcd_remap = cfg.xcd_remap;
+        cp.xcd_remap = wide_tile_order(last_chain);
         cp.v = v.ptr;
         cp.coef = (const PassCoef *)coef.ptr;
         cp.counter = (int32_t *)counter.ptr;

@@ -166,6 +166,7 @@ struct Engine {
     bool chain_select(int64_t T, int32_t cap);
     tbpm_status wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const;
     tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs);
+    int32_t wide_tile_order(const ChainShape &cs) const;
     double wide_us(const ChainSample &s, int32_t n_blk) const;
     double wide_plain_us(int32_t s_user, bool fp32) const;
     bool chain_room(bool fp32, size_t need);

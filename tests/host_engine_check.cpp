@@ -281,12 +281,33 @@ static void overlap() {
     fake::on_pass = nullptr;
 }
 
+// The wide pass orders its tiles by the size of a vector, not by a configuration that
+// was chosen for the staged pass.
+static void wide_order() {
+    int order = -1;
+    fake::on_wide = [&](const ChainParams &p, bool) { order = p.xcd_remap; };
+    tbpm_hamiltonian *H = ring(20000, {1, 2, 3, 140, 141, 142});
+    for (int remap : {0, 3, 6}) {
+        const tbpm_launch_config c{2, remap, 0, 1, 2, 1, 0};
+        CHECK(tbpm_set_launch_config(H, TBPM_FP64, &c) == TBPM_OK);
+        propagate(H, 4, 5);
+        CHECK(order == 1);
+    }
+    tbpm_hamiltonian_destroy(H);
+    H = ring(110000, {1, 2, 3, 330, 331, 332});
+    propagate(H, 64, 70);
+    CHECK(order == 6);
+    tbpm_hamiltonian_destroy(H);
+    fake::on_wide = nullptr;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
                                                            {"tables_kept", tables_kept},
                                                            {"sizes_refused", sizes_refused},
-                                                           {"overlap", overlap}};
+                                                           {"overlap", overlap},
+                                                           {"wide_order", wide_order}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

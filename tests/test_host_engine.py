@@ -72,3 +72,8 @@ def test_refused_tile_sizes_are_remembered(checker):
 def test_irregular_operators_keep_one_order_per_launch(checker):
     """The shapes on tiles with shells are taken where they are the faster ones, by a sample of the tiles."""
     _run(checker, "overlap")
+
+
+def test_wide_pass_orders_its_tiles_by_size(checker):
+    """The order of the wide pass's tiles follows the size of a vector, whatever order is configured."""
+    _run(checker, "wide_order")
