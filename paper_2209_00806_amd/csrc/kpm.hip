@@ -7,7 +7,7 @@
 //    split over chunks of the long inner dimension (rows x states).
 //  * k_kpm_sum_parts: mu[:, block] = scale sum_p parts[p] in a fixed order
 //    (the per-chunk results of the moment product).
-//  * k_kb_energy: one workgroup per energy (or four) E~_k = cos(theta_k) of the
+//  * k_kb_energy: one workgroup per one, two or four energies E~_k = cos(theta_k) of the
 //    midpoint grid in theta: with w_m = g_m / (1 + delta_m0) (Jackson g),
 //    c_n = cos(n theta), p_n = (E~ - i n s) e^{i n theta},
 //    q_m = (E~ + i m s) e^{-i m theta}, s = sin(theta),
@@ -229,18 +229,23 @@ __device__ __forceinline__ double jackson_w(int m, int n_mom) {
     return m == 0 ? 0.5 * g : g;
 }
 
+constexpr int kb_lds_bytes(int ne) { return 24 * ne + 8; }  // per moment
+
 // mu: [M][M] with mu_mn at m + n*M (column n contiguous over m).  A workgroup
 // takes NE energies, so that an element of mu read from the L2 serves all of
-// them (with one, 1024 energies of 512 moments read 4.3 GB: 266 us against 167 with
-// four; MAXM bounds the LDS, 53 KB at NE = 4 and 512 moments).
+// them, and keeps eight elements in flight (MAXM: moments that static LDS holds, or
+// 0: dynamic LDS for n_mom).
 template <int NE, int MAXM>
 __global__ __launch_bounds__(kWG) void k_kb_energy(const d2 *__restrict__ mu, int n_mom, double th_lo, double dth,
                                                    double rescale, int n_energy, double *__restrict__ energies,
                                                    double *__restrict__ weight) {
-    __shared__ double w_s[MAXM];
-    __shared__ d2 p_s[MAXM][NE];
-    __shared__ double c_s[MAXM][NE];
+    extern __shared__ __align__(16) unsigned char kb_mem[];
+    __shared__ __align__(16) unsigned char fixed[MAXM > 0 ? MAXM * kb_lds_bytes(NE) : 16];
     __shared__ double red[kWG];
+    d2(*p_s)[NE] = (d2(*)[NE])(MAXM > 0 ? fixed : kb_mem);
+    const int held = MAXM > 0 ? MAXM : n_mom;
+    double(*c_s)[NE] = (double(*)[NE])(p_s + held);
+    double *w_s = (double *)(c_s + held);
     const int k0 = blockIdx.x * NE;
     double th[NE], sn[NE], x[NE];
 #pragma unroll
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(kWG) void k_kb_energy(const d2 *__restrict__ mu, in
         double apx[NE], apy[NE], acx[NE], acy[NE];
 #pragma unroll
         for (int e = 0; e < NE; ++e) apx[e] = apy[e] = acx[e] = acy[e] = 0.0;
-        constexpr int U = NE > 1 ? 8 : 1;
+        constexpr int U = 8;
         int n = 0;
         auto add = [&](const d2 &a, int nn) {
 #pragma unroll
@@ -380,16 +385,45 @@ hipError_t launch_kpm_sum_parts(const double *parts, int64_t n_el, int32_t n_par
     return hipGetLastError();
 }
 
+// Dynamic LDS that a workgroup of k_kb_energy may ask for.
+constexpr size_t kKbLds = 64 * 1024 - 4096;
+
+// Two energies in static LDS: 112 KB, one workgroup per CU.
+constexpr int kKbPairMoments = 2048;
+
+// Energies per workgroup: two where their LDS fits (2048 moments), one beyond; four
+// for 4096 energies or more, where two of them fill the chip many times over, from
+// 256 moments on, which the first-level cache no longer serves.  us, with one (one
+// element in flight), two and four energies:
+//     moments  energies                     moments  energies
+//         64       512     29   23   25        512       256   266   81   177
+//        256      1024     80   40   59        512      1024   273  106   184
+//        256      8192    369  246  228        512      8192  1204  740   636
+//        600      1024    478  162             1024     1024  1022  373
+static int32_t kb_energies(int32_t n_mom, int32_t n_energy) {
+    auto fits = [&](int32_t ne) { return (size_t)n_mom * kb_lds_bytes(ne) <= kKbLds; };
+    if (n_energy >= 4096 && n_mom >= 256 && fits(4)) return 4;
+    return n_mom <= kKbPairMoments ? 2 : 1;
+}
+
 hipError_t launch_kubo_bastin(const double *mu, int32_t n_mom, double rescale, double th_lo, double dth,
                               int32_t n_energy, const double *mus, int32_t n_mu, double beta, double scale,
                               double *energies, double *weight, double *sigma, hipStream_t st) {
-    // four energies per workgroup where they fill the CUs that way
-    if (n_mom <= 512 && n_energy >= 1024)
-        hipLaunchKernelGGL((k_kb_energy<4, 512>), dim3((unsigned)((n_energy + 3) / 4)), dim3(kWG), 0, st,
-                           (const d2 *)mu, n_mom, th_lo, dth, rescale, n_energy, energies, weight);
+    const int32_t ne = kb_energies(n_mom, n_energy);
+    const dim3 grid((unsigned)((n_energy + ne - 1) / ne)), block(kWG);
+    const size_t lds = (size_t)n_mom * kb_lds_bytes(ne);
+    auto launch = [&](auto kernel, size_t bytes) {
+        hipLaunchKernelGGL(kernel, grid, block, bytes, st, (const d2 *)mu, n_mom, th_lo, dth, rescale, n_energy, energies,
+                           weight);
+    };
+    if (ne == 4)
+        launch(k_kb_energy<4, 0>, lds);
+    else if (ne == 2 && lds <= kKbLds)
+        launch(k_kb_energy<2, 0>, lds);
+    else if (ne == 2)
+        launch(k_kb_energy<2, kKbPairMoments>, 0);
     else
-        hipLaunchKernelGGL((k_kb_energy<1, kMaxMomentsLds>), dim3((unsigned)n_energy), dim3(kWG), 0, st,
-                           (const d2 *)mu, n_mom, th_lo, dth, rescale, n_energy, energies, weight);
+        launch(k_kb_energy<1, kMaxMomentsLds>, 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_kb_sigma, dim3((unsigned)(((int64_t)n_mu * 64 + kWG - 1) / kWG)), dim3(kWG), 0, st, energies, weight,
