@@ -235,9 +235,13 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(si
 template <typename R, int VS>
 hipError_t launch_wide_t(int width, dim3 grid, dim3 block, size_t lds, const ChainParams &p, hipStream_t st) {
     switch (width) {
+        case 6: hipLaunchKernelGGL((k_pass_wide<R, 6, VS>), grid, block, lds, st, p); break;
         case 8: hipLaunchKernelGGL((k_pass_wide<R, 8, VS>), grid, block, lds, st, p); break;
+        case 10: hipLaunchKernelGGL((k_pass_wide<R, 10, VS>), grid, block, lds, st, p); break;
         case 12: hipLaunchKernelGGL((k_pass_wide<R, 12, VS>), grid, block, lds, st, p); break;
+        case 14: hipLaunchKernelGGL((k_pass_wide<R, 14, VS>), grid, block, lds, st, p); break;
         case 16: hipLaunchKernelGGL((k_pass_wide<R, 16, VS>), grid, block, lds, st, p); break;
+        case 18: hipLaunchKernelGGL((k_pass_wide<R, 18, VS>), grid, block, lds, st, p); break;
         case 20: hipLaunchKernelGGL((k_pass_wide<R, 20, VS>), grid, block, lds, st, p); break;
         case 22: hipLaunchKernelGGL((k_pass_wide<R, 22, VS>), grid, block, lds, st, p); break;
         case 24: hipLaunchKernelGGL((k_pass_wide<R, 24, VS>), grid, block, lds, st, p); break;
