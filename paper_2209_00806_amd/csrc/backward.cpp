@@ -68,15 +68,14 @@ tbpm_status backward_impl(tbpm_hamiltonian *H, const double *psi0, int32_t s_use
     const int32_t n_b = M - 2;  // stored b_1 .. b_{M-2} per step
     const size_t n_store = (size_t)(seg_len + 1) + (size_t)seg_len * n_b;
     const size_t gacc_bytes = (cplx ? 16 : 8) * (size_t)std::max<int64_t>(eng.mat.ell_size, 1);
-    bool chain = N >= 2 && (eng.cfgs[0].fused > 0 || (!eng.cfg_set[0] && N > kChainAutoSteps)) &&
-                 n_rows * s_pad < (int64_t)INT32_MAX && eng.chain_prepare(s_user, false, M - 1, cs, Engine::kUseAdjoint) == TBPM_OK;
-    if (chain) {
-        auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+    auto need = [&](const Engine::ChainShape &q, int64_t) {
         const size_t v1 = 16 * (size_t)n_rows * s_user;
-        chain = eng.chain_room(false, grow(eng.bwd_store, v1 * n_store) + grow(eng.bwd_adj, v1 * 5) +
-                                          grow(eng.phi0, v1) + grow(eng.bwd_gacc, gacc_bytes * cs.n_grp) +
-                                          grow(eng.bwd_gdiag, 8 * (size_t)n_rows * cs.n_grp));
-    }
+        return eng.bwd_store.growth(v1 * n_store) + eng.bwd_adj.growth(v1 * 5) + eng.phi0.growth(v1) +
+               eng.bwd_gacc.growth(gacc_bytes * q.n_grp) + eng.bwd_gdiag.growth(8 * (size_t)n_rows * q.n_grp);
+    };
+    const bool chain = N >= 2 && (eng.cfgs[0].fused > 0 || (!eng.cfg_set[0] && N > kChainAutoSteps)) &&
+                       n_rows * s_pad < (int64_t)INT32_MAX &&
+                       eng.chain_prepare(s_user, false, M - 1, cs, Engine::kUseAdjoint, need) == TBPM_OK;
     bool pairs = !chain && eng.cfgs[0].fused > 0 && M - 2 >= 2;
     int32_t pvs = 1, log2pvs = 0;
     while (pvs < eng.cfgs[0].vec && pvs < s_pad && pvs < 4) {

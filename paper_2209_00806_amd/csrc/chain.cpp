@@ -148,6 +148,7 @@ tbpm_status Engine::chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows,
     up(c.lidx, t.lidx.data(), sizeof(uint16_t) * t.lidx.size());
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();  // the caller goes on with another launch shape
+        c.release();
         return fail(TBPM_E_OOM, "no memory for the chain tables");
     }
     TRY_HIP(e, "upload chain tables");
@@ -261,7 +262,8 @@ double Engine::plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t
 // S = 1); 128 rows, 9 orders 14.3 us against 19.7 (L = 128); 512 rows, 6 orders
 // 182 us against 195 for 256 rows, 9 orders and 319 for 128 rows, 9 orders
 // (L = 512, S = 4).  One order per launch: 55, 63 and 531 us.
-tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use) {
+tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use,
+                                  const ChainNeed &need) {
     if (mat.max_width < 1 || mat.max_width > kChainWidth || n_orders < 2) return fail(TBPM_E_ARG, "rows too wide");
     cs.vs = fp32 && s_user > 1 ? 2 : 1;
     cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
@@ -284,13 +286,20 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         if (r.refused || r.depth < std::min(n_orders, 3)) continue;
         shape(r.sample.tiles, r.depth);
         if (chain_us(r.sample, cs, use) > plain_us(r.sample, s_user, fp32, n_orders, use, pairs)) continue;
-        if (!chain_select(T, cap)) {
+        const bool there = chain_select(T, cap);
+        if (there) shape(ch().n_tiles, ch().depth);
+        // looked at before the tables are built: near the limit every call would build them in vain
+        if (need && !chain_room(fp32, there ? nullptr : &r.sample, need(cs, there ? ch().n_tiles : r.sample.tiles))) {
+            chain_release();
+            return fail(TBPM_E_OOM, "no memory for the chain");
+        }
+        if (!there) {
             tbpm_status st = chain_build(T, cap, r.depth, rows, rows + rows / 4);
             r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
+            shape(ch().n_tiles, ch().depth);
         }
-        shape(ch().n_tiles, ch().depth);
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no chain tile fits");
@@ -348,7 +357,7 @@ int32_t Engine::wide_tile_order(const ChainShape &cs) const {
 // instead of four) and 372 with 128 rows; the staged pass takes 433.  With one block
 // there is nothing to share the matrix entries among (FP64, one state: 165 us
 // against 155 staged).
-tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
+tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, const ChainNeed &need) {
     cs.vs = fp32 ? 2 : 1;
     cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
     if (mat.max_width <= kChainWidth || mat.max_width > kWideWidth || mat.is_complex || cs.n_blk < 2 ||
@@ -362,7 +371,12 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
         ChainReach &r = chain_reach(T, 1);
         if (r.refused || r.sample.depth < 1) continue;
         if (wide_us(r.sample, cs.n_blk) > wide_plain_us(s_user, fp32)) continue;
-        if (!chain_select(T, 1)) {
+        const bool there = chain_select(T, 1);
+        if (need && !chain_room(fp32, there ? nullptr : &r.sample, need(cs, there ? ch().n_tiles : r.sample.tiles))) {
+            chain_release();
+            return fail(TBPM_E_OOM, "no memory for the wide pass");
+        }
+        if (!there) {
             tbpm_status st = chain_build(T, 1, 1, kWideThreads, kWideStage);
             r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
@@ -375,23 +389,39 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs) {
     return fail(TBPM_E_ARG, "no tile fits");
 }
 
-// room for `need` more bytes and the tiles' matrix entries
-bool Engine::chain_room(bool fp32, size_t need) {
-    auto grow = [](const DevBuf &b, size_t n) { return n > b.bytes ? n : (size_t)0; };
-    const size_t rb = fp32 ? 4 : 8;
-    need += grow(ch_tval, rb * (mat.is_complex ? 2 : 1) * (size_t)ch().n_local * chain_width()) +
-            grow(ch_tons, rb * (size_t)ch().n_local);
+// need bytes, and 256 MiB for everything else
+bool Engine::free_memory(size_t need) {
     if (need == 0) return true;
     size_t free_b = 0, total_b = 0;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + ((size_t)256 << 20) <= free_b;
 }
 
-bool Engine::chain_fits(const ChainShape &cs, bool fp32, size_t vec) {
-    auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
-    size_t need = grow(v, vec) + grow(ba, vec) + grow(phi0, vec * (fp32 ? 2 : 1));
-    if (cs.depths.size() > 1) need += grow(bb, vec) + grow(bc, vec);
-    if (cs.depths.size() > 2) need += grow(bd, vec);
-    return chain_room(fp32, need);
+void Engine::chain_release() {
+    for (ChainTab &t : ch_tab) t.release();
+    ch_tval.release();
+    ch_tons.release();
+    ch_sel = 0;
+    ++ch_stamp;
+}
+
+bool Engine::chain_room(bool fp32, const ChainSample *sample, size_t need) {
+    const double n = (double)mat.n_rows;
+    const size_t rb = fp32 ? 4 : 8;
+    const size_t n_local = sample ? (size_t)(n * sample->rows[sample->depth - 1]) : (size_t)ch().n_local;
+    need += ch_tval.growth(rb * (mat.is_complex ? 2 : 1) * n_local * chain_width()) + ch_tons.growth(rb * n_local);
+    if (sample)
+        need += (size_t)(4 * n * sample->rows[sample->depth]) + 2 * n_local * std::max(chain_width(), 4) +
+                (size_t)sample->tiles * (sizeof(TileDesc) + 4 * ((size_t)sample->depth + 3));
+    if (free_memory(need)) return true;
+    bool gave = ch_hist.bytes > 0;
+    ch_hist.release();
+    for (int32_t i = 0; i < kChainTabs; ++i)
+        if (ch_tab[i].depth > 0 && (sample || i != ch_sel)) {
+            ch_tab[i].release();
+            gave = true;
+        }
+    if (sample) ++ch_stamp;
+    return gave && free_memory(need);
 }
 
 // The tiles' copies of the matrix entries, from the values the handle holds now

@@ -616,12 +616,21 @@ tbpm_status Engine::run(const RunArgs &a) {
     bool chain, wide;
     if (lay == kLayoutFree) {
         const bool automatic = !cfg_set[fp32 ? 1 : 0] && a.n_steps > kChainAutoSteps;
-        chain = (fused || automatic) && chain_prepare(a.s_user, fp32, n_passes, cs) == TBPM_OK;
-        if (chain && !fused && !chain_fits(cs, fp32, esize * (size_t)mat.n_rows * s_pad)) chain = false;
+        const size_t vec = esize * (size_t)mat.n_rows * s_pad;
+        auto need = [&](const ChainShape &s, int64_t nt) {
+            const size_t parts = sizeof(double) * 3 * (size_t)nt * s_pad * kStepsPerGraph;
+            size_t b = v.growth(vec) + ba.growth(vec) + phi0.growth(16 * (size_t)mat.n_rows * s_pad) +
+                       partials.growth(parts) + (a.jc_states > 0 ? jc_part.growth(parts) : 0);
+            if (s.depths.size() > 1) b += bb.growth(vec) + bc.growth(vec);
+            if (s.depths.size() > 2) b += bd.growth(vec);
+            return b;
+        };
+        chain = (fused || automatic) && chain_prepare(a.s_user, fp32, n_passes, cs, kUseClenshaw, need) == TBPM_OK;
         // operators of wider rows: a pass that keeps the rows' entries in registers, in
-        // place of the staged pass, and where nobody chose a configuration
-        wide = !chain && (staged || (!fused && automatic)) && wide_prepare(a.s_user, fp32, cs) == TBPM_OK &&
-               chain_room(fp32, 0);
+        // place of the staged pass, and where nobody chose a configuration; it takes
+        // the vectors of the pass that it replaces
+        auto tables = [](const ChainShape &, int64_t) { return (size_t)0; };
+        wide = !chain && (staged || (!fused && automatic)) && wide_prepare(a.s_user, fp32, cs, tables) == TBPM_OK;
     } else {
         chain = lay == kLayoutChain;
         wide = lay == kLayoutWide;
@@ -665,7 +674,7 @@ tbpm_status Engine::run(const RunArgs &a) {
     // Without the memory for it the accumulation runs after every step.
     const size_t hist_vec = esize * (size_t)n_el;
     bool hist = chain && (a.n_qe > 0 || a.jc_states > 0) && a.n_steps > 1;
-    if (hist && chain_room(fp32, hist_vec * kHistSteps > ch_hist.bytes ? hist_vec * kHistSteps : 0)) {
+    if (hist && free_memory(ch_hist.growth(hist_vec * kHistSteps))) {
         hipError_t he = ch_hist.ensure(hist_vec * kHistSteps);
         if (he == hipErrorOutOfMemory) (void)hipGetLastError();
         hist = he == hipSuccess;
@@ -1231,7 +1240,9 @@ tbpm_status Engine::run(const RunArgs &a) {
 bool Engine::series_chain(int32_t K, int32_t s_user, ChainShape &cs) {
     // as for propagations: 17 orders stand for a time step
     const bool want = cfgs[0].fused > 0 || (!cfg_set[0] && K - 1 > 17 * kChainAutoSteps);
-    return want && K >= 4 && chain_prepare(s_user, false, K - 1, cs) == TBPM_OK;
+    // (its vectors are there)
+    auto tables = [](const ChainShape &, int64_t) { return (size_t)0; };
+    return want && K >= 4 && chain_prepare(s_user, false, K - 1, cs, kUseClenshaw, tables) == TBPM_OK;
 }
 
 tbpm_status Engine::apply_series(const std::vector<double> &a_in, double f, int32_t log2s, const void *src, void *dst,
@@ -1461,7 +1472,6 @@ tbpm_status Engine::bench_pass(int32_t s_user, bool fp32, int32_t n_launch, hipS
         ChainShape cs;
         tbpm_status s = chain ? chain_prepare(last_s_user, fp32, last_orders, cs) : wide_prepare(last_s_user, fp32, cs);
         if (s != TBPM_OK) return s;
-        if (!chain_room(fp32, 0)) return fail(TBPM_E_OOM, "no memory for the chain tables");
         s = chain_values(fp32, stream);
         if (s != TBPM_OK) return s;
         last_chain = cs;

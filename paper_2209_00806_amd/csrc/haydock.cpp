@@ -105,13 +105,12 @@ tbpm_status Engine::haydock(const double *psi0, int32_t s_user, int32_t n_iter, 
     // Operators of up to four elements per row take one iteration per launch, under
     // the rule of the propagation.
     ChainShape cs;
-    bool chain = (cfgs[0].fused > 0 || (!cfg_set[0] && n_iter > kChainAutoSteps)) &&
-                 chain_prepare(s_user, false, 17, cs, kUseHaydock) == TBPM_OK;
-    if (chain) {
-        auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
+    auto need = [&](const ChainShape &, int64_t) {
         const size_t v1 = 16 * (size_t)n * s_user;
-        chain = chain_room(false, grow(hay_u, 2 * v1) + grow(hay_y, v1));
-    }
+        return hay_u.growth(2 * v1) + hay_y.growth(v1);
+    };
+    const bool chain = (cfgs[0].fused > 0 || (!cfg_set[0] && n_iter > kChainAutoSteps)) &&
+                       chain_prepare(s_user, false, 17, cs, kUseHaydock, need) == TBPM_OK;
     if (chain) return haydock_chain(cs, psi0, s_user, n_iter, thr, a_out, b_out, flags, st);
     // tiles and tile order of the FP64 launch configuration (the kernels take
     // one state per thread whatever its states per thread)

@@ -40,16 +40,14 @@ tbpm_status Engine::kpm_moments(const double *ja, const double *jb, const double
     // stores alone, 8.6 GB, take 1.8 ms at the rate of a copy), 12.0 ms with two
     // orders per launch and the operator in launches of its own.
     ChainShape cs;
-    bool chain = n_mom >= 3 &&
-                 (cfgs[0].fused > 0 || (!cfg_set[0] && 2 * (int64_t)n_mom > 17 * (int64_t)kChainAutoSteps)) &&
-                 chain_prepare(s_user, false, n_mom - 1, cs, kUseMoments) == TBPM_OK;
-    if (chain) {
+    auto chain_need = [&](const ChainShape &, int64_t) {
         const size_t vs1 = 16 * (size_t)n * s_user + 768, nbc = (size_t)std::min<int32_t>(n_mom, 128);
-        auto grow = [](const DevBuf &b, size_t need) { return need > b.bytes ? need : (size_t)0; };
         // 1 GiB for the product's parts at the most common sizes
-        chain = chain_room(false, grow(kp_store, vs1 * n_mom) + grow(kp_rblk, vs1 * nbc) + grow(kp_vec, vs1 * 5) +
-                                      ((size_t)1 << 30));
-    }
+        return kp_store.growth(vs1 * n_mom) + kp_rblk.growth(vs1 * nbc) + kp_vec.growth(vs1 * 5) + ((size_t)1 << 30);
+    };
+    const bool chain = n_mom >= 3 &&
+                       (cfgs[0].fused > 0 || (!cfg_set[0] && 2 * (int64_t)n_mom > 17 * (int64_t)kChainAutoSteps)) &&
+                       chain_prepare(s_user, false, n_mom - 1, cs, kUseMoments, chain_need) == TBPM_OK;
     const int64_t K = n * (chain ? s_user : s_pad);  // inner dimension of the moment product
     const int32_t nb = std::min<int32_t>(n_mom, 128);
     const size_t vec = sizeof(double) * 2 * (size_t)K;

@@ -7,6 +7,7 @@
 
 #include <complex>
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -58,6 +59,8 @@ struct DevBuf {
     size_t bytes = 0;
     hipError_t ensure(size_t need);
     void release();
+    // bytes that ensure(need) takes of the free memory (the old block is given back first)
+    size_t growth(size_t need) const { return need > bytes ? need - bytes : 0; }
 };
 
 struct PinnedBuf {
@@ -151,26 +154,31 @@ struct Engine {
     // what the orders of a chain are for; it decides what a launch reads and writes
     // beside b_{j+1} and b_{j+2}, and what the same costs without the chain
     enum ChainUse { kUseClenshaw, kUseMoments, kUseHaydock, kUseAdjoint };
-    // tables and launch sequence for n_orders orders on s_user states;
-    // TBPM_E_ARG if the operator does not suit the kernel
-    tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use = kUseClenshaw);
+    // bytes that a call with this shape and these tiles allocates beside the tables; none: the memory is not looked at
+    using ChainNeed = std::function<size_t(const ChainShape &, int64_t n_tiles)>;
+    // tables and launch sequence for n_orders orders on s_user states; TBPM_E_ARG if
+    // the operator does not suit the kernel, TBPM_E_OOM if the tables and what the call
+    // needs do not fit the free memory (the handle then holds no tables)
+    tbpm_status chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use = kUseClenshaw,
+                              const ChainNeed &need = nullptr);
     // workgroups that the chip holds: two per CU, three of complex operators
     // (hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
     int32_t chain_slots() const { return mat.is_complex ? 768 : 512; }
     double chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use) const;
     double plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t n_orders, ChainUse use, bool pairs) const;
-    // whether the vectors (vec bytes each) and tables that the chain needs beyond
-    // the ones held fit the device memory that is free
     // selects the tables of (T, cap), made for D orders if they are not there
     tbpm_status chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows);
     bool chain_select(int64_t T, int32_t cap);
     tbpm_status wide_launch(bool fp32, const ChainShape &cs, ChainParams &p, hipStream_t st) const;
-    tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs);
+    tbpm_status wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, const ChainNeed &need = nullptr);
     int32_t wide_tile_order(const ChainShape &cs) const;
     double wide_us(const ChainSample &s, int32_t n_blk) const;
     double wide_plain_us(int32_t s_user, bool fp32) const;
-    bool chain_room(bool fp32, size_t need);
-    bool chain_fits(const ChainShape &cs, bool fp32, size_t vec);
+    // whether the memory holds the tables of `sample`'s tiles (null: those in use) with
+    // their matrix entries and the call's need; tables not in use, and the kept states, make way
+    bool chain_room(bool fp32, const ChainSample *sample, size_t need);
+    static bool free_memory(size_t need);
+    void chain_release();
     tbpm_status chain_values(bool fp32, hipStream_t st);
     ChainParams chain_params(const ChainShape &cs) const;
     tbpm_status chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const;

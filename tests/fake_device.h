@@ -196,8 +196,9 @@ hipError_t launch_pack(const double *, const double *, int64_t, int32_t, int32_t
 hipError_t launch_jcorr(bool, const TileDesc *, int32_t, int32_t, int32_t, int32_t, int64_t, const void *,
                         const uint32_t *, const int32_t *, const double *, double *, int32_t, int64_t, int64_t,
                         hipStream_t) OK_
-hipError_t launch_fermi_cheb(double, double, double, int32_t, double, double *, double *, int32_t *last, hipStream_t) {
-    *last = 40;
+// 1500 coefficients, from 16384 samples on
+hipError_t launch_fermi_cheb(double, double, double, int32_t n, double, double *, double *, int32_t *last, hipStream_t) {
+    *last = n >= 16384 ? 1499 : n / 2 - 1;
     return hipSuccess;
 }
 hipError_t launch_ac_cond(const double *, int32_t, int32_t, double, double, double, int, double *, double *,

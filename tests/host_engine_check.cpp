@@ -301,13 +301,104 @@ static void wide_order() {
     fake::on_wide = nullptr;
 }
 
+static std::vector<double> current(const tbpm_hamiltonian *H) {
+    std::vector<double> j(2 * (size_t)H->csr.nnz(), 0.0);
+    for (int64_t r = 0; r < H->csr.n; ++r)
+        for (int64_t p = H->csr.row_ptr[r]; p < H->csr.row_ptr[r + 1]; ++p) j[2 * p + 1] = H->csr.col[p] > r ? 1.0 : -1.0;
+    return j;
+}
+
+// Without room for the chain's or the wide pass's tables and vectors every call goes
+// on with another shape, keeps none of the tables, and does not build them in vain.
+static void no_room() {
+    int blocked = 0, values = 0;
+    fake::on_chain = fake::on_wide = [&](const ChainParams &, bool) { ++blocked; };
+    fake::on_values = [&](bool, int) { ++values; };
+    for (int cfg = 0; cfg < 3; ++cfg)  // nobody chose a configuration; fused; staged, wide rows
+        for (int method = 0; method < (cfg == 2 ? 1 : 5); ++method) {
+            tbpm_hamiltonian *H = ring(20000, cfg == 2 ? std::vector<int64_t>{1, 2, 3, 140, 141, 142}
+                                                       : std::vector<int64_t>{1, 140});
+            const int64_t n = H->csr.n;
+            const int S = 4;
+            if (cfg == 1) config(H, TBPM_FP64, 2);
+            if (cfg == 2) config(H, TBPM_FP64, 0, 2);
+            const std::vector<double> j = current(H);
+            Dev psi(2 * n * S), mu(2 * 600 * 600), corr(2 * 70 * (size_t)S), gv(2 * j.size()), go(n), ck(2 * n * S * 80);
+            auto call = [&]() -> tbpm_status {
+                if (method == 0) return propagate(H, S, 70), TBPM_OK;
+                if (method == 1) return haydock(H, S, 70), TBPM_OK;
+                if (method == 2)
+                    return tbpm_kpm_moments(H, j.data(), j.data(), psi.p, S, 600, 5.0, mu.p, nullptr, nullptr);
+                if (method == 3)
+                    return tbpm_ac_corr(H, j.data(), j.data(), psi.p, S, 70, 0.6, 5.0, 1e-14, 10.0, 0.0, 1e-12, TBPM_FP64,
+                                        corr.p, 0, nullptr);
+                return tbpm_backward(H, psi.p, S, 70, 0.6, 5.0, 1e-14, corr.p, 10, ck.p, gv.p, go.p, nullptr);
+            };
+            blocked = values = 0;
+            CHECK(call() == TBPM_OK && blocked > 0 && values > 0);
+            tbpm_hamiltonian_destroy(H);
+            // a new handle
+            H = ring(20000, cfg == 2 ? std::vector<int64_t>{1, 2, 3, 140, 141, 142} : std::vector<int64_t>{1, 140});
+            if (cfg == 1) config(H, TBPM_FP64, 2);
+            if (cfg == 2) config(H, TBPM_FP64, 0, 2);
+            // the moments look at the memory for their own vectors: leave them enough, but
+            // not the 1 GiB more that the chain asks for
+            fake::hidden = fake::total - fake::used - (method == 2 ? (size_t)1900 << 20 : 0);
+            blocked = values = 0;
+            for (int again = 0; again < 2; ++again) {
+                CHECK(call() == TBPM_OK);
+                CHECK(blocked == 0 && values == 0);
+                CHECK(H->eng.ch_tval.bytes == 0);
+            }
+            fake::hidden = 0;
+            tbpm_hamiltonian_destroy(H);
+        }
+    fake::on_chain = fake::on_wide = nullptr;
+    fake::on_values = nullptr;
+}
+
+// The room asked for before a propagation takes the chain is what it then allocates,
+// the correlation partials of a graph's steps among it.
+static void room_is_what_it_takes() {
+    const int64_t n = 40000;
+    const int S = 64;
+    for (int old = 0; old < 2; ++old) {
+        // a new handle, and one that ran with fewer states before
+        tbpm_hamiltonian *H = ring(n, {1, 200});
+        if (old) propagate(H, 16, 70);
+        const size_t used = fake::used;
+        propagate(H, S, 70);
+        const size_t need = fake::used - used;
+        tbpm_hamiltonian_destroy(H);
+        for (int more = 0; more < 2; ++more) {
+            H = ring(n, {1, 200});
+            if (old) propagate(H, 16, 70);
+            int blocked = 0;
+            fake::on_chain = [&](const ChainParams &, bool) { ++blocked; };
+            const int64_t n_el = 2 * n * S + 2 * 70 * S;  // the caller's psi0 and correlation
+            fake::hidden = fake::total - fake::used - need - ((size_t)256 << 20) - 8 * (size_t)n_el;
+            if (more)
+                fake::hidden -= (size_t)1 << 20;
+            else
+                fake::hidden += (size_t)1 << 20;
+            propagate(H, S, 70);
+            CHECK((blocked > 0) == (more == 1));
+            fake::hidden = 0;
+            fake::on_chain = nullptr;
+            tbpm_hamiltonian_destroy(H);
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
                                                            {"tables_kept", tables_kept},
                                                            {"sizes_refused", sizes_refused},
                                                            {"overlap", overlap},
-                                                           {"wide_order", wide_order}};
+                                                           {"wide_order", wide_order},
+                                                           {"no_room", no_room},
+                                                           {"room_is_what_it_takes", room_is_what_it_takes}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

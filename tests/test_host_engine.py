@@ -77,3 +77,14 @@ def test_irregular_operators_keep_one_order_per_launch(checker):
 def test_wide_pass_orders_its_tiles_by_size(checker):
     """The order of the wide pass's tiles follows the size of a vector, whatever order is configured."""
     _run(checker, "wide_order")
+
+
+def test_calls_without_room_for_tables_go_on(checker):
+    """Without free memory for the tables of the chain or the wide pass, every method goes on with another shape
+    and keeps none of them."""
+    _run(checker, "no_room")
+
+
+def test_room_asked_for_is_what_a_run_takes(checker):
+    """The guard before a propagation on tiles counts what the run then allocates, to 1 MiB."""
+    _run(checker, "room_is_what_it_takes")
