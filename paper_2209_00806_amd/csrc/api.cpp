@@ -471,6 +471,7 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_hamiltonian *H, const double *psi0, int3
     if (flags & TBPM_FLAG_ASYNC) return TBPM_OK;
     e = hipStreamSynchronize(hs);
     if (e != hipSuccess) return hip_fail(e, "stream synchronize");
+    eng.trim_states();
     return TBPM_OK;
 }
 
@@ -619,7 +620,9 @@ tbpm_status tbpm_ac_corr(tbpm_hamiltonian *H, const double *j_alpha, const doubl
         r.jc_corr = corr;
         r.flags = flags;
         r.stream = hs;
-        return eng.run(r);
+        st = eng.run(r);
+        if (!(flags & TBPM_FLAG_ASYNC)) eng.trim_states();
+        return st;
     } catch (const std::bad_alloc &) {
         return fail(TBPM_E_OOM, "host allocation failed");
     }

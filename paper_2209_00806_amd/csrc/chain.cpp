@@ -404,6 +404,13 @@ void Engine::chain_release() {
     ++ch_stamp;
 }
 
+// 512 MiB: a call on larger vectors (64 MiB each) takes hundreds of microseconds per
+// time step, beside which allocating them again does not count.
+void Engine::trim_states() {
+    constexpr size_t kHistKeep = (size_t)512 << 20;
+    if (ch_hist.bytes > kHistKeep) ch_hist.release();
+}
+
 bool Engine::chain_room(bool fp32, const ChainSample *sample, size_t need) {
     const double n = (double)mat.n_rows;
     const size_t rb = fp32 ? 4 : 8;

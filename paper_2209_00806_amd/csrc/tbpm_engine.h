@@ -179,6 +179,8 @@ struct Engine {
     bool chain_room(bool fp32, const ChainSample *sample, size_t need);
     static bool free_memory(size_t need);
     void chain_release();
+    // after a call that kept the states of several steps: memory beyond kHistKeep is given back
+    void trim_states();
     tbpm_status chain_values(bool fp32, hipStream_t st);
     ChainParams chain_params(const ChainShape &cs) const;
     tbpm_status chain_launch(bool fp32, const ChainShape &cs, const ChainParams &p, hipStream_t st) const;

@@ -390,6 +390,29 @@ static void room_is_what_it_takes() {
     }
 }
 
+// The states of several time steps, which the accumulations of quasi-eigenstate and
+// optical calls read together, do not stay on the handle where they are large.
+static void states_given_back() {
+    const int64_t n = 80000;
+    for (int S : {4, 64}) {
+        const size_t hist = 8 * 16 * (size_t)n * S, keep = (size_t)512 << 20;
+        tbpm_hamiltonian *H = ring(n, {1, 250});
+        Dev psi(2 * n * S), states(2 * n * (size_t)S), corr(2 * 70 * (size_t)S);
+        size_t most = 0;
+        fake::on_qe_accum = [&](int64_t, int64_t) { most = std::max(most, H->eng.ch_hist.bytes); };
+        const double en = 0.3;
+        CHECK(tbpm_quasi_eigenstates(H, psi.p, S, 70, 0.5, 5.0, 1e-14, TBPM_FP64, &en, 1, TBPM_WIN_HANN, states.p, nullptr,
+                                     0, nullptr) == TBPM_OK);
+        CHECK(most == hist && H->eng.ch_hist.bytes == (hist > keep ? 0 : hist));
+        const std::vector<double> j = current(H);
+        CHECK(tbpm_ac_corr(H, j.data(), j.data(), psi.p, S / 2, 70, 0.6, 5.0, 1e-14, 10.0, 0.0, 1e-12, TBPM_FP64, corr.p, 0,
+                           nullptr) == TBPM_OK);
+        CHECK(H->eng.ch_hist.bytes == (hist > keep ? 0 : hist));
+        fake::on_qe_accum = nullptr;
+        tbpm_hamiltonian_destroy(H);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
@@ -398,7 +421,8 @@ int main(int argc, char **argv) {
                                                            {"overlap", overlap},
                                                            {"wide_order", wide_order},
                                                            {"no_room", no_room},
-                                                           {"room_is_what_it_takes", room_is_what_it_takes}};
+                                                           {"room_is_what_it_takes", room_is_what_it_takes},
+                                                           {"states_given_back", states_given_back}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

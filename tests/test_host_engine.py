@@ -88,3 +88,8 @@ def test_calls_without_room_for_tables_go_on(checker):
 def test_room_asked_for_is_what_a_run_takes(checker):
     """The guard before a propagation on tiles counts what the run then allocates, to 1 MiB."""
     _run(checker, "room_is_what_it_takes")
+
+
+def test_kept_states_are_given_back(checker):
+    """Large states of several time steps do not stay on a handle after the call that kept them."""
+    _run(checker, "states_given_back")
