@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <new>
 #include <thread>
 
 #include "tbpm_engine.h"
@@ -263,7 +264,7 @@ double Engine::plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t
 // 182 us against 195 for 256 rows, 9 orders and 319 for 128 rows, 9 orders
 // (L = 512, S = 4).  One order per launch: 55, 63 and 531 us.
 tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, ChainShape &cs, ChainUse use,
-                                  const ChainNeed &need) {
+                                  const ChainNeed &need) try {
     if (mat.max_width < 1 || mat.max_width > kChainWidth || n_orders < 2) return fail(TBPM_E_ARG, "rows too wide");
     cs.vs = fp32 && s_user > 1 ? 2 : 1;
     cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
@@ -303,6 +304,8 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no chain tile fits");
+} catch (const std::bad_alloc &) {
+    return fail(TBPM_E_OOM, "no host memory for the chain tables");  // the caller goes on with another launch shape
 }
 
 static int32_t wide_groups(int32_t n_blk, int64_t n_tiles) {
@@ -357,7 +360,7 @@ int32_t Engine::wide_tile_order(const ChainShape &cs) const {
 // instead of four) and 372 with 128 rows; the staged pass takes 433.  With one block
 // there is nothing to share the matrix entries among (FP64, one state: 165 us
 // against 155 staged).
-tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, const ChainNeed &need) {
+tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, const ChainNeed &need) try {
     cs.vs = fp32 ? 2 : 1;
     cs.n_blk = (s_user + cs.vs - 1) / cs.vs;
     if (mat.max_width <= kChainWidth || mat.max_width > kWideWidth || mat.is_complex || cs.n_blk < 2 ||
@@ -387,6 +390,8 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, cons
         return TBPM_OK;
     }
     return fail(TBPM_E_ARG, "no tile fits");
+} catch (const std::bad_alloc &) {
+    return fail(TBPM_E_OOM, "no host memory for the wide pass's tables");
 }
 
 // need bytes, and 256 MiB for everything else

@@ -19,7 +19,6 @@ size_t total = (size_t)1 << 40, used = 0;
 size_t hidden = 0;  // bytes that hipMemGetInfo holds back (taken by others)
 std::map<void *, size_t> blocks;
 int uploads = 0;              // synchronous copies to the device
-bool device_alloc = false;    // inside an allocation of device memory
 std::function<void(const tbpm::InitParams &)> on_init;
 std::function<void(int64_t n_el, int64_t n_used)> on_qe_accum;
 std::function<void(int log2s, int log2sb)> on_qe_finalize;
@@ -42,9 +41,7 @@ hipError_t hipMalloc(void **p, size_t n) {
         *p = nullptr;
         return hipErrorOutOfMemory;
     }
-    fake::device_alloc = true;
     *p = std::calloc(1, n ? n : 1);
-    fake::device_alloc = false;
     if (!*p) return hipErrorOutOfMemory;
     fake::blocks[*p] = n;
     fake::used += n;

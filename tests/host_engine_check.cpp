@@ -1,17 +1,32 @@
 // CPU checks of the library's launch decisions on a device made of host memory.
 //   host_engine_check NAME
 #include <cmath>
+#include <new>
 
 #include "fake_device.h"
 
-// the sanitizer's hook on every host allocation
-extern "C" int __sanitizer_install_malloc_and_free_hooks(void (*)(const volatile void *, size_t),
-                                                         void (*)(const volatile void *));
-// host allocations of at least big_size bytes that are not the device's memory
+// host allocations of at least big_size bytes are counted, and fail if no_big
 static size_t big_size = SIZE_MAX;
 static int big_count = 0;
-static void note_alloc(const volatile void *, size_t n) { big_count += n >= big_size && !fake::device_alloc; }
-static void note_free(const volatile void *) {}
+static bool no_big = false;
+static void *take(size_t n) {
+    if (n >= big_size) {
+        ++big_count;
+        if (no_big) return nullptr;
+    }
+    return std::malloc(n ? n : 1);
+}
+void *operator new(size_t n) {
+    if (void *p = take(n)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept { return take(n); }
+void *operator new[](size_t n) { return operator new(n); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+void operator delete(void *p, const std::nothrow_t &) noexcept { std::free(p); }
+void operator delete[](void *p) noexcept { std::free(p); }
+void operator delete[](void *p, size_t) noexcept { std::free(p); }
 
 using namespace tbpm;
 
@@ -232,7 +247,6 @@ static void tables_kept() {
 // not look at the rows again (an array of all rows would be allocated).
 static void sizes_refused() {
     const int64_t n = 12000;
-    CHECK(__sanitizer_install_malloc_and_free_hooks(note_alloc, note_free));
     for (int kind = 0; kind < 3; ++kind) {
         tbpm_hamiltonian *H = kind == 0 ? irregular(n, true, 1) : (kind == 1 ? irregular(n, true, 2) : irregular(n, false, 24));
         for (int S : {1, 8}) {
@@ -413,6 +427,28 @@ static void states_given_back() {
     }
 }
 
+// Without the host memory for tile tables a call goes on with another shape, and a
+// later one takes the tiles.
+static void no_host_memory() {
+    const int64_t n = 20000;
+    int blocked = 0;
+    fake::on_chain = fake::on_wide = [&](const ChainParams &, bool) { ++blocked; };
+    for (bool wide : {false, true}) {
+        tbpm_hamiltonian *H = ring(n, wide ? std::vector<int64_t>{1, 2, 3, 140, 141, 142} : std::vector<int64_t>{1, 140});
+        for (bool fails : {true, false}) {
+            big_size = 4 * (size_t)n;
+            no_big = fails;
+            blocked = 0;
+            propagate(H, 8, 70);
+            no_big = false;
+            big_size = SIZE_MAX;
+            CHECK((blocked > 0) == !fails);
+        }
+        tbpm_hamiltonian_destroy(H);
+    }
+    fake::on_chain = fake::on_wide = nullptr;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
@@ -422,7 +458,8 @@ int main(int argc, char **argv) {
                                                            {"wide_order", wide_order},
                                                            {"no_room", no_room},
                                                            {"room_is_what_it_takes", room_is_what_it_takes},
-                                                           {"states_given_back", states_given_back}};
+                                                           {"states_given_back", states_given_back},
+                                                           {"no_host_memory", no_host_memory}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

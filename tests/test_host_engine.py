@@ -93,3 +93,8 @@ def test_room_asked_for_is_what_a_run_takes(checker):
 def test_kept_states_are_given_back(checker):
     """Large states of several time steps do not stay on a handle after the call that kept them."""
     _run(checker, "states_given_back")
+
+
+def test_calls_without_host_memory_for_tables_go_on(checker):
+    """Where the host cannot allocate the tile tables, a call goes on with another shape."""
+    _run(checker, "no_host_memory")
