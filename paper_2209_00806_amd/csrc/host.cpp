@@ -704,7 +704,7 @@ int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int
     while (D > 0 && !tiles.empty()) {
         const Tile t = std::move(tiles.back());
         tiles.pop_back();
-        if (t.reached < D && t.td.rows >= 8) {
+        if (t.reached < D && t.td.rows >= 2) {
             const int32_t half = t.td.rows / 2;
             tiles.push_back(walk(TileDesc{t.td.row0 + half, t.td.rows - half, t.td.inst}, D));
             tiles.push_back(walk(TileDesc{t.td.row0, half, t.td.inst}, D));
@@ -771,7 +771,7 @@ void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32
                 const bool fits = chain_shells(slice_off, col, inst_row0, orders, td, D, max_eval, max_rows, tag,
                                                ++visit, rows, c, reached);
                 if (!fits) {
-                    if (td.rows < 8) {
+                    if (td.rows < 2) {
                         pt.ok = false;
                         return;
                     }

@@ -449,6 +449,34 @@ static void no_host_memory() {
     fake::on_chain = fake::on_wide = nullptr;
 }
 
+// Square lattices take the chain at any size: tiles of rows that lie apart, where
+// a member's order ends, are halved as far as it takes.
+static void scattered_tiles() {
+    for (int64_t nx : {61, 100, 181}) {
+        const int64_t ny = nx == 181 ? 170 : nx, n = nx * ny;
+        std::vector<int64_t> rp{0};
+        std::vector<int32_t> col;
+        for (int64_t y = 0; y < ny; ++y)
+            for (int64_t x = 0; x < nx; ++x) {
+                if (y > 0) col.push_back((int32_t)((y - 1) * nx + x));
+                if (x > 0) col.push_back((int32_t)(y * nx + x - 1));
+                if (x + 1 < nx) col.push_back((int32_t)(y * nx + x + 1));
+                if (y + 1 < ny) col.push_back((int32_t)((y + 1) * nx + x));
+                rp.push_back((int64_t)col.size());
+            }
+        std::vector<double> val(2 * col.size(), 0.0), on(n, 0.1);
+        for (size_t q = 0; q < col.size(); ++q) val[2 * q] = -1.0;
+        tbpm_hamiltonian *H = nullptr;
+        CHECK(tbpm_hamiltonian_create(n, rp.data(), col.data(), val.data(), on.data(), 0, &H) == TBPM_OK);
+        int blocked = 0;
+        fake::on_chain = [&](const ChainParams &, bool) { ++blocked; };
+        propagate(H, 1, 70);
+        CHECK(blocked > 0);
+        fake::on_chain = nullptr;
+        tbpm_hamiltonian_destroy(H);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
@@ -459,7 +487,8 @@ int main(int argc, char **argv) {
                                                            {"no_room", no_room},
                                                            {"room_is_what_it_takes", room_is_what_it_takes},
                                                            {"states_given_back", states_given_back},
-                                                           {"no_host_memory", no_host_memory}};
+                                                           {"no_host_memory", no_host_memory},
+                                                           {"scattered_tiles", scattered_tiles}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -98,3 +98,8 @@ def test_kept_states_are_given_back(checker):
 def test_calls_without_host_memory_for_tables_go_on(checker):
     """Where the host cannot allocate the tile tables, a call goes on with another shape."""
     _run(checker, "no_host_memory")
+
+
+def test_tiles_of_scattered_rows_are_halved_as_far_as_it_takes(checker):
+    """A few tiles of rows that lie apart do not keep an operator from the chain."""
+    _run(checker, "scattered_tiles")
