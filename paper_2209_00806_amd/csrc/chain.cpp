@@ -193,12 +193,15 @@ static double chain_rounds(int64_t groups, int32_t slots) {
     return x <= 0.9 ? 1.0 : x + 0.5;  // the last round is partial, and the number of groups an estimate
 }
 
-double Engine::chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use) const {
+double Engine::chain_us(const ChainSample &s, const ChainShape &cs, bool fp32, ChainUse use) const {
     const double n16 = 16.0 * (double)mat.n_rows, vec = n16 * cs.n_blk, rate = 5.4e6;  // bytes per us
     // bytes of matrix entries and local indices per evaluated row, in rows
     const double tab = (8.0 + 8.0 + (mat.is_complex ? 16.0 : 8.0) * chain_width()) / 16.0;
     const int32_t grp_blk = (cs.n_blk + cs.n_grp - 1) / cs.n_grp, groups = (cs.n_blk + grp_blk - 1) / grp_blk;
     const double rounds = chain_rounds(s.tiles * groups, chain_slots()) * grp_blk;
+    // FP64 kernels for real rows of four elements spill a little (a tenth of their registers)
+    const double spill = !fp32 && !mat.is_complex && chain_width() > 3 ? 1.35 : 1.0;
+    auto order_us = [&](int32_t d) { return (3.0 + 0.35 * d) * spill; };
     // the adjoint's kernel keeps more in registers, and spills with four elements per row
     auto adjoint_us = [&](int32_t d) { return (4.0 + 0.5 * d) * (chain_width() <= 3 ? 1.0 : (mat.is_complex ? 1.4 : 2.0)); };
     auto launch = [&](int32_t d, double eval_streams, double own_rows, double block_us) {
@@ -209,11 +212,11 @@ double Engine::chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use
     if (use == kUseHaydock) return 4.6 + launch(2, 1, 1, 2.0);  // u_{i-1} is read one hop out; and the sums
     double us = 0.0;
     for (const int32_t d : cs.depths) {
-        if (use == kUseClenshaw) us += launch(d, 2, 2, 3.0 + 0.35 * d);
+        if (use == kUseClenshaw) us += launch(d, 2, 2, order_us(d));
         // no psi; an order's vector, or J times it, is stored, and for one of the two recursions the last two
-        if (use == kUseMoments) us += launch(d, 1, 1 + d, 3.0 + 0.35 * d);
+        if (use == kUseMoments) us += launch(d, 1, 1 + d, order_us(d));
         // the replay stores every order; the adjoint reads them back, and lambda
-        if (use == kUseAdjoint) us += launch(d, 2, 2 + d, 3.0 + 0.35 * d) + launch(d, 1, 4 + d, adjoint_us(d));
+        if (use == kUseAdjoint) us += launch(d, 2, 2 + d, order_us(d)) + launch(d, 1, 4 + d, adjoint_us(d));
     }
     return us;
 }
@@ -286,7 +289,11 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         ChainReach &r = chain_reach(T, cap);
         if (r.refused || r.depth < std::min(n_orders, 3)) continue;
         shape(r.sample.tiles, r.depth);
-        if (chain_us(r.sample, cs, use) > plain_us(r.sample, s_user, fp32, n_orders, use, pairs)) continue;
+        auto pays = [&](const ChainSample &q) {
+            shape(q.tiles, q.depth);
+            return chain_us(q, cs, fp32, use) <= plain_us(q, s_user, fp32, n_orders, use, pairs);
+        };
+        if (!pays(r.sample) || (r.n_tiles > 0 && !pays(r.exact()))) continue;
         const bool there = chain_select(T, cap);
         if (there) shape(ch().n_tiles, ch().depth);
         // looked at before the tables are built: near the limit every call would build them in vain
@@ -299,6 +306,11 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
             r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
+            r.n_tiles = ch().n_tiles;
+            if (!pays(r.exact())) {
+                ch().release();
+                continue;
+            }
             shape(ch().n_tiles, ch().depth);
         }
         return TBPM_OK;
@@ -373,7 +385,8 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, cons
     for (; T >= kChainMinTile; T /= 2) {
         ChainReach &r = chain_reach(T, 1);
         if (r.refused || r.sample.depth < 1) continue;
-        if (wide_us(r.sample, cs.n_blk) > wide_plain_us(s_user, fp32)) continue;
+        auto pays = [&](const ChainSample &q) { return wide_us(q, cs.n_blk) <= wide_plain_us(s_user, fp32); };
+        if (!pays(r.sample) || (r.n_tiles > 0 && !pays(r.exact()))) continue;
         const bool there = chain_select(T, 1);
         if (need && !chain_room(fp32, there ? nullptr : &r.sample, need(cs, there ? ch().n_tiles : r.sample.tiles))) {
             chain_release();
@@ -384,6 +397,11 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, cons
             r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
+            r.n_tiles = ch().n_tiles;
+            if (!pays(r.exact())) {
+                ch().release();
+                continue;
+            }
         }
         cs.n_grp = wide_groups(cs.n_blk, ch().n_tiles);
         cs.depths.assign(1, 1);

@@ -140,6 +140,12 @@ struct Engine {
         int32_t cap, depth = 0;
         bool refused = false;
         ChainSample sample;
+        int64_t n_tiles = 0;  // once the tables were built
+        ChainSample exact() const {
+            ChainSample s = sample;
+            s.tiles = n_tiles;
+            return s;
+        }
     };
     std::vector<ChainReach> ch_reach;
     ChainReach &chain_reach(int64_t T, int32_t cap);
@@ -164,7 +170,7 @@ struct Engine {
     // workgroups that the chip holds: two per CU, three of complex operators
     // (hofstadter 231 x 197, 3 states, 9.7 ms against 10.1 with two)
     int32_t chain_slots() const { return mat.is_complex ? 768 : 512; }
-    double chain_us(const ChainSample &s, const ChainShape &cs, ChainUse use) const;
+    double chain_us(const ChainSample &s, const ChainShape &cs, bool fp32, ChainUse use) const;
     double plain_us(const ChainSample &s, int32_t s_user, bool fp32, int32_t n_orders, ChainUse use, bool pairs) const;
     // selects the tables of (T, cap), made for D orders if they are not there
     tbpm_status chain_build(int64_t T, int32_t cap, int32_t D, int64_t rows, int64_t max_rows);

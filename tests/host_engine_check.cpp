@@ -261,6 +261,33 @@ static void sizes_refused() {
     }
 }
 
+// two sublattices of l^3 rows, four neighbours each
+static tbpm_hamiltonian *diamond(int64_t l) {
+    const int64_t n = l * l * l;
+    std::vector<std::vector<int32_t>> adj(2 * n);
+    for (int64_t x = 0; x < l; ++x)
+        for (int64_t y = 0; y < l; ++y)
+            for (int64_t z = 0; z < l; ++z) {
+                const int64_t a = (x * l + y) * l + z, m = l - 1;
+                const int64_t b[4] = {a, ((x + m) % l * l + y) * l + z, (x * l + (y + m) % l) * l + z, (x * l + y) * l + (z + m) % l};
+                for (int64_t q : b) {
+                    adj[a].push_back((int32_t)(q + n));
+                    adj[q + n].push_back((int32_t)a);
+                }
+            }
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> col;
+    for (const auto &r : adj) {
+        col.insert(col.end(), r.begin(), r.end());
+        rp.push_back((int64_t)col.size());
+    }
+    std::vector<double> val(2 * col.size(), 0.0), on(2 * n, 0.1);
+    for (size_t q = 0; q < col.size(); ++q) val[2 * q] = -1.0;
+    tbpm_hamiltonian *H = nullptr;
+    CHECK(tbpm_hamiltonian_create(2 * n, rp.data(), col.data(), val.data(), on.data(), 0, &H) == TBPM_OK);
+    return H;
+}
+
 // Operators whose shells grow fast keep one order per launch where the overlap of the
 // tiles costs more than the launches that it saves; regular ones, and small ones,
 // which are bound by launches, take the chain or the wide pass.
@@ -281,6 +308,10 @@ static void overlap() {
     takes(irregular(20000, false, 20), 8, false);
     takes(irregular(20000, false, 6), 16, false);
     takes(ring(20000, {1, 2, 3, 140, 141, 142}), 16, true);
+    // a lattice of four neighbours in three dimensions, at the size where it ends
+    takes(diamond(16), 1, true);
+    takes(diamond(16), 10, false);
+    takes(diamond(24), 8, false);
     // and the Haydock recursion
     tbpm_hamiltonian *H = irregular(120000, true, 1);
     blocked = 0;
