@@ -101,13 +101,59 @@ void Engine::ChainTab::release() {
 Engine::ChainReach &Engine::chain_reach(int64_t T, int32_t cap) {
     for (ChainReach &r : ch_reach)
         if (r.T == T && r.cap == cap) return r;
-    ChainReach r{T, cap};
+    ch_reach.push_back(ChainReach{T, cap});
+    return ch_reach.back();
+}
+
+const ChainSample &Engine::small_sample(ChainReach &r) {
+    if (!r.has_small) chain_sample(r, 4, r.small);
+    r.has_small = true;
+    return r.small;
+}
+
+// (one hop of a wide operator's tiles differs less from tile to tile)
+const ChainSample &Engine::full_sample(ChainReach &r) {
+    if (!r.has_full) chain_sample(r, mat.max_width > kChainWidth ? 12 : 48, r.full);
+    r.has_full = true;
+    return r.full;
+}
+
+void Engine::chain_sample(const ChainReach &r, int32_t most, ChainSample &s) const {
     const bool wide = mat.max_width > kChainWidth;
     const int64_t rows = wide ? kWideThreads : chain_rows(mat.is_complex);
-    r.depth = chain_depth(h_slice_off, h_col, inst_row0, ch_orders, T, cap, rows, wide ? kWideStage : rows + rows / 4,
-                          &r.sample, wide ? 1 : 0);
-    ch_reach.push_back(std::move(r));
-    return ch_reach.back();
+    (void)chain_depth(h_slice_off, h_col, inst_row0, ch_orders, r.T, r.cap, rows, wide ? kWideStage : rows + rows / 4, &s,
+                      wide ? 1 : 0, most);
+}
+
+// Tiles cannot be more compact than balls of the row graph, whatever the row order:
+// what these would cost rules operators out before an order is made for them.
+ChainSample Engine::ball_sample(int64_t T, int32_t cap) {
+    const bool wide = mat.max_width > kChainWidth;
+    const double slack = 1.3;  // rows differ
+    const double max_eval = slack * (wide ? kWideThreads : chain_rows(mat.is_complex));
+    const double max_rows = wide ? slack * kWideStage : 1.25 * max_eval;
+    if (ch_ball.empty()) ch_ball = ball_growth(h_slice_off, h_col, mat.n_rows, 1700);
+    auto ball = [&](double r) {
+        const size_t i = (size_t)r;
+        return i + 1 >= ch_ball.size() ? ch_ball.back() : ch_ball[i] + (r - (double)i) * (ch_ball[i + 1] - ch_ball[i]);
+    };
+    ChainSample s;
+    for (; T >= 1; T /= 2) {
+        double r = 0.0;  // the ball of T rows
+        while (r < (double)ch_ball.size() && ball(r + 1.0) <= (double)T) r += 1.0;
+        const double step = ball(r + 1.0) - ball(r);
+        if (step > 0.0) r += std::min(1.0, std::max(0.0, ((double)T - ball(r)) / step));
+        const double own = std::max(1.0, ball(r));
+        int32_t d = 0;
+        while (d < cap && (double)T * ball(r + d) / own <= max_eval && (double)T * ball(r + d + 1) / own <= max_rows) ++d;
+        if (d == 0 && wide && T > 1) continue;  // halved, as the tables would
+        s.depth = d;
+        s.tiles = (mat.n_rows + T - 1) / T;
+        for (int32_t h = 0; h <= d; ++h) s.rows.push_back(ball(r + h) / own);
+        s.sectors = s.rows;
+        break;
+    }
+    return s;
 }
 
 // the tables of (T, cap), if the handle has them
@@ -275,7 +321,6 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
     const int64_t units = mat.n_rows * cs.n_blk;
     int64_t T = kChainMinTile;
     while (T < rows / 2 && T * 2 * 256 <= units) T *= 2;
-    chain_orders();
     // few tiles: their state blocks go to several workgroups each, up to what the
     // chip holds at once
     const int64_t slots = chain_slots();
@@ -284,30 +329,42 @@ tbpm_status Engine::chain_prepare(int32_t s_user, bool fp32, int32_t n_orders, C
         cs.n_grp = (int32_t)std::min<int64_t>(cs.n_blk, std::max<int64_t>(1, (slots + n_tiles - 1) / n_tiles));
         chain_split(n_orders, depth, cs.depths);
     };
+    // times `margin` of what the same takes without the chain
+    auto pays = [&](const ChainSample &s, double margin) {
+        if (s.depth < std::min(n_orders, 3)) return false;
+        shape(s.tiles, s.depth);
+        return chain_us(s, cs, fp32, use) <= margin * plain_us(s, s_user, fp32, n_orders, use, pairs);
+    };
+    auto cap_of = [&](int64_t t) { return std::min<int32_t>(n_orders, t >= 512 ? 6 : (t >= 128 ? 9 : 17)); };
+    // what the balls or a few tiles rule out is not looked at in full (0.1 ms for the
+    // balls, 0.2 for four tiles, 1 to 3 for 48, and up to 20 for an order)
+    bool any = false, sure = false;
+    for (int64_t t = T; t >= kChainMinTile && !any; t /= 2) {
+        const ChainSample ball = ball_sample(t, cap_of(t));
+        any = pays(ball, 1.3);
+        sure = pays(ball, 0.5);  // needs no small sample
+    }
+    if (!any) return fail(TBPM_E_ARG, "the chain does not pay");
+    chain_orders();
     for (; T >= kChainMinTile; T /= 2) {
-        const int32_t cap = std::min<int32_t>(n_orders, T >= 512 ? 6 : (T >= 128 ? 9 : 17));
+        const int32_t cap = cap_of(T);
         ChainReach &r = chain_reach(T, cap);
-        if (r.refused || r.depth < std::min(n_orders, 3)) continue;
-        shape(r.sample.tiles, r.depth);
-        auto pays = [&](const ChainSample &q) {
-            shape(q.tiles, q.depth);
-            return chain_us(q, cs, fp32, use) <= plain_us(q, s_user, fp32, n_orders, use, pairs);
-        };
-        if (!pays(r.sample) || (r.n_tiles > 0 && !pays(r.exact()))) continue;
+        if (r.refused || !(sure || pays(small_sample(r), 1.3)) || !pays(full_sample(r), 1.0)) continue;
+        if (r.n_tiles > 0 && !pays(r.exact(), 1.0)) continue;
         const bool there = chain_select(T, cap);
         if (there) shape(ch().n_tiles, ch().depth);
         // looked at before the tables are built: near the limit every call would build them in vain
-        if (need && !chain_room(fp32, there ? nullptr : &r.sample, need(cs, there ? ch().n_tiles : r.sample.tiles))) {
+        if (need && !chain_room(fp32, there ? nullptr : &r.full, need(cs, there ? ch().n_tiles : r.full.tiles))) {
             chain_release();
             return fail(TBPM_E_OOM, "no memory for the chain");
         }
         if (!there) {
-            tbpm_status st = chain_build(T, cap, r.depth, rows, rows + rows / 4);
+            tbpm_status st = chain_build(T, cap, r.full.depth, rows, rows + rows / 4);
             r.refused = st == TBPM_E_ARG;
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
             r.n_tiles = ch().n_tiles;
-            if (!pays(r.exact())) {
+            if (!pays(r.exact(), 1.0)) {
                 ch().release();
                 continue;
             }
@@ -381,14 +438,19 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, cons
     const int64_t units = mat.n_rows * cs.n_blk;
     int64_t T = kChainMinTile;
     while (T < kWideThreads && T * 2 * 256 <= units) T *= 2;
+    auto pays = [&](const ChainSample &q, double margin) {
+        return q.depth >= 1 && wide_us(q, cs.n_blk) <= margin * wide_plain_us(s_user, fp32);
+    };
+    bool any = false;
+    for (int64_t t = T; t >= kChainMinTile && !any; t /= 2) any = pays(ball_sample(t, 1), 1.3);
+    if (!any) return fail(TBPM_E_ARG, "the wide pass does not pay");
     chain_orders(true);
     for (; T >= kChainMinTile; T /= 2) {
         ChainReach &r = chain_reach(T, 1);
-        if (r.refused || r.sample.depth < 1) continue;
-        auto pays = [&](const ChainSample &q) { return wide_us(q, cs.n_blk) <= wide_plain_us(s_user, fp32); };
-        if (!pays(r.sample) || (r.n_tiles > 0 && !pays(r.exact()))) continue;
+        if (r.refused || !pays(small_sample(r), 1.3) || !pays(full_sample(r), 1.0)) continue;
+        if (r.n_tiles > 0 && !pays(r.exact(), 1.0)) continue;
         const bool there = chain_select(T, 1);
-        if (need && !chain_room(fp32, there ? nullptr : &r.sample, need(cs, there ? ch().n_tiles : r.sample.tiles))) {
+        if (need && !chain_room(fp32, there ? nullptr : &r.full, need(cs, there ? ch().n_tiles : r.full.tiles))) {
             chain_release();
             return fail(TBPM_E_OOM, "no memory for the wide pass");
         }
@@ -398,7 +460,7 @@ tbpm_status Engine::wide_prepare(int32_t s_user, bool fp32, ChainShape &cs, cons
             if (st == TBPM_E_ARG) continue;
             if (st != TBPM_OK) return st;
             r.n_tiles = ch().n_tiles;
-            if (!pays(r.exact())) {
+            if (!pays(r.exact(), 1.0)) {
                 ch().release();
                 continue;
             }

@@ -296,6 +296,7 @@ void Engine::release() {
     ch_sel = 0;
     ch_orders.clear();
     ch_reach.clear();
+    ch_ball.clear();
     partner_ready = false;
     staging.release();
     if (staging_done) (void)hipEventDestroy(staging_done);

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -655,11 +656,12 @@ static bool chain_shells(const std::vector<int64_t> &slice_off, const std::vecto
 
 int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                     const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
-                    int32_t cap, int64_t max_eval, int64_t max_rows, ChainSample *sample, int32_t at_least) {
+                    int32_t cap, int64_t max_eval, int64_t max_rows, ChainSample *sample, int32_t at_least,
+                    int32_t most) {
     const std::vector<TileDesc> tops = chain_parts(inst_row0, T);
     std::vector<int32_t> tag(inst_row0.back(), -1), c(cap + 1), depth;
     std::vector<uint32_t> rows;
-    const size_t n = tops.size(), samples = std::min<size_t>(n, 48);
+    const size_t n = tops.size(), samples = std::min<size_t>(n, most);
     int32_t visit = 0;
     // rows within h hops of each sampled tile that was reached to the end, and the
     // 64-byte sectors of four rows that they lie in
@@ -694,7 +696,8 @@ int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int
         if (sample) tiles.push_back(std::move(t));
     }
     std::sort(depth.begin(), depth.end());
-    const int32_t D = depth.empty() ? 0 : std::max(depth[depth.size() / 16], at_least);
+    // nearly all of a full sample, half of a small one
+    const int32_t D = depth.empty() ? 0 : std::max(depth[depth.size() / (most < 48 ? 2 : 16)], at_least);
     if (!sample) return D;
     // tiles that do not reach D are halved, as chain_tables does
     *sample = ChainSample{};
@@ -725,6 +728,37 @@ int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int
     sample->depth = D;
     sample->tiles = (int64_t)((double)n * (double)pieces / (double)samples + 0.5);
     return D;
+}
+
+std::vector<double> ball_growth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col, int64_t n_rows,
+                                int64_t max_rows) {
+    constexpr int64_t kBalls = 4;
+    constexpr size_t kHops = 64;
+    std::vector<int32_t> tag(n_rows, -1);
+    std::vector<uint32_t> rows;
+    std::vector<double> b;
+    for (int64_t k = 0; k < kBalls; ++k) {
+        rows.assign(1, (uint32_t)((2 * k + 1) * n_rows / (2 * kBalls)));
+        tag[rows[0]] = (int32_t)k;
+        size_t from = 0;
+        for (size_t h = 0; h < kHops; ++h) {
+            if (b.size() <= h) b.push_back(0.0);
+            b[h] += (double)rows.size() / kBalls;
+            if ((int64_t)rows.size() > max_rows) continue;  // the ball counts as no larger from here on
+            const size_t end = rows.size();
+            for (; from < end; ++from) {
+                const int64_t r = rows[from], s0 = slice_off[r / kSliceRows], w = (slice_off[r / kSliceRows + 1] - s0) / kSliceRows;
+                for (int64_t e = 0; e < w; ++e) {
+                    const int32_t g = col[s0 + e * kSliceRows + r % kSliceRows];
+                    if (tag[g] != (int32_t)k) {
+                        tag[g] = (int32_t)k;
+                        rows.push_back((uint32_t)g);
+                    }
+                }
+            }
+        }
+    }
+    return b;
 }
 
 void chain_tables(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,

@@ -134,21 +134,30 @@ struct Engine {
     const ChainTab &ch() const { return ch_tab[ch_sel]; }
     // the tiles' matrix entries (taken anew by every call that uses them)
     DevBuf ch_tval, ch_tons;
-    // what a sample says of tiles of T rows for up to cap orders; refused: no tiling was found
+    // what a small and a full sample say of tiles of T rows for up to cap orders (the
+    // full one is taken where the small one does not rule the tiles out, and their
+    // number is known once they were built); refused: no tiling was found
     struct ChainReach {
         int64_t T;
-        int32_t cap, depth = 0;
+        int32_t cap;
         bool refused = false;
-        ChainSample sample;
+        ChainSample small, full;
+        bool has_small = false, has_full = false;
         int64_t n_tiles = 0;  // once the tables were built
         ChainSample exact() const {
-            ChainSample s = sample;
+            ChainSample s = full;
             s.tiles = n_tiles;
             return s;
         }
     };
     std::vector<ChainReach> ch_reach;
     ChainReach &chain_reach(int64_t T, int32_t cap);
+    void chain_sample(const ChainReach &r, int32_t most, ChainSample &s) const;
+    const ChainSample &small_sample(ChainReach &r);
+    const ChainSample &full_sample(ChainReach &r);
+    // rows within h hops of a row, and from it tiles of T rows as compact as a ball
+    std::vector<double> ch_ball;
+    ChainSample ball_sample(int64_t T, int32_t cap);
     std::vector<std::vector<int32_t>> ch_orders;  // per member: row order its tiles follow (empty: as stored)
     struct ChainShape {
         int32_t vs = 1, n_blk = 1, n_grp = 1;

@@ -332,12 +332,16 @@ struct ChainSample {
     std::vector<double> rows, sectors;  // [depth + 1]
 };
 // The depth to build tiles of T rows for: the largest up to cap that nearly all
-// of a sample of tiles reach within the bounds; 0 if none (or at_least: the others
-// are halved until they reach it)
+// of a sample of tiles reach within the bounds (half of a sample of `most` < 48); 0 if
+// none (or at_least: the others are halved until they reach it)
 int32_t chain_depth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col,
                     const std::vector<int64_t> &inst_row0, const std::vector<std::vector<int32_t>> &orders, int64_t T,
                     int32_t cap, int64_t max_eval, int64_t max_rows, ChainSample *sample = nullptr,
-                    int32_t at_least = 0);
+                    int32_t at_least = 0, int32_t most = 48);
+// Mean number of rows within h = 0, 1, ... hops of a row (four rows, whatever the
+// row order), up to max_rows
+std::vector<double> ball_growth(const std::vector<int64_t> &slice_off, const std::vector<int32_t> &col, int64_t n_rows,
+                                int64_t max_rows);
 
 // LDS budget of a fused-shape tile for tier t = 1 .. 6: 1/(t+2) of a CU's
 // 160 KiB, i.e. room for t+2 resident workgroups per CU

@@ -508,6 +508,22 @@ static void scattered_tiles() {
     }
 }
 
+// Operators whose balls grow so fast that no tiles can pay are not ordered or sampled:
+// a first call allocates one array of all rows, for the balls.
+static void ruled_out() {
+    const int64_t n = 12000;
+    for (int kind = 0; kind < 2; ++kind) {
+        tbpm_hamiltonian *H = kind == 0 ? irregular(n, false, 24) : irregular(n, true, 2);
+        Dev psi(2 * n * 16), corr(2 * 70 * 16);
+        big_size = 4 * (size_t)n;
+        big_count = 0;
+        CHECK(tbpm_propagate(H, psi.p, 16, 70, 0.6, 5.0, 1e-14, TBPM_FP64, corr.p, nullptr, 0, nullptr, 0, nullptr) == TBPM_OK);
+        big_size = SIZE_MAX;
+        CHECK(big_count == 1 && H->eng.ch_orders.empty());
+        tbpm_hamiltonian_destroy(H);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
@@ -519,7 +535,8 @@ int main(int argc, char **argv) {
                                                            {"room_is_what_it_takes", room_is_what_it_takes},
                                                            {"states_given_back", states_given_back},
                                                            {"no_host_memory", no_host_memory},
-                                                           {"scattered_tiles", scattered_tiles}};
+                                                           {"scattered_tiles", scattered_tiles},
+                                                           {"ruled_out", ruled_out}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

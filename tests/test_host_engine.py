@@ -103,3 +103,8 @@ def test_calls_without_host_memory_for_tables_go_on(checker):
 def test_tiles_of_scattered_rows_are_halved_as_far_as_it_takes(checker):
     """A few tiles of rows that lie apart do not keep an operator from the chain."""
     _run(checker, "scattered_tiles")
+
+
+def test_hopeless_operators_are_ruled_out_early(checker):
+    """A first call on an operator whose balls grow too fast for any tile makes no order and no samples."""
+    _run(checker, "ruled_out")
