@@ -1,6 +1,7 @@
 // CPU checks of the library's launch decisions on a device made of host memory.
 //   host_engine_check NAME
 #include <cmath>
+#include <memory>
 #include <new>
 
 #include "fake_device.h"
@@ -524,6 +525,46 @@ static void ruled_out() {
     }
 }
 
+// The members of a batch are ordered on several threads, the large ones on several
+// each: every member gets the order that it gets alone, whichever comes first.
+static void batch_orders() {
+    std::vector<tbpm_hamiltonian *> Hs;
+    for (int64_t n : {300, 9000, 700, 64, 5000, 40, 2500}) Hs.push_back(ring(n, {1, n / 3}));
+    const int S = 4, ni = (int)Hs.size();
+    std::vector<std::unique_ptr<Dev>> mem;
+    std::vector<const double *> psi;
+    std::vector<double *> corr;
+    for (tbpm_hamiltonian *H : Hs) {
+        mem.push_back(std::make_unique<Dev>(2 * H->csr.n * S));
+        psi.push_back(mem.back()->p);
+        mem.push_back(std::make_unique<Dev>(2 * 70 * S));
+        corr.push_back(mem.back()->p);
+    }
+    const std::vector<double> dt(ni, 0.6), f(ni, 5.0);
+    tbpm_batch *B = nullptr;
+    CHECK(tbpm_batch_create(Hs.data(), ni, &B) == TBPM_OK);
+    for (int k = 0; k < 2; ++k)
+        CHECK(tbpm_propagate_batched(B, psi.data(), S, 70, dt.data(), f.data(), 1e-14, TBPM_FP64, corr.data(), nullptr, 0,
+                                     nullptr) == TBPM_OK);
+    CHECK((int)B->eng.ch_orders.size() == ni);
+    for (int i = 0; i < ni; ++i) {
+        const HostCsr &h = Hs[i]->csr;
+        std::vector<int64_t> rp{0};
+        std::vector<int32_t> cc;
+        for (int64_t r = 0; r < h.n; ++r) {
+            const int64_t s0 = Hs[i]->eng.h_slice_off[r / 32], w = (Hs[i]->eng.h_slice_off[r / 32 + 1] - s0) / 32;
+            for (int64_t e = 0; e < w; ++e) {
+                const int32_t g = Hs[i]->eng.h_col[s0 + e * 32 + r % 32];
+                if (g != r) cc.push_back(g);
+            }
+            rp.push_back((int64_t)cc.size());
+        }
+        CHECK(B->eng.ch_orders[i] == (h.n > 64 ? bisection_order(h.n, rp.data(), cc.data(), 64, 1) : std::vector<int32_t>{}));
+    }
+    tbpm_batch_destroy(B);
+    for (tbpm_hamiltonian *H : Hs) tbpm_hamiltonian_destroy(H);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {{"quasi_layout", quasi_layout}, {"bench_pass", bench_pass},
                                                            {"haydock_places", haydock_places},
@@ -536,7 +577,8 @@ int main(int argc, char **argv) {
                                                            {"states_given_back", states_given_back},
                                                            {"no_host_memory", no_host_memory},
                                                            {"scattered_tiles", scattered_tiles},
-                                                           {"ruled_out", ruled_out}};
+                                                           {"ruled_out", ruled_out},
+                                                           {"batch_orders", batch_orders}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     CHECK(fake::blocks.empty());  // every handle gave its memory back

@@ -1,7 +1,8 @@
 """CPU checks of the launch decisions of the library's host side:
-tests/host_engine_check.cpp, compiled with AddressSanitizer and UBSan against
-every host source of the library and a device made of host memory
-(tests/fake_device.h), whose free memory a check may change at any time."""
+tests/host_engine_check.cpp, compiled with AddressSanitizer and UBSan (what runs
+on several threads with ThreadSanitizer too) against every host source of the
+library and a device made of host memory (tests/fake_device.h), whose free
+memory a check may change at any time."""
 import concurrent.futures as cf
 import glob
 import os
@@ -11,18 +12,18 @@ import subprocess
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
+ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1",
+           TSAN_OPTIONS="halt_on_error=1")
 
 
-@pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def _build(tmp_path_factory, sanitizer):
     cxx = shutil.which("g++")
     if not cxx or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
         pytest.skip("g++ or the HIP headers are not available")
     tmp = str(tmp_path_factory.mktemp("host_engine"))
     srcs = sorted(glob.glob(os.path.join(ROOT, "paper_2209_00806_amd", "csrc", "*.cpp")))
     srcs.append(os.path.join(ROOT, "tests", "host_engine_check.cpp"))
-    flags = ["-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+    flags = ["-O1", "-g", "-std=c++17", f"-fsanitize={sanitizer}", "-fno-omit-frame-pointer",
              "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"]
     objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in srcs]
 
@@ -34,6 +35,16 @@ def checker(tmp_path_factory):
     out = os.path.join(tmp, "host_engine_check")
     subprocess.run([cxx, *flags, *objs, "-pthread", "-o", out], check=True, capture_output=True, timeout=600)
     return out
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    return _build(tmp_path_factory, "address,undefined")
+
+
+@pytest.fixture(scope="module")
+def thread_checker(tmp_path_factory):
+    return _build(tmp_path_factory, "thread")
 
 
 def _run(exe, name):
@@ -108,3 +119,14 @@ def test_tiles_of_scattered_rows_are_halved_as_far_as_it_takes(checker):
 def test_hopeless_operators_are_ruled_out_early(checker):
     """A first call on an operator whose balls grow too fast for any tile makes no order and no samples."""
     _run(checker, "ruled_out")
+
+
+def test_members_are_ordered_on_threads(checker, thread_checker):
+    """The row orders of a batch's members, made on several threads, are those each member gets alone."""
+    _run(checker, "batch_orders")
+    _run(thread_checker, "batch_orders")
+
+
+def test_tables_on_threads(thread_checker):
+    """Tile tables of the chain, made on several threads for calls of several kinds."""
+    _run(thread_checker, "tables_kept")
