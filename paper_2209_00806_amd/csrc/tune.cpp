@@ -60,7 +60,7 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
     const bool wide_rows = eng.mat.n_rows > 0 && (double)eng.mat.ell_size > 8.0 * (double)eng.mat.n_rows;
     Engine::ChainShape cs;
     const bool chain = st == TBPM_OK && eng.chain_prepare(n_states, fp32, 17, cs) == TBPM_OK;
-    // the wide pass: the library picks tiles and states per thread, whatever tier and vec
+    // the wide pass: the library picks tiles, their order and states per thread, whatever tier, remap and vec
     const bool wide_pass = st == TBPM_OK && eng.wide_prepare(n_states, fp32, cs) == TBPM_OK;
     auto vec_ok = [&](int vec) { return !(fp32 && vec == 1 && s_pad > 1); };  // 8-byte units never beat 16
     for (int vec = 1; vec <= 4 && vec <= s_pad; vec *= 2) {
@@ -73,11 +73,12 @@ tbpm_status autotune_impl(Engine &eng, const std::vector<double> &rescale, int32
     }
     // the staged shape; for wide rows also the smaller LDS tiers, where the
     // halo sets the trade between tile size and resident workgroups, and the
-    // tile orders that give each XCD runs of consecutive tiles
+    // tile orders that give each XCD runs of consecutive tiles (the wide pass
+    // orders its tiles itself)
     for (int tier = 1; tier <= (wide_rows && !wide_pass ? 4 : 1); ++tier)
         for (int vec = 1; vec <= 4 && vec <= s_pad; vec *= 2) {
             if (!vec_ok(vec) || (wide_pass && vec > (fp32 ? 2 : 1))) continue;
-            for (int remap = 0; remap <= (wide_rows || wide_pass ? 6 : 1); ++remap)
+            for (int remap = wide_pass ? 1 : 0; remap <= (wide_rows && !wide_pass ? 6 : 1); ++remap)
                 for (int nt = 0; nt <= (tier == 1 && !wide_pass ? 1 : 0); ++nt)
                     cands.push_back(tbpm_launch_config{2, remap, nt, 1, tier, vec, 0});
         }

@@ -344,6 +344,16 @@ static void wide_order() {
     propagate(H, 64, 70);
     CHECK(order == 6);
     tbpm_hamiltonian_destroy(H);
+    // the tuner times it in one order (a run twice)
+    int runs = 0;
+    fake::on_init = [&](const InitParams &p) { runs += p.log2sb == 0; };
+    H = ring(20000, {1, 2, 3, 140, 141, 142});
+    tbpm_launch_config best;
+    double ms = 0.0;
+    CHECK(tbpm_autotune(H, 4, TBPM_FP64, &best, &ms, nullptr) == TBPM_OK);
+    CHECK(runs == 2);
+    tbpm_hamiltonian_destroy(H);
+    fake::on_init = nullptr;
     fake::on_wide = nullptr;
 }
 
