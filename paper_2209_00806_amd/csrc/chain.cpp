@@ -414,13 +414,21 @@ double Engine::wide_plain_us(int32_t s_user, bool fp32) const {
 
 // The order in which a wide pass's workgroups take the tiles, whatever the
 // configuration's, which was chosen for another kernel: each XCD a contiguous range
-// (1) while a vector leaves the caches room for the others, and runs of 64 tiles in
-// turn (6) beyond (70 samples, orders 1, 3 and 6: cubic 60^3, 16 FP64 states, 55 MB
-// a vector, 52.2, 60.1 and 56.2 ms; bilayer 448^2, 16 FP32 states, 103 MB, 109.9,
-// 109.8 and 108.6; 16 FP64 states 231, 225 and 225; cubic 110^3, 16 FP64 states, 341
-// MB, 394, 377 and 370).
+// (1) while a vector leaves the caches room for the others, then runs of 64 tiles in
+// turn (6), and runs of 32 (5) for the largest vectors.  Time of
+// 70 samples (33 of the largest bilayer), ms, 16 states but for the 4 of one row:
+//     order                                1       5       6
+//     cubic 60^3, FP64       55 MB      52.2       -    56.2
+//     bilayer 448^2, FP32   103 MB     109.9   108.7   108.6
+//     bilayer 448^2, FP64   206 MB       231   223.5   224.8
+//     cubic 110^3, FP64     341 MB       394   370.6   369.6
+//     bilayer 1024^2, FP64, 4 states
+//                           268 MB     202.2   199.8   197.9
+//     bilayer 1024^2, FP32  537 MB     282.6   272.6   278.7
+//                     FP64 1074 MB       563     529     544
 int32_t Engine::wide_tile_order(const ChainShape &cs) const {
-    return 16 * mat.n_rows * cs.n_blk > ((int64_t)96 << 20) ? 6 : 1;
+    const int64_t mb = 16 * mat.n_rows * cs.n_blk >> 20;
+    return mb <= 96 ? 1 : (mb <= 384 ? 6 : 5);
 }
 
 // One order of a wide operator per launch (wide.hip), for two blocks of states or

@@ -343,6 +343,11 @@ static void wide_order() {
     H = ring(110000, {1, 2, 3, 330, 331, 332});
     propagate(H, 64, 70);
     CHECK(order == 6);
+    Engine::ChainShape cs;
+    for (const auto &[n_blk, o] : {std::pair<int32_t, int32_t>{32, 1}, {64, 6}, {192, 6}, {256, 5}, {1024, 5}}) {
+        cs.n_blk = n_blk;
+        CHECK(H->eng.wide_tile_order(cs) == o);
+    }
     tbpm_hamiltonian_destroy(H);
     // the tuner times it in one order (a run twice)
     int runs = 0;
