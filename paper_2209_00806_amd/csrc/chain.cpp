@@ -23,14 +23,14 @@ namespace tbpm {
 // from it (the storage order, and with it every sum's order, stays).  keep_local:
 // not for members whose tiles in the caller's order reference few rows besides their
 // own (the wide pass, one hop: on bilayers in the builder's order a bisection saves
-// 5 to 8% of the rows, and takes 12 ms for 14400 of them).
+// 5 to 8% of the rows, and takes 8 ms for 13456 of them).
 void Engine::chain_orders(bool keep_local) {
     if (!ch_orders.empty()) return;
     const int32_t ni = n_inst();
     std::vector<std::vector<int32_t>> orders(ni);
     // the largest members first, up to 16 threads in all and 8 within a member
-    // (14400 rows of 19 elements: 35 ms with one, 12 with eight; a batch of 12
-    // members of 5000 to 20000 rows: 13.5 ms one member after another, 3.1 so)
+    // (13456 rows of 19 elements: 16 ms with one, 8 with eight; 12 graphene members of
+    // 5000 to 20000 rows: 33 ms one member after another, 8 so)
     auto size = [&](int32_t i) { return inst_row0[i + 1] - inst_row0[i]; };
     std::vector<int32_t> todo;
     int64_t rows = 0;
